@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvla.so")
 SOURCES = ["api.hip", "gemm_f16.hip", "decode_gemm.hip", "kernels.hip", "attention.hip", "batcher.cpp"]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
 
@@ -21,7 +21,7 @@ def build_library(verbose: bool = False) -> str:
     def compile_one(src: str) -> str:
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
         host_only = src.endswith(".cpp")
-        flags = ["-O2", "-std=c++17", "-fPIC"] if host_only else FLAGS + os.environ.get("VLA_EXTRA_HIPCC_FLAGS", "").split()
+        flags = ["-O2", "-std=c++20", "-fPIC"] if host_only else FLAGS + os.environ.get("VLA_EXTRA_HIPCC_FLAGS", "").split()
         cmd = [hipcc, *flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:

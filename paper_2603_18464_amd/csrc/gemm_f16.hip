@@ -9,123 +9,93 @@
 //       row n0 + (l & 31), k = k0 + 8*(l >> 5) .. +7; blocks are ordered [n/32][k/16].  A wave
 //       reads one block with a single fully coalesced 16-byte-per-lane load, from global memory or
 //       from LDS, with no bank conflicts and no swizzle.
-// The kernel keeps a BM x 64 slab of A (16-byte chunk c of row r sits in slot c ^ ((r >> 1) & 7), so
-// that any 16 consecutive rows of one chunk column cover all 64 LDS banks) and a BN x 64 slab of Wp in
-// LDS, double buffered, and each of the WGM x WGN waves owns a (BM/WGM) x (BN/WGN) accumulator tile made
-// of 32x32x16 MFMAs.
+#include <cmath>
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 
 namespace vla {
 
-constexpr int BK = 64;
-
 // ---- epilogues ------------------------------------------------------------------------------------
-// Accumulator layout of v_mfma_f32_32x32x16_f16: lane l, register 4*blk + r holds
-// C[row = 8*blk + 4*(l >> 5) + r][col = l & 31].
-
-// Staged epilogues (large-tile kernel): a wave first writes a 32 x 128 float accumulator sub-tile to its
-// private LDS region in row-major order (pitch kStagePitch floats: the two half-waves of a store hit
-// disjoint banks), then reads it back as float4 row chunks, so that global memory sees 16-byte accesses
-// that cover whole 128- to 512-byte row segments instead of scattered 2- and 4-byte ones.
-constexpr int kStagePitch = 136;
-constexpr int kStageFloats = 32 * kStagePitch;   // per wave
-
-__device__ __forceinline__ void stage_tile(const f32x16 (&a)[4], float* tile, int lane) {
-  const int h = lane >> 5, c = lane & 31;
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) tile[(8 * (e >> 2) + 4 * h + (e & 3)) * kStagePitch + nt * 32 + c] = a[nt][e];
-}
+// A wave (or a pair of waves side by side, where a wave's columns do not cover the span an epilogue needs) writes
+// 32 rows of accumulators to LDS in row-major order and hands them to consume(), which reads them back as float4 row
+// chunks, so that global memory sees 16-byte accesses that cover whole 128- to 512-byte row segments instead of
+// scattered 2- and 4-byte ones.
+//   consume<COLS, PITCH, ROWS>(tile, m_base, nb, lane, M): rows m_base .. + ROWS - 1 and columns nb .. + COLS - 1 of
+//   the product, element (r, c) at tile[r * PITCH + c].
+//   kSpan: columns that have to be handed over together.
 
 struct EpiResid {
+  static constexpr int kSpan = 32;
   float* x;
   int ldx;
-  // rows m_base .. m_base+31, columns nb .. nb+127 of x += tile / kWeightScale
+  // x += tile / kWeightScale: all loads of the rows are issued before the first store (a store followed by a load of
+  // the same array would otherwise serialise on the memory latency); rows past M are read from row M-1, not stored
+  template <int COLS, int PITCH, int ROWS>
   __device__ __forceinline__ void consume(const float* tile, int m_base, int nb, int lane, int M) const {
-    const int r0 = lane >> 5, c4 = (lane & 31) * 4;
-    f32x4 v[16], old[16];
+    constexpr int LPR = COLS / 4, RPI = 64 / LPR, IT = ROWS / RPI;
+    const int r0 = lane / LPR, c4 = (lane % LPR) * 4;
+    f32x4 v[IT], old[IT];
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int r = it * 2 + r0;
-      v[it] = *(const f32x4*)(tile + r * kStagePitch + c4);
+    for (int it = 0; it < IT; ++it) {
+      const int r = it * RPI + r0;
+      v[it] = *(const f32x4*)(tile + r * PITCH + c4);
       old[it] = *(const f32x4*)(x + (size_t)min(m_base + r, M - 1) * ldx + nb + c4);
     }
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int m = m_base + it * 2 + r0;
+    for (int it = 0; it < IT; ++it) {
+      const int m = m_base + it * RPI + r0;
       if (m < M) *(f32x4*)(x + (size_t)m * ldx + nb + c4) = old[it] + v[it] * (1.0f / kWeightScale);
-    }
-  }
-  template <int MT, int NT>
-  __device__ __forceinline__ void apply(f32x16 (&acc)[MT][NT], int mb, int nb, int lane, int M) const {
-    const int h = lane >> 5, c = lane & 31;
-    // Read-modify-write of the float32 residual stream.  All loads of a 32-row tile are issued before
-    // its first store (a store followed by a load of the same array would otherwise serialise on the
-    // memory latency); rows past M are read from row M-1 and not stored.
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      float old[16][NT];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = min(mb + mt * 32 + 8 * (e >> 2) + 4 * h + (e & 3), M - 1);
-        const float* row = x + (size_t)m * ldx + nb + c;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) old[e][nt] = row[nt * 32];
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = mb + mt * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-        if (m < M) {
-          float* row = x + (size_t)m * ldx + nb + c;
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) row[nt * 32] = old[e][nt] + acc[mt][nt][e] * (1.0f / kWeightScale);
-        }
-      }
     }
   }
 };
 
-// Fused gate/up weights are interleaved in blocks of 32 rows: [gate 0..31, up 0..31, gate 32..63, ...]
-// so that a wave's even 32-column tiles are gates and the following odd tiles the matching ups.
 // Split-K form (decode steps of large batches): the tile's partial sums over one K slice go, with the weight scale
 // divided out, to plane `kz` of part[ksplit][plane_rows][N]; the reduce kernels of the decode path add the planes.
 struct EpiPartial {
+  static constexpr int kSpan = 32;
   float* part;          // plane 0; the kernel moves it to its slice's plane
   int plane_rows, row0, N;
   const f16* a_lo;      // low-term activation fragments (two-term operands), or nullptr
+  template <int COLS, int PITCH, int ROWS>
   __device__ __forceinline__ void consume(const float* tile, int m_base, int nb, int lane, int M) const {
-    const int r0 = lane >> 5, c4 = (lane & 31) * 4;
+    constexpr int LPR = COLS / 4, RPI = 64 / LPR;
+    const int r0 = lane / LPR, c4 = (lane % LPR) * 4;
 #pragma unroll
-    for (int it = 0; it < 16; ++it) {
-      const int m = m_base + it * 2 + r0;
-      const f32x4 v = *(const f32x4*)(tile + (it * 2 + r0) * kStagePitch + c4);
+    for (int it = 0; it < ROWS / RPI; ++it) {
+      const int r = it * RPI + r0, m = m_base + r;
+      const f32x4 v = *(const f32x4*)(tile + r * PITCH + c4);
       if (m < M) *(f32x4*)(part + (size_t)(row0 + m) * N + nb + c4) = v * (1.0f / kWeightScale);
     }
   }
 };
 
 // silu(g) * u for accumulator values G = g * kWeightScale, U = u * kWeightScale, with the scale folded into the
-// constants: (G * U / scale^2) / (1 + 2^(-G * log2(e) / scale)).  One form for both kernels (same bits).
+// constants: (G * U / scale^2) / (1 + 2^(-G * log2(e) / scale)).
 __device__ __forceinline__ float swiglu_scaled(float G, float U) {
   constexpr float c1 = 1.44269504088896341f / kWeightScale, c2 = 1.0f / (kWeightScale * kWeightScale);
   return (G * U * c2) * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-(G * c1)));
 }
 
+// Fused gate/up weights are interleaved in blocks of 32 rows: [gate 0..31, up 0..31, gate 32..63, ...]
+// so that every 64 columns of the product are 32 gates followed by the matching 32 ups.
 struct EpiSwiglu {
+  static constexpr int kSpan = 64;
   f16* act;
   int ld;
   int f;        // number of outputs per row
   int lo_mode;  // 0: single-term; 1: half-precision low terms at act[m][f + j]; 2: bytes at ((char*)&act[m][f])[j]
-  // the 128 tile columns are [gate 32 | up 32 | gate 32 | up 32] -> 64 outputs per row
+  template <int COLS, int PITCH, int ROWS>
   __device__ __forceinline__ void consume(const float* tile, int m_base, int nb, int lane, int M) const {
     typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-    const int rs = lane >> 4, q = lane & 15, jb = q >> 3, c4 = (q & 7) * 4;
+    constexpr int LPR = COLS / 8, RPI = 64 / LPR;
+    const int rs = lane / LPR, q = lane % LPR, jb = q >> 3, c4 = (q & 7) * 4;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int r = it * 4 + rs, m = m_base + r;
-      const f32x4 g = *(const f32x4*)(tile + r * kStagePitch + jb * 64 + c4);
-      const f32x4 u = *(const f32x4*)(tile + r * kStagePitch + jb * 64 + 32 + c4);
+    for (int it = 0; it < ROWS / RPI; ++it) {
+      const int r = it * RPI + rs, m = m_base + r;
+      const f32x4 g = *(const f32x4*)(tile + r * PITCH + jb * 64 + c4);
+      const f32x4 u = *(const f32x4*)(tile + r * PITCH + jb * 64 + 32 + c4);
       f16x4 o;
       float a[4];
 #pragma unroll
@@ -152,69 +122,45 @@ struct EpiSwiglu {
       }
     }
   }
-  template <int MT, int NT>
-  __device__ __forceinline__ void apply(f32x16 (&acc)[MT][NT], int mb, int nb, int lane, int M) const {
-    static_assert(NT % 2 == 0, "gate/up tiles come in pairs");
-    const int h = lane >> 5, c = lane & 31;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + mt * 32 + 8 * blk + 4 * h + r;
-          if (m < M) {
-            f16* row = act + (size_t)m * ld + nb / 2 + c;
-#pragma unroll
-            for (int j = 0; j < NT / 2; ++j) {
-              const float a = swiglu_scaled(acc[mt][2 * j][4 * blk + r], acc[mt][2 * j + 1][4 * blk + r]);
-              const f16 a16 = from_f32<f16>(a);
-              row[j * 32] = a16;
-              if (lo_mode == 1) row[f + j * 32] = from_f32<f16>(a - (float)a16);
-              if (lo_mode == 2)
-                ((unsigned char*)(act + (size_t)m * ld + f))[nb / 2 + c + j * 32] =
-                    (unsigned char)(pack_lo8(a - (float)a16, 0.f, 0.f, 0.f) & 0xff);
-            }
-          }
-        }
-  }
 };
 
-// Columns [0,d) are queries, [d,2d) keys, [2d,3d) values.  A wave tile covers whole heads, so the
-// rotary partner (i, i + hd/2) of every column sits in the same lane, HD/64 tiles further on.
+// Columns [0,d) are queries, [d,2d) keys, [2d,3d) values.  The columns handed over are whole heads of one section, so
+// the rotary partner (i, i + hd/2) of every column is at hand.
 template <int HD>
 struct EpiQkv {
+  static constexpr int kSpan = HD;
   RopeKv o;
-  // the 128 tile columns are 128/HD whole heads of one section (q, k or v)
+  template <int COLS, int PITCH, int ROWS>
   __device__ __forceinline__ void consume(const float* tile, int m_base, int nb, int lane, int M) const {
     typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-    constexpr int HALF = HD / 2, LPH = HD / 8;      // lanes per head: 16 lanes cover the 128/HD heads of a row
-    const int rs = lane >> 4, q = lane & 15, hh = q / LPH, c4 = (q % LPH) * 4;
+    constexpr int HALF = HD / 2, LPH = HD / 8;      // lanes per head
+    constexpr int LPR = COLS / 8, RPI = 64 / LPR, IT = ROWS / RPI;
+    const int rs = lane / LPR, q = lane % LPR, hh = q / LPH, c4 = (q % LPH) * 4;
     const int d = o.d_model;
     const int sect = nb / d;
     const int head = (nb - sect * d) / HD + hh;
-    // Positions, slots and rotary factors of all eight row groups are fetched up front (rows past M clamped), so
-    // the two dependent global loads per row overlap instead of forming eight serial chains.
-    int pos[8], slot[8];
+    // Positions, slots and rotary factors of all row groups are fetched up front (rows past M clamped), so
+    // the two dependent global loads per row overlap instead of forming serial chains.
+    int pos[IT], slot[IT];
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int m = min(m_base + it * 4 + rs, M - 1);
+    for (int it = 0; it < IT; ++it) {
+      const int m = min(m_base + it * RPI + rs, M - 1);
       pos[it] = o.tok_pos[m];
       slot[it] = o.tok_seq[m];
     }
-    f32x4 cs[8], sn[8];
+    f32x4 cs[IT], sn[IT];
     if (sect < 2) {
 #pragma unroll
-      for (int it = 0; it < 8; ++it) {
+      for (int it = 0; it < IT; ++it) {
         cs[it] = *(const f32x4*)(o.rope_cos + (size_t)pos[it] * HALF + c4);
         sn[it] = *(const f32x4*)(o.rope_sin + (size_t)pos[it] * HALF + c4);
       }
     }
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const int r = it * 4 + rs, m = m_base + r;
-      f32x4 lo = *(const f32x4*)(tile + r * kStagePitch + hh * HD + c4) * (1.0f / kWeightScale);
-      f32x4 hi = *(const f32x4*)(tile + r * kStagePitch + hh * HD + HALF + c4) * (1.0f / kWeightScale);
+    for (int it = 0; it < IT; ++it) {
+      const int r = it * RPI + rs, m = m_base + r;
+      f32x4 lo = *(const f32x4*)(tile + r * PITCH + hh * HD + c4) * (1.0f / kWeightScale);
+      f32x4 hi = *(const f32x4*)(tile + r * PITCH + hh * HD + HALF + c4) * (1.0f / kWeightScale);
       f16* dst;
       f16* dst_lo = nullptr;                 // two-term mode: low terms of the queries (half precision, column d + ...)
       unsigned char* dst_lo8 = nullptr;      // ... and of the cached keys / values (one byte each)
@@ -269,67 +215,6 @@ struct EpiQkv {
       }
     }
   }
-  template <int MT, int NT>
-  __device__ __forceinline__ void apply(f32x16 (&acc)[MT][NT], int mb, int nb, int lane, int M) const {
-    constexpr int HT = HD / 32;              // 32-column tiles per head
-    constexpr int HALF = HD / 2;
-    static_assert(NT % HT == 0, "wave tile must cover whole heads");
-    const int h = lane >> 5, c = lane & 31;
-    const int d = o.d_model;
-    const int sect = nb / d;                 // 0 q, 1 k, 2 v (a wave tile never straddles)
-    const int col0 = nb - sect * d;          // first column inside the section
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int blk = 0; blk < 4; ++blk)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = mb + mt * 32 + 8 * blk + 4 * h + r;
-          if (m >= M) continue;
-          const int pos = o.tok_pos[m], slot = o.tok_seq[m];
-          const int ai = 4 * blk + r;
-          const float* cs_row = o.rope_cos + (size_t)pos * HALF;
-          const float* sn_row = o.rope_sin + (size_t)pos * HALF;
-#pragma unroll
-          for (int hh = 0; hh < NT / HT; ++hh) {
-            const int head = (col0 + hh * HD) / HD;
-            f16* dst;
-            f16* dst_lo = nullptr;
-            unsigned char* dst_lo8 = nullptr;
-            if (sect == 0) {
-              dst = (f16*)o.q + (size_t)m * o.ldq + (size_t)head * HD;
-              if (o.k_lo) dst_lo = dst + d;
-            } else {
-              const size_t at = (((size_t)slot * o.n_heads + head) * o.max_seq + pos) * HD;
-              dst = (f16*)(sect == 1 ? o.k_cache : o.v_cache) + at;
-              if (o.k_lo) dst_lo8 = (unsigned char*)(sect == 1 ? o.k_lo : o.v_lo) + at;
-            }
-#pragma unroll
-            for (int ht = 0; ht < HT / 2; ++ht) {
-              const int j = ht * 32 + c;     // index of the pair inside the head
-              float lo = acc[mt][hh * HT + ht][ai] * (1.0f / kWeightScale);
-              float hi = acc[mt][hh * HT + ht + HT / 2][ai] * (1.0f / kWeightScale);
-              if (sect < 2) {
-                float a, b;
-                rope_pair(lo, hi, cs_row[j], sn_row[j], a, b);
-                lo = a;
-                hi = b;
-              }
-              const f16 l16 = from_f32<f16>(lo), h16 = from_f32<f16>(hi);
-              dst[j] = l16;
-              dst[j + HALF] = h16;
-              if (dst_lo) {
-                dst_lo[j] = from_f32<f16>(lo - (float)l16);
-                dst_lo[j + HALF] = from_f32<f16>(hi - (float)h16);
-              }
-              if (dst_lo8) {
-                dst_lo8[j] = (unsigned char)(pack_lo8(lo - (float)l16, 0.f, 0.f, 0.f) & 0xff);
-                dst_lo8[j + HALF] = (unsigned char)(pack_lo8(hi - (float)h16, 0.f, 0.f, 0.f) & 0xff);
-              }
-            }
-          }
-        }
-  }
 };
 
 // ---- 8-bit low terms --------------------------------------------------------------------------------------
@@ -356,182 +241,27 @@ __device__ __forceinline__ f32x16 mfma_lo8(const f16x8& a0, const f16x8& a1, con
 #endif
 }
 
-// ---- kernel -----------------------------------------------------------------------------------------
-// LO8: the launch has 8-bit low-term slabs (W8 != nullptr); a template flag so that launches without them carry
-// no trace of that pass and the two kinds of launch have names of their own in a profile.
-template <int BM, int BN, int WGM, int WGN, class Epi, bool LO8>
-__global__ __launch_bounds__(WGM* WGN * 64, 1) void gemm_f16_kernel(
-    const f16* __restrict__ A, int lda, const f16* __restrict__ Wp, const f16* __restrict__ W8, int M, int N, int K,
-    int Kw, int tiles_m, int tiles_n, Epi epi) {
-  constexpr int NTHR = WGM * WGN * 64;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN, MT = WTM / 32, NT = WTN / 32;
-  constexpr int A_ITERS = BM * 8 / NTHR;   // 16-byte chunks of the A slab per thread
-  constexpr int W_ITERS = BN * 8 / NTHR;
-  static_assert(BM * 8 % NTHR == 0 && BN * 8 % NTHR == 0, "slab must divide among threads");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f16* As = (f16*)smem;                       // [2][BM*64]
-  f16* Ws = As + 2 * BM * BK;                  // [2][BN*64]
+// ---- the kernel ---------------------------------------------------------------------------------------------
+// One kernel template for every size: a workgroup of WGM x WGN waves computes a BM x BN tile (a wave WM x WN of it).
+//
+// * Slabs of PK k of A and W go straight from global memory into LDS (global_load_lds_dwordx4: lane l of a wave
+//   instruction deposits its 16 bytes at the wave-uniform LDS base + 16*l), S slabs ahead of the MFMAs, through a
+//   ring of S stages; one barrier per slab publishes the landed slab and frees the one everybody has in registers.
+// * Fragments are double buffered in registers: while the MFMAs of one unit (KU k-steps) run, the reads of the next
+//   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
+//   for ALL outstanding LDS loads before any LDS read, so the reads are inline assembly and the waits explicit.
+// * The instruction: 16x16x32 where every operand is half precision, 32x32x16 where the launch has a pass of 8-bit
+//   low terms (its 32x32x64 product needs that accumulator layout).  On real operands the matrix cores are limited by
+//   power, not issue: an MFMA-only loop on random activations and bf16-exact weights sustains 1.94 PFLOP/s with
+//   16x16x32 (half the accumulator traffic per product) against 1.68 with 32x32x16.  In this kernel that is 2.59 ms
+//   instead of 2.85 (gate/up, 18560 x 22016 x 4096), 1.40 instead of 1.48 (down), 0.56 instead of 0.61 (o).
+// * A slab layout: rows of PK halves; chunk c (16 bytes) of row r sits in slot c ^ swz(r).  The LDS serves a 16-byte
+//   read in groups of 16 lanes, {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} of each half-wave pair, so a group of the
+//   16x16 reads mixes two chunk columns; swz is chosen so that such a group covers all 64 banks (plain (r >> 2) & 3
+//   for 64-byte rows costs a two-way conflict there).  The weight slab is in fragment order and needs no swizzle.
+// * Every variant runs the same sequence of MFMAs per output element (k ascending, one chain), so a sequence's bits do
+//   not depend on which tile its batch selects.
 
-  // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a
-  // contiguous run of tiles, walked in groups of GM row-tiles that share the same weight columns.
-  const int nblk = tiles_m * tiles_n;
-  const int per_xcd = gridDim.x >> 3;
-  const int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (pid >= nblk) return;
-  constexpr int GM = 4;
-  const int per_group = GM * tiles_n;
-  const int grp = pid / per_group;
-  const int first_m = grp * GM;
-  const int gm = min(tiles_m - first_m, GM);
-  const int in_grp = pid - grp * per_group;
-  const int tm = first_m + in_grp % gm;
-  const int tn = in_grp / gm;
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  // K == 2 * Kw: two-term A with half-precision low terms, the weight slabs wrap; K == 1.5 * Kw and W8: 8-bit low
-  // terms (128 k per slab) against W8
-  const int KB16 = Kw >> 4, KT = K / BK, KTw = Kw / BK;
-
-  // Global -> register -> LDS staging.  Thread t moves 16-byte chunks: chunk (t & 7) of rows
-  // (t >> 3) + i * NTHR/8 of the A slab (XOR-swizzled on the way into LDS), and the linear chunks
-  // t + i * NTHR of the weight slab (fragment order needs no swizzle).
-  const int a_c = t & 7, a_r = t >> 3;
-  const f16* a_ptr[A_ITERS];
-#pragma unroll
-  for (int i = 0; i < A_ITERS; ++i)
-    a_ptr[i] = A + (size_t)min(m0 + a_r + i * (NTHR / 8), M - 1) * lda + a_c * 8;
-  const int a_dst = a_r * BK + ((a_c ^ ((a_r >> 1) & 7)) << 3);   // rows advance by multiples of 16: same swizzle
-  const f16* w_ptr[W_ITERS];
-#pragma unroll
-  for (int i = 0; i < W_ITERS; ++i) {
-    const int q = t + i * NTHR;
-    w_ptr[i] = Wp + ((size_t)(n0 / 32 + (q >> 8)) * KB16) * 512 + (q & 255) * 8;
-  }
-  const f16* w8_ptr[W_ITERS];
-#pragma unroll
-  for (int i = 0; i < W_ITERS; ++i) {
-    const int q = t + i * NTHR;
-    w8_ptr[i] = W8 + ((size_t)(n0 / 32 + (q >> 8)) * KB16) * 256 + (q & 255) * 8;
-  }
-
-  f32x16 acc[MT][NT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-  // fragment addresses inside a slab (elements)
-  const int frow = wm * WTM + (lane & 31);
-  const int fhalf = lane >> 5;
-  int a_off[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) a_off[kk] = frow * BK + (((kk * 2 + fhalf) ^ ((frow >> 1) & 7)) << 3);
-  const int w_off = wn * NT * 4 * 512 + lane * 8;
-
-  u32x4 ra[A_ITERS], rw[W_ITERS];
-#pragma unroll
-  for (int i = 0; i < A_ITERS; ++i) ra[i] = *(const u32x4*)(a_ptr[i]);
-#pragma unroll
-  for (int i = 0; i < W_ITERS; ++i) rw[i] = *(const u32x4*)(w_ptr[i]);
-#pragma unroll
-  for (int i = 0; i < A_ITERS; ++i) *(u32x4*)(As + a_dst + i * (NTHR / 8) * BK) = ra[i];
-#pragma unroll
-  for (int i = 0; i < W_ITERS; ++i) *(u32x4*)(Ws + (t + i * NTHR) * 8) = rw[i];
-  __syncthreads();
-
-  for (int kt = 0; kt < KT; ++kt) {
-    // Prefetch the next slab into registers (the last iteration re-reads its own slab: harmless, and
-    // it keeps the loop body one straight-line block that the scheduler can interleave freely).
-    const int kn = min(kt + 1, KT - 1);
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) ra[i] = *(const u32x4*)(a_ptr[i] + kn * BK);
-    const int knw = kn >= KTw ? kn - KTw : kn;
-#pragma unroll
-    for (int i = 0; i < W_ITERS; ++i)
-      rw[i] = *(const u32x4*)((LO8 && kn >= KTw ? w8_ptr[i] : w_ptr[i]) + (size_t)knw * 4 * 512);
-    __builtin_amdgcn_sched_barrier(0);   // keep the prefetch at the top: its latency hides under the MFMAs
-    const f16* as = As + (kt & 1) * BM * BK;
-    const f16* ws = Ws + (kt & 1) * BN * BK + w_off;
-    if (LO8 && kt >= KTw) {              // a slab of 8-bit low terms: two 64-k products per accumulator tile
-      f16x8 a4[4][MT], b4[4][NT];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) a4[kk][mt] = *(const f16x8*)(as + a_off[kk] + mt * 32 * BK);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) b4[kk][nt] = *(const f16x8*)(ws + (nt * 4 + kk) * 512);
-      }
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            acc[mt][nt] = mfma_lo8(a4[2 * m][mt], a4[2 * m + 1][mt], b4[2 * m][nt], b4[2 * m + 1][nt], acc[mt][nt]);
-      __builtin_amdgcn_sched_barrier(0);
-      f16* asn = As + ((kt + 1) & 1) * BM * BK;
-      f16* wsn = Ws + ((kt + 1) & 1) * BN * BK;
-#pragma unroll
-      for (int i = 0; i < A_ITERS; ++i) *(u32x4*)(asn + a_dst + i * (NTHR / 8) * BK) = ra[i];
-#pragma unroll
-      for (int i = 0; i < W_ITERS; ++i) *(u32x4*)(wsn + (t + i * NTHR) * 8) = rw[i];
-      __syncthreads();
-      continue;
-    }
-    f16x8 af[2][MT], bfr[2][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) af[0][mt] = *(const f16x8*)(as + a_off[0] + mt * 32 * BK);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) bfr[0][nt] = *(const f16x8*)(ws + nt * 4 * 512);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int cur = kk & 1, nxt = cur ^ 1;
-      if (kk + 1 < 4) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) af[nxt][mt] = *(const f16x8*)(as + a_off[kk + 1] + mt * 32 * BK);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) bfr[nxt][nt] = *(const f16x8*)(ws + (nt * 4 + kk + 1) * 512);
-      }
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[cur][mt], bfr[cur][nt], acc[mt][nt], 0, 0, 0);
-      // Scheduling hint: spread the LDS reads of the next k-step between the MFMAs of this one.
-      if (kk + 1 < 4) {
-#pragma unroll
-        for (int i = 0; i < MT + NT; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, (MT * NT) / (MT + NT), 0);   // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                       // DS read
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f16* asn = As + ((kt + 1) & 1) * BM * BK;
-    f16* wsn = Ws + ((kt + 1) & 1) * BN * BK;
-#pragma unroll
-    for (int i = 0; i < A_ITERS; ++i) *(u32x4*)(asn + a_dst + i * (NTHR / 8) * BK) = ra[i];
-#pragma unroll
-    for (int i = 0; i < W_ITERS; ++i) *(u32x4*)(wsn + (t + i * NTHR) * 8) = rw[i];
-    __syncthreads();
-  }
-  epi.template apply<MT, NT>(acc, m0 + wm * WTM, n0 + wn * WTN, lane, M);
-}
-
-// ---- variant with direct global->LDS loads -----------------------------------------------------------
-// Same tiling and LDS layout, but the slabs go from global memory straight into LDS
-// (global_load_lds_dwordx4: lane l of a wave instruction deposits its 16 bytes at the wave-uniform
-// LDS base + 16*l), so there is no register staging and no ds_write.  For the row-major A slab one
-// instruction covers 8 rows x 128 bytes and the swizzle is applied on the source side: the lane that
-// fills slot s of row r fetches chunk s ^ ((r >> 1) & 7).  The weight slab is already in fragment
-// order, so it is a linear copy.  Per k-tile every wave first reads ALL its fragments of the current
-// slab into registers, then issues the loads of the next slab into the other buffer, then runs its
-// MFMAs; the loads have the whole MFMA phase to land and are waited for (vmcnt) only before the
-// barrier that opens the next k-tile.
 // 16 bytes per lane from global memory straight into LDS at lds_wave_base + 16 * lane.  The builtin only
 // exists in the device pass; the host pass just needs the kernel's stub.
 __device__ __forceinline__ void load_to_lds_16(const f16* src, f16* lds_wave_base) {
@@ -542,149 +272,97 @@ __device__ __forceinline__ void load_to_lds_16(const f16* src, f16* lds_wave_bas
   (void)lds_wave_base;
 #endif
 }
-
-// ---- 4-stage pipelined variant ------------------------------------------------------------------------
-// 256x256 tiles, k-slabs of 32 (16 KiB of A + 16 KiB of W per stage, four stages = 128 KiB of LDS), loaded
-// straight into LDS three slabs ahead of the MFMAs.  The compiler cannot tell the stages apart and would
-// wait for ALL outstanding LDS loads before any LDS read, so the fragment reads are issued from inline
-// assembly and the waits are explicit: vmcnt(2 * loads-per-slab) leaves the two newest slabs in flight,
-// one barrier per slab publishes the landed slab and retires the oldest buffer, which is refilled at once.
-// A slab layout: 64-byte rows, 16-byte chunk c of row r in slot c ^ ((r >> 2) & 3) (any 16 consecutive
-// rows of a chunk column then cover all 64 banks); one load instruction covers 16 rows.
-constexpr int PK = 32;                       // slab depth
-constexpr int P_STAGES = 4;
-constexpr int P_STAGE_HALVES = 256 * PK;     // per operand
-
-// Issues the fragment reads of one slab (no wait).  The destination registers must not be touched
-// until frags_arrived() has been executed on them.  Two wave tiles are supported: 64x128 and 128x128.
-__device__ __forceinline__ void read_frags_asm(f16x8 (&af)[2][2], f16x8 (&bfr)[2][4], unsigned a0, unsigned a1,
-                                               unsigned w) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile(
-      "ds_read_b128 %0, %12\n\t"
-      "ds_read_b128 %1, %12 offset:2048\n\t"
-      "ds_read_b128 %4, %14\n\t"
-      "ds_read_b128 %5, %14 offset:2048\n\t"
-      "ds_read_b128 %6, %14 offset:4096\n\t"
-      "ds_read_b128 %7, %14 offset:6144\n\t"
-      "ds_read_b128 %2, %13\n\t"
-      "ds_read_b128 %3, %13 offset:2048\n\t"
-      "ds_read_b128 %8, %14 offset:1024\n\t"
-      "ds_read_b128 %9, %14 offset:3072\n\t"
-      "ds_read_b128 %10, %14 offset:5120\n\t"
-      "ds_read_b128 %11, %14 offset:7168"
-      : "=&v"(af[0][0]), "=&v"(af[0][1]), "=&v"(af[1][0]), "=&v"(af[1][1]), "=&v"(bfr[0][0]), "=&v"(bfr[0][1]),
-        "=&v"(bfr[0][2]), "=&v"(bfr[0][3]), "=&v"(bfr[1][0]), "=&v"(bfr[1][1]), "=&v"(bfr[1][2]), "=&v"(bfr[1][3])
-      : "v"(a0), "v"(a1), "v"(w)
-      : "memory");
-#endif
-}
-__device__ __forceinline__ void read_frags_asm(f16x8 (&af)[2][4], f16x8 (&bfr)[2][4], unsigned a0, unsigned a1,
-                                               unsigned w) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile(
-      "ds_read_b128 %0, %16\n\t"
-      "ds_read_b128 %1, %16 offset:2048\n\t"
-      "ds_read_b128 %8, %18\n\t"
-      "ds_read_b128 %9, %18 offset:2048\n\t"
-      "ds_read_b128 %2, %16 offset:4096\n\t"
-      "ds_read_b128 %3, %16 offset:6144\n\t"
-      "ds_read_b128 %10, %18 offset:4096\n\t"
-      "ds_read_b128 %11, %18 offset:6144\n\t"
-      "ds_read_b128 %4, %17\n\t"
-      "ds_read_b128 %5, %17 offset:2048\n\t"
-      "ds_read_b128 %12, %18 offset:1024\n\t"
-      "ds_read_b128 %13, %18 offset:3072\n\t"
-      "ds_read_b128 %6, %17 offset:4096\n\t"
-      "ds_read_b128 %7, %17 offset:6144\n\t"
-      "ds_read_b128 %14, %18 offset:5120\n\t"
-      "ds_read_b128 %15, %18 offset:7168"
-      : "=&v"(af[0][0]), "=&v"(af[0][1]), "=&v"(af[0][2]), "=&v"(af[0][3]), "=&v"(af[1][0]), "=&v"(af[1][1]),
-        "=&v"(af[1][2]), "=&v"(af[1][3]), "=&v"(bfr[0][0]), "=&v"(bfr[0][1]), "=&v"(bfr[0][2]), "=&v"(bfr[0][3]),
-        "=&v"(bfr[1][0]), "=&v"(bfr[1][1]), "=&v"(bfr[1][2]), "=&v"(bfr[1][3])
-      : "v"(a0), "v"(a1), "v"(w)
-      : "memory");
-#endif
-}
-
-// Waits for every outstanding LDS read of this wave; the fragments are in/out operands so that nothing
-// that uses them can be scheduled above the wait.
-__device__ __forceinline__ void frags_arrived(f16x8 (&af)[2][2], f16x8 (&bfr)[2][4]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(af[0][0]), "+v"(af[0][1]), "+v"(af[1][0]), "+v"(af[1][1]), "+v"(bfr[0][0]), "+v"(bfr[0][1]),
-                 "+v"(bfr[0][2]), "+v"(bfr[0][3]), "+v"(bfr[1][0]), "+v"(bfr[1][1]), "+v"(bfr[1][2]), "+v"(bfr[1][3])
-               :
-               : "memory");
-#endif
-}
-__device__ __forceinline__ void frags_arrived(f16x8 (&af)[2][4], f16x8 (&bfr)[2][4]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(0)"
-               : "+v"(af[0][0]), "+v"(af[0][1]), "+v"(af[0][2]), "+v"(af[0][3]), "+v"(af[1][0]), "+v"(af[1][1]),
-                 "+v"(af[1][2]), "+v"(af[1][3]), "+v"(bfr[0][0]), "+v"(bfr[0][1]), "+v"(bfr[0][2]), "+v"(bfr[0][3]),
-                 "+v"(bfr[1][0]), "+v"(bfr[1][1]), "+v"(bfr[1][2]), "+v"(bfr[1][3])
-               :
-               : "memory");
-#endif
-}
-
-// One fragment read with a compile-time byte offset (no wait; see frags_arrived).
+// One fragment read with a compile-time byte offset (no wait: the register must not be touched before wait_lds() and
+// hold() have been executed).
 template <int OFF>
 __device__ __forceinline__ void read_frag_asm(f16x8& dst, unsigned addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 #endif
 }
-
-// Waits until at most N LDS reads of this wave are outstanding (they complete in issue order) and ties the
-// eight fragments of one k-step to the wait, so that nothing that uses them is scheduled above it.
-template <int N>
-__device__ __forceinline__ void frags_fence(f16x8 (&a)[4], f16x8 (&b)[4]) {
+__device__ __forceinline__ void wait_lds() {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(%8)"
-               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3])
-               : "n"(N)
-               : "memory");
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #endif
 }
-
+// Ties a fragment to the wait before it: nothing that uses it can be scheduled above.
+__device__ __forceinline__ void hold(f16x8& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 #endif
 }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+  (std::make_integer_sequence<int, N>{});
+}
 
-// SPLITK (with EpiPartial; one row of tiles, M <= 256): A is in the fragment order of the decode path
-// ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), `tiles_m` is
-// the number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
-template <int WGM, int WGN, class Epi, bool LO8, bool SPLITK = false>
-__global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_f16_pipe_kernel(const f16* __restrict__ A, int lda,
-                                                                         const f16* __restrict__ Wp,
-                                                                         const f16* __restrict__ W8, int M, int N,
-                                                                         int K, int Kw, int tiles_m, int tiles_n,
-                                                                         Epi epi_in) {
-  constexpr int BM = 256, BN = 256, NW = WGM * WGN;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN, MT = WTM / 32, NT = WTN / 32;
-  constexpr int A_INSTR = (BM / 16) / NW;      // 16 rows per load instruction -> 2 per wave
-  constexpr int W_INSTR = (BN * PK * 2 / 1024) / NW;   // 2 per wave
-  constexpr int LPS = A_INSTR + W_INSTR;       // loads per slab per wave
+template <int INST> struct MfmaAcc;
+template <> struct MfmaAcc<32> { typedef f32x16 type; static constexpr int regs = 16, k = 16; };
+template <> struct MfmaAcc<16> { typedef f32x4 type; static constexpr int regs = 4, k = 32; };
+
+// acc += one product of the fragments: half precision (a0, b0), or the 8-bit low terms held by (a0, a1), (b0, b1)
+template <bool LOW>
+__device__ __forceinline__ void mma(f32x16& acc, const f16x8& a0, const f16x8& a1, const f16x8& b0, const f16x8& b1) {
+  if constexpr (LOW) acc = mfma_lo8(a0, a1, b0, b1, acc);
+  else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b0, acc, 0, 0, 0);
+}
+template <bool LOW>
+__device__ __forceinline__ void mma(f32x4& acc, const f16x8& a0, const f16x8&, const f16x8& b0, const f16x8&) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b0, acc, 0, 0, 0);
+}
+
+template <int PK>
+__device__ __forceinline__ int a_swizzle(int r) {
+  if constexpr (PK == 32) {
+    const int q = (r >> 2) & 3;
+    return ((q & 1) << 1) ^ ((q >> 1) * 3);            // 0, 2, 3, 1
+  } else {
+    return (r >> 1) & 7;
+  }
+}
+
+// LO8: the launch has slabs of 8-bit low terms (W8 != nullptr): K == 1.5 * Kw, A row = [hi: Kw halves | lo8: Kw bytes].
+// Otherwise K == Kw, or K == 2 * Kw (half-precision low terms behind the high terms: the weight slabs wrap).
+// SPLITK (with EpiPartial; one row of tiles, M <= BM): A is in the fragment order of the decode path
+// ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), tiles_m is the
+// number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
+template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, class Epi, bool LO8, bool SPLITK>
+__global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16* __restrict__ A, int lda,
+                                                                   const f16* __restrict__ Wp,
+                                                                   const f16* __restrict__ W8, int M, int K, int Kw,
+                                                                   int tiles_m, int tiles_n, Epi epi_in) {
+  static_assert(INST == 32 || !LO8, "the 8-bit low-term pass is written for the 32x32x64 instruction");
+  typedef typename MfmaAcc<INST>::type Acc;
+  constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / INST, NT = WN / INST;
+  constexpr int KS = PK / MfmaAcc<INST>::k, KS16 = PK / 16;   // k-steps of a slab; 16-k blocks of a slab
+  constexpr int AP = BM * PK / 512 / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;   // KiB pieces per wave and slab
+  static_assert(AP * NW * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
+  constexpr int A_HALVES = BM * PK, STAGE_HALVES = (BM + BN) * PK;
+  constexpr int RPP = 512 / PK;                        // rows of A per piece
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f16* As = (f16*)smem;                        // [4][256*32]
-  f16* Ws = As + P_STAGES * P_STAGE_HALVES;    // [4][256*32]
+  f16* lds = (f16*)smem;                               // [S][A slab | W slab]
 
+  // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a contiguous run of
+  // tiles, walked in groups of GM row-tiles that share the same weight columns (4 and 8 measure alike for the small
+  // tiles; the 256-row tile is 4 % slower with 8 at 18560 rows, where the L2 then holds too few weight columns).
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = gridDim.x >> 3;
   const int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (pid >= nblk) return;
   int tm, tn, kz = 0;
-  if constexpr (SPLITK) {                      // consecutive workgroups of an XCD share a K slice (the A slabs)
+  if constexpr (SPLITK) {                              // consecutive workgroups of an XCD share a K slice (the A slabs)
     tm = 0;
     tn = pid % tiles_n;
     kz = pid / tiles_n;
   } else {
-    constexpr int GM = 4;
+    constexpr int GM = BM >= 256 ? 4 : 8;
     const int per_group = GM * tiles_n;
     const int grp = pid / per_group;
     const int first_m = grp * GM;
@@ -699,272 +377,208 @@ __global__ __launch_bounds__(WGM * WGN * 64, 1) void gemm_f16_pipe_kernel(const 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  // K == 2 * Kw: two-term A with half-precision low terms, the weight slabs wrap; K == 1.5 * Kw and W8: 8-bit low
-  // terms, whose slabs (64 k each, same bytes as a 32-k slab of halves) come after the KTw slabs of high terms
   const int KB16 = Kw >> 4;
-  int KT = K / PK, KTw = Kw / PK;
-  size_t slab0 = 0;                                      // first slab of this workgroup's K range
+  int KT = K / PK, KTw = Kw / PK;                      // slabs; of which the first KTw are high terms
+  size_t kb0 = 0;                                      // first 16-k block of this workgroup's K range
   if constexpr (SPLITK) {
-    // slices in units of two slabs (64 k), so that every slice has an even number of slabs; K == 2 * Kw: the
-    // slice of low-term slabs follows the slice of high-term slabs, against the same weight slabs
-    const int U = Kw >> 6, u0 = (int)((long long)kz * U / tiles_m), u1 = (int)((long long)(kz + 1) * U / tiles_m);
-    slab0 = 2 * (size_t)u0;
-    KTw = 2 * (u1 - u0);
-    KT = K > Kw ? 2 * KTw : KTw;
+    static_assert(PK == 64, "slices are cut in units of 64 k");
+    const int u0 = (int)((long long)kz * KTw / tiles_m), u1 = (int)((long long)(kz + 1) * KTw / tiles_m);
+    kb0 = (size_t)u0 * KS16;
+    KTw = u1 - u0;
+    KT = K > Kw ? 2 * KTw : KTw;                       // the low-term slabs of the slice follow its high-term slabs
     epi.part += (size_t)kz * epi.plane_rows * epi.N;
   }
 
-  const f16* a_src[A_INSTR];
-  const f16* a_lo_src[A_INSTR];
+  const f16* a_src[AP];
+  const f16* a_lo_src[AP];
 #pragma unroll
-  for (int i = 0; i < A_INSTR; ++i) {
+  for (int i = 0; i < AP; ++i) {
     if constexpr (SPLITK) {
-      const int j = wave * A_INSTR + i;                  // KiB of the slab: block row j/2 (clamped to the rows
-      const int rb = min(j >> 1, (M - 1) >> 5);          // that exist), k-step j%2
-      const size_t off = ((size_t)rb * KB16 + 2 * slab0 + (j & 1)) * 512 + lane * 8;
+      const int j = wave * AP + i;                     // piece of the slab: block row j / KS16 (clamped to the rows
+      const int rb = min(j / KS16, (M - 1) >> 5);      // that exist), 16-k block j % KS16
+      const size_t off = ((size_t)rb * KB16 + kb0 + j % KS16) * 512 + lane * 8;
       a_src[i] = A + off;
       a_lo_src[i] = (epi.a_lo ? epi.a_lo : A) + off;
     } else {
-      const int r = (wave * A_INSTR + i) * 16 + (lane >> 2);
-      const int c = (lane & 3) ^ ((r >> 2) & 3);
+      const int r = (wave * AP + i) * RPP + lane / (PK / 8);
+      const int c = (lane % (PK / 8)) ^ a_swizzle<PK>(r);
       a_src[i] = A + (size_t)min(m0 + r, M - 1) * lda + c * 8;
-      a_lo_src[i] = a_src[i];
+      a_lo_src[i] = nullptr;
     }
   }
-  auto a_slab = [&](int i, int ks) {                     // source of the i-th activation load of slab ks
-    if constexpr (SPLITK) return ks < KTw ? a_src[i] + (size_t)ks * 2 * 512 : a_lo_src[i] + (size_t)(ks - KTw) * 2 * 512;
-    else return a_src[i] + (size_t)ks * PK;
-  };
-  const f16* w_src[W_INSTR];
+  const f16* w_src[WP];
+  const f16* w8_src[WP];
 #pragma unroll
-  for (int i = 0; i < W_INSTR; ++i) {
-    const int j = wave * W_INSTR + i;                    // KiB of the slab: block row j/2, k-step j%2
-    w_src[i] = Wp + ((size_t)(n0 / 32 + (j >> 1)) * KB16 + 2 * slab0 + (j & 1)) * 512 + lane * 8;
+  for (int i = 0; i < WP; ++i) {
+    const int j = wave * WP + i;                       // piece of the slab: block row j / KS16, 16-k block j % KS16
+    w_src[i] = Wp + ((size_t)(n0 / 32 + j / KS16) * KB16 + kb0 + j % KS16) * 512 + lane * 8;
+    w8_src[i] = LO8 ? W8 + (size_t)(n0 / 32 + j / KS16) * KB16 * 256 + (j % KS16) * 512 + lane * 8 : nullptr;
   }
-  const f16* w8_src[W_INSTR];
-#pragma unroll
-  for (int i = 0; i < W_INSTR; ++i) {
-    const int j = wave * W_INSTR + i;
-    w8_src[i] = W8 + (size_t)(n0 / 32 + (j >> 1)) * KB16 * 256 + (j & 1) * 512 + lane * 8;
-  }
-  auto w_slab = [&](int i, int ks) {                     // source of the i-th weight load of slab ks
-    return ks < KTw ? w_src[i] + (size_t)ks * 2 * 512 : (LO8 ? w8_src[i] : w_src[i]) + (size_t)(ks - KTw) * 2 * 512;
-  };
-  auto issue = [&](int kt) {                             // slab kt (clamped) into buffer kt % 4
-    const int buf = kt & (P_STAGES - 1);
-    const int ks = min(kt, KT - 1);
-    f16* as = As + buf * P_STAGE_HALVES + wave * A_INSTR * 512;
-    f16* ws = Ws + buf * P_STAGE_HALVES + wave * W_INSTR * 512;
-#pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) load_to_lds_16(a_slab(i, ks), as + i * 512);
-#pragma unroll
-    for (int i = 0; i < W_INSTR; ++i) load_to_lds_16(w_slab(i, ks), ws + i * 512);
+  auto issue_one = [&](int kt, auto I) {               // piece I of this wave's share of slab kt (clamped)
+    constexpr int i = decltype(I)::value;
+    const int ks = min(kt, KT - 1), kw = ks >= KTw ? ks - KTw : ks;
+    f16* base = lds + (kt % S) * STAGE_HALVES;
+    if constexpr (i < AP) {
+      const f16* src;
+      if constexpr (SPLITK) src = (ks >= KTw ? a_lo_src[i] : a_src[i]) + (size_t)kw * KS16 * 512;
+      else src = a_src[i] + (size_t)ks * PK;
+      load_to_lds_16(src, base + (wave * AP + i) * 512);
+    } else {
+      constexpr int j = i - AP;
+      load_to_lds_16((LO8 && ks >= KTw ? w8_src[j] : w_src[j]) + (size_t)kw * KS16 * 512,
+                     base + A_HALVES + (wave * WP + j) * 512);
+    }
   };
 
-  f32x16 acc[MT][NT];
+  Acc acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < MfmaAcc<INST>::regs; ++e) acc[i][j][e] = 0.0f;
 
-  // LDS byte addresses of this lane's fragments inside buffer 0
+  // LDS byte addresses of this lane's fragments inside stage 0.  A lane of a fragment is (row l % INST, k group
+  // l / INST of 8 k); in fragment order its 16 bytes are at 16 * (row & 31) + 512 * (group & 1) of 16-k block group / 2.
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char*)smem);
-  const int frow = wm * WTM + (lane & 31);
-  const int fhalf = lane >> 5;
-  // (SPLITK: the A slab sits in LDS in fragment order like the weights: block row rb, k-step s at KiB 2 rb + s)
-  const unsigned a_k0 = SPLITK ? lds0 + (unsigned)(wm * MT * 2) * 1024u + (unsigned)lane * 16u
-                               : lds0 + 2u * (unsigned)(frow * PK + (((0 + fhalf) ^ ((frow >> 2) & 3)) << 3));
-  const unsigned a_k1 = SPLITK ? a_k0 + 1024u
-                               : lds0 + 2u * (unsigned)(frow * PK + (((2 + fhalf) ^ ((frow >> 2) & 3)) << 3));
-  const unsigned w_b = lds0 + 2u * (unsigned)(P_STAGES * P_STAGE_HALVES + wn * NT * 2 * 512 + lane * 8);
-
-  // Fragments are double buffered in registers: while the MFMAs of slab kt run, the reads of slab kt+1
-  // are already in flight, so the LDS latency and the read burst after each barrier hide under MFMA work.
-  f16x8 af[2][2][MT], bfr[2][2][NT];
-  auto stage_off = [&](int kt) { return (unsigned)(kt & (P_STAGES - 1)) * (2u * P_STAGE_HALVES); };
-  // One workgroup-wide slab step.  With two waves per SIMD (8 waves) the other wave's MFMAs cover this wave's
-  // bursts of fragment reads and load issues; with one wave per SIMD (4 waves, 128x128 wave tile) every read and
-  // every load is slotted between two MFMAs instead, so the matrix pipe never waits for the issue of a burst.
-  auto issue_one = [&](int kt, int i) {      // i-th load instruction of slab kt (A first, then W)
-    const int buf = kt & (P_STAGES - 1);
-    const int ks = min(kt, KT - 1);
-    if (i < A_INSTR)
-      load_to_lds_16(a_slab(i, ks), As + buf * P_STAGE_HALVES + (wave * A_INSTR + i) * 512);
-    else
-      load_to_lds_16(w_slab(i - A_INSTR, ks), Ws + buf * P_STAGE_HALVES + (wave * W_INSTR + i - A_INSTR) * 512);
-  };
-  auto step = [&](int kt, int f) {           // f = kt & 1, passed as a constant by the unrolled caller
-    wait_vmcnt<LPS>();                       // this wave's loads of slab kt+1 have landed (kt+2 may be in flight)
-    __builtin_amdgcn_s_barrier();            // ... everyone's have; everyone holds slab kt in registers
-    if constexpr (NW == 8) {
-      // 16 MFMAs, and between them the 12 fragment reads of slab kt+1 and the 4 loads of slab kt+3, one each
-      const unsigned so = stage_off(kt + 1);
-      const unsigned ra0 = a_k0 + so, ra1 = a_k1 + so, rw = w_b + so;
-#define VLA_MF(kk, mt, nt) \
-  acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[f][kk][mt], bfr[f][kk][nt], acc[mt][nt], 0, 0, 0)
-#define VLA_SB __builtin_amdgcn_sched_barrier(0)
-      VLA_MF(0, 0, 0); read_frag_asm<0>(af[f ^ 1][0][0], ra0); VLA_SB;
-      VLA_MF(0, 0, 1); read_frag_asm<0>(bfr[f ^ 1][0][0], rw); VLA_SB;
-      VLA_MF(0, 0, 2); read_frag_asm<2048>(af[f ^ 1][0][1], ra0); VLA_SB;
-      VLA_MF(0, 0, 3); read_frag_asm<2048>(bfr[f ^ 1][0][1], rw); VLA_SB;
-      VLA_MF(0, 1, 0); read_frag_asm<4096>(bfr[f ^ 1][0][2], rw); VLA_SB;
-      VLA_MF(0, 1, 1); read_frag_asm<6144>(bfr[f ^ 1][0][3], rw); VLA_SB;
-      VLA_MF(0, 1, 2); read_frag_asm<0>(af[f ^ 1][1][0], ra1); VLA_SB;
-      VLA_MF(0, 1, 3); read_frag_asm<2048>(af[f ^ 1][1][1], ra1); VLA_SB;
-      VLA_MF(1, 0, 0); read_frag_asm<1024>(bfr[f ^ 1][1][0], rw); VLA_SB;
-      VLA_MF(1, 0, 1); issue_one(kt + 3, 0); VLA_SB;
-      VLA_MF(1, 0, 2); read_frag_asm<3072>(bfr[f ^ 1][1][1], rw); VLA_SB;
-      VLA_MF(1, 0, 3); issue_one(kt + 3, 1); VLA_SB;
-      VLA_MF(1, 1, 0); read_frag_asm<5120>(bfr[f ^ 1][1][2], rw); VLA_SB;
-      VLA_MF(1, 1, 1); issue_one(kt + 3, 2); VLA_SB;
-      VLA_MF(1, 1, 2); read_frag_asm<7168>(bfr[f ^ 1][1][3], rw); VLA_SB;
-      VLA_MF(1, 1, 3); issue_one(kt + 3, 3); VLA_SB;
-#undef VLA_MF
-#undef VLA_SB
-    } else {
-      static_assert(NW == 8 || (MT == 4 && NT == 4 && LPS == 8), "interleaved schedule is written for 128x128 wave tiles");
-      const unsigned so = stage_off(kt + 1);
-      const unsigned ra0 = a_k0 + so, ra1 = a_k1 + so, rw = w_b + so;
-#define VLA_MF(kk, mt, nt) \
-  acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[f][kk][mt], bfr[f][kk][nt], acc[mt][nt], 0, 0, 0)
-#define VLA_SB __builtin_amdgcn_sched_barrier(0)
-      // Slots between the 32 MFMAs: a fragment read of slab kt+1 after every even one (first its k-step 0, then
-      // its k-step 1), a load of slab kt+3 after every fourth.  The LDS thus sees one read per two MFMAs instead
-      // of a burst, and the two waits below only ask for the eight reads that are needed next.
-      VLA_MF(0, 0, 0); read_frag_asm<0>(af[f ^ 1][0][0], ra0); VLA_SB;
-      VLA_MF(0, 0, 1); issue_one(kt + 3, 0); VLA_SB;
-      VLA_MF(0, 0, 2); read_frag_asm<0>(bfr[f ^ 1][0][0], rw); VLA_SB;
-      VLA_MF(0, 0, 3); VLA_SB;
-      VLA_MF(0, 1, 0); read_frag_asm<2048>(af[f ^ 1][0][1], ra0); VLA_SB;
-      VLA_MF(0, 1, 1); issue_one(kt + 3, 1); VLA_SB;
-      VLA_MF(0, 1, 2); read_frag_asm<2048>(bfr[f ^ 1][0][1], rw); VLA_SB;
-      VLA_MF(0, 1, 3); VLA_SB;
-      VLA_MF(0, 2, 0); read_frag_asm<4096>(af[f ^ 1][0][2], ra0); VLA_SB;
-      VLA_MF(0, 2, 1); issue_one(kt + 3, 2); VLA_SB;
-      VLA_MF(0, 2, 2); read_frag_asm<4096>(bfr[f ^ 1][0][2], rw); VLA_SB;
-      VLA_MF(0, 2, 3); VLA_SB;
-      VLA_MF(0, 3, 0); read_frag_asm<6144>(af[f ^ 1][0][3], ra0); VLA_SB;
-      VLA_MF(0, 3, 1); issue_one(kt + 3, 3); VLA_SB;
-      VLA_MF(0, 3, 2); read_frag_asm<6144>(bfr[f ^ 1][0][3], rw); VLA_SB;
-      VLA_MF(0, 3, 3); VLA_SB;
-      // k-step 1 of slab kt was read during the second half of the previous step: eight newer reads may be pending
-      frags_fence<8>(af[f][1], bfr[f][1]);
-      VLA_SB;
-      VLA_MF(1, 0, 0); read_frag_asm<0>(af[f ^ 1][1][0], ra1); VLA_SB;
-      VLA_MF(1, 0, 1); issue_one(kt + 3, 4); VLA_SB;
-      VLA_MF(1, 0, 2); read_frag_asm<1024>(bfr[f ^ 1][1][0], rw); VLA_SB;
-      VLA_MF(1, 0, 3); VLA_SB;
-      VLA_MF(1, 1, 0); read_frag_asm<2048>(af[f ^ 1][1][1], ra1); VLA_SB;
-      VLA_MF(1, 1, 1); issue_one(kt + 3, 5); VLA_SB;
-      VLA_MF(1, 1, 2); read_frag_asm<3072>(bfr[f ^ 1][1][1], rw); VLA_SB;
-      VLA_MF(1, 1, 3); VLA_SB;
-      VLA_MF(1, 2, 0); read_frag_asm<4096>(af[f ^ 1][1][2], ra1); VLA_SB;
-      VLA_MF(1, 2, 1); issue_one(kt + 3, 6); VLA_SB;
-      VLA_MF(1, 2, 2); read_frag_asm<5120>(bfr[f ^ 1][1][2], rw); VLA_SB;
-      VLA_MF(1, 2, 3); VLA_SB;
-      VLA_MF(1, 3, 0); read_frag_asm<6144>(af[f ^ 1][1][3], ra1); VLA_SB;
-      VLA_MF(1, 3, 1); issue_one(kt + 3, 7); VLA_SB;
-      VLA_MF(1, 3, 2); read_frag_asm<7168>(bfr[f ^ 1][1][3], rw); VLA_SB;
-      VLA_MF(1, 3, 3); VLA_SB;
-      // k-step 0 of slab kt+1 must be in registers before the next step; its k-step 1 may still be on its way
-      frags_fence<8>(af[f ^ 1][0], bfr[f ^ 1][0]);
-#undef VLA_MF
-#undef VLA_SB
-    }
-    if constexpr (NW == 8) frags_arrived(af[f ^ 1], bfr[f ^ 1]);
-  };
-  // The same step for a slab of 8-bit low terms: one 64-k product per accumulator tile (as long as two of the
-  // half-precision ones), operands = the lane's k-step 0 and k-step 1 fragments of the slab taken together.  All
-  // fragment reads of slab kt+1 go into the first half of the step, so they have landed when it ends.
-  auto step8 = [&](int kt, int f) {
-    wait_vmcnt<LPS>();
-    __builtin_amdgcn_s_barrier();
-    frags_arrived(af[f], bfr[f]);            // both k-steps of slab kt are needed at once
-    const unsigned so = stage_off(kt + 1);
-    const unsigned ra0 = a_k0 + so, ra1 = a_k1 + so, rw = w_b + so;
-#define VLA_MF8(mt, nt) acc[mt][nt] = mfma_lo8(af[f][0][mt], af[f][1][mt], bfr[f][0][nt], bfr[f][1][nt], acc[mt][nt])
-#define VLA_SB __builtin_amdgcn_sched_barrier(0)
-    if constexpr (NW == 8) {
-      VLA_MF8(0, 0); read_frag_asm<0>(af[f ^ 1][0][0], ra0); read_frag_asm<0>(bfr[f ^ 1][0][0], rw); VLA_SB;
-      VLA_MF8(0, 1); read_frag_asm<2048>(af[f ^ 1][0][1], ra0); read_frag_asm<2048>(bfr[f ^ 1][0][1], rw); VLA_SB;
-      VLA_MF8(0, 2); read_frag_asm<4096>(bfr[f ^ 1][0][2], rw); read_frag_asm<6144>(bfr[f ^ 1][0][3], rw); VLA_SB;
-      VLA_MF8(0, 3); read_frag_asm<0>(af[f ^ 1][1][0], ra1); read_frag_asm<2048>(af[f ^ 1][1][1], ra1); VLA_SB;
-      VLA_MF8(1, 0); read_frag_asm<1024>(bfr[f ^ 1][1][0], rw); read_frag_asm<3072>(bfr[f ^ 1][1][1], rw); VLA_SB;
-      VLA_MF8(1, 1); read_frag_asm<5120>(bfr[f ^ 1][1][2], rw); read_frag_asm<7168>(bfr[f ^ 1][1][3], rw); VLA_SB;
-      VLA_MF8(1, 2); issue_one(kt + 3, 0); issue_one(kt + 3, 1); VLA_SB;
-      VLA_MF8(1, 3); issue_one(kt + 3, 2); issue_one(kt + 3, 3); VLA_SB;
-    } else {
-      VLA_MF8(0, 0); read_frag_asm<0>(af[f ^ 1][0][0], ra0); read_frag_asm<0>(bfr[f ^ 1][0][0], rw); VLA_SB;
-      VLA_MF8(0, 1); read_frag_asm<2048>(af[f ^ 1][0][1], ra0); read_frag_asm<2048>(bfr[f ^ 1][0][1], rw); VLA_SB;
-      VLA_MF8(0, 2); read_frag_asm<4096>(af[f ^ 1][0][2], ra0); read_frag_asm<4096>(bfr[f ^ 1][0][2], rw); VLA_SB;
-      VLA_MF8(0, 3); read_frag_asm<6144>(af[f ^ 1][0][3], ra0); read_frag_asm<6144>(bfr[f ^ 1][0][3], rw); VLA_SB;
-      VLA_MF8(1, 0); read_frag_asm<0>(af[f ^ 1][1][0], ra1); read_frag_asm<1024>(bfr[f ^ 1][1][0], rw); VLA_SB;
-      VLA_MF8(1, 1); read_frag_asm<2048>(af[f ^ 1][1][1], ra1); read_frag_asm<3072>(bfr[f ^ 1][1][1], rw); VLA_SB;
-      VLA_MF8(1, 2); read_frag_asm<4096>(af[f ^ 1][1][2], ra1); read_frag_asm<5120>(bfr[f ^ 1][1][2], rw); VLA_SB;
-      VLA_MF8(1, 3); read_frag_asm<6144>(af[f ^ 1][1][3], ra1); read_frag_asm<7168>(bfr[f ^ 1][1][3], rw); VLA_SB;
-      VLA_MF8(2, 0); issue_one(kt + 3, 0); VLA_SB;
-      VLA_MF8(2, 1); issue_one(kt + 3, 1); VLA_SB;
-      VLA_MF8(2, 2); issue_one(kt + 3, 2); VLA_SB;
-      VLA_MF8(2, 3); issue_one(kt + 3, 3); VLA_SB;
-      VLA_MF8(3, 0); issue_one(kt + 3, 4); VLA_SB;
-      VLA_MF8(3, 1); issue_one(kt + 3, 5); VLA_SB;
-      VLA_MF8(3, 2); issue_one(kt + 3, 6); VLA_SB;
-      VLA_MF8(3, 3); issue_one(kt + 3, 7); VLA_SB;
-    }
-#undef VLA_MF8
-#undef VLA_SB
-    frags_arrived(af[f ^ 1], bfr[f ^ 1]);
-  };
-  issue(0);
-  issue(1);
-  issue(2);
-  wait_vmcnt<2 * LPS>();
-  __builtin_amdgcn_s_barrier();
-  read_frags_asm(af[0], bfr[0], a_k0, a_k1, w_b);
-  frags_arrived(af[0], bfr[0]);
-  const int KTh = LO8 ? KTw : KT;            // slabs of half-precision terms; the rest are 8-bit low terms
-  for (int kt = 0; kt < KTh; kt += 2) {      // Kw is a multiple of 64: an even number of slabs
-    step(kt, 0);
-    step(kt + 1, 1);
-  }
-  if constexpr (LO8) {
-    for (int kt = KTh; kt < KT; kt += 2) {   // Kw a multiple of 128 (the launcher checks): again an even number
-      step8(kt, 0);
-      step8(kt + 1, 1);
-    }
-  }
-  if constexpr (NW == 4) {                   // the last step leaves eight fragment reads in flight: they must land
-    frags_arrived(af[0], bfr[0]);            // before the registers they write are used for anything else
-    frags_arrived(af[1], bfr[1]);
-  }
-  wait_vmcnt<0>();                           // the clamped tail loads still target this workgroup's LDS
-  __syncthreads();                           // every wave is done with the slabs: LDS becomes epilogue staging
-  float* tile = (float*)smem + wave * kStageFloats;
+  const int frow = wm * WM + (lane & (INST - 1)), fgrp = lane / INST;
+  const unsigned in_block = (unsigned)(fgrp >> 1) * 1024u + (unsigned)(fgrp & 1) * 512u + (unsigned)(lane & (INST - 1)) * 16u;
+  unsigned a_k[KS];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    stage_tile(acc[mt], tile, lane);
-    epi.consume(tile, m0 + wm * WTM + mt * 32, n0 + wn * WTN, lane, M);
+  for (int s = 0; s < KS; ++s) {
+    const int c = (64 / INST) * s + fgrp;              // 16-byte chunk of the row
+    if constexpr (SPLITK) a_k[s] = lds0 + (unsigned)(wm * (WM / 32) * KS16) * 1024u + in_block;
+    else a_k[s] = lds0 + 2u * (unsigned)(frow * PK + ((c ^ a_swizzle<PK>(frow)) << 3));
+  }
+  const unsigned w_b = lds0 + 2u * (unsigned)(A_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
+
+  constexpr int KU = INST == 32 ? 2 : 1, US = KS / KU;         // k-steps per unit, units per slab
+  f16x8 af[2][KU][MT], bf[2][KU][NT];
+  constexpr int RPK = MT + NT, R = KU * RPK, MF = KU * MT * NT;
+  auto read_one = [&](unsigned so, int f, auto U, auto I) {    // I-th fragment read of unit U of a slab
+    constexpr int s = decltype(I)::value / RPK, x = decltype(I)::value % RPK, ss = decltype(U)::value * KU + s;
+    constexpr int j = x < MT ? x : x - MT;
+    // block j of an operand in fragment order: 32 rows hold one or two fragments
+    constexpr int frag = INST == 32 ? (j * KS16 + ss) * 1024 : (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256;
+    if constexpr (x < MT) read_frag_asm<SPLITK ? frag : j * INST * PK * 2>(af[f][s][j], a_k[ss] + so);
+    else read_frag_asm<frag>(bf[f][s][j], w_b + so);
+  };
+  auto arrived = [&](int f) {
+    wait_lds();
+#pragma unroll
+    for (int s = 0; s < KU; ++s) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) hold(af[f][s][i]);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) hold(bf[f][s][j]);
+    }
+  };
+  // One unit of slab kt, its fragments in register buffer F: the MFMAs, and between them the reads of the next unit (in
+  // the first three quarters, so that they have landed at the end).  In the last unit of a slab the next one belongs
+  // to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes slab kt + S.
+  auto unit = [&](int kt, auto F, auto U, auto L8) {
+    constexpr int f = decltype(F)::value, u = decltype(U)::value;
+    constexpr bool low = decltype(L8)::value, last = u == US - 1;
+    constexpr int n_mf = low ? MF / 2 : MF, n_rd = n_mf * 3 / 4 > 0 ? n_mf * 3 / 4 : 1;
+    if constexpr (last) {
+      wait_vmcnt<(S - 2) * LPS>();
+      __builtin_amdgcn_s_barrier();
+    }
+    const unsigned so = (unsigned)((kt + (last ? 1 : 0)) % S) * (2u * STAGE_HALVES);
+    static_for<n_mf>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      constexpr int s = i / (MT * NT), mt = i / NT % MT, nt = i % NT;
+      constexpr int sl = low ? 2 * s : s, sh = low ? 2 * s + 1 : s;
+      mma<low>(acc[mt][nt], af[f][sl][mt], af[f][sh][mt], bf[f][sl][nt], bf[f][sh][nt]);
+      constexpr int r0 = i < n_rd ? i * R / n_rd : R, r1 = i < n_rd ? (i + 1) * R / n_rd : R;
+      static_for<r1 - r0>([&](auto J) {
+        read_one(so, f ^ 1, std::integral_constant<int, last ? 0 : u + 1>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
+      });
+      if constexpr (last) {
+        constexpr int l0 = i * LPS / n_mf, l1 = (i + 1) * LPS / n_mf;
+        static_for<l1 - l0>([&](auto J) { issue_one(kt + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    arrived(f ^ 1);
+  };
+  auto slab = [&](int kt, auto F0, auto L8) {          // slab kt starts in register buffer F0
+    static_for<US>([&](auto U) { unit(kt, std::integral_constant<int, (decltype(F0)::value + decltype(U)::value) & 1>{}, U, L8); });
+  };
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, US & 1> cn{};  // buffer of an odd slab's first unit
+  constexpr std::false_type hi_t{};
+  constexpr std::true_type lo_t{};
+  static_for<S>([&](auto I) { static_for<LPS>([&](auto J) { issue_one(decltype(I)::value, J); }); });
+  wait_vmcnt<(S - 1) * LPS>();
+  __builtin_amdgcn_s_barrier();
+  static_for<R>([&](auto I) { read_one(0u, 0, c0, I); });
+  arrived(0);
+  const int KTh = LO8 ? KTw : KT;
+  int kt = 0;
+  for (; kt + 1 < KTh; kt += 2) {
+    slab(kt, c0, hi_t);
+    slab(kt + 1, cn, hi_t);
+  }
+  if constexpr (LO8) {                                 // Kw is a multiple of 128 here: an even number of high slabs
+    for (; kt + 1 < KT; kt += 2) {
+      slab(kt, c0, lo_t);
+      slab(kt + 1, cn, lo_t);
+    }
+    if (kt < KT) slab(kt, c0, lo_t);
+  } else if (kt < KTh) {
+    slab(kt, c0, hi_t);
+  }
+  wait_vmcnt<0>();                                     // the clamped tail loads still target this workgroup's LDS
+  __syncthreads();                                     // every wave is done with the slabs: LDS becomes epilogue staging
+
+  // The pitch keeps the stores of a 32-row group conflict free: the row groups a store instruction covers (2 of 4 rows
+  // for 32x32, 4 for 16x16) start 32 or 16 banks apart.
+  constexpr bool PAIR = WN < Epi::kSpan;               // two waves side by side share a staging tile
+  static_assert(!PAIR || (WGN % 2 == 0 && 2 * WN >= Epi::kSpan), "an epilogue's span is one or two wave tiles");
+  constexpr int COLS = PAIR ? 2 * WN : WN, PITCH = COLS + (INST == 32 ? 8 : 4), ROWS = PAIR ? 16 : 32;
+  float* tile = (float*)smem + (PAIR ? wave >> 1 : wave) * 32 * PITCH;
+  const int side = PAIR ? wn & 1 : 0;
+#pragma unroll
+  for (int mb = 0; mb < WM / 32; ++mb) {
+    if constexpr (PAIR) {
+      if (mb > 0) __syncthreads();                     // the partner has read the previous rows
+    }
+#pragma unroll
+    for (int mi = 0; mi < 32 / INST; ++mi)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int e = 0; e < MfmaAcc<INST>::regs; ++e) {
+          const int row = INST == 32 ? 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) : mi * 16 + 4 * (lane >> 4) + e;
+          tile[row * PITCH + side * WN + nt * INST + (lane & (INST - 1))] = acc[mb * (32 / INST) + mi][nt][e];
+        }
+    if constexpr (PAIR) __syncthreads();
+    epi.template consume<COLS, PITCH, ROWS>(tile + side * ROWS * PITCH, m0 + wm * WM + mb * 32 + side * ROWS,
+                                            n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
   }
 }
 
-template <int WGM, int WGN, class Epi, bool LO8>
-static void launch_pipe(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  const int tiles_m = (g.M + 255) / 256, tiles_n = g.N / 256;
-  const int nblk = tiles_m * tiles_n;
-  const int grid = (nblk + 7) / 8 * 8;
-  constexpr size_t slabs = 2 * (size_t)P_STAGES * P_STAGE_HALVES * sizeof(f16);
-  constexpr size_t stage = (size_t)WGM * WGN * kStageFloats * sizeof(float);
+template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, bool SPLITK, class Epi>
+static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, int M, int K, int Kw, int tiles_m,
+                         int tiles_n, const Epi& epi, hipStream_t st) {
+  const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
+  constexpr size_t slabs = (size_t)S * (WGM * WM + WGN * WN) * PK * sizeof(f16);
+  constexpr bool pair = WN < Epi::kSpan;
+  constexpr size_t stage = (size_t)WGM * WGN / (pair ? 2 : 1) * 32 * ((pair ? 2 : 1) * WN + (INST == 32 ? 8 : 4)) * sizeof(float);
   constexpr size_t smem = slabs > stage ? slabs : stage;
-  auto kern = gemm_f16_pipe_kernel<WGM, WGN, Epi, LO8>;
+  auto kern = gemm_f16_kernel<INST, WGM, WGN, WM, WN, PK, S, OCC, Epi, LO8, SPLITK>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, g.A, g.lda, g.Wp, g.W8, g.M, g.N, g.K, g.Kw,
-                     tiles_m, tiles_n, epi);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, A, lda, Wp, W8, M, K, Kw, tiles_m, tiles_n, epi);
+}
+template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, class Epi>
+static void launch(const GemmF16& g, const Epi& epi, hipStream_t st) {
+  launch_tiles<INST, WGM, WGN, WM, WN, PK, S, OCC, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
+                                                               (g.M + WGM * WM - 1) / (WGM * WM), g.N / (WGN * WN), epi, st);
 }
 
 // Decode GEMM of a large batch: partial sums of `ksplit` K slices, see EpiPartial and the SPLITK form of the kernel.
@@ -973,73 +587,79 @@ bool splitk_gemm_fits(int M, int N, int K) { return M <= 256 && N % 256 == 0 && 
 int splitk_ksplit(int N, int K) {
   int ks = 256 / (N / 256);                  // about one workgroup per compute unit
   if (ks > kMaxKSplit) ks = kMaxKSplit;
-  while (ks > 1 && K / 64 < 4 * ks) --ks;    // at least 8 slabs per slice
+  while (ks > 1 && K / 64 < 4 * ks) --ks;    // at least 4 slabs per slice
   return ks < 1 ? 1 : ks;
 }
 void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,
                  int plane_rows, int row0, hipStream_t st) {
-  const int tiles_n = N / 256, nblk = tiles_n * ksplit;
-  const int grid = (nblk + 7) / 8 * 8;
-  constexpr size_t slabs = 2 * (size_t)P_STAGES * P_STAGE_HALVES * sizeof(f16);
-  constexpr size_t stage = (size_t)4 * kStageFloats * sizeof(float);
-  constexpr size_t smem = slabs > stage ? slabs : stage;
-  auto kern = gemm_f16_pipe_kernel<2, 2, EpiPartial, false, true>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attr_set = true;
-  }
   const f16* no8 = nullptr;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, st, Afrag, 0, Wp, no8, M, N, Afrag_lo ? 2 * K : K, K, ksplit,
-                     tiles_n, EpiPartial{part, plane_rows, row0, N, Afrag_lo});
+  launch_tiles<16, 4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, Afrag_lo ? 2 * K : K, K, ksplit, N / 256,
+                                                         EpiPartial{part, plane_rows, row0, N, Afrag_lo}, st);
 }
 
-template <int BM, int BN, int WGM, int WGN, class Epi, bool LO8>
-static void launch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = g.N / BN;
-  const int nblk = tiles_m * tiles_n;
-  const int grid = (nblk + 7) / 8 * 8;
-  constexpr size_t smem = 2 * (size_t)(BM + BN) * BK * sizeof(f16);
-  auto kern = gemm_f16_kernel<BM, BN, WGM, WGN, Epi, LO8>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    attr_set = true;
+// ---- tile choice ------------------------------------------------------------------------------------------------
+// The time of a launch is modelled from two measured figures per tile: what a workgroup takes on a chip that is not
+// full (latency and LDS-fill bound: fixed + per_k * K / 1024), and the rate of a chip full of them (power and L2
+// bound).  Full rounds of 256 workgroups cost the larger of the two, the last partial round likewise for its share.
+// Measured on 7B shapes (us at K = 4096 / 11008, PFLOP/s): 64x128 20.5 / 49, 0.84; 128x128 28.6 / 71, 0.97; 128x256
+// 40 / 96, 1.16; 256x256 70 / 175, 1.30.  The model is within 10 % of the measured time of every tile for 64 to 18560
+// rows (o at 290 rows: 21 us with the tile it picks against 70 with 256x256; gate/up at 580: 103 against 157; down at
+// 4640: 395 against 455), so that the right tile is at most a few percent away.
+enum Tile { T_64x128, T_128x128, T_128x256, T_256x256, T_COUNT };
+struct TileCost { int bm, bn; float fixed, per_k, rate; };
+constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.6f, 4.22f, 0.84f}, {128, 128, 3.4f, 6.3f, 0.97f},
+                                         {128, 256, 6.8f, 8.3f, 1.16f}, {256, 256, 8.6f, 15.5f, 1.30f}};
+static Tile pick_tile(int M, int N, int K) {
+  Tile best = T_64x128;
+  float best_us = 1e30f;
+  for (int t = 0; t < T_COUNT; ++t) {
+    const TileCost& c = kTileCost[t];
+    if (N % c.bn) continue;
+    const long long tiles = (long long)((M + c.bm - 1) / c.bm) * (N / c.bn);
+    const float alone = c.fixed + c.per_k * (float)K / 1024.0f;
+    const float per_tile = 2.0f * (float)c.bm * (float)c.bn * (float)K / (c.rate * 1e9f);      // us, full chip
+    const long long rounds = tiles / 256, rest = tiles % 256;
+    const float us = (float)rounds * fmaxf(alone, 256.0f * per_tile) + (rest ? fmaxf(alone, (float)rest * per_tile) : 0.f);
+    if (us < best_us) {
+      best_us = us;
+      best = (Tile)t;
+    }
   }
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, g.A, g.lda, g.Wp, g.W8, g.M, g.N, g.K, g.Kw,
-                     tiles_m, tiles_n, epi);
+  return best;
 }
 
-// Tile choice: big square tiles when there are enough rows to fill them, a 64-row tile for the
-// decode-sized problems.  The QKV epilogue needs wave tiles that cover whole heads (128 columns).
-// kWaves4: the 4-wave (128x128 wave tile) schedule reads a third less from LDS per MFMA and is the faster one
-// for the residual and SwiGLU epilogues; the QKV epilogue measures marginally faster with 8 waves.
-template <bool kWaves4, bool LO8, class Epi>
-static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  if (g.M > 128 && g.N % 256 == 0) {
-    if (kWaves4) launch_pipe<2, 2, Epi, LO8>(g, epi, st);
-    else launch_pipe<4, 2, Epi, LO8>(g, epi, st);
-  } else if (g.N % 256 == 0) {
-    launch<64, 256, 2, 2, Epi, LO8>(g, epi, st);
-  } else {
-    launch<64, 128, 2, 1, Epi, LO8>(g, epi, st);   // N multiple of 128
+// The tiles of up to 128 rows keep two workgroups on a compute unit (64x128, 128x128) or 8 waves (128x256).  256x256:
+// 8 waves of 64x128; slabs of 64 k (half the barriers: 358 against 374 us, gate/up at 2338 rows) except for the residual
+// epilogue over many rounds, where the deeper ring of 32-k slabs hides the reads of x better (18560 rows: o 563
+// against 575 us, down 1436 against 1456).  With low terms: 4 waves of 128x128, a third fewer LDS reads per product,
+// which is what the 32x32 instructions have left to save.
+template <bool LO8, class Epi>
+static void dispatch_lo(const GemmF16& g, const Epi& epi, bool deep_ring, hipStream_t st) {
+  constexpr int I = LO8 ? 32 : 16;
+  switch (pick_tile(g.M, g.N, g.K)) {
+    case T_64x128: launch<I, 2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st); break;
+    case T_128x128: launch<I, 2, 2, 64, 64, 32, 4, 2, LO8>(g, epi, st); break;
+    case T_128x256: launch<I, 2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
+    default:
+      if constexpr (LO8) launch<32, 2, 2, 128, 128, 32, 4, 1, true>(g, epi, st);
+      else if (deep_ring) launch<16, 4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
+      else launch<16, 4, 2, 64, 128, 64, 2, 1, false>(g, epi, st);
   }
 }
-template <bool kWaves4, class Epi>
+template <class Epi>
 static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  if (g.W8) dispatch_lo<kWaves4, true>(g, epi, st);
-  else dispatch_lo<kWaves4, false>(g, epi, st);
+  const bool deep = std::is_same<Epi, EpiResid>::value && (long long)((g.M + 255) / 256) * (g.N / 256) > 512;
+  if (g.W8) dispatch_lo<true>(g, epi, deep, st);
+  else dispatch_lo<false>(g, epi, deep, st);
 }
 
-void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st) {
-  dispatch<true>(g, EpiResid{x, ldx}, st);
-}
+void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st) { dispatch(g, EpiResid{x, ldx}, st); }
 void gemm_f16_swiglu(const GemmF16& g, f16* act, int ldact, int lo_mode, hipStream_t st) {
-  dispatch<true>(g, EpiSwiglu{act, ldact, g.N / 2, lo_mode}, st);
+  dispatch(g, EpiSwiglu{act, ldact, g.N / 2, lo_mode}, st);
 }
 void gemm_f16_qkv(const GemmF16& g, const RopeKv& o, hipStream_t st) {
-  if (o.head_dim == 128) dispatch<false>(g, EpiQkv<128>{o}, st);
-  else dispatch<false>(g, EpiQkv<64>{o}, st);
+  if (o.head_dim == 128) dispatch(g, EpiQkv<128>{o}, st);
+  else dispatch(g, EpiQkv<64>{o}, st);
 }
 
 // ---- weight repacking -------------------------------------------------------------------------------

@@ -1,0 +1,45 @@
+"""The prefill GEMMs choose their tile by the number of rows: at the edges of every tile, and with every tile chosen,
+a sequence gets the same bits whatever its batch (one chain of matrix instructions over ascending k per element), and
+those bits are the oracle's within the tolerance of the 16-bit path."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import vla_oracle as O
+from tests import parity as P
+from tests.test_gpu_parity import ragged_obs
+
+pytestmark = pytest.mark.gpu
+
+# one prefix of 63 rows is filled up to: the edges of the 64-, 128- and 256-row tiles, and enough rows that the cost
+# model moves on to each larger tile (the wide matrices of this shape: 3072 and 5632 columns)
+ROWS = [63, 64, 65, 127, 128, 129, 255, 257, 700, 1500, 4100]
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("hd,ffn,fast", [(128, 2816, False), (128, 2816, True), (64, 1472, False), (64, 704, True)])
+def test_rows_do_not_depend_on_the_tile(hd, ffn, fast):
+    from paper_2603_18464_amd import VlaPolicy
+    # 1472 and 704: gate/up widths that are multiples of 128 only, contractions that are odd multiples of 64
+    shape = W.PolicyShape(2, 1024, 1024 // hd, hd, ffn, 700, dtype="bf16")
+    weights = W.make_weights(shape, 5)
+    first, ref = 63, None
+    for rows in ROWS:
+        rest = rows - first
+        nps = [first - 5] + [120] * (rest // 120) + ([rest % 120] if rest % 120 else [])
+        lens = [5] + [0] * (len(nps) - 1)
+        wl = W.Workload("Gt", 77, shape, batch=len(nps), n_patches=120, instr_len=(0, 5), n_tokens=1)
+        obs = ragged_obs(wl, nps, lens, seed=11)
+        obs["instr_ids"][:] = [3, 99, 5, 400, 17]             # (the generator draws them behind the patches)
+        pol = VlaPolicy(shape, len(nps), 130, rows, precision=1 if fast else 0, two_term_layers=1)
+        pol.load_weights(weights)
+        dev = P.device_inputs(pol, obs)
+        got = pol.prefill(dev["patch_emb"], obs["cu_patch"], dev["instr_ids"], obs["cu_instr"]).cpu().numpy()
+        pol.close()
+        assert np.isfinite(got).all(), rows
+        if ref is None:
+            ref = got[0]
+            pes, ids = P.split_obs(obs, [0])
+            ora = O.OraclePolicy(shape, weights).policy_step(pes, ids, 1, mode="cached")
+            assert np.abs(ref - ora["logits"][0, 0]).max() <= P.tolerances(wl, fast)["logit"]
+        assert np.array_equal(got[0], ref), f"{rows} rows"
