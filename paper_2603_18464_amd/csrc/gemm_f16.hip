@@ -598,19 +598,22 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
-// The time of a launch is modelled from two measured figures per tile: what a workgroup takes on a chip that is not
-// full (latency and LDS-fill bound: fixed + per_k * K / 1024), and the rate of a chip full of them (power and L2
-// bound).  Full rounds of 256 workgroups cost the larger of the two, the last partial round likewise for its share.
-// Measured on 7B shapes (us at K = 4096 / 11008, PFLOP/s): 64x128 20.5 / 49, 0.84; 128x128 28.6 / 71, 0.97; 128x256
-// 40 / 96, 1.16; 256x256 70 / 175, 1.30.  The model is within 10 % of the measured time of every tile for 64 to 18560
-// rows (o at 290 rows: 21 us with the tile it picks against 70 with 256x256; gate/up at 580: 103 against 157; down at
-// 4640: 395 against 455), so that the right tile is at most a few percent away.
-enum Tile { T_64x128, T_128x128, T_128x256, T_256x256, T_COUNT };
+// The time of a launch is modelled from two figures per tile, measured on 7B shapes with weights that come from HBM:
+// what a workgroup takes on a chip that is not full (bound by the latency and rate of its LDS fills: fixed + per_k *
+// K / 1024), and the rate of a chip full of them (bound by power and the L2).  Full rounds of 256 workgroups cost the
+// larger of the two, the last partial round likewise for its share.  us at K = 4096 / 11008, and PFLOP/s:
+//   64x128 27.6 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 256x256
+//   76 / 185, 1.30.
+// The pick is the fastest of the five at 290, 580, 1160 and 2338 rows of all four matrices: o at 290 rows 28 us (256x256:
+// 75), down 68 (180), qkv 48 (78), gate/up 81 (the others 90 and more); gate/up at 580 113 (164), down 84 (190).
+enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
-constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.6f, 4.22f, 0.84f}, {128, 128, 3.4f, 6.3f, 0.97f},
-                                         {128, 256, 6.8f, 8.3f, 1.16f}, {256, 256, 8.6f, 15.5f, 1.30f}};
-static Tile pick_tile(int M, int N, int K) {
-  Tile best = T_64x128;
+constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.9f, 5.9f, 0.68f}, {128, 128, 4.3f, 7.4f, 0.92f},
+                                         {64, 256, 6.8f, 9.3f, 0.80f}, {128, 256, 4.2f, 11.4f, 1.15f},
+                                         {256, 256, 11.5f, 16.1f, 1.30f}};
+struct TilePick { Tile tile; long long tiles; };
+static TilePick pick_tile(int M, int N, int K) {
+  TilePick best{T_64x128, 0};
   float best_us = 1e30f;
   for (int t = 0; t < T_COUNT; ++t) {
     const TileCost& c = kTileCost[t];
@@ -622,35 +625,44 @@ static Tile pick_tile(int M, int N, int K) {
     const float us = (float)rounds * fmaxf(alone, 256.0f * per_tile) + (rest ? fmaxf(alone, (float)rest * per_tile) : 0.f);
     if (us < best_us) {
       best_us = us;
-      best = (Tile)t;
+      best = TilePick{(Tile)t, tiles};
     }
   }
   return best;
 }
 
-// The tiles of up to 128 rows keep two workgroups on a compute unit (64x128, 128x128) or 8 waves (128x256).  256x256:
-// 8 waves of 64x128; slabs of 64 k (half the barriers: 358 against 374 us, gate/up at 2338 rows) except for the residual
-// epilogue over many rounds, where the deeper ring of 32-k slabs hides the reads of x better (18560 rows: o 563
-// against 575 us, down 1436 against 1456).  With low terms: 4 waves of 128x128, a third fewer LDS reads per product,
-// which is what the 32x32 instructions have left to save.
+// Rings are as deep as the LDS allows: cold weights take longer than two slabs to arrive (64x128 with 6 stages 28 and
+// 68 us for o and down at 290 rows, with 3 stages and two workgroups per compute unit 30 and 73), except where several
+// rounds of 64x128 tiles share the compute units.  256x256: 8 waves of 64x128, slabs of 64 k (half the barriers: gate/up
+// 363 against 371 us at 2338 rows, qkv 1399 against 1429 at 18560) once there are three rounds to hide the shorter
+// look-ahead, else and for the residual epilogue four stages of 32 (o 551 against 563 at 18560 rows, gate/up 81 against
+// 92 at 290).  With low terms: 4 waves of 128x128, a third fewer LDS reads per product, which is what the 32x32
+// instructions have left to save.
 template <bool LO8, class Epi>
-static void dispatch_lo(const GemmF16& g, const Epi& epi, bool deep_ring, hipStream_t st) {
+static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr int I = LO8 ? 32 : 16;
-  switch (pick_tile(g.M, g.N, g.K)) {
-    case T_64x128: launch<I, 2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st); break;
-    case T_128x128: launch<I, 2, 2, 64, 64, 32, 4, 2, LO8>(g, epi, st); break;
+  const TilePick p = pick_tile(g.M, g.N, g.K);
+  switch (p.tile) {
+    case T_64x128:
+      if (p.tiles <= 256) launch<I, 2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st);
+      else launch<I, 2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st);
+      break;
+    case T_128x128: launch<I, 4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
+    case T_64x256: launch<I, 2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
     case T_128x256: launch<I, 2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
     default:
-      if constexpr (LO8) launch<32, 2, 2, 128, 128, 32, 4, 1, true>(g, epi, st);
-      else if (deep_ring) launch<16, 4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
-      else launch<16, 4, 2, 64, 128, 64, 2, 1, false>(g, epi, st);
+      if constexpr (LO8) {
+        launch<32, 2, 2, 128, 128, 32, 4, 1, true>(g, epi, st);
+      } else {
+        if (!std::is_same<Epi, EpiResid>::value && p.tiles >= 768) launch<16, 4, 2, 64, 128, 64, 2, 1, false>(g, epi, st);
+        else launch<16, 4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
+      }
   }
 }
 template <class Epi>
 static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  const bool deep = std::is_same<Epi, EpiResid>::value && (long long)((g.M + 255) / 256) * (g.N / 256) > 512;
-  if (g.W8) dispatch_lo<true>(g, epi, deep, st);
-  else dispatch_lo<false>(g, epi, deep, st);
+  if (g.W8) dispatch_lo<true>(g, epi, st);
+  else dispatch_lo<false>(g, epi, st);
 }
 
 void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st) { dispatch(g, EpiResid{x, ldx}, st); }
