@@ -154,9 +154,9 @@ int vla_decode_step(vla_ctx* ctx, int32_t B, const int32_t* token_ids, float* lo
 
 /* vla_decode_step for callers that cannot provide or allocate staging memory at call time (code under HIP
  * graph capture, tight serving loops, harnesses that forbid allocation): same arguments, same results bit for
- * bit, but the step's GEMM staging (the split-K partial sums of the 16-bit path, the GEMM output of the float32
- * path) lives in a 32 MiB array that is part of the library's device code instead of the bound workspace, and
- * the call allocates nothing.  The step needs 4 * B * max(3 d_model, 2 d_ffn) * 4 bytes (VLA_BF16) or
+ * bit, but the step's GEMM staging (the split-K partial sums of the 16-bit path; the float32 path has none) lives
+ * in a 32 MiB array that is part of the library's device code instead of the bound workspace, and
+ * the call allocates nothing.  A step may take 4 * B * max(3 d_model, 2 d_ffn) * 4 bytes (VLA_BF16) or
  * B * max(3 d_model, 2 d_ffn) * 4 bytes (VLA_F32); VLA_E_CAPACITY if that exceeds the array (e.g. the 7B shape
  * fits up to B = 95).  Every context on a GPU shares that GPU's one array: calls that overlap in time on one GPU
  * (two streams, two contexts, two threads) race; calls ordered on one stream do not.  Nothing in the array has

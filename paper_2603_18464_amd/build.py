@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libvla.so")
-SOURCES = ["api.hip", "gemm_f16.hip", "decode_gemm.hip", "kernels.hip", "attention.hip", "batcher.cpp"]
+SOURCES = ["api.hip", "gemm_f16.hip", "gemm_f32.hip", "decode_gemm.hip", "kernels.hip", "attention.hip", "batcher.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

@@ -36,7 +36,7 @@ struct ArenaLayout {
   std::vector<LayerW> layers;
 };
 struct WorkLayout {
-  size_t x, hn, q, att, act, scratch, part, rope_cos, rope_sin, tok_seq, tok_pos, tok_src, last_row, seq_len,
+  size_t x, hn, q, att, act, part, rope_cos, rope_sin, tok_seq, tok_pos, tok_src, last_row, seq_len,
       cu_patch, cu_instr, cur_ids, logits, vz, vml, vu, vh, ids2, tail, chunk_rows, chunk_logits, slot_map, range_flag,
       total;
 };
@@ -138,7 +138,6 @@ WorkLayout work_layout(const vla_config& c) {
   w.att = take(T * d * es * terms);
   w.act = take(T * f * es * terms);
   const size_t widest = 3 * d > 2 * f ? 3 * d : 2 * f;
-  w.scratch = take(c.dtype == VLA_F32 ? T * widest * 4 : 0);
   w.part = take(c.dtype == VLA_BF16 ? (size_t)kMaxKSplit * part_rows(c) * widest * 4 : 0);
   w.rope_cos = take((size_t)c.max_seq * (c.head_dim / 2) * 4);
   w.rope_sin = take((size_t)c.max_seq * (c.head_dim / 2) * 4);
@@ -296,7 +295,6 @@ const char* kFamilyNames[FAM_COUNT] = {"gemm_qkv_prefill", "gemm_o_prefill", "ge
 template <class T> T* at(char* base, size_t off) { return reinterpret_cast<T*>(base + off); }
 
 // ---- one pass over the layers for `rows` packed tokens (prefill: all prefix tokens; decode: B) ------
-// T is the activation type: f16 on the 16-bit path (bf16 storage), float on the float32 path.
 void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_need, hipStream_t st);
 
 RopeKv layer_rope_kv(vla_ctx* ctx, int l) {
@@ -322,101 +320,106 @@ RopeKv layer_rope_kv(vla_ctx* ctx, int l) {
   return rk;
 }
 
-// need / n_need (prefill only): the packed rows whose final hidden state is read afterwards.  When they are
+// Prefill of the 16-bit path.  need / n_need: the packed rows whose final hidden state is read afterwards.  When they are
 // few, the last layer's output projection and feed-forward run on those rows alone.
-// Two-term layers (16-bit path, the leading layers of the high-precision mode): the normalised rows that feed the
+// Two-term layers (the leading layers of the high-precision mode): the normalised rows that feed the
 // QKV and the gate/up GEMMs, q / k / v, the attention output and the SwiGLU output are carried as [hi | lo].
-template <class T>
-int run_layers(vla_ctx* ctx, int rows, bool decode, hipStream_t st, const int32_t* need = nullptr, int n_need = 0) {
+int run_layers_f16(vla_ctx* ctx, int rows, hipStream_t st, const int32_t* need, int n_need) {
   const vla_config& c = ctx->cfg;
   const WorkLayout& w = ctx->wl;
   const int d = c.d_model, f = c.d_ffn;
   const f16* no8 = nullptr;
   float* x = at<float>(ctx->work, w.x);
-  T* hn = at<T>(ctx->work, w.hn);
-  T* q = at<T>(ctx->work, w.q);
-  T* att = at<T>(ctx->work, w.att);
-  T* act = at<T>(ctx->work, w.act);
-  float* gemm_out = ctx->part_override ? ctx->part_override : at<float>(ctx->work, w.scratch);
-  const int32_t* tok_seq = at<int32_t>(ctx->work, w.tok_seq);
-  const int32_t* tok_pos = at<int32_t>(ctx->work, w.tok_pos);
-  const int fam_attn = decode ? FAM_ATTN_DECODE : FAM_ATTN_PREFILL;
+  f16* hn = at<f16>(ctx->work, w.hn);
+  f16* q = at<f16>(ctx->work, w.q);
+  f16* att = at<f16>(ctx->work, w.att);
+  f16* act = at<f16>(ctx->work, w.act);
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);
     const bool two = two_term_layer(c, l);
     const int pd = two_pitch(two, d), pf = two_pitch(two, f);     // row pitch of this layer's operands with K = d, f
-    const int fam_gemm = decode ? FAM_GEMM_QKV_DECODE                  // + 0 qkv, 1 o, 2 gate-up, 3 down
-                                : (two ? FAM_GEMM_QKV_TWO_PREFILL : FAM_GEMM_QKV_PREFILL);
+    const int fam_gemm = two ? FAM_GEMM_QKV_TWO_PREFILL : FAM_GEMM_QKV_PREFILL;   // + 0 qkv, 1 o, 2 gate-up, 3 down
     {
       ProfScope ps(ctx, FAM_NORM, st);
-      rmsnorm<T>(x, nullptr, at<float>(ctx->arena, lw.g_attn), hn, rows, d, c.rms_eps, nullptr, lo_mode(two, d), st);
+      rmsnorm(x, at<float>(ctx->arena, lw.g_attn), hn, rows, d, c.rms_eps, lo_mode(two, d), st);
     }
     {
       ProfScope ps(ctx, fam_gemm + 0, st);
-      if constexpr (sizeof(T) == 2) {
-        gemm_f16_qkv(GemmF16{(const f16*)hn, pd, at<f16>(ctx->arena, lw.w_qkv), rows, 3 * d, pd, d,
-                             lo8(two, d) ? at<f16>(ctx->arena, lw.w_qkv8) : no8}, rk, st);
-      } else {
-        gemm_f32((const float*)hn, d, at<float>(ctx->arena, lw.w_qkv), gemm_out, rows, 3 * d, d, st);
-        rope_kv_f32(gemm_out, rows, rk, st);
-      }
+      gemm_f16_qkv(GemmF16{hn, pd, at<f16>(ctx->arena, lw.w_qkv), rows, 3 * d, pd, d,
+                           lo8(two, d) ? at<f16>(ctx->arena, lw.w_qkv8) : no8}, rk, st);
     }
     {
-      ProfScope ps(ctx, fam_attn, st);
-      if constexpr (sizeof(T) == 2) {
-        flash_prefill((const f16*)q, rk.ldq, (const f16*)rk.k_cache, (const f16*)rk.v_cache, (const unsigned char*)rk.k_lo,
-                      (const unsigned char*)rk.v_lo, at<int32_t>(ctx->work, w.cu_patch), at<int32_t>(ctx->work, w.cu_instr),
-                      ctx->run_slots, (f16*)att, pd, lo8(two, d), ctx->run_B, ctx->run_max_len, c.n_heads, c.head_dim,
-                      kv_pitch(c), st);
-      } else {
-        attention_rows<T>(q, d, (const T*)rk.k_cache, (const T*)rk.v_cache, tok_seq, tok_pos, att, d, rows,
-                          c.n_heads, c.head_dim, kv_pitch(c), false, st);
-      }
+      ProfScope ps(ctx, FAM_ATTN_PREFILL, st);
+      flash_prefill(q, rk.ldq, (const f16*)rk.k_cache, (const f16*)rk.v_cache, (const unsigned char*)rk.k_lo,
+                    (const unsigned char*)rk.v_lo, at<int32_t>(ctx->work, w.cu_patch), at<int32_t>(ctx->work, w.cu_instr),
+                    ctx->run_slots, att, pd, lo8(two, d), ctx->run_B, ctx->run_max_len, c.n_heads, c.head_dim,
+                    kv_pitch(c), st);
     }
-    if constexpr (sizeof(T) == 2) {
-      // the compact set lives in buffers that are dead by now (see run_tail_f16): it must fit them
-      const size_t pad32 = ((size_t)n_need + 31) / 32 * 32;
-      const bool fits = pad32 <= max_rows(c) &&
-                        align_up(pad32 * f * sizeof(f16)) + (size_t)n_need * d * 4 <= max_rows(c) * (size_t)f * sizeof(f16);
-      if (!decode && l == c.n_layers - 1 && need && n_need > 0 && (size_t)n_need * 2 <= (size_t)rows && fits) {
-        run_tail_f16(ctx, lw, need, n_need, st);
-        break;
-      }
+    // the compact set lives in buffers that are dead by now (see run_tail_f16): it must fit them
+    const size_t pad32 = ((size_t)n_need + 31) / 32 * 32;
+    const bool fits = pad32 <= max_rows(c) &&
+                      align_up(pad32 * f * sizeof(f16)) + (size_t)n_need * d * 4 <= max_rows(c) * (size_t)f * sizeof(f16);
+    if (l == c.n_layers - 1 && need && n_need > 0 && (size_t)n_need * 2 <= (size_t)rows && fits) {
+      run_tail_f16(ctx, lw, need, n_need, st);
+      break;
     }
     {
       ProfScope ps(ctx, fam_gemm + 1, st);
-      if constexpr (sizeof(T) == 2) {
-        gemm_f16_resid(GemmF16{(const f16*)att, pd, at<f16>(ctx->arena, lw.w_o), rows, d, pd, d,
-                               lo8(two, d) ? at<f16>(ctx->arena, lw.w_o8) : no8}, x, d, st);
-      } else {
-        gemm_f32((const float*)att, d, at<float>(ctx->arena, lw.w_o), gemm_out, rows, d, d, st);
-        resid_add_f32(x, gemm_out, (size_t)rows * d, st);
-      }
+      gemm_f16_resid(GemmF16{att, pd, at<f16>(ctx->arena, lw.w_o), rows, d, pd, d,
+                             lo8(two, d) ? at<f16>(ctx->arena, lw.w_o8) : no8}, x, d, st);
     }
     {
       ProfScope ps(ctx, FAM_NORM, st);
-      rmsnorm<T>(x, nullptr, at<float>(ctx->arena, lw.g_ffn), hn, rows, d, c.rms_eps, nullptr, lo_mode(two, d), st);
+      rmsnorm(x, at<float>(ctx->arena, lw.g_ffn), hn, rows, d, c.rms_eps, lo_mode(two, d), st);
     }
     {
       ProfScope ps(ctx, fam_gemm + 2, st);
-      if constexpr (sizeof(T) == 2) {
-        gemm_f16_swiglu(GemmF16{(const f16*)hn, pd, at<f16>(ctx->arena, lw.w_gu), rows, 2 * f, pd, d,
-                                lo8(two, d) ? at<f16>(ctx->arena, lw.w_gu8) : no8}, (f16*)act, pf, lo_mode(two, f), st);
-      } else {
-        gemm_f32((const float*)hn, d, at<float>(ctx->arena, lw.w_gu), gemm_out, rows, 2 * f, d, st);
-        swiglu_f32(gemm_out, (float*)act, rows, f, st);
-      }
+      gemm_f16_swiglu(GemmF16{hn, pd, at<f16>(ctx->arena, lw.w_gu), rows, 2 * f, pd, d,
+                              lo8(two, d) ? at<f16>(ctx->arena, lw.w_gu8) : no8}, act, pf, lo_mode(two, f), st);
     }
     {
       ProfScope ps(ctx, fam_gemm + 3, st);
-      if constexpr (sizeof(T) == 2) {
-        gemm_f16_resid(GemmF16{(const f16*)act, pf, at<f16>(ctx->arena, lw.w_down), rows, d, pf, f,
-                               lo8(two, f) ? at<f16>(ctx->arena, lw.w_down8) : no8}, x, d, st);
-      } else {
-        gemm_f32((const float*)act, f, at<float>(ctx->arena, lw.w_down), gemm_out, rows, d, f, st);
-        resid_add_f32(x, gemm_out, (size_t)rows * d, st);
-      }
+      gemm_f16_resid(GemmF16{act, pf, at<f16>(ctx->arena, lw.w_down), rows, d, pf, f,
+                             lo8(two, f) ? at<f16>(ctx->arena, lw.w_down8) : no8}, x, d, st);
+    }
+  }
+  return VLA_OK;
+}
+
+// The float32 path, prefill and decode alike: five launches a layer, the norms and the elementwise steps are part of the
+// GEMMs.
+int run_layers_f32(vla_ctx* ctx, int rows, bool decode, hipStream_t st) {
+  const vla_config& c = ctx->cfg;
+  const WorkLayout& w = ctx->wl;
+  const int d = c.d_model, f = c.d_ffn;
+  float* x = at<float>(ctx->work, w.x);
+  float* att = at<float>(ctx->work, w.att);
+  float* act = at<float>(ctx->work, w.act);
+  const int fam_gemm = decode ? FAM_GEMM_QKV_DECODE : FAM_GEMM_QKV_PREFILL;       // + 0 qkv, 1 o, 2 gate-up, 3 down
+  for (int l = 0; l < c.n_layers; ++l) {
+    const LayerW& lw = ctx->al.layers[l];
+    const RopeKv rk = layer_rope_kv(ctx, l);
+    {
+      ProfScope ps(ctx, fam_gemm + 0, st);
+      gemm_f32_qkv(x, at<float>(ctx->arena, lw.g_attn), c.rms_eps, at<float>(ctx->arena, lw.w_qkv), rows, rk, st);
+    }
+    {
+      ProfScope ps(ctx, decode ? FAM_ATTN_DECODE : FAM_ATTN_PREFILL, st);
+      attention_rows_f32((const float*)rk.q, (const float*)rk.k_cache, (const float*)rk.v_cache, rk.tok_seq, rk.tok_pos, att,
+                         rows, c.n_heads, c.head_dim, kv_pitch(c), st);
+    }
+    {
+      ProfScope ps(ctx, fam_gemm + 1, st);
+      gemm_f32_resid(att, at<float>(ctx->arena, lw.w_o), x, rows, d, d, st);
+    }
+    {
+      ProfScope ps(ctx, fam_gemm + 2, st);
+      gemm_f32_swiglu(x, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, at<float>(ctx->arena, lw.w_gu), act, rows, d, f, st);
+    }
+    {
+      ProfScope ps(ctx, fam_gemm + 3, st);
+      gemm_f32_resid(act, at<float>(ctx->arena, lw.w_down), x, rows, d, f, st);
     }
   }
   return VLA_OK;
@@ -473,11 +476,6 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     }
   };
   f16* const none = nullptr;
-  {
-    ProfScope ps(ctx, FAM_NORM, st);
-    rmsnorm_frag(x, B, d, at<float>(ctx->arena, ctx->al.layers[0].g_attn), c.rms_eps, hn,
-                 two_term_layer(c, 0) ? hn_lo : none, st);
-  }
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);      // low-term planes only in two-term layers
@@ -667,9 +665,6 @@ int ensure_tables(vla_ctx* ctx, hipStream_t st) {
   return VLA_OK;
 }
 
-template <class S> struct ActOf { typedef float type; };
-template <> struct ActOf<bf16> { typedef f16 type; };
-
 // S is the storage type of the caller's tensors (bf16 or float).
 template <class T>
 int do_prefill(vla_ctx* ctx, int32_t B, const void* patch_emb, const int32_t* cu_patch, const int32_t* instr_ids,
@@ -726,7 +721,8 @@ int do_prefill(vla_ctx* ctx, int32_t B, const void* patch_emb, const int32_t* cu
     chunk_rows(at<int32_t>(ctx->work, w.last_row), B, n_last, at<int32_t>(ctx->work, w.chunk_rows), st);
     need = at<int32_t>(ctx->work, w.chunk_rows);
   }
-  run_layers<typename ActOf<T>::type>(ctx, (int)T_tokens, false, st, need, B * n_last);
+  if (sizeof(T) == 2) run_layers_f16(ctx, (int)T_tokens, st, need, B * n_last);
+  else run_layers_f32(ctx, (int)T_tokens, false, st);
   if (logits) run_head<T>(ctx, B, at<int32_t>(ctx->work, w.last_row), logits, ld_logits, st);
   HIP_TRY(ctx, hipGetLastError());
   // host mirror of the sequence lengths, by slot (0: free)
@@ -761,16 +757,16 @@ int do_decode(vla_ctx* ctx, int32_t B, const int32_t* token_ids, float* logits, 
   }
   {
     ProfScope ps(ctx, FAM_MISC, st);
-    embed_tokens<T>(token_ids, at<T>(ctx->arena, ctx->al.embed), at<float>(ctx->work, w.x), B, c.d_model, c.vocab, st);
-    decode_maps(at<int32_t>(ctx->work, w.seq_len), slot_map, B, at<int32_t>(ctx->work, w.tok_seq), at<int32_t>(ctx->work, w.tok_pos), st);
+    const bool half = sizeof(T) == 2;
+    f16* hn = at<f16>(ctx->work, w.hn);
+    decode_begin<T>(token_ids, at<T>(ctx->arena, ctx->al.embed), c.vocab, at<int32_t>(ctx->work, w.seq_len), slot_map,
+                    at<int32_t>(ctx->work, w.tok_seq), at<int32_t>(ctx->work, w.tok_pos), at<float>(ctx->work, w.x), B,
+                    c.d_model, half ? at<float>(ctx->arena, ctx->al.layers[0].g_attn) : nullptr, c.rms_eps, hn,
+                    half && two_term_layer(c, 0) ? frag_lo(c, hn, c.d_model) : nullptr, st);
   }
   if (sizeof(T) == 2) run_layers_decode_f16(ctx, B, st);
-  else run_layers<typename ActOf<T>::type>(ctx, B, true, st);
+  else run_layers_f32(ctx, B, true, st);
   if (logits) run_head<T>(ctx, B, nullptr, logits, ld_logits, st);
-  {
-    ProfScope ps(ctx, FAM_MISC, st);
-    advance_lengths(at<int32_t>(ctx->work, w.seq_len), slot_map, B, st);
-  }
   HIP_TRY(ctx, hipGetLastError());
   for (int b = 0; b < B; ++b) ctx->len[slots ? slots[b] : b] += 1;
   return VLA_OK;
@@ -1204,8 +1200,8 @@ int vla_decode_step_static(vla_ctx* ctx, int32_t B, const int32_t* token_ids, fl
   if (!token_ids) return fail(ctx, VLA_E_NULL, "token_ids is NULL");
   if ((rc = check_decode(ctx, B, 1))) return rc;
   const vla_config& c = ctx->cfg;
-  // staging the step's GEMMs need: the split-K partial planes of the 16-bit path (rows of one chunk), or the
-  // plain GEMM output of the float32 path
+  // staging the step's GEMMs need: the split-K partial planes of the 16-bit path (rows of one chunk); the float32 path
+  // stages nothing and keeps the limit of one GEMM output per row
   const size_t widest = 3 * (size_t)c.d_model > 2 * (size_t)c.d_ffn ? 3 * (size_t)c.d_model : 2 * (size_t)c.d_ffn;
   const size_t rows = c.dtype == VLA_BF16 ? (size_t)kMaxKSplit * B : (size_t)B;
   const size_t need = rows * widest * sizeof(float);

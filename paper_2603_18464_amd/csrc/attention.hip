@@ -1,39 +1,45 @@
-// Causal attention of single query rows against the KV cache.
+// Causal attention against the KV cache: the float32 rows kernel, flash attention of the 16-bit prefill, and the decode
+// kernel of the 16-bit path.
 //
-// attention_rows: one wave per (token, head).  Lanes first split the keys (each lane scores keys
+// attention_rows (float32): one wave per (token, head).  Lanes first split the keys (each lane scores keys
 // lane, lane+64, ...), the softmax statistics are reduced across the wave, then lanes split the
 // head dimension and accumulate the probability-weighted values.  Keys/values of a (slot, head)
-// are contiguous [position][head_dim] rows in the cache.
+// are contiguous [position][head_dim] rows in the cache.  A few dozen keys: bound by latency, so a key is read as
+// 16-byte pieces and the values of eight keys are requested together.
 #include "common.h"
 
 namespace vla {
 
-template <class T, int HD>
+template <int HD>
 __global__ __launch_bounds__(256) void attention_rows_kernel(
-    const T* __restrict__ q, int ldq, const T* __restrict__ k_cache, const T* __restrict__ v_cache,
-    const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos, T* __restrict__ out, int ldo,
-    int n_items, int n_heads, int max_seq, bool out_frag) {
-  extern __shared__ float smem[];                    // per wave: [HD] query + [max_seq] scores
+    const float* __restrict__ q, const float* __restrict__ k_cache, const float* __restrict__ v_cache,
+    const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos, float* __restrict__ out, int n_items,
+    int n_heads, int max_seq) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // [4 waves][HD] queries, [4][max_seq] scores
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int item = blockIdx.x * 4 + wave;            // (token, head)
   if (item >= n_items) return;                       // whole wave leaves; no block barrier is used
-  float* qs = smem + (size_t)wave * (HD + max_seq);
-  float* sc = qs + HD;
+  float* qs = smem + wave * HD;
+  float* sc = smem + 4 * HD + (size_t)wave * max_seq;
   const int tok = item / n_heads, head = item - tok * n_heads;
   const int slot = tok_seq[tok], pos = tok_pos[tok];
   const int ctx = pos + 1;                           // keys 0..pos
-  const T* qrow = q + (size_t)tok * ldq + head * HD;
-  for (int i = lane; i < HD; i += 64) qs[i] = to_f32(qrow[i]);
-  const T* kbase = k_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
-  const T* vbase = v_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
+  const float* qrow = q + (size_t)item * HD;
+  for (int i = lane; i < HD; i += 64) qs[i] = qrow[i];
+  const float* kbase = k_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
+  const float* vbase = v_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
   const float scale = rsqrtf((float)HD);
   __builtin_amdgcn_wave_barrier();
   float mx = -INFINITY;
   for (int key = lane; key < ctx; key += 64) {
-    const T* kr = kbase + (size_t)key * HD;
+    const float* kr = kbase + (size_t)key * HD;
     float s = 0.f;
 #pragma unroll 8
-    for (int i = 0; i < HD; ++i) s = fmaf(qs[i], to_f32(kr[i]), s);
+    for (int i = 0; i < HD; i += 4) {
+      const f32x4 kv = *(const f32x4*)(kr + i), qv = *(const f32x4*)(qs + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(qv[e], kv[e], s);
+    }
     s *= scale;
     sc[key] = s;
     mx = fmaxf(mx, s);
@@ -48,17 +54,19 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
   sum = wave_sum(sum);
   __builtin_amdgcn_wave_barrier();
   const float inv = 1.0f / sum;
-  T* orow = out + (size_t)tok * ldo + head * HD;
+  float* orow = out + (size_t)item * HD;
   for (int i = lane; i < HD; i += 64) {
     float acc = 0.f;
-    for (int key = 0; key < ctx; ++key) acc = fmaf(sc[key], to_f32(vbase[(size_t)key * HD + i]), acc);
-    if (out_frag) {   // [m/32][k/16][lane][8] fragment order with K = ldo (input of the decode GEMMs)
-      const int m = tok, k = head * HD + i;
-      out[((size_t)(m >> 5) * (ldo >> 4) + (k >> 4)) * 512 + ((m & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7)] =
-          from_f32<T>(acc * inv);
-    } else {
-      orow[i] = from_f32<T>(acc * inv);
+    int key = 0;
+    for (; key + 8 <= ctx; key += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = vbase[(size_t)(key + u) * HD + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc = fmaf(sc[key + u], v[u], acc);
     }
+    for (; key < ctx; ++key) acc = fmaf(sc[key], vbase[(size_t)key * HD + i], acc);
+    orow[i] = acc * inv;
   }
 }
 
@@ -595,17 +603,16 @@ void decode_attention_fused(const float* part, int ksplit, int part_rows, const 
 #undef VLA_DEC_ATT
 }
 
-template <class T>
-void attention_rows(const T* q, int ldq, const T* k_cache, const T* v_cache, const int32_t* tok_seq,
-                    const int32_t* tok_pos, T* out, int ldo, int n_tok, int n_heads, int head_dim, int max_seq,
-                    bool out_frag, hipStream_t st) {
+void attention_rows_f32(const float* q, const float* k_cache, const float* v_cache, const int32_t* tok_seq,
+                        const int32_t* tok_pos, float* out, int n_tok, int n_heads, int head_dim, int max_seq,
+                        hipStream_t st) {
   const int n_items = n_tok * n_heads;
   const int blocks = (n_items + 3) / 4;
   const size_t smem = 4 * (size_t)(head_dim + max_seq) * sizeof(float);
 #define VLA_ATTN_CASE(HD)                                                                                   \
   case HD:                                                                                                  \
-    hipLaunchKernelGGL((attention_rows_kernel<T, HD>), dim3(blocks), dim3(256), smem, st, q, ldq, k_cache,  \
-                       v_cache, tok_seq, tok_pos, out, ldo, n_items, n_heads, max_seq, out_frag);                     \
+    hipLaunchKernelGGL((attention_rows_kernel<HD>), dim3(blocks), dim3(256), smem, st, q, k_cache, v_cache, \
+                       tok_seq, tok_pos, out, n_items, n_heads, max_seq);                                   \
     break;
   switch (head_dim) {
     VLA_ATTN_CASE(32)
@@ -616,6 +623,4 @@ void attention_rows(const T* q, int ldq, const T* k_cache, const T* v_cache, con
   }
 #undef VLA_ATTN_CASE
 }
-template void attention_rows<float>(const float*, int, const float*, const float*, const int32_t*, const int32_t*,
-                                    float*, int, int, int, int, int, bool, hipStream_t);
 }  // namespace vla

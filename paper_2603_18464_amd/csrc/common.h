@@ -138,28 +138,22 @@ void gemm_f16_qkv(const GemmF16& g, const RopeKv& o, hipStream_t st);           
 void pack_weight_f16(const bf16* src, int rows, int K, f16* dst, unsigned char* dst8, int row0, int interleave_mode,
                      int* range_flag, hipStream_t st);
 
-// fp32 path (plain, unfused).
-void gemm_f32(const float* A, int lda, const float* W, float* C, int M, int N, int K, hipStream_t st);
-void rope_kv_f32(const float* qkv, int T, const RopeKv& o, hipStream_t st);
-void resid_add_f32(float* x, const float* c, size_t n, hipStream_t st);
-void swiglu_f32(const float* gu, float* act, int T, int f, hipStream_t st);
+// float32 path: W [N, K] row-major; the q/k/v and gate/up products take the RMSNorm of the x rows [M, d_model] with them.
+void gemm_f32_qkv(const float* x, const float* gain, float eps, const float* W, int M, const RopeKv& o, hipStream_t st);
+void gemm_f32_swiglu(const float* x, const float* gain, float eps, const float* W /* [gate | up] */, float* act, int M,
+                     int d, int f, hipStream_t st);
+void gemm_f32_resid(const float* A, const float* W, float* x, int M, int d, int K, hipStream_t st);   // x += A * W^T
 
 // Row-wise kernels.
-template <class T>
-void rmsnorm(const float* x, const T* /*unused tag*/, const float* gain, T* out, int rows, int d,
-             float eps, const int32_t* row_index, int lo_mode /* 0: rows of d; 1: [hi | lo] of 2 d; 2: [hi | lo8] of 1.5 d */,
-             hipStream_t st);
+void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float eps,
+             int lo_mode /* 0: rows of d; 1: [hi | lo] of 2 d; 2: [hi | lo8] of 1.5 d */, hipStream_t st);
 template <class T>
 void assemble_prefix(const T* patch_emb, const int32_t* instr_ids, const T* embed,
                      const int32_t* tok_src, float* x, int T_tokens, int d, int vocab, hipStream_t st);
-template <class T>
-void embed_tokens(const int32_t* ids, const T* embed, float* x, int B, int d, int vocab, hipStream_t st);
-
 // Attention: one query row per (token, head) against the cache.
-template <class T>
-void attention_rows(const T* q, int ldq, const T* k_cache, const T* v_cache, const int32_t* tok_seq,
-                    const int32_t* tok_pos, T* out, int ldo, int n_tok, int n_heads, int head_dim,
-                    int max_seq, bool out_frag, hipStream_t st);
+void attention_rows_f32(const float* q, const float* k_cache, const float* v_cache, const int32_t* tok_seq,
+                        const int32_t* tok_pos, float* out, int n_tok, int n_heads, int head_dim, int max_seq,
+                        hipStream_t st);
 
 // Prefill attention for the 16-bit path: causal flash attention over whole prefixes (MFMA).
 // cu_patch / cu_instr are the device copies of the cumulative offsets; max_len = longest prefix; slot_map
@@ -189,8 +183,12 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
                  int plane_rows, int prow0, hipStream_t st);
 void reduce_resid_norm(const float* part, int ksplit, int plane_rows, int prow0, int M, int d, float* x,
                        const float* gain, float eps, f16* hn_frag, f16* hn_frag_lo, int row0, hipStream_t st);
-void rmsnorm_frag(const float* x, int M, int d, const float* gain, float eps, f16* hn_frag, f16* hn_frag_lo,
-                  hipStream_t st);
+// Start of a decode step: x rows from the embedding table, tok_seq / tok_pos of the step, lengths + 1, and with a gain the
+// first norm in fragment order.  slot_map: device [M] cache slot of each row, nullptr = identity.
+template <class T>
+void decode_begin(const int32_t* ids, const T* embed, int vocab, int32_t* seq_len, const int32_t* slot_map,
+                  int32_t* tok_seq, int32_t* tok_pos, float* x, int M, int d, const float* gain, float eps, f16* hn_frag,
+                  f16* hn_frag_lo, hipStream_t st);
 void reduce_swiglu(const float* part, int ksplit, int plane_rows, int prow0, int M, int f, f16* act_frag,
                    f16* act_frag_lo, int row0, hipStream_t st);
 
@@ -243,8 +241,6 @@ void rope_table(float* cos_t, float* sin_t, int max_seq, int head_dim, float the
 void build_token_maps(const int32_t* cu_patch_dev, const int32_t* cu_instr_dev, const int32_t* slot_map, int B,
                       int T_tokens, int32_t* tok_seq, int32_t* tok_pos, int32_t* tok_src, int32_t* last_row,
                       int32_t* seq_len, hipStream_t st);
-void decode_maps(int32_t* seq_len, const int32_t* slot_map, int B, int32_t* tok_seq, int32_t* tok_pos, hipStream_t st);
-void advance_lengths(int32_t* seq_len, const int32_t* slot_map, int B, hipStream_t st);
 template <class T>
 void convert_copy(const T* src, float* dst, size_t n, hipStream_t st);   // gains -> float32
 template <class T>

@@ -258,37 +258,76 @@ void reduce_resid_norm(const float* part, int ksplit, int plane_rows, int prow0,
                      eps, hn_frag, hn_frag_lo, row0);
 }
 
-// Plain RMSNorm of x rows into fragment order (first norm of a decode step).
-__global__ __launch_bounds__(256) void rmsnorm_frag_kernel(const float* __restrict__ x, int d,
-                                                           const float* __restrict__ gain, float eps,
-                                                           f16* __restrict__ hn_frag, f16* __restrict__ hn_frag_lo) {
+// Start of a decode step, one workgroup per row: the token's embedding becomes row b of the residual stream, the row's
+// cache slot and position are noted for the layers and the sequence grows by one; with a gain (16-bit path) the first
+// layer's normalised row goes to fragment order too.  (One launch: four of them, a few us each, are a tenth of a step of
+// a small model.)
+template <class T>
+__global__ __launch_bounds__(256) void decode_begin_kernel(const int32_t* __restrict__ ids, const T* __restrict__ embed,
+                                                           int vocab, int32_t* seq_len,
+                                                           const int32_t* __restrict__ slot_map,
+                                                           int32_t* __restrict__ tok_seq, int32_t* __restrict__ tok_pos,
+                                                           float* __restrict__ x, int d, const float* __restrict__ gain,
+                                                           float eps, f16* __restrict__ hn_frag,
+                                                           f16* __restrict__ hn_frag_lo) {
   __shared__ float red[4];
   const int m = blockIdx.x;
-  const float* row = x + (size_t)m * d;
+  if (threadIdx.x == 0) {
+    const int slot = slot_map ? slot_map[m] : m;
+    const int pos = seq_len[slot];
+    tok_seq[m] = slot;
+    tok_pos[m] = pos;
+    seq_len[slot] = pos + 1;
+  }
+  int id = ids[m];
+  id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);   // ids come from device memory: stay in bounds
+  const T* src = embed + (size_t)id * d;
+  float* row = x + (size_t)m * d;
+  auto load = [&](int i) {
+    f32x4 v;
+    if constexpr (sizeof(T) == 2) {
+      const bf16x4 e = *(const bf16x4*)(src + i);
+      v = f32x4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
+    } else {
+      v = *(const f32x4*)(src + i);
+    }
+    return v;
+  };
   float ss = 0.f;
   for (int i = threadIdx.x * 4; i < d; i += 1024) {
-    const float4 v = *(const float4*)(row + i);
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    const f32x4 v = load(i);
+    *(f32x4*)(row + i) = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
+  if (!gain) return;
   ss = block_sum_256d(ss, red);
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int i = threadIdx.x * 8; i < d; i += 2048) {
-    f16x8 o, oe;
+  typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+  for (int i = threadIdx.x * 4; i < d; i += 1024) {
+    const f32x4 v = load(i), g = *(const f32x4*)(gain + i);
+    f16x4 o, oe;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float h = row[i + j] * inv * gain[i + j];
+    for (int j = 0; j < 4; ++j) {
+      const float h = v[j] * inv * g[j];
       o[j] = from_f32<f16>(h);
       oe[j] = from_f32<f16>(h - (float)o[j]);
     }
     const size_t at = frag_index(m, i, d);
-    *(f16x8*)(hn_frag + at) = o;
-    if (hn_frag_lo) *(f16x8*)(hn_frag_lo + at) = oe;
+    *(f16x4*)(hn_frag + at) = o;
+    if (hn_frag_lo) *(f16x4*)(hn_frag_lo + at) = oe;
   }
 }
-void rmsnorm_frag(const float* x, int M, int d, const float* gain, float eps, f16* hn_frag, f16* hn_frag_lo,
-                  hipStream_t st) {
-  hipLaunchKernelGGL(rmsnorm_frag_kernel, dim3(M), dim3(256), 0, st, x, d, gain, eps, hn_frag, hn_frag_lo);
+template <class T>
+void decode_begin(const int32_t* ids, const T* embed, int vocab, int32_t* seq_len, const int32_t* slot_map,
+                  int32_t* tok_seq, int32_t* tok_pos, float* x, int M, int d, const float* gain, float eps, f16* hn_frag,
+                  f16* hn_frag_lo, hipStream_t st) {
+  hipLaunchKernelGGL(decode_begin_kernel<T>, dim3(M), dim3(256), 0, st, ids, embed, vocab, seq_len, slot_map, tok_seq,
+                     tok_pos, x, d, gain, eps, hn_frag, hn_frag_lo);
 }
+template void decode_begin<float>(const int32_t*, const float*, int, int32_t*, const int32_t*, int32_t*, int32_t*, float*,
+                                  int, int, const float*, float, f16*, f16*, hipStream_t);
+template void decode_begin<bf16>(const int32_t*, const bf16*, int, int32_t*, const int32_t*, int32_t*, int32_t*, float*,
+                                 int, int, const float*, float, f16*, f16*, hipStream_t);
 
 // act (fragment order, [M, f]) = silu(gate) * up, gate/up summed over the K slices.  The fused
 // gate-up columns are interleaved in blocks of 32: gate j at (j/32)*64 + j%32, up 32 further.

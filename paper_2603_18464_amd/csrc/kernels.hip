@@ -1,6 +1,6 @@
 // Row-wise and small kernels of the VLA policy path: prefix assembly, RMSNorm, the action head
 // (final norm + slimmed LM head), token selection with log-probs and de-tokenisation, rotary
-// tables, token maps, and the plain float32 path used when the storage dtype is float32.
+// tables, token maps.
 #include "common.h"
 
 namespace vla {
@@ -38,28 +38,6 @@ void build_token_maps(const int32_t* cu_patch_dev, const int32_t* cu_instr_dev, 
   const int n = T_tokens > B ? T_tokens : B;
   hipLaunchKernelGGL(token_maps_kernel, dim3((n + 255) / 256), dim3(256), 0, st, cu_patch_dev, cu_instr_dev,
                      slot_map, B, T_tokens, tok_seq, tok_pos, tok_src, last_row, seq_len);
-}
-
-__global__ void decode_maps_kernel(const int32_t* seq_len, const int32_t* __restrict__ slot_map, int B,
-                                   int32_t* tok_seq, int32_t* tok_pos) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) {
-    const int slot = slot_map ? slot_map[b] : b;
-    tok_seq[b] = slot;
-    tok_pos[b] = seq_len[slot];
-  }
-}
-void decode_maps(int32_t* seq_len, const int32_t* slot_map, int B, int32_t* tok_seq, int32_t* tok_pos, hipStream_t st) {
-  hipLaunchKernelGGL(decode_maps_kernel, dim3((B + 255) / 256), dim3(256), 0, st, seq_len, slot_map, B, tok_seq,
-                     tok_pos);
-}
-
-__global__ void advance_kernel(int32_t* seq_len, const int32_t* __restrict__ slot_map, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) seq_len[slot_map ? slot_map[b] : b] += 1;
-}
-void advance_lengths(int32_t* seq_len, const int32_t* slot_map, int B, hipStream_t st) {
-  hipLaunchKernelGGL(advance_kernel, dim3((B + 255) / 256), dim3(256), 0, st, seq_len, slot_map, B);
 }
 
 // ---- rotary table ---------------------------------------------------------------------------------
@@ -273,23 +251,6 @@ void score_rows(const float* logits, int rows, int A, float temperature, const i
                      ratio_out, weight_out);
 }
 
-template <class T>
-__global__ void embed_kernel(const int32_t* __restrict__ ids, const T* __restrict__ embed,
-                             float* __restrict__ x, int d, int vocab) {
-  const int b = blockIdx.x;
-  int id = ids[b];
-  id = id < 0 ? 0 : (id >= vocab ? vocab - 1 : id);   // ids come from device memory: stay in bounds
-  const T* row = embed + (size_t)id * d;
-  float* out = x + (size_t)b * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) out[i] = to_f32(row[i]);
-}
-template <class T>
-void embed_tokens(const int32_t* ids, const T* embed, float* x, int B, int d, int vocab, hipStream_t st) {
-  hipLaunchKernelGGL(embed_kernel<T>, dim3(B), dim3(256), 0, st, ids, embed, x, d, vocab);
-}
-template void embed_tokens<float>(const int32_t*, const float*, float*, int, int, int, hipStream_t);
-template void embed_tokens<bf16>(const int32_t*, const bf16*, float*, int, int, int, hipStream_t);
-
 // ---- RMSNorm ----------------------------------------------------------------------------------------
 // out[r, :] = x[row, :] * gain / sqrt(mean(x^2) + eps), statistics in float32; one workgroup per row.
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
@@ -301,14 +262,12 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-template <class T>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gain,
-                                                      T* __restrict__ out, int d, float eps,
-                                                      const int32_t* __restrict__ row_index, int ldo, int lo_mode) {
-  typedef __attribute__((ext_vector_type(4))) T T4;
+                                                      f16* __restrict__ out, int d, float eps, int ldo, int lo_mode) {
+  typedef __attribute__((ext_vector_type(4))) f16 f16x4;
   __shared__ float red[4];
   const int r = blockIdx.x;
-  const float* row = x + (size_t)(row_index ? row_index[r] : r) * d;
+  const float* row = x + (size_t)r * d;
   constexpr int kHeld = 8;                 // float4 per thread kept in registers: rows up to 8192 wide are read once
   f32x4 held[kHeld];
   float ss = 0.f;
@@ -324,21 +283,21 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
   ss = block_sum_256(ss, red);
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  T* o = out + (size_t)r * ldo;
+  f16* o = out + (size_t)r * ldo;
   // lo_mode 1 (two-term output): the low terms go to column d + i; 2: as bytes behind the d high terms
   auto emit = [&](int i, const f32x4& v) {
     const f32x4 g = *(const f32x4*)(gain + i);
-    T4 q, qe;
+    f16x4 q, qe;
     float e[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float h = v[j] * inv * g[j];
-      q[j] = from_f32<T>(h);
+      q[j] = from_f32<f16>(h);
       e[j] = h - to_f32(q[j]);
-      qe[j] = from_f32<T>(e[j]);
+      qe[j] = from_f32<f16>(e[j]);
     }
-    *(T4*)(o + i) = q;
-    if (lo_mode == 1) *(T4*)(o + d + i) = qe;
+    *(f16x4*)(o + i) = q;
+    if (lo_mode == 1) *(f16x4*)(o + d + i) = qe;
     if (lo_mode == 2) *(int*)((unsigned char*)(o + d) + i) = pack_lo8(e[0], e[1], e[2], e[3]);
   };
 #pragma unroll
@@ -348,16 +307,10 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
   }
   for (int i = threadIdx.x * 4 + kHeld * 1024; i < d; i += 1024) emit(i, *(const f32x4*)(row + i));
 }
-template <class T>
-void rmsnorm(const float* x, const T*, const float* gain, T* out, int rows, int d, float eps,
-             const int32_t* row_index, int lo_mode, hipStream_t st) {
-  hipLaunchKernelGGL(rmsnorm_kernel<T>, dim3(rows), dim3(256), 0, st, x, gain, out, d, eps, row_index,
+void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float eps, int lo_mode, hipStream_t st) {
+  hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, st, x, gain, out, d, eps,
                      lo_mode == 1 ? 2 * d : (lo_mode == 2 ? d + d / 2 : d), lo_mode);
 }
-template void rmsnorm<float>(const float*, const float*, const float*, float*, int, int, float, const int32_t*,
-                             int, hipStream_t);
-template void rmsnorm<f16>(const float*, const f16*, const float*, f16*, int, int, float, const int32_t*,
-                           int, hipStream_t);
 
 // ---- action head ------------------------------------------------------------------------------------
 // Workgroup (b, g): final RMSNorm of sequence b's row (float32, kept in LDS), then 32 action rows of
@@ -657,97 +610,6 @@ void select_tokens(const float* logits, int ld_logits, int B, int A, float tempe
   hipLaunchKernelGGL(select_kernel, dim3(B), dim3(64), 0, st, logits, ld_logits, A, temperature, gumbel, k, n_tokens,
                      act_scale, act_offset, action_dim, tokens_out, logp_out, actions_out, out_stride, next_ids,
                      id0);
-}
-
-// ---- float32 path -------------------------------------------------------------------------------------
-// C[M,N] = A[M,K] * W[N,K]^T, 64x64 tiles, 16-deep K slabs in LDS, 4x4 outputs per thread.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda,
-                                                       const float* __restrict__ W, float* __restrict__ C, int M,
-                                                       int N, int K) {
-  __shared__ float As[16][64 + 1];
-  __shared__ float Ws[16][64 + 1];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      const int r = i >> 4, kk = i & 15;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      As[kk][r] = (gm < M && gk < K) ? A[(size_t)gm * lda + gk] : 0.f;
-      Ws[kk][r] = (gn < N && gk < K) ? W[(size_t)gn * K + gk] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = Ws[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) C[(size_t)m * N + n] = acc[i][j];
-    }
-}
-void gemm_f32(const float* A, int lda, const float* W, float* C, int M, int N, int K, hipStream_t st) {
-  hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, lda, W, C, M, N, K);
-}
-
-// qkv [T, 3d] float32 -> rotated q [T, d], rotated k and plain v into the cache.
-__global__ void rope_kv_f32_kernel(const float* __restrict__ qkv, RopeKv o) {
-  const int t = blockIdx.x;
-  const int d = o.d_model, hd = o.head_dim, half = hd >> 1;
-  const int pos = o.tok_pos[t], slot = o.tok_seq[t];
-  const float* row = qkv + (size_t)t * 3 * d;
-  for (int idx = threadIdx.x; idx < d / 2; idx += blockDim.x) {
-    const int head = idx / half, i = idx - head * half;
-    const float cs = o.rope_cos[pos * half + i], sn = o.rope_sin[pos * half + i];
-    const int c0 = head * hd + i, c1 = c0 + half;
-    const size_t kv = (((size_t)slot * o.n_heads + head) * o.max_seq + pos) * hd;
-    const float q0 = row[c0], q1 = row[c1], k0 = row[d + c0], k1 = row[d + c1];
-    float* q = (float*)o.q + (size_t)t * d;
-    q[c0] = q0 * cs - q1 * sn;
-    q[c1] = q1 * cs + q0 * sn;
-    ((float*)o.k_cache)[kv + i] = k0 * cs - k1 * sn;
-    ((float*)o.k_cache)[kv + i + half] = k1 * cs + k0 * sn;
-    ((float*)o.v_cache)[kv + i] = row[2 * d + c0];
-    ((float*)o.v_cache)[kv + i + half] = row[2 * d + c1];
-  }
-}
-void rope_kv_f32(const float* qkv, int T, const RopeKv& o, hipStream_t st) {
-  hipLaunchKernelGGL(rope_kv_f32_kernel, dim3(T), dim3(128), 0, st, qkv, o);
-}
-
-__global__ void resid_add_kernel(float* x, const float* c, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) x[i] += c[i];
-}
-void resid_add_f32(float* x, const float* c, size_t n, hipStream_t st) {
-  hipLaunchKernelGGL(resid_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, c, n);
-}
-
-// gu [T, 2f] = [gate | up] -> act [T, f] = silu(gate) * up
-__global__ void swiglu_f32_kernel(const float* __restrict__ gu, float* __restrict__ act, int f, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const size_t t = i / f;
-  const int j = (int)(i - t * f);
-  const float g = gu[t * 2 * f + j], u = gu[t * 2 * f + f + j];
-  act[i] = g / (1.0f + expf(-g)) * u;
-}
-void swiglu_f32(const float* gu, float* act, int T, int f, hipStream_t st) {
-  const size_t n = (size_t)T * f;
-  hipLaunchKernelGGL(swiglu_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, gu, act, f, n);
 }
 
 }  // namespace vla
