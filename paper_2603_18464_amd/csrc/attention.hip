@@ -6,6 +6,8 @@
 // head dimension and accumulate the probability-weighted values.  Keys/values of a (slot, head)
 // are contiguous [position][head_dim] rows in the cache.  A few dozen keys: bound by latency, so a key is read as
 // 16-byte pieces and the values of eight keys are requested together.
+#include <type_traits>
+
 #include "common.h"
 
 namespace vla {
@@ -400,17 +402,18 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
 }
 
 // ---- decode: one new query per (sequence, head) against the whole cache -------------------------------
-// HBM-bound: the keys and values of a (slot, head) are one contiguous [position][HD] block each, and the
-// kernel streams them once with 16-byte-per-lane loads (a wave instruction covers 64*16/(2*HD) whole
-// rows).  One workgroup = 4 waves per (sequence, head); wave w takes every 4th group of rows.  A lane
-// owns 8 head dimensions of one row at a time: scores are reduced across the HD/8 lanes of a row with
-// shuffles, the probability-weighted values stay in 8 per-lane accumulators, and the partial softmax
+// HBM-bound at large batches, bound by its chain of latencies at small ones: the keys and values of a (slot, head) are
+// one contiguous [position][HD] block each, and the kernel streams them once with 16-byte-per-lane loads (a wave
+// instruction covers 64*16/(2*HD) whole rows).  One workgroup = 8 waves per (sequence, head); wave w takes every 8th
+// group of rows.  A lane owns 8 head dimensions of one row at a time: scores are reduced across the HD/8 lanes of a row
+// with shuffles, the probability-weighted values stay in 8 per-lane accumulators, and the partial softmax
 // statistics and outputs of the waves are merged through LDS at the end.
 //
 // The query and the new key / value row of this (sequence, head) are not read from memory but formed here from
 // the split-K partial sums of the QKV GEMM (summed in plane order, RoPE applied; the query stays in float32, the
 // key / value row is rounded as the cache holds it); the new row is appended to the cache for the following steps
-// and used from LDS in this one.
+// and used from LDS in this one.  The first two groups of cache rows are requested before that work, which needs none of
+// them, and every group's successor as soon as its registers are free.
 struct QkvPartials {
   const float* part;       // [ksplit][rows][3 * d_model]
   int ksplit, rows;
@@ -422,7 +425,7 @@ struct QkvPartials {
 // (k_lo / v_lo, same indexing, bf8(16 * lo)); both are streamed and added in float32; the output is written as hi
 // and lo fragments (out_frag_lo).
 template <int HD, bool TWO>
-__global__ __launch_bounds__(256) void decode_attention_kernel(
+__global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     f16* __restrict__ k_cache, f16* __restrict__ v_cache,
     unsigned char* __restrict__ k_lo, unsigned char* __restrict__ v_lo, const int32_t* __restrict__ tok_seq,
     const int32_t* __restrict__ tok_pos,
@@ -430,8 +433,10 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     QkvPartials qp) {
   constexpr int LPR = HD / 8;            // lanes per row
   constexpr int RPI = 64 / LPR;          // rows per wave instruction
-  __shared__ float s_m[4], s_l[4];
-  __shared__ float s_o[4][HD];
+  constexpr int NW = 8;                  // waves
+  constexpr int G = TWO ? 3 : 4;         // instructions of a group (what the registers hold twice)
+  __shared__ float s_m[NW], s_l[NW];
+  __shared__ float s_o[NW][HD];
   __shared__ __attribute__((aligned(16))) float s_q[HD], s_k[HD], s_v[HD];   // the new row, unrounded
   const int b = blockIdx.x, head = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -444,17 +449,48 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
   unsigned char* kbl = TWO ? k_lo + blk : nullptr;     // low terms: one byte per element, bf8(16 * lo)
   unsigned char* vbl = TWO ? v_lo + blk : nullptr;
   const int last_global = ctx - 2;                     // last row that is read from the cache
+
+  typedef __attribute__((ext_vector_type(2))) int i32x2;
+  f16x8 kv[2][G], vv[2][G];
+  i32x2 kl[2][TWO ? G : 1], vl[2][TWO ? G : 1];         // low terms of the same rows: 8 bytes per lane
+  const int n_it = (ctx + NW * RPI - 1) / (NW * RPI);   // instructions of a wave
+  auto row_of = [&](int it) { return (it * NW + wave) * RPI + sub; };
+  auto request = [&](auto S, int it0) {
+    constexpr int s = decltype(S)::value;
+    if (it0 >= n_it) return;                            // uniform
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const size_t off = (size_t)min(row_of(it0 + u), last_global) * HD + c * 8;
+      kv[s][u] = *(const f16x8*)(kb + off);
+      vv[s][u] = *(const f16x8*)(vb + off);
+      if constexpr (TWO) {
+        kl[s][u] = *(const i32x2*)(kbl + off);
+        vl[s][u] = *(const i32x2*)(vbl + off);
+      }
+    }
+  };
+  constexpr std::integral_constant<int, 0> s0{};
+  constexpr std::integral_constant<int, 1> s1{};
+  request(s0, 0);
+  request(s1, G);
   {
     constexpr int HALF = HD / 2;
     if (threadIdx.x < HALF) {
       const int i = threadIdx.x, c0 = head * HD + i, c1 = c0 + HALF, d = d_model, pos = ctx - 1;
       const size_t N = 3 * (size_t)d;
-      float v[6] = {};
-      for (int ks = 0; ks < qp.ksplit; ++ks) {
-        const float* p = qp.part + ((size_t)ks * qp.rows + b) * N;
-        v[0] += p[c0]; v[1] += p[c1]; v[2] += p[d + c0]; v[3] += p[d + c1]; v[4] += p[2 * d + c0]; v[5] += p[2 * d + c1];
-      }
       const float cs = qp.rope_cos[pos * HALF + i], sn = qp.rope_sin[pos * HALF + i];
+      float p[kMaxKSplit][6];
+#pragma unroll
+      for (int ks = 0; ks < kMaxKSplit; ++ks) {         // all planes in flight; planes past the last repeat it, unused
+        const float* pp = qp.part + ((size_t)min(ks, qp.ksplit - 1) * qp.rows + b) * N;
+        p[ks][0] = pp[c0]; p[ks][1] = pp[c1]; p[ks][2] = pp[d + c0]; p[ks][3] = pp[d + c1];
+        p[ks][4] = pp[2 * d + c0]; p[ks][5] = pp[2 * d + c1];
+      }
+      float v[6] = {};
+#pragma unroll
+      for (int ks = 0; ks < kMaxKSplit; ++ks)
+#pragma unroll
+        for (int j = 0; j < 6; ++j) v[j] = ks < qp.ksplit ? v[j] + p[ks][j] : v[j];
       float q0, q1, k0f, k1f;
       rope_pair(v[0], v[1], cs, sn, q0, q1);
       rope_pair(v[2], v[3], cs, sn, k0f, k1f);
@@ -482,63 +518,70 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
   for (int j = 0; j < 8; ++j) qf[j] = s_q[c * 8 + j];
   const float scale = rsqrtf((float)HD);
 
-  // One pass with a running maximum per lane (row = (it*4 + wave)*RPI + sub): the key row and the value row of
-  // an iteration are requested together, so twice as many bytes are in flight as with a score pass followed by
-  // a value pass, and no scores have to be kept.
+  // One pass with a running maximum per lane: the key rows and the value rows of a group are requested together, so
+  // twice as many bytes are in flight as with a score pass followed by a value pass, and no scores have to be kept.  The
+  // maximum moves once per group.
   float m_run = -INFINITY, lsum = 0.f;
   float acc[8] = {};
-  const int n_it = (ctx + 4 * RPI - 1) / (4 * RPI);
-  typedef __attribute__((ext_vector_type(2))) int i32x2;
-  constexpr int U = 8;                     // iterations whose loads are issued together (16 rows of 16 bytes per lane)
-  for (int it0 = 0; it0 < n_it; it0 += U) {
-    f16x8 kv[U], vv[U];
-    i32x2 kl[TWO ? U : 1], vl[TWO ? U : 1];               // low terms of the same rows: 8 bytes per lane
+  auto consume = [&](auto S, int it0) {
+    constexpr int s = decltype(S)::value;
+    float sc[G];
+    float m_new = m_run;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = ((it0 + u) * 4 + wave) * RPI + sub;
-      const size_t off = (size_t)min(row, last_global) * HD + c * 8;
-      kv[u] = *(const f16x8*)(kb + off);
-      vv[u] = *(const f16x8*)(vb + off);
-      if constexpr (TWO) {
-        kl[u] = *(const i32x2*)(kbl + off);
-        vl[u] = *(const i32x2*)(vbl + off);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int row = ((it0 + u) * 4 + wave) * RPI + sub;
-      float kf[8], vf[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        kf[j] = (float)kv[u][j];
-        vf[j] = (float)vv[u][j];
-        if constexpr (TWO) {
-          kf[j] += unpack_lo8(kl[u][j >> 2], j & 3);
-          vf[j] += unpack_lo8(vl[u][j >> 2], j & 3);
-        }
-      }
+    for (int u = 0; u < G; ++u) {
+      const int row = row_of(it0 + u);
+      float t = 0.f;
       if (row > last_global) {                               // the new row, from LDS
 #pragma unroll
+        for (int j = 0; j < 8; ++j) t = fmaf(qf[j], s_k[c * 8 + j], t);
+      } else {
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
-          kf[j] = s_k[c * 8 + j];
-          vf[j] = s_v[c * 8 + j];
+          float kf = (float)kv[s][u][j];
+          if constexpr (TWO) kf += unpack_lo8(kl[s][u][j >> 2], j & 3);
+          t = fmaf(qf[j], kf, t);
         }
       }
-      float s = 0.f;
+      sc[u] = t;
+    }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) s = fmaf(qf[j], kf[j], s);
+    for (int o = LPR / 2; o > 0; o >>= 1)
 #pragma unroll
-      for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (row < ctx) {                                      // uniform over the LPR lanes of a row
-        s *= scale;
-        const float m_new = fmaxf(m_run, s);
-        const float alpha = __expf(m_run - m_new);          // exp(-inf) = 0 on the lane's first row
-        const float p = __expf(s - m_new);
-        lsum = lsum * alpha + p;
+      for (int u = 0; u < G; ++u) sc[u] += __shfl_xor(sc[u], o, 64);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = fmaf(p, vf[j], acc[j] * alpha);
-        m_run = m_new;
+    for (int u = 0; u < G; ++u) {
+      sc[u] = row_of(it0 + u) < ctx ? sc[u] * scale : -INFINITY;   // uniform over the LPR lanes of a row
+      m_new = fmaxf(m_new, sc[u]);
+    }
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;          // no live row so far: everything stays zero
+    const float alpha = __expf(m_run - m_use);                     // exp(-inf) = 0 on the lane's first live group
+    m_run = m_new;
+    lsum *= alpha;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] *= alpha;
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const float p = __expf(sc[u] - m_use);
+      lsum += p;
+      if (row_of(it0 + u) > last_global) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = fmaf(p, s_v[c * 8 + j], acc[j]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          float vf = (float)vv[s][u][j];
+          if constexpr (TWO) vf += unpack_lo8(vl[s][u][j >> 2], j & 3);
+          acc[j] = fmaf(p, vf, acc[j]);
+        }
       }
+    }
+  };
+  for (int it0 = 0; it0 < n_it; it0 += 2 * G) {
+    consume(s0, it0);
+    request(s0, it0 + 2 * G);
+    if (it0 + G < n_it) {                                          // uniform
+      consume(s1, it0 + G);
+      request(s1, it0 + 3 * G);
     }
   }
   // bring the lanes of the wave to a common maximum, then add the row groups
@@ -565,10 +608,12 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
   __syncthreads();
   if (threadIdx.x < HD) {
     const int i = threadIdx.x;
-    const float m = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+    float m = s_m[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, s_m[w]);
     float l = 0.f, o = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float f = s_m[w] == -INFINITY ? 0.f : __expf(s_m[w] - m);
       l += s_l[w] * f;
       o += s_o[w][i] * f;
@@ -591,7 +636,7 @@ void decode_attention_fused(const float* part, int ksplit, int part_rows, const 
   const dim3 grid(B, n_heads);
   const QkvPartials qp{part, ksplit, part_rows, rope_cos, rope_sin};
 #define VLA_DEC_ATT(HDV, TWOV)                                                                                     \
-  hipLaunchKernelGGL((decode_attention_kernel<HDV, TWOV>), grid, dim3(256), 0, st, k_cache, v_cache,              \
+  hipLaunchKernelGGL((decode_attention_kernel<HDV, TWOV>), grid, dim3(512), 0, st, k_cache, v_cache,              \
                      k_lo, v_lo, tok_seq, tok_pos, out_frag, out_frag_lo, d_model, n_heads, max_seq, qp)
   if (k_lo) {
     if (head_dim == 128) VLA_DEC_ATT(128, true);

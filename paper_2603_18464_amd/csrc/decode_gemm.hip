@@ -208,54 +208,74 @@ __device__ __forceinline__ float block_sum_256d(float v, float* red) {
 
 // x[m,:] += sum_ks part[ks][m,:]; if gain: hn (fragment order) = f16(x * gain / rms(x)), and with hn_frag_lo the
 // low terms f16(h - hi) as well.  Row m of the launch is row prow0 + m of each plane (plane_rows rows per plane) and
-// row row0 + m of x and hn.
-__global__ __launch_bounds__(256) void reduce_resid_norm_kernel(const float* __restrict__ part, int ksplit,
-                                                                int plane_rows, int prow0, int d,
-                                                                float* __restrict__ x, const float* __restrict__ gain,
-                                                                float eps, f16* __restrict__ hn_frag,
-                                                                f16* __restrict__ hn_frag_lo, int row0) {
-  __shared__ float red[4];
+// row row0 + m of x and hn.  Bound by latency (one row is 16 KiB a plane at d = 4096): up to 1024 threads a row, so that
+// all of a row's loads are one round, and the sums stay in registers between the statistics and the output.
+template <int VPT>                                         // float4 per thread
+__global__ __launch_bounds__(1024) void reduce_resid_norm_kernel(const float* __restrict__ part, int ksplit,
+                                                                 int plane_rows, int prow0, int d,
+                                                                 float* __restrict__ x, const float* __restrict__ gain,
+                                                                 float eps, f16* __restrict__ hn_frag,
+                                                                 f16* __restrict__ hn_frag_lo, int row0) {
+  __shared__ float red[16];
   const int m = blockIdx.x;
   float* row = x + (size_t)(row0 + m) * d;
+  f32x4 v[VPT], g[VPT];
   float ss = 0.f;
-  for (int i = threadIdx.x * 4; i < d; i += 1024) {
-    float4 v = *(const float4*)(row + i);
-    float4 p[kMaxKSplit];
 #pragma unroll
-    for (int ks = 0; ks < kMaxKSplit; ++ks)            // all loads in flight first; summed in slice order
-      p[ks] = ks < ksplit ? *(const float4*)(part + ((size_t)ks * plane_rows + prow0 + m) * d + i)
-                          : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int it = 0; it < VPT; ++it) {
+    const int i = (threadIdx.x + it * blockDim.x) * 4;
+    if (i < d) {
+      f32x4 p[kMaxKSplit];
+      v[it] = *(const f32x4*)(row + i);
 #pragma unroll
-    for (int ks = 0; ks < kMaxKSplit; ++ks) {
-      v.x += p[ks].x; v.y += p[ks].y; v.z += p[ks].z; v.w += p[ks].w;
+      for (int ks = 0; ks < kMaxKSplit; ++ks)              // all loads in flight first; summed in slice order
+        p[ks] = ks < ksplit ? *(const f32x4*)(part + ((size_t)ks * plane_rows + prow0 + m) * d + i)
+                            : f32x4{0.f, 0.f, 0.f, 0.f};
+      if (gain) g[it] = *(const f32x4*)(gain + i);
+#pragma unroll
+      for (int ks = 0; ks < kMaxKSplit; ++ks)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[it][j] += p[ks][j];
+      *(f32x4*)(row + i) = v[it];
+      ss += v[it][0] * v[it][0] + v[it][1] * v[it][1] + v[it][2] * v[it][2] + v[it][3] * v[it][3];
     }
-    *(float4*)(row + i) = v;
-    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
   }
   if (!gain) return;
-  ss = block_sum_256d(ss, red);
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  ss = 0.f;
+  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) ss += red[w];
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int i = threadIdx.x * 4; i < d; i += 1024) {      // same mapping as above: a thread re-reads its own sums
-    const float4 v = *(const float4*)(row + i);
-    const float4 g = *(const float4*)(gain + i);
-    typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-    const float h[4] = {v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w};
-    f16x4 o, oe;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      o[j] = from_f32<f16>(h[j]);
-      oe[j] = from_f32<f16>(h[j] - (float)o[j]);
+  for (int it = 0; it < VPT; ++it) {
+    const int i = (threadIdx.x + it * blockDim.x) * 4;
+    if (i < d) {
+      typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+      f16x4 o, oe;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float h = v[it][j] * inv * g[it][j];
+        o[j] = from_f32<f16>(h);
+        oe[j] = from_f32<f16>(h - (float)o[j]);
+      }
+      const size_t at = frag_index(row0 + m, i, d);
+      *(f16x4*)(hn_frag + at) = o;
+      if (hn_frag_lo) *(f16x4*)(hn_frag_lo + at) = oe;
     }
-    const size_t at = frag_index(row0 + m, i, d);
-    *(f16x4*)(hn_frag + at) = o;
-    if (hn_frag_lo) *(f16x4*)(hn_frag_lo + at) = oe;
   }
 }
 
 void reduce_resid_norm(const float* part, int ksplit, int plane_rows, int prow0, int M, int d, float* x,
                        const float* gain, float eps, f16* hn_frag, f16* hn_frag_lo, int row0, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_resid_norm_kernel, dim3(M), dim3(256), 0, st, part, ksplit, plane_rows, prow0, d, x, gain,
-                     eps, hn_frag, hn_frag_lo, row0);
+  const int n4 = d / 4, threads = n4 >= 1024 ? 1024 : (n4 + 63) / 64 * 64;     // d <= 16384 (configuration checks)
+#define VLA_REDUCE(V)                                                                                                 \
+  hipLaunchKernelGGL(reduce_resid_norm_kernel<V>, dim3(M), dim3(threads), 0, st, part, ksplit, plane_rows, prow0, d, x, \
+                     gain, eps, hn_frag, hn_frag_lo, row0)
+  if (n4 <= 1024) VLA_REDUCE(1);
+  else if (n4 <= 2048) VLA_REDUCE(2);
+  else VLA_REDUCE(4);
+#undef VLA_REDUCE
 }
 
 // Start of a decode step, one workgroup per row: the token's embedding becomes row b of the residual stream, the row's
@@ -335,32 +355,42 @@ __global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float* __restr
                                                             int prow0, int f, f16* __restrict__ act_frag,
                                                             f16* __restrict__ act_frag_lo, int row0) {
   const int m = blockIdx.y;
-  const int j0 = (blockIdx.x * 256 + threadIdx.x) * 8;      // 8 consecutive outputs (same 32-block)
+  const int j0 = (blockIdx.x * 256 + threadIdx.x) * 4;      // 4 consecutive outputs (same 32-block)
   if (j0 >= f) return;
   const int col = (j0 >> 5) * 64 + (j0 & 31);
-  float g[8] = {}, u[8] = {};
-  for (int ks = 0; ks < ksplit; ++ks) {
-    const float* p = part + ((size_t)ks * plane_rows + prow0 + m) * (2 * (size_t)f) + col;
+  f32x4 gp[kMaxKSplit], up[kMaxKSplit];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      g[j] += p[j];
-      u[j] += p[32 + j];
+  for (int ks = 0; ks < kMaxKSplit; ++ks)                    // all loads in flight first; summed in slice order
+    if (ks < ksplit) {
+      const float* p = part + ((size_t)ks * plane_rows + prow0 + m) * (2 * (size_t)f) + col;
+      gp[ks] = *(const f32x4*)p;
+      up[ks] = *(const f32x4*)(p + 32);
     }
-  }
-  f16x8 o, oe;
+  f32x4 g = {0.f, 0.f, 0.f, 0.f}, u = g;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
+  for (int ks = 0; ks < kMaxKSplit; ++ks)
+    if (ks < ksplit) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        g[j] += gp[ks][j];
+        u[j] += up[ks][j];
+      }
+    }
+  typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+  f16x4 o, oe;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
     const float a = g[j] / (1.0f + __expf(-g[j])) * u[j];
     o[j] = from_f32<f16>(a);
     oe[j] = from_f32<f16>(a - (float)o[j]);
   }
   const size_t at = frag_index(row0 + m, j0, f);
-  *(f16x8*)(act_frag + at) = o;
-  if (act_frag_lo) *(f16x8*)(act_frag_lo + at) = oe;
+  *(f16x4*)(act_frag + at) = o;
+  if (act_frag_lo) *(f16x4*)(act_frag_lo + at) = oe;
 }
 void reduce_swiglu(const float* part, int ksplit, int plane_rows, int prow0, int M, int f, f16* act_frag,
                    f16* act_frag_lo, int row0, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_swiglu_kernel, dim3((f / 8 + 255) / 256, M), dim3(256), 0, st, part, ksplit, plane_rows,
+  hipLaunchKernelGGL(reduce_swiglu_kernel, dim3((f / 4 + 255) / 256, M), dim3(256), 0, st, part, ksplit, plane_rows,
                      prow0, f, act_frag, act_frag_lo, row0);
 }
 
