@@ -220,22 +220,22 @@ struct EpiQkv {
 // ---- 8-bit low terms --------------------------------------------------------------------------------------
 // Two-term activations may carry their low term as one byte: lo8 = bf8(16 * (a - f16(a))) (1-5-2 format), stored
 // behind the high terms of the same row, A row = [hi: Kw halves | lo8: Kw bytes].  The low-term product then runs
-// on v_mfma_f32_32x32x64 in 8-bit formats (twice the rate of the half-precision instruction) against a second
+// on v_mfma_f32_16x16x128 in 8-bit formats (twice the rate of the half-precision instruction) against a second
 // copy of the weights, W8 = fp8(w * 16) (1-4-3 format, saturating at +-448, i.e. |w| = 28), so that
 // lo8 * W8 = 2^8 * lo * w lands in the same accumulator as hi * (w * 2^8).  The correction term only has to be good
 // to a few percent (it is itself 2^-12 of the result), which three and two mantissa bits give.
-// Layout: a 64-byte row slab of lo8 has the geometry of a 32-half slab of hi (64-byte rows), and W8 is packed so
-// that its 64-k slab of a 32-row block is two 1 KiB pieces, lane (n, g) of piece j holding k = 32 j + 16 g .. + 15;
-// a lane's operand is its 16 bytes of "k-step 0" followed by its 16 bytes of "k-step 1", for both operands.
+// Layout: a 128-byte row slab of lo8 has the geometry of a 64-half slab of hi, and W8 is packed so that the 16-byte
+// chunk c (16 k) of a row lies where the 16-byte chunk c (8 k) of the row lies in the fragment-order halves; a lane's
+// operand of the 128-deep product is its 16 bytes of k-step 0 followed by its 16 bytes of k-step 1, for both operands.
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-__device__ __forceinline__ f32x16 mfma_lo8(const f16x8& a0, const f16x8& a1, const f16x8& b0, const f16x8& b1,
-                                           const f32x16& c) {
+__device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, const f16x8& b0, const f16x8& b1,
+                                          const f32x4& c) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const i32x8 a = __builtin_shufflevector(__builtin_bit_cast(i32x4, a0), __builtin_bit_cast(i32x4, a1), 0, 1, 2, 3, 4, 5, 6, 7);
   const i32x8 b = __builtin_shufflevector(__builtin_bit_cast(i32x4, b0), __builtin_bit_cast(i32x4, b1), 0, 1, 2, 3, 4, 5, 6, 7);
   // A: bf8 (format 1), B: fp8 (format 0), no block scales
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 1, 0, 0, 0, 0, 0);
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 1, 0, 0, 0, 0, 0);
 #else
   return c;
 #endif
@@ -247,14 +247,21 @@ __device__ __forceinline__ f32x16 mfma_lo8(const f16x8& a0, const f16x8& a1, con
 // * Slabs of PK k of A and W go straight from global memory into LDS (global_load_lds_dwordx4: lane l of a wave
 //   instruction deposits its 16 bytes at the wave-uniform LDS base + 16*l), S slabs ahead of the MFMAs, through a
 //   ring of S stages; one barrier per slab publishes the landed slab and frees the one everybody has in registers.
-// * Fragments are double buffered in registers: while the MFMAs of one unit (KU k-steps) run, the reads of the next
+// * Fragments are double buffered in registers: while the MFMAs of one k-step run, the reads of the next
 //   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
 //   for ALL outstanding LDS loads before any LDS read, so the reads are inline assembly and the waits explicit.
-// * The instruction: 16x16x32 where every operand is half precision, 32x32x16 where the launch has a pass of 8-bit
-//   low terms (its 32x32x64 product needs that accumulator layout).  On real operands the matrix cores are limited by
-//   power, not issue: an MFMA-only loop on random activations and bf16-exact weights sustains 1.94 PFLOP/s with
-//   16x16x32 (half the accumulator traffic per product) against 1.68 with 32x32x16.  In this kernel that is 2.59 ms
-//   instead of 2.85 (gate/up, 18560 x 22016 x 4096), 1.40 instead of 1.48 (down), 0.56 instead of 0.61 (o).
+// * The instruction: 16x16x32.  On real operands the matrix cores are limited by power, not issue: an MFMA-only loop on
+//   random activations and bf16-exact weights sustains 1.94 PFLOP/s with 16x16x32 (half the accumulator traffic per
+//   product) against 1.68 with 32x32x16.  In this kernel that is 2.59 ms instead of 2.85 (gate/up, 18560 x 22016 x 4096),
+//   1.40 instead of 1.48 (down), 0.56 instead of 0.61 (o).
+// * A pass of 8-bit low terms (LO8) follows on 16x16x128: both k-steps of a slab are one product, so the two register
+//   buffers hold one slab and there is none to spare for the next.  Each register is refilled as soon as its last
+//   product has issued instead: a slab runs as two halves of the wave's rows, the first half's A fragments are refilled
+//   during the second half, a column's B fragments behind their last product there, and the second half's A fragments
+//   at its end, so that every refill has half a slab of products to arrive under.
+//   Against 4 waves of 128x128 with 32x32x16 and 32x32x64 the 7B policy step of 64 takes 244.5 instead of 247.5 ms (its
+//   4 two-term layers are a sixth of it), of 8 54.0 instead of 54.2, the 12-layer model's of 32 6.24 instead of 6.29;
+//   with 128x256 tiles at every size 247.9, 54.3 and 6.22.
 // * A slab layout: rows of PK halves; chunk c (16 bytes) of row r sits in slot c ^ swz(r).  The LDS serves a 16-byte
 //   read in groups of 16 lanes, {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} of each half-wave pair, so a group of the
 //   16x16 reads mixes two chunk columns; swz is chosen so that such a group covers all 64 banks (plain (r >> 2) & 3
@@ -262,13 +269,18 @@ __device__ __forceinline__ f32x16 mfma_lo8(const f16x8& a0, const f16x8& a1, con
 // * Every variant runs the same sequence of MFMAs per output element (k ascending, one chain), so a sequence's bits do
 //   not depend on which tile its batch selects.
 
-// 16 bytes per lane from global memory straight into LDS at lds_wave_base + 16 * lane.  The builtin only
-// exists in the device pass; the host pass just needs the kernel's stub.
-__device__ __forceinline__ void load_to_lds_16(const f16* src, f16* lds_wave_base) {
+// 16 bytes per lane from global memory straight into LDS at lds_wave_base + 16 * lane.  base and soff (bytes) are the same
+// for the whole wave and live in scalar registers, off is the lane's offset in bytes: a buffer load takes the three as
+// they are, where a 64-bit address per lane would cost an addition and two registers a load (with the pass of low terms
+// those registers spilled).  The builtins only exist in the device pass; the host pass just needs the kernel's stub.
+__device__ __forceinline__ void load_to_lds_16(const f16* base, unsigned off, unsigned soff, f16* lds_wave_base) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_global_load_lds(src, lds_wave_base, 16, 0, 0);
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000);   // raw, 4 GiB
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds_wave_base, 16, off, soff, 0, 0);
 #else
-  (void)src;
+  (void)base;
+  (void)off;
+  (void)soff;
   (void)lds_wave_base;
 #endif
 }
@@ -280,13 +292,26 @@ __device__ __forceinline__ void read_frag_asm(f16x8& dst, unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 #endif
 }
+// Until at most N of the reads issued so far are outstanding (they return in order; the loops hold no scalar loads).
+template <int N = 0>
 __device__ __forceinline__ void wait_lds() {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N < 15 ? N : 15) : "memory");
 #endif
 }
 // Ties a fragment to the wait before it: nothing that uses it can be scheduled above.
 __device__ __forceinline__ void hold(f16x8& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+__device__ __forceinline__ void hold_acc(f32x4& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+// Keeps what is computed from v from being computed ahead of a loop and kept in registers.
+__device__ __forceinline__ void hold32(unsigned& v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(v));
 #endif
@@ -297,25 +322,26 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 #endif
 }
+#define VLA_INLINE __attribute__((always_inline))    // the kernel's lambdas: a call would put the captured arrays in memory
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
-  [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+  [&]<int... I>(std::integer_sequence<int, I...>) VLA_INLINE { (f(std::integral_constant<int, I>{}), ...); }
   (std::make_integer_sequence<int, N>{});
 }
 
-template <int INST> struct MfmaAcc;
-template <> struct MfmaAcc<32> { typedef f32x16 type; static constexpr int regs = 16, k = 16; };
-template <> struct MfmaAcc<16> { typedef f32x4 type; static constexpr int regs = 4, k = 32; };
-
-// acc += one product of the fragments: half precision (a0, b0), or the 8-bit low terms held by (a0, a1), (b0, b1)
-template <bool LOW>
-__device__ __forceinline__ void mma(f32x16& acc, const f16x8& a0, const f16x8& a1, const f16x8& b0, const f16x8& b1) {
-  if constexpr (LOW) acc = mfma_lo8(a0, a1, b0, b1, acc);
-  else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b0, acc, 0, 0, 0);
+// acc += a * b, the sum in the registers of acc.  With two loops over the same accumulators the compiler gives the
+// products of the first separate source and result registers, and the 256 of a wave run out (12 spilled, reloaded in
+// the loop with a wait for every load in flight).  The compiler does not know the latency of the statement: settle()
+// before anything but another of these touches the accumulators.
+__device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const f16x8& b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+#endif
 }
-template <bool LOW>
-__device__ __forceinline__ void mma(f32x4& acc, const f16x8& a0, const f16x8&, const f16x8& b0, const f16x8&) {
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b0, acc, 0, 0, 0);
+__device__ __forceinline__ void settle() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#endif
 }
 
 template <int PK>
@@ -328,20 +354,22 @@ __device__ __forceinline__ int a_swizzle(int r) {
   }
 }
 
+template <class Epi> __device__ __forceinline__ const f16* epi_a_lo(const Epi&) { return nullptr; }
+__device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a_lo; }
+
 // LO8: the launch has slabs of 8-bit low terms (W8 != nullptr): K == 1.5 * Kw, A row = [hi: Kw halves | lo8: Kw bytes].
 // Otherwise K == Kw, or K == 2 * Kw (half-precision low terms behind the high terms: the weight slabs wrap).
 // SPLITK (with EpiPartial; one row of tiles, M <= BM): A is in the fragment order of the decode path
 // ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), tiles_m is the
 // number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
-template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, class Epi, bool LO8, bool SPLITK>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, class Epi, bool LO8, bool SPLITK>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16* __restrict__ A, int lda,
                                                                    const f16* __restrict__ Wp,
                                                                    const f16* __restrict__ W8, int M, int K, int Kw,
                                                                    int tiles_m, int tiles_n, Epi epi_in) {
-  static_assert(INST == 32 || !LO8, "the 8-bit low-term pass is written for the 32x32x64 instruction");
-  typedef typename MfmaAcc<INST>::type Acc;
-  constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / INST, NT = WN / INST;
-  constexpr int KS = PK / MfmaAcc<INST>::k, KS16 = PK / 16;   // k-steps of a slab; 16-k blocks of a slab
+  static_assert(!LO8 || PK == 64, "a slab of low terms is one 128-deep product");
+  constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / 16, NT = WN / 16;
+  constexpr int KS = PK / 32, KS16 = PK / 16;          // k-steps of a slab; 16-k blocks of a slab
   constexpr int AP = BM * PK / 512 / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;   // KiB pieces per wave and slab
   static_assert(AP * NW * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
   constexpr int A_HALVES = BM * PK, STAGE_HALVES = (BM + BN) * PK;
@@ -389,154 +417,217 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     epi.part += (size_t)kz * epi.plane_rows * epi.N;
   }
 
-  const f16* a_src[AP];
-  const f16* a_lo_src[AP];
-#pragma unroll
-  for (int i = 0; i < AP; ++i) {
-    if constexpr (SPLITK) {
-      const int j = wave * AP + i;                     // piece of the slab: block row j / KS16 (clamped to the rows
-      const int rb = min(j / KS16, (M - 1) >> 5);      // that exist), 16-k block j % KS16
-      const size_t off = ((size_t)rb * KB16 + kb0 + j % KS16) * 512 + lane * 8;
-      a_src[i] = A + off;
-      a_lo_src[i] = (epi.a_lo ? epi.a_lo : A) + off;
-    } else {
-      const int r = (wave * AP + i) * RPP + lane / (PK / 8);
-      const int c = (lane % (PK / 8)) ^ a_swizzle<PK>(r);
-      a_src[i] = A + (size_t)min(m0 + r, M - 1) * lda + c * 8;
-      a_lo_src[i] = nullptr;
-    }
-  }
-  const f16* w_src[WP];
-  const f16* w8_src[WP];
-#pragma unroll
-  for (int i = 0; i < WP; ++i) {
-    const int j = wave * WP + i;                       // piece of the slab: block row j / KS16, 16-k block j % KS16
-    w_src[i] = Wp + ((size_t)(n0 / 32 + j / KS16) * KB16 + kb0 + j % KS16) * 512 + lane * 8;
-    w8_src[i] = LO8 ? W8 + (size_t)(n0 / 32 + j / KS16) * KB16 * 256 + (j % KS16) * 512 + lane * 8 : nullptr;
-  }
-  auto issue_one = [&](int kt, auto I) {               // piece I of this wave's share of slab kt (clamped)
+  const unsigned lane16 = (unsigned)lane * 16u;        // lane offset in an operand in fragment order
+  const f16* a_base = SPLITK ? A + kb0 * 512 : A + (size_t)m0 * lda;
+  const f16* a_lo_base = SPLITK && epi_a_lo(epi) ? epi_a_lo(epi) + kb0 * 512 : a_base;
+  const f16* w_base = Wp + ((size_t)(n0 / 32) * KB16 + kb0) * 512;
+  const f16* w8_base = LO8 ? W8 + (size_t)(n0 / 32) * KB16 * 256 : w_base;
+  // Rows of A: piece i of a wave holds rows r0 + i * RPP (clamped to the last one), whose swizzle is that of r0 with the
+  // chunk's bits of swz(i * RPP) flipped, so two registers serve all pieces.
+  const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)(M - 1 - m0) * a_pitch;
+  const int r0 = wave * AP * RPP + lane / (PK / 8);
+  const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle<PK>(r0)) * 16u;
+  auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped)
     constexpr int i = decltype(I)::value;
     const int ks = min(kt, KT - 1), kw = ks >= KTw ? ks - KTw : ks;
     f16* base = lds + (kt % S) * STAGE_HALVES;
     if constexpr (i < AP) {
-      const f16* src;
-      if constexpr (SPLITK) src = (ks >= KTw ? a_lo_src[i] : a_src[i]) + (size_t)kw * KS16 * 512;
-      else src = a_src[i] + (size_t)ks * PK;
-      load_to_lds_16(src, base + (wave * AP + i) * 512);
+      f16* dst = base + (wave * AP + i) * 512;
+      if constexpr (SPLITK) {
+        const int j = wave * AP + i;                   // piece of the slab: block row j / KS16 (clamped to the rows
+        const int rb = min(j / KS16, (M - 1) >> 5);    // that exist), 16-k block j % KS16
+        load_to_lds_16(ks >= KTw ? a_lo_base : a_base, lane16, 1024u * (unsigned)(rb * KB16 + j % KS16 + kw * KS16), dst);
+      } else {
+        unsigned row = a_row;
+        hold32(row);                                   // the offset is formed here, three instructions a load, and not kept
+        row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle<PK>(i * RPP) * 16));
+        load_to_lds_16(a_base, row, 2u * PK * (unsigned)ks, dst);
+      }
     } else {
-      constexpr int j = i - AP;
-      load_to_lds_16((LO8 && ks >= KTw ? w8_src[j] : w_src[j]) + (size_t)kw * KS16 * 512,
-                     base + A_HALVES + (wave * WP + j) * 512);
+      const int j = wave * WP + i - AP;                // piece of the slab: block row j / KS16, 16-k block j % KS16
+      const bool low = LO8 && ks >= KTw;
+      const unsigned blk = (unsigned)(j / KS16 * KB16) * (low ? 512u : 1024u) + (unsigned)(j % KS16) * 1024u;
+      load_to_lds_16(low ? w8_base : w_base, lane16, blk + 1024u * KS16 * (unsigned)kw, base + A_HALVES + j * 512);
     }
   };
 
-  Acc acc[MT][NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int e = 0; e < MfmaAcc<INST>::regs; ++e) acc[i][j][e] = 0.0f;
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // LDS byte addresses of this lane's fragments inside stage 0.  A lane of a fragment is (row l % INST, k group
-  // l / INST of 8 k); in fragment order its 16 bytes are at 16 * (row & 31) + 512 * (group & 1) of 16-k block group / 2.
+  // LDS byte addresses of this lane's fragments inside stage 0.  A lane of a fragment is (row l % 16, k group
+  // l / 16 of 8 k); in fragment order its 16 bytes are at 16 * (row & 31) + 512 * (group & 1) of 16-k block group / 2.
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char*)smem);
-  const int frow = wm * WM + (lane & (INST - 1)), fgrp = lane / INST;
-  const unsigned in_block = (unsigned)(fgrp >> 1) * 1024u + (unsigned)(fgrp & 1) * 512u + (unsigned)(lane & (INST - 1)) * 16u;
+  const int frow = wm * WM + (lane & 15), fgrp = lane >> 4;
+  const unsigned in_block = (unsigned)(fgrp >> 1) * 1024u + (unsigned)(fgrp & 1) * 512u + (unsigned)(lane & 15) * 16u;
   unsigned a_k[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
-    const int c = (64 / INST) * s + fgrp;              // 16-byte chunk of the row
+    const int c = 4 * s + fgrp;                        // 16-byte chunk of the row
     if constexpr (SPLITK) a_k[s] = lds0 + (unsigned)(wm * (WM / 32) * KS16) * 1024u + in_block;
     else a_k[s] = lds0 + 2u * (unsigned)(frow * PK + ((c ^ a_swizzle<PK>(frow)) << 3));
   }
   const unsigned w_b = lds0 + 2u * (unsigned)(A_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
 
-  constexpr int KU = INST == 32 ? 2 : 1, US = KS / KU;         // k-steps per unit, units per slab
-  f16x8 af[2][KU][MT], bf[2][KU][NT];
-  constexpr int RPK = MT + NT, R = KU * RPK, MF = KU * MT * NT;
-  auto read_one = [&](unsigned so, int f, auto U, auto I) {    // I-th fragment read of unit U of a slab
-    constexpr int s = decltype(I)::value / RPK, x = decltype(I)::value % RPK, ss = decltype(U)::value * KU + s;
-    constexpr int j = x < MT ? x : x - MT;
-    // block j of an operand in fragment order: 32 rows hold one or two fragments
-    constexpr int frag = INST == 32 ? (j * KS16 + ss) * 1024 : (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256;
-    if constexpr (x < MT) read_frag_asm<SPLITK ? frag : j * INST * PK * 2>(af[f][s][j], a_k[ss] + so);
-    else read_frag_asm<frag>(bf[f][s][j], w_b + so);
+  f16x8 af[2][MT], bf[2][NT];
+  constexpr int R = MT + NT, MF = MT * NT;             // reads and products of a k-step
+  // fragment reads of k-step ss of the stage at byte offset so (block j of an operand in fragment order: 32 rows hold two
+  // fragments)
+  auto read_a = [&](unsigned so, f16x8& dst, auto SS, auto J) VLA_INLINE {
+    constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
+    read_frag_asm<SPLITK ? (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256 : j * 16 * PK * 2>(dst, a_k[ss] + so);
   };
-  auto arrived = [&](int f) {
+  auto read_b = [&](unsigned so, f16x8& dst, auto SS, auto J) VLA_INLINE {
+    constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
+    read_frag_asm<(j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256>(dst, w_b + so);
+  };
+  auto read_one = [&](unsigned so, int f, auto SS, auto I) VLA_INLINE {   // I-th fragment read of a k-step
+    constexpr int x = decltype(I)::value;
+    if constexpr (x < MT) read_a(so, af[f][x], SS, I);
+    else read_b(so, bf[f][x - MT], SS, std::integral_constant<int, x - MT>{});
+  };
+  auto arrived = [&](int f) VLA_INLINE {
     wait_lds();
 #pragma unroll
-    for (int s = 0; s < KU; ++s) {
+    for (int i = 0; i < MT; ++i) hold(af[f][i]);
 #pragma unroll
-      for (int i = 0; i < MT; ++i) hold(af[f][s][i]);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) hold(bf[f][s][j]);
-    }
+    for (int j = 0; j < NT; ++j) hold(bf[f][j]);
   };
-  // One unit of slab kt, its fragments in register buffer F: the MFMAs, and between them the reads of the next unit (in
-  // the first three quarters, so that they have landed at the end).  In the last unit of a slab the next one belongs
-  // to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes slab kt + S.
-  auto unit = [&](int kt, auto F, auto U, auto L8) {
-    constexpr int f = decltype(F)::value, u = decltype(U)::value;
-    constexpr bool low = decltype(L8)::value, last = u == US - 1;
-    constexpr int n_mf = low ? MF / 2 : MF, n_rd = n_mf * 3 / 4 > 0 ? n_mf * 3 / 4 : 1;
+  // One k-step of slab kt, its fragments in register buffer F: the MFMAs, and between them the reads of the next k-step
+  // (in the first three quarters, so that they have landed at the end).  In the last k-step of a slab the next one
+  // belongs to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes slab kt + S.
+  auto step = [&](int kt, auto F, auto SS) VLA_INLINE {
+    constexpr int f = decltype(F)::value, ss = decltype(SS)::value;
+    constexpr bool last = ss == KS - 1;
+    constexpr int n_rd = MF * 3 / 4 > 0 ? MF * 3 / 4 : 1;
     if constexpr (last) {
       wait_vmcnt<(S - 2) * LPS>();
       __builtin_amdgcn_s_barrier();
     }
     const unsigned so = (unsigned)((kt + (last ? 1 : 0)) % S) * (2u * STAGE_HALVES);
-    static_for<n_mf>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      constexpr int s = i / (MT * NT), mt = i / NT % MT, nt = i % NT;
-      constexpr int sl = low ? 2 * s : s, sh = low ? 2 * s + 1 : s;
-      mma<low>(acc[mt][nt], af[f][sl][mt], af[f][sh][mt], bf[f][sl][nt], bf[f][sh][nt]);
+    static_for<MF>([&](auto I) VLA_INLINE {
+      constexpr int i = decltype(I)::value, mt = i / NT, nt = i % NT;
+      if constexpr (LO8) mfma_in_place(acc[mt][nt], af[f][mt], bf[f][nt]);
+      else acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[f][mt], bf[f][nt], acc[mt][nt], 0, 0, 0);
       constexpr int r0 = i < n_rd ? i * R / n_rd : R, r1 = i < n_rd ? (i + 1) * R / n_rd : R;
-      static_for<r1 - r0>([&](auto J) {
-        read_one(so, f ^ 1, std::integral_constant<int, last ? 0 : u + 1>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
+      static_for<r1 - r0>([&](auto J) VLA_INLINE {
+        read_one(so, f ^ 1, std::integral_constant<int, last ? 0 : ss + 1>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
       });
       if constexpr (last) {
-        constexpr int l0 = i * LPS / n_mf, l1 = (i + 1) * LPS / n_mf;
-        static_for<l1 - l0>([&](auto J) { issue_one(kt + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
+        constexpr int l0 = i * LPS / MF, l1 = (i + 1) * LPS / MF;
+        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_one(kt + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
       }
       __builtin_amdgcn_sched_barrier(0);
     });
     arrived(f ^ 1);
   };
-  auto slab = [&](int kt, auto F0, auto L8) {          // slab kt starts in register buffer F0
-    static_for<US>([&](auto U) { unit(kt, std::integral_constant<int, (decltype(F0)::value + decltype(U)::value) & 1>{}, U, L8); });
+  auto slab = [&](int kt, auto F0) VLA_INLINE {                   // slab kt starts in register buffer F0
+    static_for<KS>([&](auto SS) VLA_INLINE { step(kt, std::integral_constant<int, (decltype(F0)::value + decltype(SS)::value) & 1>{}, SS); });
   };
   constexpr std::integral_constant<int, 0> c0{};
-  constexpr std::integral_constant<int, US & 1> cn{};  // buffer of an odd slab's first unit
-  constexpr std::false_type hi_t{};
-  constexpr std::true_type lo_t{};
-  static_for<S>([&](auto I) { static_for<LPS>([&](auto J) { issue_one(decltype(I)::value, J); }); });
+  constexpr std::integral_constant<int, 1> c1{};
+  constexpr std::integral_constant<int, KS & 1> cn{};  // buffer of an odd slab's first k-step
+  static_for<S>([&](auto I) VLA_INLINE { static_for<LPS>([&](auto J) VLA_INLINE { issue_one(decltype(I)::value, J); }); });
   wait_vmcnt<(S - 1) * LPS>();
   __builtin_amdgcn_s_barrier();
-  static_for<R>([&](auto I) { read_one(0u, 0, c0, I); });
+  static_for<R>([&](auto I) VLA_INLINE { read_one(0u, 0, c0, I); });
   arrived(0);
   const int KTh = LO8 ? KTw : KT;
   int kt = 0;
-  for (; kt + 1 < KTh; kt += 2) {
-    slab(kt, c0, hi_t);
-    slab(kt + 1, cn, hi_t);
-  }
-  if constexpr (LO8) {                                 // Kw is a multiple of 128 here: an even number of high slabs
-    for (; kt + 1 < KT; kt += 2) {
-      slab(kt, c0, lo_t);
-      slab(kt + 1, cn, lo_t);
+  if constexpr (LO8) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) hold_acc(acc[i][j]);
+    settle();                                          // the zeros are written
+    for (; kt < KTh; ++kt) slab(kt, c0);
+    settle();
+    // Fragments of one slab, k-steps 0 and 1: variables of their own, read afresh, since the product wants the two in
+    // adjacent registers and the loop above must not be bound by that.  Reads are issued in the order: first-half A
+    // fragments, B fragments column by column, second-half A fragments.
+    constexpr int H = MT / 2;
+    f16x8 al[2][MT], bl[2][NT];
+    auto refill_a = [&](unsigned so, auto J) VLA_INLINE {
+      read_a(so, al[0][decltype(J)::value], c0, J);
+      read_a(so, al[1][decltype(J)::value], c1, J);
+    };
+    auto refill_b = [&](unsigned so, auto J) VLA_INLINE {
+      read_b(so, bl[0][decltype(J)::value], c0, J);
+      read_b(so, bl[1][decltype(J)::value], c1, J);
+    };
+    auto hold_a = [&](int i) VLA_INLINE {
+      hold(al[0][i]);
+      hold(al[1][i]);
+    };
+    auto product = [&](auto MI, auto NI) VLA_INLINE {
+      constexpr int mt = decltype(MI)::value, nt = decltype(NI)::value;
+      acc[mt][nt] = mfma_lo8(al[0][mt], al[1][mt], bl[0][nt], bl[1][nt], acc[mt][nt]);
+    };
+    auto low_slab = [&](int t) VLA_INLINE {
+      static_for<NT>([&](auto NI) VLA_INLINE {         // rows of the first half
+        constexpr int nt = decltype(NI)::value;
+        wait_lds<2 * (NT - 1 - nt) + 2 * (MT - H)>();
+        if constexpr (nt == 0) {
+#pragma unroll
+          for (int i = 0; i < H; ++i) hold_a(i);
+        }
+        hold(bl[0][nt]);
+        hold(bl[1][nt]);
+        static_for<H>([&](auto MI) VLA_INLINE { product(MI, NI); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      wait_lds();
+#pragma unroll
+      for (int i = H; i < MT; ++i) hold_a(i);
+      wait_vmcnt<(S - 2) * LPS>();                     // slab t + 1 has landed, slab t is in everybody's registers
+      __builtin_amdgcn_s_barrier();
+      const unsigned so = (unsigned)((t + 1) % S) * (2u * STAGE_HALVES);
+      static_for<NT>([&](auto NI) VLA_INLINE {         // rows of the second half
+        constexpr int nt = decltype(NI)::value;
+        static_for<MT - H>([&](auto MI) VLA_INLINE {
+          product(std::integral_constant<int, H + decltype(MI)::value>{}, NI);
+          if constexpr (decltype(MI)::value == 0) {
+            if constexpr (nt == 0) static_for<H>([&](auto J) VLA_INLINE { refill_a(so, J); });
+            else refill_b(so, std::integral_constant<int, nt - 1>{});
+          }
+        });
+        constexpr int l0 = nt * LPS / NT, l1 = (nt + 1) * LPS / NT;
+        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_one(t + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      refill_b(so, std::integral_constant<int, NT - 1>{});
+      static_for<MT - H>([&](auto J) VLA_INLINE { refill_a(so, std::integral_constant<int, H + decltype(J)::value>{}); });
+    };
+    const unsigned so0 = (unsigned)(kt % S) * (2u * STAGE_HALVES);
+    static_for<H>([&](auto J) VLA_INLINE { refill_a(so0, J); });
+    static_for<NT>([&](auto J) VLA_INLINE { refill_b(so0, J); });
+    static_for<MT - H>([&](auto J) VLA_INLINE { refill_a(so0, std::integral_constant<int, H + decltype(J)::value>{}); });
+    for (; kt < KT; ++kt) low_slab(kt);
+    wait_lds();                                        // the last slab's refills
+#pragma unroll
+    for (int i = 0; i < MT; ++i) hold_a(i);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      hold(bl[0][j]);
+      hold(bl[1][j]);
     }
-    if (kt < KT) slab(kt, c0, lo_t);
-  } else if (kt < KTh) {
-    slab(kt, c0, hi_t);
+  } else {
+    for (; kt + 1 < KTh; kt += 2) {
+      slab(kt, c0);
+      slab(kt + 1, cn);
+    }
+    if (kt < KTh) slab(kt, c0);
   }
   wait_vmcnt<0>();                                     // the clamped tail loads still target this workgroup's LDS
   __syncthreads();                                     // every wave is done with the slabs: LDS becomes epilogue staging
 
-  // The pitch keeps the stores of a 32-row group conflict free: the row groups a store instruction covers (2 of 4 rows
-  // for 32x32, 4 for 16x16) start 32 or 16 banks apart.
+  // The pitch keeps the stores of a 32-row group conflict free: the four row groups a store instruction covers start 16
+  // banks apart.
   constexpr bool PAIR = WN < Epi::kSpan;               // two waves side by side share a staging tile
   static_assert(!PAIR || (WGN % 2 == 0 && 2 * WN >= Epi::kSpan), "an epilogue's span is one or two wave tiles");
-  constexpr int COLS = PAIR ? 2 * WN : WN, PITCH = COLS + (INST == 32 ? 8 : 4), ROWS = PAIR ? 16 : 32;
+  constexpr int COLS = PAIR ? 2 * WN : WN, PITCH = COLS + 4, ROWS = PAIR ? 16 : 32;
   float* tile = (float*)smem + (PAIR ? wave >> 1 : wave) * 32 * PITCH;
   const int side = PAIR ? wn & 1 : 0;
 #pragma unroll
@@ -545,29 +636,27 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       if (mb > 0) __syncthreads();                     // the partner has read the previous rows
     }
 #pragma unroll
-    for (int mi = 0; mi < 32 / INST; ++mi)
+    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int e = 0; e < MfmaAcc<INST>::regs; ++e) {
-          const int row = INST == 32 ? 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3) : mi * 16 + 4 * (lane >> 4) + e;
-          tile[row * PITCH + side * WN + nt * INST + (lane & (INST - 1))] = acc[mb * (32 / INST) + mi][nt][e];
-        }
+        for (int e = 0; e < 4; ++e)
+          tile[(mi * 16 + 4 * (lane >> 4) + e) * PITCH + side * WN + nt * 16 + (lane & 15)] = acc[mb * 2 + mi][nt][e];
     if constexpr (PAIR) __syncthreads();
     epi.template consume<COLS, PITCH, ROWS>(tile + side * ROWS * PITCH, m0 + wm * WM + mb * 32 + side * ROWS,
                                             n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
   }
 }
 
-template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, bool SPLITK, class Epi>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, bool SPLITK, class Epi>
 static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, int M, int K, int Kw, int tiles_m,
                          int tiles_n, const Epi& epi, hipStream_t st) {
   const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
   constexpr size_t slabs = (size_t)S * (WGM * WM + WGN * WN) * PK * sizeof(f16);
   constexpr bool pair = WN < Epi::kSpan;
-  constexpr size_t stage = (size_t)WGM * WGN / (pair ? 2 : 1) * 32 * ((pair ? 2 : 1) * WN + (INST == 32 ? 8 : 4)) * sizeof(float);
+  constexpr size_t stage = (size_t)WGM * WGN / (pair ? 2 : 1) * 32 * ((pair ? 2 : 1) * WN + 4) * sizeof(float);
   constexpr size_t smem = slabs > stage ? slabs : stage;
-  auto kern = gemm_f16_kernel<INST, WGM, WGN, WM, WN, PK, S, OCC, Epi, LO8, SPLITK>;
+  auto kern = gemm_f16_kernel<WGM, WGN, WM, WN, PK, S, OCC, Epi, LO8, SPLITK>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -575,9 +664,9 @@ static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, in
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, A, lda, Wp, W8, M, K, Kw, tiles_m, tiles_n, epi);
 }
-template <int INST, int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, class Epi>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, class Epi>
 static void launch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  launch_tiles<INST, WGM, WGN, WM, WN, PK, S, OCC, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
+  launch_tiles<WGM, WGN, WM, WN, PK, S, OCC, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
                                                                (g.M + WGM * WM - 1) / (WGM * WM), g.N / (WGN * WN), epi, st);
 }
 
@@ -593,7 +682,7 @@ int splitk_ksplit(int N, int K) {
 void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,
                  int plane_rows, int row0, hipStream_t st) {
   const f16* no8 = nullptr;
-  launch_tiles<16, 4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, Afrag_lo ? 2 * K : K, K, ksplit, N / 256,
+  launch_tiles<4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, Afrag_lo ? 2 * K : K, K, ksplit, N / 256,
                                                          EpiPartial{part, plane_rows, row0, N, Afrag_lo}, st);
 }
 
@@ -636,27 +725,21 @@ static TilePick pick_tile(int M, int N, int K) {
 // rounds of 64x128 tiles share the compute units.  256x256: 8 waves of 64x128, slabs of 64 k (half the barriers: gate/up
 // 363 against 371 us at 2338 rows, qkv 1399 against 1429 at 18560) once there are three rounds to hide the shorter
 // look-ahead, else and for the residual epilogue four stages of 32 (o 551 against 563 at 18560 rows, gate/up 81 against
-// 92 at 290).  With low terms: 4 waves of 128x128, a third fewer LDS reads per product, which is what the 32x32
-// instructions have left to save.
+// 92 at 290).  With low terms always slabs of 64 k: one 128-deep product of the low-term pass.
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  constexpr int I = LO8 ? 32 : 16;
   const TilePick p = pick_tile(g.M, g.N, g.K);
   switch (p.tile) {
     case T_64x128:
-      if (p.tiles <= 256) launch<I, 2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st);
-      else launch<I, 2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st);
+      if (p.tiles <= 256) launch<2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st);
+      else launch<2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st);
       break;
-    case T_128x128: launch<I, 4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case T_64x256: launch<I, 2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case T_128x256: launch<I, 2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
+    case T_128x128: launch<4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
+    case T_64x256: launch<2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
+    case T_128x256: launch<2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
     default:
-      if constexpr (LO8) {
-        launch<32, 2, 2, 128, 128, 32, 4, 1, true>(g, epi, st);
-      } else {
-        if (!std::is_same<Epi, EpiResid>::value && p.tiles >= 768) launch<16, 4, 2, 64, 128, 64, 2, 1, false>(g, epi, st);
-        else launch<16, 4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
-      }
+      if (LO8 || (!std::is_same<Epi, EpiResid>::value && p.tiles >= 768)) launch<4, 2, 64, 128, 64, 2, 1, LO8>(g, epi, st);
+      else if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
   }
 }
 template <class Epi>
