@@ -460,16 +460,17 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
   };
   auto planes = [&](int N, int K) { return tiled(N, K) ? splitk_ksplit(N, K) : skinny_ksplit(N, K); };
   const int ks_qkv = planes(3 * d, d), ks_o = planes(d, d), ks_gu = planes(2 * f, d), ks_dn = planes(d, f);
-  auto gemm = [&](f16* a, f16* a_lo, size_t w_off, int N, int K, int ks) {
+  auto gemm_tiled = [&](f16* a, f16* a_lo, size_t w_off, int N, int K, int ks) {     // returns the rows it has done
     int r0 = 0;
-    if (tiled(N, K)) {
-      for (; B - r0 > kSkinnyMaxRows; r0 += 256) {
-        const int m = B - r0 < 256 ? B - r0 : 256;
-        splitk_gemm(frag_rows(a, r0, K), a_lo ? frag_rows(a_lo, r0, K) : nullptr, at<f16>(ctx->arena, w_off), part, m,
-                    N, K, ks, B, r0, st);
-      }
+    for (; B - r0 > kSkinnyMaxRows; r0 += 256) {
+      const int m = B - r0 < 256 ? B - r0 : 256;
+      splitk_gemm(frag_rows(a, r0, K), a_lo ? frag_rows(a_lo, r0, K) : nullptr, at<f16>(ctx->arena, w_off), part, m, N, K,
+                  ks, B, r0, st);
     }
-    for (; r0 < B; r0 += kSkinnyMaxRows) {
+    return r0 < B ? r0 : B;
+  };
+  auto gemm = [&](f16* a, f16* a_lo, size_t w_off, int N, int K, int ks) {
+    for (int r0 = tiled(N, K) ? gemm_tiled(a, a_lo, w_off, N, K, ks) : 0; r0 < B; r0 += kSkinnyMaxRows) {
       const int m = B - r0 < kSkinnyMaxRows ? B - r0 : kSkinnyMaxRows;
       skinny_gemm(frag_rows(a, r0, K), a_lo ? frag_rows(a_lo, r0, K) : nullptr, at<f16>(ctx->arena, w_off), part, m, N, K,
                   ks, B, r0, st);
@@ -501,8 +502,16 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     }
     {
       ProfScope ps(ctx, FAM_GEMM_GATEUP_DECODE, st);
-      gemm(hn, two ? hn_lo : none, lw.w_gu, 2 * f, d, ks_gu);
-      reduce_swiglu(part, ks_gu, B, 0, B, f, act, two ? act_lo : none, 0, st);
+      // chunks of at most 128 rows finish the elementwise step inside the product; the tiled kernel's planes need a launch
+      int r0 = 0;
+      if (tiled(2 * f, d)) {
+        r0 = gemm_tiled(hn, two ? hn_lo : none, lw.w_gu, 2 * f, d, ks_gu);
+        reduce_swiglu(part, ks_gu, B, 0, r0, f, act, two ? act_lo : none, 0, st);
+      }
+      for (; r0 < B; r0 += kSkinnyMaxRows)
+        skinny_swiglu(frag_rows(hn, r0, d), two ? frag_rows(hn_lo, r0, d) : none, at<f16>(ctx->arena, lw.w_gu),
+                      frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : none,
+                      B - r0 < kSkinnyMaxRows ? B - r0 : kSkinnyMaxRows, f, d, st);
     }
     {
       ProfScope ps(ctx, FAM_GEMM_DOWN_DECODE, st);
@@ -539,7 +548,7 @@ void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_nee
   float* x_c = reinterpret_cast<float*>(reinterpret_cast<char*>(act) +
                                         (two ? max_rows(c) * (size_t)f * sizeof(f16) : 0) +
                                         align_up(pad32 * f * sizeof(f16)));
-  const int ks_o = skinny_ksplit(d, d), ks_gu = skinny_ksplit(2 * f, d), ks_dn = skinny_ksplit(d, f);
+  const int ks_o = skinny_ksplit(d, d), ks_dn = skinny_ksplit(d, f);
   const int chunk = (int)(part_rows(c) < (size_t)kSkinnyMaxRows ? part_rows(c) : (size_t)kSkinnyMaxRows);
   gather_tail(att, two_pitch(two, d), lo8(two, d), x, need, n_need, d, att_frag, att_frag_lo, x_c, st);
   for (int r0 = 0; r0 < n_need; r0 += chunk) {
@@ -547,9 +556,8 @@ void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_nee
     skinny_gemm(frag_rows(att_frag, r0, d), two ? frag_rows(att_frag_lo, r0, d) : nullptr, at<f16>(ctx->arena, lw.w_o),
                 part, m, d, d, ks_o, m, 0, st);
     reduce_resid_norm(part, ks_o, m, 0, m, d, x_c, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, hn, hn_lo, r0, st);
-    skinny_gemm(frag_rows(hn, r0, d), two ? frag_rows(hn_lo, r0, d) : nullptr, at<f16>(ctx->arena, lw.w_gu), part, m,
-                2 * f, d, ks_gu, m, 0, st);
-    reduce_swiglu(part, ks_gu, m, 0, m, f, act, act_lo, r0, st);
+    skinny_swiglu(frag_rows(hn, r0, d), two ? frag_rows(hn_lo, r0, d) : nullptr, at<f16>(ctx->arena, lw.w_gu),
+                  frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : nullptr, m, f, d, st);
     skinny_gemm(frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : nullptr, at<f16>(ctx->arena, lw.w_down), part, m, d,
                 f, ks_dn, m, 0, st);
     reduce_resid_norm(part, ks_dn, m, 0, m, d, x_c, nullptr, c.rms_eps, hn, nullptr, r0, st);

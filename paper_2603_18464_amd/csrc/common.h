@@ -174,6 +174,9 @@ constexpr int kSkinnyMaxRows = 128;   // most rows of one weight-streaming GEMM 
 // The M rows of a launch are rows prow0 .. prow0 + M - 1 of partial planes of plane_rows rows each.
 void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,
                  int plane_rows, int prow0, hipStream_t st);
+// The gate/up product of at most kSkinnyMaxRows rows with its elementwise step, straight to fragments (K >= 128).
+void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
+                   int K, hipStream_t st);
 // The same product for up to 256 rows on the 256 x 256 tiled kernel, split over `ksplit` K slices (one partial plane
 // each): activations go through LDS once per workgroup instead of once per wave, which is what a large batch needs
 // to stream every weight once at full rate.  Needs N % 256 == 0 and K % 64 == 0 (splitk_gemm_fits).

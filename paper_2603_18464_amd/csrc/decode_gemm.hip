@@ -17,40 +17,56 @@
 
 namespace vla {
 
+// Element (m, k) of an [M, K] operand in fragment order.
+__device__ __forceinline__ size_t frag_index(int m, int k, int K) {
+  return ((size_t)(m >> 5) * (K >> 4) + (k >> 4)) * 512 + ((m & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+}
+
+// acc += a * b, the sum in the registers of acc: left to itself the compiler gives products separate source and result
+// registers, and from two blocks of rows on it spills and moves accumulators in the streaming loop.  It does not know the
+// latency of the statement: settle() before anything but another of these touches the accumulators.
+__device__ __forceinline__ void mfma_in_place(f32x16& acc, const f16x8& a, const f16x8& b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+#endif
+}
+__device__ __forceinline__ void settle() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#endif
+}
+__device__ __forceinline__ void hold_acc(f32x16& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
+// One wave's share of the product: k-blocks kb_begin .. kb_end - 1 (16 k each) of column pair nbp, all MT * 32 rows.
 // TWO: two-term activations.  Af_lo holds the low terms in the same fragment order; every weight fragment is
 // used for the hi and the lo activation fragments (weights are read once, the MFMA work doubles).
-// Output rows: the M rows of this launch are rows row0 .. row0 + M - 1 of planes of plane_rows rows each.
+// D: ring depth.  Rows of A past M - 1 are read from row M - 1: their results are not used, and a few rows then cost the
+// L2 a few lines per fragment instead of sixteen.
 template <int MT, int D, bool TWO>
-__global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_kernel(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
-                                                          const f16* __restrict__ Wp, float* __restrict__ part, int M,
-                                                          int N, int K, int kgroups, int plane_rows, int row0) {
-  // Workgroup = one pair of 32-row weight blocks (64 output columns) x one group of 4 K slices; wave w
-  // streams slice 4*kg + w.  The four partial tiles are added through LDS in the fixed order
-  // (w0 + w2) + (w1 + w3), so one plane part[kg] is written per group, deterministically.
-  extern __shared__ float red[];                          // [2][MT*32 regs][64 lanes]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int NP = N >> 6;
-  const int nbp = blockIdx.x % NP, kg = blockIdx.x / NP;
-  const int KB16 = K >> 4;
-  const int slices = 4 * kgroups, sl = 4 * kg + wave;
-  const int kb_begin = (int)((long long)sl * KB16 / slices);
-  const int kb_end = (int)((long long)(sl + 1) * KB16 / slices);   // non-empty: slices <= KB16
-
-  const f16* w0 = Wp + ((size_t)(2 * nbp) * KB16) * 512 + lane * 8;
+__device__ __forceinline__ void stream_slice(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
+                                             const f16* __restrict__ Wp, int nbp, int kb_begin, int kb_end, int KB16,
+                                             int M, f32x16 (&acc0)[MT], f32x16 (&acc1)[MT]) {
+  // bases are the same for the whole wave (scalar registers), a lane adds its 16 bytes of a fragment
+  const unsigned lane = threadIdx.x & 63, at_lane = lane * 8;
+  const unsigned at_last = (min(lane & 31, (unsigned)(M - 1 - 32 * (MT - 1))) + (lane & 32)) * 8;   // last block of rows
+  const f16* w0 = Wp + ((size_t)(2 * nbp) * KB16) * 512;
   const f16* w1 = w0 + (size_t)KB16 * 512;
-  const f16* a0 = Af + lane * 8;
-  const f16* a0l = TWO ? Af_lo + lane * 8 : nullptr;
 
-  // two arrays (one per 32-column block) rather than one: the compiler splits an array into scalars only up to a
-  // bounded number of accesses, and an unsplit accumulator array would live in scratch memory
-  f32x16 acc0[MT], acc1[MT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int i = 0; i < MT; ++i) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       acc0[i][e] = 0.f;
       acc1[i][e] = 0.f;
     }
+    hold_acc(acc0[i]);
+    hold_acc(acc1[i]);
+  }
+  settle();                                                // the zeros are written
 
   // Each wave walks its slice from a different starting point (rotated by its column pair).  The rows of
   // the packed matrix are a power-of-two number of bytes apart for K = 4096, so waves marching through k
@@ -64,22 +80,23 @@ __global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_ke
   constexpr int NA = TWO ? 2 * MT : MT;                    // activation fragments per k-step: hi (then lo)
   f16x8 wq[D][2], aq[D][NA];
   auto load_stage = [&](int s, size_t kb) {
-    wq[s][0] = *(const f16x8*)(w0 + kb * 512);
-    wq[s][1] = *(const f16x8*)(w1 + kb * 512);
+    wq[s][0] = *(const f16x8*)(w0 + kb * 512 + at_lane);
+    wq[s][1] = *(const f16x8*)(w1 + kb * 512 + at_lane);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      aq[s][mt] = *(const f16x8*)(a0 + ((size_t)mt * KB16 + kb) * 512);
-      if constexpr (TWO) aq[s][MT + mt] = *(const f16x8*)(a0l + ((size_t)mt * KB16 + kb) * 512);
+      const size_t at = ((size_t)mt * KB16 + kb) * 512;
+      aq[s][mt] = *(const f16x8*)(Af + at + (mt == MT - 1 ? at_last : at_lane));
+      if constexpr (TWO) aq[s][MT + mt] = *(const f16x8*)(Af_lo + at + (mt == MT - 1 ? at_last : at_lane));
     }
   };
   auto mfma_stage = [&](int s) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      acc0[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aq[s][mt], wq[s][0], acc0[mt], 0, 0, 0);
-      acc1[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aq[s][mt], wq[s][1], acc1[mt], 0, 0, 0);
+      mfma_in_place(acc0[mt], aq[s][mt], wq[s][0]);
+      mfma_in_place(acc1[mt], aq[s][mt], wq[s][1]);
       if constexpr (TWO) {
-        acc0[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aq[s][MT + mt], wq[s][0], acc0[mt], 0, 0, 0);
-        acc1[mt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aq[s][MT + mt], wq[s][1], acc1[mt], 0, 0, 0);
+        mfma_in_place(acc0[mt], aq[s][MT + mt], wq[s][0]);
+        mfma_in_place(acc1[mt], aq[s][MT + mt], wq[s][1]);
       }
     }
   };
@@ -103,48 +120,169 @@ __global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_ke
 #pragma unroll
   for (int s = 0; s < D; ++s)
     if (s < rem) mfma_stage(s);
-  // tree reduction over the four waves
-  constexpr int REGS = MT * 32;
-  auto put = [&](int slot) {
+  settle();
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        red[((size_t)slot * REGS + (mt * 2 + 0) * 16 + e) * 64 + lane] = acc0[mt][e];
-        red[((size_t)slot * REGS + (mt * 2 + 1) * 16 + e) * 64 + lane] = acc1[mt][e];
-      }
-  };
-  auto add = [&](int slot) {
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        acc0[mt][e] += red[((size_t)slot * REGS + (mt * 2 + 0) * 16 + e) * 64 + lane];
-        acc1[mt][e] += red[((size_t)slot * REGS + (mt * 2 + 1) * 16 + e) * 64 + lane];
-      }
-  };
-  if (wave >= 2) put(wave - 2);
-  __syncthreads();
-  if (wave < 2) add(wave);                                  // w0 += w2, w1 += w3
-  __syncthreads();
-  if (wave == 1) put(0);
-  __syncthreads();
-  if (wave != 0) return;
-  add(0);
-  const int h = lane >> 5, c = lane & 31;
-  float* out = part + ((size_t)kg * plane_rows + row0) * N + nbp * 64 + c;
+  for (int i = 0; i < MT; ++i) {
+    hold_acc(acc0[i]);
+    hold_acc(acc1[i]);
+  }
+}
+
+// Accumulators to / from LDS slot `slot` of [slots][MT * 32 registers][64 lanes].
+template <int MT>
+__device__ __forceinline__ void put_acc(float* red, int slot, const f32x16 (&acc0)[MT], const f32x16 (&acc1)[MT]) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk)
+    for (int e = 0; e < 16; ++e) {
+      red[(((size_t)slot * MT + mt) * 32 + e) * 64 + lane] = acc0[mt][e];
+      red[(((size_t)slot * MT + mt) * 32 + 16 + e) * 64 + lane] = acc1[mt][e];
+    }
+}
+template <int MT>
+__device__ __forceinline__ void add_acc(const float* red, int slot, f32x16 (&acc0)[MT], f32x16 (&acc1)[MT]) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = mt * 32 + 8 * blk + 4 * h + r;
-        if (m < M) {
-          out[(size_t)m * N] = acc0[mt][4 * blk + r] * (1.0f / kWeightScale);
-          out[(size_t)m * N + 32] = acc1[mt][4 * blk + r] * (1.0f / kWeightScale);
-        }
-      }
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      acc0[mt][e] += red[(((size_t)slot * MT + mt) * 32 + e) * 64 + lane];
+      acc1[mt][e] += red[(((size_t)slot * MT + mt) * 32 + 16 + e) * 64 + lane];
+    }
+}
+
+// Where element (m, c) of the 64-column tile lies in a slot: row 32 mt + r is register 4 * (r >> 3) + (r & 3) of the lanes
+// of half (r >> 2) & 1, column c is lane c & 31 of the half, columns 32 .. 63 are registers 16 .. 31.
+__device__ __forceinline__ int acc_at(int m, int c) {
+  const int r = m & 31;
+  return ((m >> 5) * 32 + (c >> 5) * 16 + 4 * (r >> 3) + (r & 3)) * 64 + 32 * ((r >> 2) & 1) + (c & 31);
+}
+
+// Output rows: the M rows of this launch are rows row0 .. row0 + M - 1 of planes of plane_rows rows each.
+template <int MT, int D, bool TWO>
+__global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_kernel(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
+                                                          const f16* __restrict__ Wp, float* __restrict__ part, int M,
+                                                          int N, int K, int kgroups, int plane_rows, int row0) {
+  // Workgroup = one pair of 32-row weight blocks (64 output columns) x one group of 4 K slices; wave w
+  // streams slice 4*kg + w.  The four partial tiles are added through LDS in the fixed order
+  // (w0 + w2) + (w1 + w3), so one plane part[kg] is written per group, deterministically.
+  extern __shared__ float red[];                          // [2][MT*32 regs][64 lanes]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NP = N >> 6;
+  const int nbp = blockIdx.x % NP, kg = blockIdx.x / NP;
+  const int KB16 = K >> 4;
+  const int slices = 4 * kgroups, sl = 4 * kg + wave;
+  const int kb_begin = (int)((long long)sl * KB16 / slices);
+  const int kb_end = (int)((long long)(sl + 1) * KB16 / slices);   // non-empty: slices <= KB16
+
+  // two arrays (one per 32-column block) rather than one: the compiler splits an array into scalars only up to a
+  // bounded number of accesses, and an unsplit accumulator array would live in scratch memory
+  f32x16 acc0[MT], acc1[MT];
+  stream_slice<MT, D, TWO>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
+  if (wave >= 2) put_acc<MT>(red, wave - 2, acc0, acc1);
+  __syncthreads();
+  if (wave < 2) add_acc<MT>(red, wave, acc0, acc1);         // w0 += w2, w1 += w3
+  __syncthreads();
+  if (wave < 2) put_acc<MT>(red, wave, acc0, acc1);
+  __syncthreads();
+  // all threads add the last two and write 16-byte row pieces
+  float* out = part + ((size_t)kg * plane_rows + row0) * N + nbp * 64;
+  for (int i = threadIdx.x; i < MT * 32 * 16; i += 256) {
+    const int m = i >> 4, c = (i & 15) * 4;
+    if (m >= M) break;
+    const float* p = red + acc_at(m, c);
+    const f32x4 p0 = *(const f32x4*)p, p1 = *(const f32x4*)(p + MT * 32 * 64);
+    *(f32x4*)(out + (size_t)m * N + c) = (p0 + p1) * (1.0f / kWeightScale);
+  }
+}
+
+// The gate/up product with its elementwise step: a column pair is 32 gates and the matching 32 ups, so a workgroup that
+// covers all of K has both sums at hand and writes silu(gate) * up as fragments, with no partial planes in memory and no
+// launch behind it.  Eight waves, slice w each; the partial tiles are added as ((w0 + w2) + (w1 + w3)) + ((w4 + w6) +
+// (w5 + w7)), which is the order two planes of four waves and a sum over the planes would have.
+// Two workgroups per compute unit up to 64 rows (the register budget behind the ring depths): all 344 of the 7B matrix
+// are then resident at once.
+template <int MT, int D, bool TWO>
+__global__ __launch_bounds__(512, MT == 1 || (MT == 2 && !TWO) ? 4 : 2) void skinny_swiglu_kernel(const f16* __restrict__ Af,
+                                                                             const f16* __restrict__ Af_lo,
+                                                                             const f16* __restrict__ Wp,
+                                                                             f16* __restrict__ act_frag,
+                                                                             f16* __restrict__ act_frag_lo, int M, int f,
+                                                                             int K) {
+  extern __shared__ float red[];                          // [4][MT*32 regs][64 lanes]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nbp = blockIdx.x, KB16 = K >> 4;
+  const int kb_begin = (int)((long long)wave * KB16 / 8);
+  const int kb_end = (int)((long long)(wave + 1) * KB16 / 8);      // non-empty: K >= 128
+  f32x16 acc0[MT], acc1[MT];
+  stream_slice<MT, D, TWO>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
+  const int pair = (wave >> 2) * 2 + (wave & 1);          // slot of waves {0, 2}, {1, 3}, {4, 6}, {5, 7}
+  if (wave & 2) put_acc<MT>(red, pair, acc0, acc1);
+  __syncthreads();
+  if (!(wave & 2)) add_acc<MT>(red, pair, acc0, acc1);
+  __syncthreads();
+  if (!(wave & 2)) put_acc<MT>(red, pair, acc0, acc1);
+  __syncthreads();
+  // a thread finishes four consecutive outputs of a row
+  for (int i = threadIdx.x; i < MT * 32 * 8; i += 512) {
+    const int m = i >> 3, c = (i & 7) * 4;
+    if (m >= M) break;
+    f32x4 s[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float* p = red + acc_at(m, j * 32 + c);         // gates, ups
+      constexpr int slot = MT * 32 * 64;
+      const f32x4 p0 = *(const f32x4*)p, p1 = *(const f32x4*)(p + slot), p4 = *(const f32x4*)(p + 2 * slot),
+                  p5 = *(const f32x4*)(p + 3 * slot);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[j][e] = (p0[e] + p1[e]) * (1.0f / kWeightScale) + (p4[e] + p5[e]) * (1.0f / kWeightScale);
+    }
+    typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
+    f16x4 o, oe;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float a = s[0][e] / (1.0f + __expf(-s[0][e])) * s[1][e];
+      o[e] = from_f32<f16>(a);
+      oe[e] = from_f32<f16>(a - (float)o[e]);
+    }
+    const size_t to = frag_index(m, nbp * 32 + c, f);
+    *(f16x4*)(act_frag + to) = o;
+    if (act_frag_lo) *(f16x4*)(act_frag_lo + to) = oe;
+  }
+}
+
+// M <= kSkinnyMaxRows rows (fragment blocks start at the first of them); Wp: the fused gate/up matrix [2 f, K].
+// act_frag_lo may be given with single-term operands and the other way round.
+void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
+                   int K, hipStream_t st) {
+  const dim3 grid(f / 32), block(512);
+  const int MT = (M + 31) / 32;
+#define VLA_SKINNY_LAUNCH(MTV, DV, TWOV)                                                                          \
+  {                                                                                                               \
+    auto kern = skinny_swiglu_kernel<MTV, DV, TWOV>;                                                              \
+    constexpr size_t smem = (size_t)4 * MTV * 32 * 64 * sizeof(float);                                            \
+    static bool attr_set = false;                                                                                 \
+    if (!attr_set) {                                                                                              \
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);        \
+      attr_set = true;                                                                                            \
+    }                                                                                                             \
+    hipLaunchKernelGGL(kern, grid, block, smem, st, Afrag, Afrag_lo, Wp, act_frag, act_frag_lo, M, f, K);         \
+  }
+#define VLA_SKINNY_CASE(MTV, DV, DV2)                  \
+  case MTV:                                            \
+    if (Afrag_lo) VLA_SKINNY_LAUNCH(MTV, DV2, true)    \
+    else VLA_SKINNY_LAUNCH(MTV, DV, false)             \
+    break;
+  switch (MT) {
+    VLA_SKINNY_CASE(1, 6, 4)
+    VLA_SKINNY_CASE(2, 3, 4)
+    VLA_SKINNY_CASE(3, 5, 3)
+    VLA_SKINNY_CASE(4, 4, 2)
+    default: break;                                        // callers keep M <= kSkinnyMaxRows
+  }
+#undef VLA_SKINNY_CASE
+#undef VLA_SKINNY_LAUNCH
 }
 
 #ifndef VLA_SKINNY_UNITS
@@ -185,7 +323,7 @@ void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
     VLA_SKINNY_CASE(1, 8, 6)
     VLA_SKINNY_CASE(2, 6, 4)
     VLA_SKINNY_CASE(3, 4, 3)
-    VLA_SKINNY_CASE(4, 3, 3)
+    VLA_SKINNY_CASE(4, 3, 2)
     default: break;                                        // callers keep M <= kSkinnyMaxRows
   }
 #undef VLA_SKINNY_CASE
@@ -193,10 +331,6 @@ void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 }
 
 // ---- reduce + elementwise kernels ---------------------------------------------------------------------
-__device__ __forceinline__ size_t frag_index(int m, int k, int K) {
-  return ((size_t)(m >> 5) * (K >> 4) + (k >> 4)) * 512 + ((m & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
-}
-
 __device__ __forceinline__ float block_sum_256d(float v, float* red) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
