@@ -695,10 +695,10 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 //   76 / 185, 1.30.
 // The pick is the fastest of the five at 290, 580, 1160 and 2338 rows of all four matrices: o at 290 rows 28 us (256x256:
 // 75), down 68 (180), qkv 48 (78), gate/up 81 (the others 90 and more); gate/up at 580 113 (164), down 84 (190).
-enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_256x256, T_COUNT };
+enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_192x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
 constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.9f, 5.9f, 0.68f}, {128, 128, 4.3f, 7.4f, 0.92f},
-                                         {64, 256, 6.8f, 9.3f, 0.80f}, {128, 256, 4.2f, 11.4f, 1.15f},
+                                         {64, 256, 6.8f, 9.3f, 0.80f}, {128, 256, 4.2f, 11.4f, 1.15f}, {192, 256, 8.0f, 13.7f, 1.18f},
                                          {256, 256, 11.5f, 16.1f, 1.30f}};
 struct TilePick { Tile tile; long long tiles; };
 static TilePick pick_tile(int M, int N, int K) {
@@ -737,6 +737,7 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
     case T_128x128: launch<4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
     case T_64x256: launch<2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
     case T_128x256: launch<2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
+    case T_192x256: launch<2, 4, 96, 64, 64, 2, 1, LO8>(g, epi, st); break;
     default:
       if (LO8 || (!std::is_same<Epi, EpiResid>::value && p.tiles >= 768)) launch<4, 2, 64, 128, 64, 2, 1, LO8>(g, epi, st);
       else if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);

@@ -43,3 +43,24 @@ def test_rows_do_not_depend_on_the_tile(hd, ffn, fast):
             ora = O.OraclePolicy(shape, weights).policy_step(pes, ids, 1, mode="cached")
             assert np.abs(ref - ora["logits"][0, 0]).max() <= P.tolerances(wl, fast)["logit"]
         assert np.array_equal(got[0], ref), f"{rows} rows"
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("rows", [2881, 2945, 3072])     # 16 row tiles of 192: one row, a ragged half and all of the last
+def test_192_row_tile(rows):
+    """4096 gate/up columns of a short contraction fill the chip once with tiles of 192 rows."""
+    from paper_2603_18464_amd import VlaPolicy
+    shape = W.PolicyShape(2, 256, 2, 128, 2048, 700, dtype="bf16")
+    weights = W.make_weights(shape, 5)
+    nps = [120] * (rows // 120) + ([rows % 120] if rows % 120 else [])
+    wl = W.Workload("Gt2", 78, shape, batch=len(nps), n_patches=120, instr_len=(0, 0), n_tokens=1)
+    obs = ragged_obs(wl, nps, [0] * len(nps), seed=12)
+    pol = VlaPolicy(shape, len(nps), 130, rows, two_term_layers=1)
+    pol.load_weights(weights)
+    dev = P.device_inputs(pol, obs)
+    got = pol.prefill(dev["patch_emb"], obs["cu_patch"], dev["instr_ids"], obs["cu_instr"]).cpu().numpy()
+    pol.close()
+    check = [0, len(nps) // 2, len(nps) - 2, len(nps) - 1]
+    pes, ids = P.split_obs(obs, check)
+    ora = O.OraclePolicy(shape, weights).policy_step(pes, ids, 1, mode="cached")
+    assert np.abs(got[check] - ora["logits"][:, 0]).max() <= P.tolerances(wl, False)["logit"]
