@@ -84,18 +84,25 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
 //                  may be permuted freely as long as both operands agree), A operand = V^T read from an
 //                  LDS tile that was transposed while staging, with the key order inside each group of
 //                  16 arranged so that a lane's 8 keys are contiguous.
+// Bound by latency: a workgroup lives for three key tiles on average (prefixes of 290) and starts with two dependent
+// rounds of loads.  Per layer, 64 prefixes of 290, 32 heads of 128: 169 us with a head's tiles on one XCD (180 with them
+// dealt over three), 32 prefixes, 12 heads of 64: 20.6 us with four workgroups per compute unit (23.0 with two).
 // TWO (two-term mode): queries, keys and values each come as hi + lo terms (the low terms of the queries in half
 // precision at column lo_off of the same rows, those of the cache as bytes, lo8 = bf8(16 * lo), in k_lo / v_lo
 // with the cache's indexing; they are widened exactly to half precision while the tile is staged), the
 // scores are K_hi Q_hi + K_lo Q_hi + K_hi Q_lo, the output sum takes V_hi + V_lo, and the output rows are written
 // as [hi | lo] as well.  The staging tiles double, so one workgroup runs per compute unit instead of two.
+// The LDS serves a 16-byte read in groups of 16 lanes that here are 16 keys whose numbers differ in their low four bits:
+// the swizzle puts their chunks in 16 different slots of the 64 banks (two rows of 64 dimensions share the banks).
+template <int HD>
+__device__ __forceinline__ int k_swizzle(int kk) { return HD == 128 ? kk & 15 : (kk >> 1) & 7; }
 template <int HD, bool TWO>
-__global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
+__global__ __launch_bounds__(256, !TWO && HD == 64 ? 4 : 2) void flash_prefill_kernel(
     const f16* __restrict__ q, int ldq, const f16* __restrict__ k_cache, const f16* __restrict__ v_cache,
     const unsigned char* __restrict__ k_lo, const unsigned char* __restrict__ v_lo,
     const int32_t* __restrict__ cu_patch,
     const int32_t* __restrict__ cu_instr, const int32_t* __restrict__ slot_map, f16* __restrict__ out, int ldo,
-    int n_heads, int max_seq, int lo_off, int out_lo8) {
+    int n_qt, int B, int n_heads, int max_seq, int lo_off, int out_lo8) {
   constexpr int KS = HD / 16;          // k-steps of the QK^T contraction
   constexpr int DT = HD / 32;          // 32-row tiles of O^T
   constexpr int KCH = HD / 8;          // 16-byte chunks per key row
@@ -104,14 +111,19 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
   __shared__ __attribute__((aligned(16))) f16 Ks[NP][64 * HD];
   __shared__ __attribute__((aligned(16))) f16 Vt[NP][HD * VPITCH];
 
-  const int b = blockIdx.y, head = blockIdx.z;
+  // Workgroups are dealt to the eight XCDs in turn: give each XCD a contiguous run of (sequence, head, query tile), query
+  // tiles innermost, so that the tiles of a head find its keys and values in one L2.
+  const int pid = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int qt = pid % n_qt, bh = pid / n_qt;
+  if (bh >= B * n_heads) return;
+  const int b = bh % B, head = bh / B;
   const int row0 = cu_patch[b] + cu_instr[b];
   const int S = cu_patch[b + 1] + cu_instr[b + 1] - row0;
   // Query tiles of 128 are aligned to the END of the sequence (the first tile is the short one): a tile needs the
   // keys up to its last query, so a prefix of 290 costs 1 + 3 + 5 key tiles instead of 2 + 4 + 5.
   const int nq = (S + 127) / 128;
-  if ((int)blockIdx.x >= nq) return;
-  const int q0 = S - 128 * (nq - (int)blockIdx.x);        // negative for a short first tile: those lanes are idle
+  if (qt >= nq) return;
+  const int q0 = S - 128 * (nq - qt);        // negative for a short first tile: those lanes are idle
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int qpos = q0 + wave * 32 + col;                 // this lane's query position (< S; idle if negative)
@@ -123,23 +135,13 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
   const unsigned char* kbase8 = TWO ? k_lo + blk : nullptr;   // low terms of the cache: one byte per element
   const unsigned char* vbase8 = TWO ? v_lo + blk : nullptr;
 
-  // Single-term: the wave's query fragments live in LDS (chunk c of query column `col` in slot c ^ (col & 7):
-  // conflict-free 16-byte accesses); the registers they would occupy hold the prefetched next key / value tile
-  // instead.  Two-term: the doubled key / value tiles take the LDS (two workgroups per compute unit must fit), so
-  // the query fragments, high and low terms, stay in registers.
-  __shared__ __attribute__((aligned(16))) f16 Qs[TWO ? 1 : 4][TWO ? 8 : 32 * HD];
-  f16x8 qreg[TWO ? 2 : 1][TWO ? KS : 1];
+  // The wave's query fragments (low terms too in two-term mode) stay in registers.
+  f16x8 qreg[NP][KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const int ch = ks * 2 + half;
-    if constexpr (TWO) {
-      qreg[0][ks] = *(const f16x8*)(q + (size_t)qrow * ldq + head * HD + ch * 8);
-      qreg[1][ks] = *(const f16x8*)(q + (size_t)qrow * ldq + lo_off + head * HD + ch * 8);
-    } else {
-      *(f16x8*)(Qs[wave] + col * HD + ((ch ^ (col & 7)) << 3)) =
-          *(const f16x8*)(q + (size_t)qrow * ldq + head * HD + ch * 8);
-    }
-  }
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl)
+      qreg[pl][ks] = *(const f16x8*)(q + (size_t)qrow * ldq + pl * lo_off + head * HD + (ks * 2 + half) * 8);
 
   f32x16 o[DT];
 #pragma unroll
@@ -150,6 +152,7 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
   // exponential is a bare exp2.  m_run is a reference point, not necessarily the running maximum: it is moved up
   // (and the accumulators rescaled) only when some query of the wave has found a score more than kLazy above it,
   // so most tiles skip the rescaling; probabilities relative to it stay below 2^kLazy, well inside half precision.
+  // l_run is this lane's share: the two halves of a query are added at the end.
   float m_run = -INFINITY, l_run = 0.f;
   const float scale2 = rsqrtf((float)HD) * 1.44269504088896341f;
   constexpr float kLazy = 8.0f;
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
     __syncthreads();                                      // previous tile fully consumed
 #pragma unroll
     for (int pl = 0; pl < NP; ++pl) {
-      // K tile: 64 keys x KCH chunks, chunk c of key kk stored at slot c ^ (kk & 7) (low 3 bits)
+      // K tile: 64 keys x KCH chunks, chunk c of key kk stored at slot c ^ k_swizzle(kk)
 #pragma unroll
       for (int i = 0; i < KI; ++i) {
         const int item = t + 256 * i;
@@ -220,7 +223,7 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
         if constexpr (TWO) {
           if (pl == 1) v = __builtin_bit_cast(u32x4, widen8(kreg8[i]));
         }
-        *(u32x4*)(Ks[pl] + kk * HD + ((c ^ (kk & 7)) << 3)) = v;
+        *(u32x4*)(Ks[pl] + kk * HD + ((c ^ k_swizzle<HD>(kk)) << 3)) = v;
       }
       // V tile, transposed: Vt[dim][pos(key)], two keys per 32-bit store
 #pragma unroll
@@ -259,23 +262,17 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
     // k-step outermost: one query fragment serves both key sub-tiles, and the two accumulator chains alternate
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      f16x8 qfr, qfl;
-      if constexpr (TWO) {
-        qfr = qreg[0][ks];
-        qfl = qreg[1][ks];
-      } else {
-        qfr = *(const f16x8*)(Qs[wave] + col * HD + (((ks * 2 + half) ^ (col & 7)) << 3));
-      }
+      const f16x8 qfr = qreg[0][ks];
 #pragma unroll
       for (int st = 0; st < 2; ++st) {
         const int kk = st * 32 + col;
-        const int koff = kk * HD + (((ks * 2 + half) ^ (kk & 7)) << 3);
+        const int koff = kk * HD + (((ks * 2 + half) ^ k_swizzle<HD>(kk)) << 3);
         const f16x8 kf = *(const f16x8*)(Ks[0] + koff);
         sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qfr, sacc[st], 0, 0, 0);
         if constexpr (TWO) {
           const f16x8 kl = *(const f16x8*)(Ks[NP - 1] + koff);
           sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qfr, sacc[st], 0, 0, 0);
-          sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qfl, sacc[st], 0, 0, 0);
+          sacc[st] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qreg[NP - 1][ks], sacc[st], 0, 0, 0);
         }
       }
     }
@@ -324,7 +321,6 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
         sacc[st][e] = p;
         l_tile += p;
       }
-    l_tile += __shfl_xor(l_tile, 32, 64);
     l_run += l_tile;
     // O^T += V^T P^T   (two-term mode: P too is split, P_hi V_hi + P_hi V_lo + P_lo V_hi)
 #pragma unroll
@@ -350,6 +346,7 @@ __global__ __launch_bounds__(256, 2) void flash_prefill_kernel(
         }
       }
   }
+  l_run += __shfl_xor(l_run, 32, 64);
   if (qpos >= 0) {
     const float inv = 1.0f / l_run;
     f16* orow = out + (size_t)(row0 + qpos) * ldo + head * HD;
@@ -386,11 +383,12 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
                    const unsigned char* v_lo, const int32_t* cu_patch, const int32_t* cu_instr, const int32_t* slot_map,
                    f16* out, int ldo, bool out_lo8, int B, int max_len, int n_heads, int head_dim, int max_seq,
                    hipStream_t st) {
-  const dim3 grid((max_len + 127) / 128, B, n_heads);
+  const int n_qt = (max_len + 127) / 128;
+  const dim3 grid((n_qt * B * n_heads + 7) / 8 * 8);
   const int lo_off = n_heads * head_dim;
 #define VLA_FLASH(HDV, TWOV)                                                                                       \
   hipLaunchKernelGGL((flash_prefill_kernel<HDV, TWOV>), grid, dim3(256), 0, st, q, ldq, k_cache, v_cache, k_lo, v_lo, \
-                     cu_patch, cu_instr, slot_map, out, ldo, n_heads, max_seq, lo_off, out_lo8 ? 1 : 0)
+                     cu_patch, cu_instr, slot_map, out, ldo, n_qt, B, n_heads, max_seq, lo_off, out_lo8 ? 1 : 0)
   if (k_lo) {
     if (head_dim == 128) VLA_FLASH(128, true);
     else VLA_FLASH(64, true);

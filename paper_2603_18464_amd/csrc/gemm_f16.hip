@@ -691,9 +691,10 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // what a workgroup takes on a chip that is not full (bound by the latency and rate of its LDS fills: fixed + per_k *
 // K / 1024), and the rate of a chip full of them (bound by power and the L2).  Full rounds of 256 workgroups cost the
 // larger of the two, the last partial round likewise for its share.  us at K = 4096 / 11008, and PFLOP/s:
-//   64x128 27.6 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 256x256
+//   64x128 27.6 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 192x256
+//   63 / 155, 1.18 (from 2338 rows: o 87.6 us, 256x256 90; 9216 rows of d 768: gate/up 63.3, 128x256 74.6); 256x256
 //   76 / 185, 1.30.
-// The pick is the fastest of the five at 290, 580, 1160 and 2338 rows of all four matrices: o at 290 rows 28 us (256x256:
+// The pick is the fastest (of the others) at 290, 580, 1160 and 2338 rows of all four matrices: o at 290 rows 28 us (256x256:
 // 75), down 68 (180), qkv 48 (78), gate/up 81 (the others 90 and more); gate/up at 580 113 (164), down 84 (190).
 enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_192x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
