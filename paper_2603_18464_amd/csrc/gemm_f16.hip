@@ -682,8 +682,12 @@ int splitk_ksplit(int N, int K) {
 void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,
                  int plane_rows, int row0, hipStream_t st) {
   const f16* no8 = nullptr;
-  launch_tiles<4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, Afrag_lo ? 2 * K : K, K, ksplit, N / 256,
-                                                         EpiPartial{part, plane_rows, row0, N, Afrag_lo}, st);
+  const EpiPartial epi{part, plane_rows, row0, N, Afrag_lo};
+  const int k = Afrag_lo ? 2 * K : K;
+  // 256 columns a workgroup re-read the activations least, but a matrix of 4096 columns would occupy 64 compute units: 64
+  // columns then.  256 rows, K = 4096 / 11008: 17 / 39 us (256 columns 46 / 83, two weight-streaming launches 45 / 72).
+  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
+  else launch_tiles<4, 2, 64, 32, 64, 4, 1, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------

@@ -456,13 +456,13 @@ __global__ __launch_bounds__(256) void value_pool_kernel(const float* __restrict
 }
 
 // vh[b][j] = w2[j] * gelu(W1[j,:] . u[b] + b1[j]).  A workgroup keeps RB rows of u in LDS; each wave then walks
-// 16 rows of W1, reading every weight once from memory for all RB rows.
+// 4 rows of W1, reading every weight once from memory for all RB rows.
 template <class T, int RB>
 __global__ __launch_bounds__(256) void value_mlp_kernel(const T* __restrict__ w1, const float* __restrict__ b1,
                                                         const float* __restrict__ w2, const float* __restrict__ vu,
                                                         int B, int d, float* __restrict__ vh) {
   extern __shared__ float us[];                             // [RB][d]
-  constexpr int JPW = 16;                                   // rows of W1 per wave
+  constexpr int JPW = 4;                                    // rows of W1 per wave (16: 64 workgroups at d = 4096, 194 us)
   const int b0 = blockIdx.x * RB, nb = min(RB, B - b0);
   for (int i = threadIdx.x * 4; i < RB * d; i += 1024) {
     const int r = i / d, c = i - r * d;                     // d is a multiple of 4: a float4 stays inside a row
@@ -508,7 +508,7 @@ static void launch_value_mlp(const T* w1, const float* b1, const float* w2, cons
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3((B + RB - 1) / RB, (d + 63) / 64), dim3(256), smem, st, w1, b1, w2, vu, B, d, vh);
+  hipLaunchKernelGGL(kern, dim3((B + RB - 1) / RB, (d + 15) / 16), dim3(256), smem, st, w1, b1, w2, vu, B, d, vh);
 }
 
 __global__ __launch_bounds__(256) void value_sum_kernel(const float* __restrict__ vh, const float* __restrict__ b2,
