@@ -203,10 +203,10 @@ def main():
     # is not counted as work.
     per_launch = {"gemm_qkv_prefill": nums["qkv_flops"], "gemm_o_prefill": nums["o_flops"],
                   "gemm_gateup_prefill": nums["gateup_flops"], "gemm_down_prefill": nums["down_flops"]}
-    kernel_names = {"gemm_qkv_prefill": "gemm_f16_pipe_kernel<4,2,EpiQkv,%s> (prefill QKV GEMM)",
-                    "gemm_o_prefill": "gemm_f16_pipe_kernel<2,2,EpiResid,%s> (prefill output projection)",
-                    "gemm_gateup_prefill": "gemm_f16_pipe_kernel<2,2,EpiSwiglu,%s> (prefill gate/up GEMM)",
-                    "gemm_down_prefill": "gemm_f16_pipe_kernel<2,2,EpiResid,%s> (prefill down projection)"}
+    kernel_names = {"gemm_qkv_prefill": "gemm_f16_kernel<EpiQkv,%s> (prefill QKV GEMM)",
+                    "gemm_o_prefill": "gemm_f16_kernel<EpiResid,%s> (prefill output projection)",
+                    "gemm_gateup_prefill": "gemm_f16_kernel<EpiSwiglu,%s> (prefill gate/up GEMM)",
+                    "gemm_down_prefill": "gemm_f16_kernel<EpiResid,%s> (prefill down projection)"}
     for k in list(per_launch):
         k2 = k.replace("_prefill", "_two_prefill")
         per_launch[k2] = per_launch[k]

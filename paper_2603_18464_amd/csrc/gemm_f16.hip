@@ -424,7 +424,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   const f16* w8_base = LO8 ? W8 + (size_t)(n0 / 32) * KB16 * 256 : w_base;
   // Rows of A: piece i of a wave holds rows r0 + i * RPP (clamped to the last one), whose swizzle is that of r0 with the
   // chunk's bits of swz(i * RPP) flipped, so two registers serve all pieces.
-  const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)(M - 1 - m0) * a_pitch;
+  const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)min(M - 1 - m0, BM - 1) * a_pitch;   // (fits 32 bits)
   const int r0 = wave * AP * RPP + lane / (PK / 8);
   const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle<PK>(r0)) * 16u;
   auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped)

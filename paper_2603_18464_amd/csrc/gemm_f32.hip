@@ -72,13 +72,13 @@ struct F32Qkv {
 // the row's factor onto the sum.  VEC: K is a multiple of 4, so that every 16-byte load is aligned.
 template <int MT, bool VEC, bool NORM, class Epi>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W,
-                                                       const float* __restrict__ gain, float eps, int M, int K, Epi epi) {
+                                                       const float* __restrict__ gain, float eps, int M, int K, int tiles, Epi epi) {
   constexpr int NT = Epi::kNT, U = MT == 1 ? 6 : 4;        // k-steps (16 k) requested together
   __shared__ float red[4][MT * NT][256];
   __shared__ float s_ss[4][MT * 16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, g = lane >> 4;                  // operand row, k group (4 k of each step)
-  const int tile = blockIdx.x, m0 = blockIdx.y * 16 * MT;
+  const int tile = blockIdx.x % tiles, m0 = blockIdx.x / tiles * 16 * MT;
   const int steps = (K + 15) >> 4;
   const int s_begin = wave * steps / 4, s_end = (wave + 1) * steps / 4;
 
@@ -177,8 +177,8 @@ static void launch(const float* A, int lda, const float* W, const float* gain, f
   // 32-row tiles once 16-row ones would be more than about four workgroups per compute unit
   const bool wide = (long long)((M + 15) / 16) * tiles > 1024;
 #define VLA_F32_LAUNCH(MTV, VECV)                                                                                    \
-  hipLaunchKernelGGL((gemm_f32_kernel<MTV, VECV, NORM, Epi>), dim3(tiles, (M + 16 * MTV - 1) / (16 * MTV)), dim3(256), \
-                     0, st, A, lda, W, gain, eps, M, K, epi)
+  hipLaunchKernelGGL((gemm_f32_kernel<MTV, VECV, NORM, Epi>), dim3(tiles * ((M + 16 * MTV - 1) / (16 * MTV))), dim3(256), \
+                     0, st, A, lda, W, gain, eps, M, K, tiles, epi)
   if (K % 4 == 0) {
     if (wide) VLA_F32_LAUNCH(2, true);
     else VLA_F32_LAUNCH(1, true);

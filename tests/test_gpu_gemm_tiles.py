@@ -64,3 +64,32 @@ def test_192_row_tile(rows):
     pes, ids = P.split_obs(obs, check)
     ora = O.OraclePolicy(shape, weights).policy_step(pes, ids, 1, mode="cached")
     assert np.abs(got[check] - ora["logits"][:, 0]).max() <= P.tolerances(wl, False)["logit"]
+
+
+@pytest.mark.timeout(300)
+def test_operand_beyond_4_gib():
+    """The activations of the down projection span more than 2^32 bytes (88 200 rows of 49 152): row offsets inside a tile
+    are 32-bit, everything above a tile is not.  The first and the last sequences have the bits of a small batch."""
+    from paper_2603_18464_amd import VlaPolicy
+    shape = W.PolicyShape(2, 128, 2, 64, 16384, 700, dtype="bf16")
+    weights = W.make_weights(shape, 5)
+    n, L = 700, 126
+    wl = W.Workload("Gt3", 79, shape, batch=n, n_patches=L, instr_len=(0, 0), n_tokens=1)
+    obs = ragged_obs(wl, [L] * n, [0] * n, seed=13)
+
+    def prefill(seqs):
+        rows = np.concatenate([np.arange(b * L, (b + 1) * L) for b in seqs])
+        pol = VlaPolicy(shape, len(seqs), L + 2, len(rows), two_term_layers=1)
+        pol.load_weights(weights)
+        pe = pol.to_device(np.ascontiguousarray(obs["patch_emb"][rows]))
+        cu = (np.arange(len(seqs) + 1) * L).astype(np.int32)
+        ids = P.device_inputs(pol, obs)["instr_ids"]
+        got = pol.prefill(pe, cu, ids, np.zeros(len(seqs) + 1, np.int32)).cpu().numpy()
+        pol.close()
+        return got
+
+    assert n * L * shape.d_ffn * 3 > 2 ** 32
+    few = [0, 1, n - 2, n - 1]
+    small = prefill(few)
+    assert np.isfinite(small).all()
+    assert np.array_equal(prefill(list(range(n)))[few], small)
