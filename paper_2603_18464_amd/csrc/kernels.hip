@@ -456,13 +456,12 @@ __global__ __launch_bounds__(256) void value_pool_kernel(const float* __restrict
 }
 
 // vh[b][j] = w2[j] * gelu(W1[j,:] . u[b] + b1[j]).  A workgroup keeps RB rows of u in LDS; each wave then walks
-// 4 rows of W1, reading every weight once from memory for all RB rows.
+// jpw rows of W1, reading every weight once from memory for all RB rows.
 template <class T, int RB>
 __global__ __launch_bounds__(256) void value_mlp_kernel(const T* __restrict__ w1, const float* __restrict__ b1,
                                                         const float* __restrict__ w2, const float* __restrict__ vu,
-                                                        int B, int d, float* __restrict__ vh) {
+                                                        int B, int d, int jpw, float* __restrict__ vh) {
   extern __shared__ float us[];                             // [RB][d]
-  constexpr int JPW = 4;                                    // rows of W1 per wave (16: 64 workgroups at d = 4096, 194 us)
   const int b0 = blockIdx.x * RB, nb = min(RB, B - b0);
   for (int i = threadIdx.x * 4; i < RB * d; i += 1024) {
     const int r = i / d, c = i - r * d;                     // d is a multiple of 4: a float4 stays inside a row
@@ -470,8 +469,8 @@ __global__ __launch_bounds__(256) void value_mlp_kernel(const T* __restrict__ w1
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int jj = 0; jj < JPW; ++jj) {
-    const int j = (blockIdx.y * 4 + wave) * JPW + jj;
+  for (int jj = 0; jj < jpw; ++jj) {
+    const int j = (blockIdx.y * 4 + wave) * jpw + jj;
     if (j >= d) break;                                      // uniform per wave
     const T* wr = w1 + (size_t)j * d;
     float acc[RB];
@@ -508,7 +507,10 @@ static void launch_value_mlp(const T* w1, const float* b1, const float* w2, cons
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3((B + RB - 1) / RB, (d + 15) / 16), dim3(256), smem, st, w1, b1, w2, vu, B, d, vh);
+  // 16 rows a wave re-fill the LDS least; fewer when that would not be a workgroup per compute unit (d = 4096: 8 pooled
+  // rows 194 us with 64 workgroups, a quarter of a ms less per step of 8 with 256; 64 rows 325 us with 16, 383 with 4)
+  const int groups = (B + RB - 1) / RB, jpw = groups * ((d + 63) / 64) >= 256 ? 16 : 4;
+  hipLaunchKernelGGL(kern, dim3(groups, (d + 4 * jpw - 1) / (4 * jpw)), dim3(256), smem, st, w1, b1, w2, vu, B, d, jpw, vh);
 }
 
 __global__ __launch_bounds__(256) void value_sum_kernel(const float* __restrict__ vh, const float* __restrict__ b2,
