@@ -30,14 +30,18 @@ __device__ __forceinline__ void mfma_in_place(f32x16& acc, const f16x8& a, const
   asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 #endif
 }
-__device__ __forceinline__ void settle() {
+// The wait on both sides of a run of such products (12 issue slots behind a product, 2 in front of one; 32 given).  It
+// takes the accumulators and gives them back, so whatever reads them, register copies included, depends on it.
+template <int MT>
+__device__ __forceinline__ void settle(f32x16 (&p)[MT], f32x16 (&q)[MT]) {
+  static_assert(MT >= 1 && MT <= 4, "one statement names every accumulator");
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-#endif
-}
-__device__ __forceinline__ void hold_acc(f32x16& v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(v));
+#define VLA_SETTLE(...) asm volatile("s_nop 15\n\ts_nop 15" : __VA_ARGS__)
+  if constexpr (MT == 1) VLA_SETTLE("+v"(p[0]), "+v"(q[0]));
+  else if constexpr (MT == 2) VLA_SETTLE("+v"(p[0]), "+v"(q[0]), "+v"(p[1]), "+v"(q[1]));
+  else if constexpr (MT == 3) VLA_SETTLE("+v"(p[0]), "+v"(q[0]), "+v"(p[1]), "+v"(q[1]), "+v"(p[2]), "+v"(q[2]));
+  else VLA_SETTLE("+v"(p[0]), "+v"(q[0]), "+v"(p[1]), "+v"(q[1]), "+v"(p[2]), "+v"(q[2]), "+v"(p[3]), "+v"(q[3]));
+#undef VLA_SETTLE
 #endif
 }
 
@@ -63,10 +67,8 @@ __device__ __forceinline__ void stream_slice(const f16* __restrict__ Af, const f
       acc0[i][e] = 0.f;
       acc1[i][e] = 0.f;
     }
-    hold_acc(acc0[i]);
-    hold_acc(acc1[i]);
   }
-  settle();                                                // the zeros are written
+  settle<MT>(acc0, acc1);                                  // the zeros are written
 
   // Each wave walks its slice from a different starting point (rotated by its column pair).  The rows of
   // the packed matrix are a power-of-two number of bytes apart for K = 4096, so waves marching through k
@@ -120,12 +122,7 @@ __device__ __forceinline__ void stream_slice(const f16* __restrict__ Af, const f
 #pragma unroll
   for (int s = 0; s < D; ++s)
     if (s < rem) mfma_stage(s);
-  settle();
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    hold_acc(acc0[i]);
-    hold_acc(acc1[i]);
-  }
+  settle<MT>(acc0, acc1);
 }
 
 // Accumulators to / from LDS slot `slot` of [slots][MT * 32 registers][64 lanes].

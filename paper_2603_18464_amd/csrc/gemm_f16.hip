@@ -305,11 +305,6 @@ __device__ __forceinline__ void hold(f16x8& v) {
   asm volatile("" : "+v"(v));
 #endif
 }
-__device__ __forceinline__ void hold_acc(f32x4& v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(v));
-#endif
-}
 // Keeps what is computed from v from being computed ahead of a loop and kept in registers.
 __device__ __forceinline__ void hold32(unsigned& v) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -338,9 +333,19 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const 
   asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 #endif
 }
-__device__ __forceinline__ void settle() {
+// The wait on both sides of a run of such products (8 issue slots behind a product, 2 in front of one; 32 given), eight
+// accumulators a statement.  It takes them and gives them back, so whatever reads them, register copies included,
+// depends on it.
+template <int MT, int NT>
+__device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
+  static_assert(MT * NT % 8 == 0, "whole groups of eight");
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#define VLA_ACC(j) "+v"(acc[(g + j) / NT][(g + j) % NT])
+#pragma unroll
+  for (int g = 0; g < MT * NT; g += 8)
+    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
+                 VLA_ACC(7));
+#undef VLA_ACC
 #endif
 }
 
@@ -537,13 +542,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   const int KTh = LO8 ? KTw : KT;
   int kt = 0;
   if constexpr (LO8) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) hold_acc(acc[i][j]);
-    settle();                                          // the zeros are written
+    settle(acc);                                       // the zeros are written
     for (; kt < KTh; ++kt) slab(kt, c0);
-    settle();
+    settle(acc);
     // Fragments of one slab, k-steps 0 and 1: variables of their own, read afresh, since the product wants the two in
     // adjacent registers and the loop above must not be bound by that.  Reads are issued in the order: first-half A
     // fragments, B fragments column by column, second-half A fragments.
