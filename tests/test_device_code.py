@@ -203,17 +203,28 @@ def test_the_check_sees_early_uses(lines, bad):
     assert bool(kernel_faults(parse(text)["k"])) == bad
 
 
-def test_built_code_waits_for_its_products_and_reads(tmp_path):
-    lib = str(tmp_path / "libvla.so")
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    """{kernel: instructions} of the built library."""
+    lib = str(tmp_path_factory.mktemp("code") / "libvla.so")
     shutil.copy(binding.library_path(), lib)
     subprocess.run([LLVM + "llvm-objdump", "--offloading", lib], check=True, capture_output=True)
-    objects = glob.glob(lib + ".*gfx950*")
-    assert objects
-    n_mfma, faults = 0, []
-    for obj in objects:
-        listing = subprocess.run([LLVM + "llvm-objdump", "-d", obj], check=True, capture_output=True, text=True).stdout
-        for name, code in parse(listing).items():
-            n_mfma += sum(ins[1].startswith("v_mfma") for ins in code)
-            faults += [f"{name}: {f}" for f in sorted(kernel_faults(code))]
-    assert n_mfma > 4000
+    kernels = {}
+    for obj in glob.glob(lib + ".*gfx950*"):
+        kernels.update(parse(subprocess.run([LLVM + "llvm-objdump", "-d", obj], check=True, capture_output=True,
+                                            text=True).stdout))
+    return kernels
+
+
+def test_built_code_waits_for_its_products_and_reads(built):
+    assert sum(ins[1].startswith("v_mfma") for code in built.values() for ins in code) > 4000
+    faults = [f"{name}: {f}" for name, code in built.items() for f in sorted(kernel_faults(code))]
     assert not faults[:5], len(faults)
+
+
+def test_float32_rows_that_are_not_aligned_are_loaded_16_bytes_at_a_time(built):
+    """Unlike the rest of this file about time, not values: an odd d_ffn must not cost a load per element."""
+    odd = {n: [ins[1] for ins in code] for n, code in built.items() if "gemm_f32_kernelILi" in n and "ELb0E" in n.split("gemm_f32_kernel")[1][:9]}
+    assert odd
+    for name, ops in odd.items():
+        assert ops.count("global_load_dwordx4") >= 12, name
