@@ -313,88 +313,80 @@ void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float
 }
 
 // ---- action head ------------------------------------------------------------------------------------
-// Workgroup (g, h): final RMSNorm of RB hidden rows (float32, kept in LDS), then `rows` action rows of the slimmed head
-// for all of them, one row per wave at a time, lanes striding over d with a wave reduction per output.  A few hidden
-// rows are bound by latency: the action rows are then spread over more workgroups (4 a workgroup, one per wave; the norm
-// is recomputed by each, 16 KiB from L2).  Many hidden rows are bound by the L2 reads of the head: four share each.
-// The sum of an output does not depend on the split.  d = 4096, 256 bins: 1 hidden row 67 us with 32 action rows a
-// workgroup, 6.5 with 4; 32 rows of d = 768: 14.8 and 9.9.
+// Workgroup (b, h): final RMSNorm of a hidden row (float32, kept in LDS), then `rows` action rows of the slimmed head, one
+// row per wave at a time, lanes striding over d with a wave reduction per output.  A few hidden rows are bound by latency:
+// the action rows are then spread over more workgroups (4 a workgroup, one per wave; the norm is recomputed by each, 16 KiB
+// from L2).  DEEP: eight loads of an action row in flight.  It takes a row long enough to fill them, the chip being full
+// of waves otherwise.  The sum of an output does not depend on either.  256 bins, us, one load at a time / eight:
+//   d 4096  1 hidden row 9.4 / 5.4, 64 rows 46 / 15, 1792 rows 345 / 230     d 2048  64 rows 25 / 10, 1792 rows 161 / 118
+//   d 1536  64 rows 20 / 20, 256 rows 22 / 38, 1792 rows 118 / 160           d 768   256 rows 14 / 21, 1792 rows 69 / 96
+// (Four hidden rows a workgroup, to share the reads of the head: 341, 164, 138 and 91 us at 1792 rows; its LDS leaves too
+// few waves.)
 __device__ __forceinline__ f32x4 load4_f32(const float* p) { return *(const f32x4*)p; }
 __device__ __forceinline__ f32x4 load4_f32(const bf16* p) {
   const bf16x4 v = *(const bf16x4*)p;
   return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
 }
-template <class T, int RB>
+template <class T, bool DEEP>
 __global__ __launch_bounds__(256) void head_kernel(const float* __restrict__ x, const int32_t* __restrict__ row_index,
                                                    const float* __restrict__ gain, const T* __restrict__ w_head,
-                                                   float* __restrict__ logits, int ld_logits, int B, int d, int A,
-                                                   int rows, float eps) {
-  extern __shared__ __attribute__((aligned(16))) float hrow[];   // [RB][d]
+                                                   float* __restrict__ logits, int ld_logits, int d, int A, int rows,
+                                                   float eps) {
+  extern __shared__ __attribute__((aligned(16))) float hrow[];   // [d]
   __shared__ float red[4];
-  const int b0 = blockIdx.x * RB;
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    const int b = min(b0 + r, B - 1);
-    const float* row = x + (size_t)(row_index ? row_index[b] : b) * d;
-    float ss = 0.f;
-    for (int i = threadIdx.x * 4; i < d; i += 1024) {
-      const float4 v = *(const float4*)(row + i);
-      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-    }
-    ss = block_sum_256(ss, red);
-    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int i = threadIdx.x * 4; i < d; i += 1024) {
-      const float4 v = *(const float4*)(row + i);
-      const float4 g = *(const float4*)(gain + i);
-      *(float4*)(hrow + r * d + i) = make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
-    }
+  const int b = blockIdx.x;
+  const float* row = x + (size_t)(row_index ? row_index[b] : b) * d;
+  float ss = 0.f;
+  for (int i = threadIdx.x * 4; i < d; i += 1024) {
+    const float4 v = *(const float4*)(row + i);
+    ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+  }
+  ss = block_sum_256(ss, red);
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+  for (int i = threadIdx.x * 4; i < d; i += 1024) {
+    const float4 v = *(const float4*)(row + i);
+    const float4 g = *(const float4*)(gain + i);
+    *(float4*)(hrow + i) = make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w);
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j0 = blockIdx.y * rows;
   for (int j = j0 + wave; j < min(j0 + rows, A); j += 4) {
     const T* w = w_head + (size_t)j * d;
-    float acc[RB];
-#pragma unroll
-    for (int r = 0; r < RB; ++r) acc[r] = 0.f;
+    float acc = 0.f;
+    auto columns = [&](int i) {
+      const f32x4 wv = load4_f32(w + i), h = *(const f32x4*)(hrow + i);
+      acc += wv[0] * h[0] + wv[1] * h[1] + wv[2] * h[2] + wv[3] * h[3];
+    };
+    if constexpr (DEEP) {
 #pragma unroll 8
-    for (int i = lane * 4; i < d; i += 256) {
-      const f32x4 wv = load4_f32(w + i);
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const f32x4 h = *(const f32x4*)(hrow + r * d + i);
-        acc[r] += wv[0] * h[0] + wv[1] * h[1] + wv[2] * h[2] + wv[3] * h[3];
-      }
+      for (int i = lane * 4; i < d; i += 256) columns(i);
+    } else {
+      for (int i = lane * 4; i < d; i += 256) columns(i);
     }
-#pragma unroll
-    for (int r = 0; r < RB; ++r) {
-      acc[r] = wave_sum(acc[r]);
-      if (lane == 0 && b0 + r < B) logits[(size_t)(b0 + r) * ld_logits + j] = acc[r];
-    }
+    acc = wave_sum(acc);
+    if (lane == 0) logits[(size_t)b * ld_logits + j] = acc;
   }
 }
-template <class T, int RB>
+template <class T, bool DEEP>
 static void launch_head(const float* x, const int32_t* row_index, const float* gain, const T* w_head, float* logits,
                         int ld_logits, int B, int d, int A, int rows, float eps, hipStream_t st) {
-  auto kern = head_kernel<T, RB>;
+  auto kern = head_kernel<T, DEEP>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3((B + RB - 1) / RB, (A + rows - 1) / rows), dim3(256), (size_t)RB * d * sizeof(float), st,
-                     x, row_index, gain, w_head, logits, ld_logits, B, d, A, rows, eps);
+  hipLaunchKernelGGL(kern, dim3(B, (A + rows - 1) / rows), dim3(256), (size_t)d * sizeof(float), st, x, row_index, gain,
+                     w_head, logits, ld_logits, d, A, rows, eps);
 }
 template <class T>
 void head_logits(const float* x, const int32_t* row_index, const float* gain, const T* w_head, float* logits,
                  int ld_logits, int B, int d, int A, float eps, hipStream_t st) {
-  if (B >= 256 && d <= 4096) {                              // 4 * d floats of LDS <= 64 KiB
-    launch_head<T, 4>(x, row_index, gain, w_head, logits, ld_logits, B, d, A, 32, eps, st);
-    return;
-  }
   int rows = 32;                                            // at least about two workgroups per compute unit
   while (rows > 4 && (long long)B * ((A + rows - 1) / rows) < 512) rows >>= 1;
-  launch_head<T, 1>(x, row_index, gain, w_head, logits, ld_logits, B, d, A, rows, eps, st);
+  if (d >= 2048) launch_head<T, true>(x, row_index, gain, w_head, logits, ld_logits, B, d, A, rows, eps, st);
+  else launch_head<T, false>(x, row_index, gain, w_head, logits, ld_logits, B, d, A, rows, eps, st);
 }
 template void head_logits<float>(const float*, const int32_t*, const float*, const float*, float*, int, int, int,
                                  int, float, hipStream_t);
