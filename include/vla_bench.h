@@ -14,8 +14,9 @@ extern "C" {
 /* Practical ceilings of the device the context runs on, for reporting next to the vendor peaks (benchmark
  * support, not part of the policy path; unlike every other call it waits for its own kernels).  Needs loaded
  * weights on the 16-bit path.
- *   kind 0: an MFMA-only loop (8 independent 32x32x16 half-precision MFMAs per iteration and wave, two waves
- *           per SIMD, operands = real weight fragments held in registers) -> *value_out in TFLOP/s
+ *   kind 0: an MFMA-only loop (32 independent 16x16x32 half-precision MFMAs per iteration and wave, the prefill
+ *           GEMMs' instruction; two waves per SIMD, operands = real weight fragments held in registers)
+ *                                                                                        -> *value_out in TFLOP/s
  *   kind 1: a plain 16-byte-per-lane streaming read of all layer weights                -> *value_out in GB/s
  * Best of three timed runs after a warm-up. */
 int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);

@@ -1455,7 +1455,7 @@ int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream) {
   hipEvent_t e0, e1;
   HIP_TRY(ctx, hipEventCreate(&e0));
   HIP_TRY(ctx, hipEventCreate(&e1));
-  const int n_wg = 512, iters = 8192, reps = 3;
+  const int n_wg = 512, iters = 4096, reps = 3;
   float best = 1e30f;
   for (int r = 0; r < reps + 1; ++r) {     // first run warms up
     HIP_TRY(ctx, hipEventRecord(e0, st));
@@ -1470,7 +1470,7 @@ int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   HIP_TRY(ctx, hipGetLastError());
-  if (kind == 0) *value_out = (double)n_wg * 4 * iters * 8 * 32768.0 / (best * 1e-3) / 1e12;   // TFLOP/s
+  if (kind == 0) *value_out = probe_mfma_flops(n_wg, iters) / (best * 1e-3) / 1e12;                // TFLOP/s
   else *value_out = (double)bytes / (best * 1e-3) / 1e9;                                        // GB/s
   return VLA_OK;
 }

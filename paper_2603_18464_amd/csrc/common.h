@@ -236,6 +236,7 @@ void score_rows(const float* logits, int rows, int A, float temperature, const i
 
 // Ceiling probes (see vla_probe): an MFMA-only loop on weight bits and a plain streaming read.
 void probe_mfma(const f16* w, size_t n_frag, int n_wg, int iters, float* sink, hipStream_t st);
+double probe_mfma_flops(int n_wg, int iters);
 void probe_stream(const void* src, size_t bytes, int n_wg, unsigned* sink, hipStream_t st);
 
 // Small utilities.

@@ -533,36 +533,38 @@ template void value_finish<bf16>(const float*, const float*, const bf16*, int, c
                                  hipStream_t);
 
 // ---- practical ceilings, measured on request ------------------------------------------------------------
-// MFMA-only loop: every wave loads two A and four B fragments once (real weight bits, so the operands toggle
-// like real data) and issues 8 independent 32x32x16 MFMAs per iteration on them; nothing else runs.
-__global__ __launch_bounds__(256) void probe_mfma_kernel(const f16* __restrict__ w, size_t n_frag, int iters,
-                                                         float* __restrict__ sink) {
+// MFMA-only loop with the instruction and the wave tile of the prefill GEMM (64 x 128 on 16x16x32): every wave loads four
+// A and eight B fragments once (real weight bits, so the operands toggle like real data) and issues 32 independent MFMAs
+// per iteration on them; nothing else runs.  Bound by power: 32x32x16 instructions sustain less (twice the accumulator
+// traffic per product).
+__global__ __launch_bounds__(256, 2) void probe_mfma_kernel(const f16* __restrict__ w, size_t n_frag, int iters,
+                                                            float* __restrict__ sink) {
+  constexpr int MT = 4, NT = 8;
   const int lane = threadIdx.x & 63;
   const size_t wave = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  f16x8 a[2], b[4];
+  f16x8 a[MT], b[NT];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) a[i] = *(const f16x8*)(w + ((wave * 6 + i) % n_frag) * 512 + lane * 8);
+  for (int i = 0; i < MT; ++i) a[i] = *(const f16x8*)(w + ((wave * (MT + NT) + i) % n_frag) * 512 + lane * 8);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) b[i] = *(const f16x8*)(w + ((wave * 6 + 2 + i) % n_frag) * 512 + lane * 8);
-  f32x16 acc[2][4];
+  for (int j = 0; j < NT; ++j) b[j] = *(const f16x8*)(w + ((wave * (MT + NT) + MT + j) % n_frag) * 512 + lane * 8);
+  f32x4 acc[MT][NT];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int it = 0; it < iters; ++it)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i], b[j], acc[i][j], 0, 0, 0);
   float t = 0.f;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) t += acc[i][j][0];
+    for (int j = 0; j < NT; ++j) t += acc[i][j][0];
   if (t == 123.456f) sink[0] = t;      // keeps the loop alive; never true in practice
 }
+double probe_mfma_flops(int n_wg, int iters) { return (double)n_wg * 4 * iters * 32 * (2.0 * 16 * 16 * 32); }
 void probe_mfma(const f16* w, size_t n_frag, int n_wg, int iters, float* sink, hipStream_t st) {
   hipLaunchKernelGGL(probe_mfma_kernel, dim3(n_wg), dim3(256), 0, st, w, n_frag, iters, sink);
 }

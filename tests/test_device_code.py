@@ -228,3 +228,10 @@ def test_float32_rows_that_are_not_aligned_are_loaded_16_bytes_at_a_time(built):
     assert odd
     for name, ops in odd.items():
         assert ops.count("global_load_dwordx4") >= 12, name
+
+
+def test_the_ceiling_probe_runs_the_instruction_of_the_prefill_gemm(built):
+    """A ceiling measured with another instruction is no ceiling: 32x32x16 sustains less than 16x16x32."""
+    def products(name, part):
+        return {ins[1] for n, code in built.items() if name in n and part in n for ins in code if ins[1].startswith("v_mfma")}
+    assert products("probe_mfma_kernel", "") == products("gemm_f16_kernel", "EpiSwigluELb0ELb0E") == {"v_mfma_f32_16x16x32_f16"}
