@@ -21,6 +21,11 @@ extern "C" {
  * Best of three timed runs after a warm-up. */
 int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);
 
+/* Which variant of the prefill GEMM a product [rows, k] x [n, k]^T takes ("128x256", ...): a static text, "" for sizes
+ * the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer; resid: the output projection and
+ * the down projection (0: the QKV and gate/up products). */
+const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t resid);
+
 /* Timing hooks for the benchmark: duration of the launches of one kernel family, measured with
  * HIP events recorded on the launch stream around each launch.  vla_prof_enable(ctx, mask) clears
  * what was collected and then times the families whose bit (1 << index) is set in mask (0 = off).

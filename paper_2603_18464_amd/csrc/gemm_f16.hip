@@ -697,10 +697,15 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // K / 1024), and the rate of a chip full of them (bound by power and the L2).  Full rounds of 256 workgroups cost the
 // larger of the two, the last partial round likewise for its share.  us at K = 4096 / 11008, and PFLOP/s:
 //   64x128 27.6 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 192x256
-//   63 / 155, 1.18 (from 2338 rows: o 87.6 us, 256x256 90; 9216 rows of d 768: gate/up 63.3, 128x256 74.6); 256x256
-//   76 / 185, 1.30.
-// The pick is the fastest (of the others) at 290, 580, 1160 and 2338 rows of all four matrices: o at 290 rows 28 us (256x256:
-// 75), down 68 (180), qkv 48 (78), gate/up 81 (the others 90 and more); gate/up at 580 113 (164), down 84 (190).
+//   63 / 155, 1.18; 256x256 76 / 185, 1.30.
+// The pick against the fastest of the six, each forced in turn (the four matrices of the 7B model at 64 to 18560 rows and
+// of the 12-layer one at 145 to 9216, single- and two-term, 160 products): 0.7 % slower in the median, 1.7 % in the mean,
+// up to 5 % in nine of ten.  us single-term, pick and others: 290 rows qkv 49 (64x256; 256x256 76), o 28 (64x128; 72),
+// down 68 (64x128; 178); 580 rows gate/up 111 (128x256; 256x256 161), down 85 (128x128; 185); 2338 rows gate/up 361
+// (256x256; 128x256 374), o 90 (192x256; 256x256 95); 9216 rows of d 768 gate/up 62 (192x256; 128x256 72).
+// Where it is off: gate/up at 290 rows 87 (192x256; 256x256 79), down at 2338 231 (256x256; 192x256 217) and at 4640 435
+// (192x256; 128x256 405), qkv and gate/up at 1740 by 5 to 7 %, two-term qkv at 870 149 (256x256; 192x256 128).  The model
+// has 192x256 too fast in a partial round (o at 2338 rows: 71 predicted).
 enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_192x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
 constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.9f, 5.9f, 0.68f}, {128, 128, 4.3f, 7.4f, 0.92f},
@@ -732,21 +737,34 @@ static TilePick pick_tile(int M, int N, int K) {
 // 363 against 371 us at 2338 rows, qkv 1399 against 1429 at 18560) once there are three rounds to hide the shorter
 // look-ahead, else and for the residual epilogue four stages of 32 (o 551 against 563 at 18560 rows, gate/up 81 against
 // 92 at 290).  With low terms always slabs of 64 k: one 128-deep product of the low-term pass.
+const char* const kGemmF16Variants[kGemmF16VariantCount] = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256",
+                                                            "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"};
+int gemm_f16_variant(int M, int N, int K, bool lo8, bool resid) {
+  const TilePick p = pick_tile(M, N, K);
+  switch (p.tile) {
+    case T_64x128: return p.tiles <= 256 ? 0 : 1;
+    case T_128x128: return 2;
+    case T_64x256: return 3;
+    case T_128x256: return 4;
+    case T_192x256: return 5;
+    default: return lo8 || (!resid && p.tiles >= 768) ? 6 : 7;
+  }
+}
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  const TilePick p = pick_tile(g.M, g.N, g.K);
-  switch (p.tile) {
-    case T_64x128:
-      if (p.tiles <= 256) launch<2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st);
-      else launch<2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st);
+  constexpr bool resid = std::is_same<Epi, EpiResid>::value;
+  switch (gemm_f16_variant(g.M, g.N, g.K, LO8, resid)) {
+    case 0: launch<2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st); break;
+    case 1: launch<2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st); break;
+    case 2: launch<4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
+    case 3: launch<2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
+    case 4: launch<2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
+    case 5: launch<2, 4, 96, 64, 64, 2, 1, LO8>(g, epi, st); break;
+    case 6:
+      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 64, 2, 1, LO8>(g, epi, st);
       break;
-    case T_128x128: launch<4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case T_64x256: launch<2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case T_128x256: launch<2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
-    case T_192x256: launch<2, 4, 96, 64, 64, 2, 1, LO8>(g, epi, st); break;
     default:
-      if (LO8 || (!std::is_same<Epi, EpiResid>::value && p.tiles >= 768)) launch<4, 2, 64, 128, 64, 2, 1, LO8>(g, epi, st);
-      else if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
+      if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
   }
 }
 template <class Epi>

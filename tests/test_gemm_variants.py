@@ -1,0 +1,81 @@
+"""Every variant of the prefill GEMM (tile, ring depth, epilogue, with and without low terms) that the choice of tile
+reaches: a sequence has the same bits at the front, in the middle and at the end of every batch as alone, and alone it is
+the oracle's.  That the shapes do reach all of them is asked of the library on the CPU, so that a change of the cost
+model cannot quietly take a variant out of the test."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import vla_oracle as O
+from paper_2603_18464_amd.binding import vla_gemm_variant
+from tests import parity as P
+from tests.test_gpu_parity import ragged_obs
+
+ALL = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"}
+# Not reached: three stages need more than 256 of the smallest tiles to be the fastest choice, which takes a wide matrix of
+# a short contraction (gate/up only); 32-k slabs have no room for 8-bit low terms, 64-k ones are not for the residual add.
+REACHED = {(two, epi): ALL - ({"64x128 3 stages"} if epi != "gate/up" else set())
+           for two in (False, True) for epi in ("qkv", "gate/up", "resid")}
+REACHED[False, "resid"] -= {"256x256 64-k slabs"}
+REACHED[True, "qkv"] -= {"256x256 32-k slabs"}
+REACHED[True, "gate/up"] -= {"256x256 32-k slabs"}
+
+# (d_model, d_ffn, head_dim, rows): three layers, the first two-term, the last one partly on the rows of the head only
+CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 64, 64, [2881, 4100, 6000]),
+         (128, 2048, 128, [1100, 2300]), (512, 2048, 64, [3500]), (1536, 64, 128, [8000]), (128, 16448, 64, [64]),
+         (1024, 64, 64, [1300]), (2048, 704, 128, [8000]), (512, 4096, 128, [6000]), (1280, 2816, 128, [700]),
+         (3072, 64, 128, [400, 1300])]
+
+
+def launches(d, f, rows):
+    for two in (False, True):
+        for epi, n, k in (("qkv", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
+            yield (two, epi), vla_gemm_variant(rows, n, k, two, epi == "resid")
+
+
+def test_the_cases_reach_every_variant():
+    reached = {key: set() for key in REACHED}
+    for d, f, _, rows_list in CASES:
+        for rows in rows_list:
+            for key, variant in launches(d, f, rows):
+                reached[key].add(variant)
+    assert reached == REACHED
+    assert vla_gemm_variant(64, 100, 128, False, False) == ""
+
+
+@pytest.mark.gpu
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("d,f,hd,rows_list", CASES)
+def test_a_sequence_has_the_same_bits_in_every_batch(d, f, hd, rows_list):
+    from paper_2603_18464_amd import VlaPolicy
+    shape = W.PolicyShape(3, d, d // hd, hd, f, 700, dtype="bf16")
+    weights = W.make_weights(shape, 5)
+    own = 33                                                  # rows of the sequence that is compared: no multiple of a tile
+    alone = None
+    for rows in [own] + rows_list:
+        rest = rows - own if rows < 3 * own else rows - 3 * own
+        nps = [own] + [120] * (rest // 120) + ([rest % 120] if rest % 120 else [])
+        where = [0]
+        if rows >= 3 * own:
+            nps = nps[:len(nps) // 2 + 1] + [own] + nps[len(nps) // 2 + 1:] + [own]
+            where += [i for i in range(1, len(nps)) if i == len(nps) - 1 or (nps[i] == own and i not in where)]
+        assert sum(nps) == rows
+        wl = W.Workload("Gv", 92, shape, batch=len(nps), n_patches=120, instr_len=(0, 0), n_tokens=1)
+        obs = ragged_obs(wl, nps, [0] * len(nps), seed=15)
+        cu = obs["cu_patch"]
+        for i in where:
+            obs["patch_emb"][cu[i]:cu[i + 1]] = obs["patch_emb"][:own]
+        pol = VlaPolicy(shape, len(nps), 122, 8192, two_term_layers=1)   # (capacity: the last layer always in compact rows)
+        pol.load_weights(weights)
+        dev = P.device_inputs(pol, obs)
+        got = pol.prefill(dev["patch_emb"], cu, dev["instr_ids"], obs["cu_instr"]).cpu().numpy()
+        pol.close()
+        assert np.isfinite(got).all(), rows
+        if alone is None:
+            alone, first = got[0], obs["patch_emb"][:own].copy()
+            pes, ids = P.split_obs(obs, [0])
+            ora = O.OraclePolicy(shape, weights).policy_step(pes, ids, 1, mode="cached")
+            assert np.abs(alone - ora["logits"][0, 0]).max() <= P.tolerances(wl, False)["logit"]
+        assert np.array_equal(obs["patch_emb"][:own], first)   # (the generator draws the sequences in order)
+        for i in where:
+            assert np.array_equal(got[i], alone), f"{rows} rows, sequence {i}"

@@ -1,6 +1,6 @@
-"""The prefill GEMMs choose their tile by the number of rows: at the edges of every tile, and with every tile chosen,
-a sequence gets the same bits whatever its batch (one chain of matrix instructions over ascending k per element), and
-those bits are the oracle's within the tolerance of the 16-bit path."""
+"""The prefill GEMMs choose their tile by the number of rows: at row counts on both sides of the tiles' edges a sequence
+gets the same bits whatever its batch (one chain of matrix instructions over ascending k per element), and those bits are
+the oracle's within the tolerance of the 16-bit path.  (test_gemm_variants.py reaches every variant of the kernel.)"""
 import numpy as np
 import pytest
 
