@@ -1201,8 +1201,9 @@ int vla_decode_step_static(vla_ctx* ctx, int32_t B, const int32_t* token_ids, fl
   if (!token_ids) return fail(ctx, VLA_E_NULL, "token_ids is NULL");
   if ((rc = check_decode(ctx, B, 1))) return rc;
   const vla_config& c = ctx->cfg;
-  // staging the step's GEMMs need: the split-K partial planes of the 16-bit path (rows of one chunk); the float32 path
-  // stages nothing and keeps the limit of one GEMM output per row
+  // The limit is the split-K partial planes (the whole batch's rows) of the widest product.  Less is staged than that: up
+  // to kSkinnyMaxRows rows the gate/up product has no planes, and the float32 path has none at all; what is refused does
+  // not hang on which kernel takes a product.
   const size_t widest = 3 * (size_t)c.d_model > 2 * (size_t)c.d_ffn ? 3 * (size_t)c.d_model : 2 * (size_t)c.d_ffn;
   const size_t rows = c.dtype == VLA_BF16 ? (size_t)kMaxKSplit * B : (size_t)B;
   const size_t need = rows * widest * sizeof(float);

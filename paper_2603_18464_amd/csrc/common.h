@@ -182,9 +182,9 @@ void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // The gate/up product of at most kSkinnyMaxRows rows with its elementwise step, straight to fragments (K >= 128).
 void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
                    int K, hipStream_t st);
-// The same product for up to 256 rows on the 256 x 256 tiled kernel, split over `ksplit` K slices (one partial plane
-// each): activations go through LDS once per workgroup instead of once per wave, which is what a large batch needs
-// to stream every weight once at full rate.  Needs N % 256 == 0 and K % 64 == 0 (splitk_gemm_fits).
+// The same product for up to 256 rows on the tiled kernel (256 rows x 256 or 64 columns a workgroup), split over `ksplit`
+// K slices (one partial plane each): activations go through LDS once per workgroup instead of once per wave, which is what
+// a large batch needs to stream every weight once at full rate.  Needs N % 256 == 0 and K % 64 == 0 (splitk_gemm_fits).
 bool splitk_gemm_fits(int M, int N, int K);
 int splitk_ksplit(int N, int K);
 void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,

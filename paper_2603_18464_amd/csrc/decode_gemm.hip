@@ -198,8 +198,9 @@ __global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_ke
 // covers all of K has both sums at hand and writes silu(gate) * up as fragments, with no partial planes in memory and no
 // launch behind it.  Eight waves, slice w each; the partial tiles are added as ((w0 + w2) + (w1 + w3)) + ((w4 + w6) +
 // (w5 + w7)), which is the order two planes of four waves and a sum over the planes would have.
-// Two workgroups per compute unit up to 64 rows (the register budget behind the ring depths): all 344 of the 7B matrix
-// are then resident at once.
+// Two workgroups per compute unit up to 32 rows, and with single-term operands up to 64 (the register budget behind the
+// ring depths): all 344 of the 7B matrix are then resident at once.  From 65 rows on the LDS (96 or 128 KiB) holds one,
+// and 344 of them are two rounds on 256 compute units: single-term 45.5 us at 64 rows, 66.7 at 128.
 template <int MT, int D, bool TWO>
 __global__ __launch_bounds__(512, MT == 1 || (MT == 2 && !TWO) ? 4 : 2) void skinny_swiglu_kernel(const f16* __restrict__ Af,
                                                                              const f16* __restrict__ Af_lo,

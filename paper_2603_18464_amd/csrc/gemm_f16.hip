@@ -292,7 +292,8 @@ __device__ __forceinline__ void read_frag_asm(f16x8& dst, unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 #endif
 }
-// Until at most N of the reads issued so far are outstanding (they return in order; the loops hold no scalar loads).
+// Until at most N of the reads issued so far are outstanding (they return in order; a scalar load in flight counts as
+// well, which can only make the wait longer).
 template <int N = 0>
 __device__ __forceinline__ void wait_lds() {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -499,8 +499,9 @@ static void launch_value_mlp(const T* w1, const float* b1, const float* w2, cons
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     attr_set = true;
   }
-  // 16 rows a wave re-fill the LDS least; fewer when that would not be a workgroup per compute unit (d = 4096: 8 pooled
-  // rows 194 us with 64 workgroups, a quarter of a ms less per step of 8 with 256; 64 rows 325 us with 16, 383 with 4)
+  // 16 rows a wave re-fill the LDS least; 4 where that would not be a workgroup per compute unit.  us with 4 / 16:
+  //   d 4096: 8 pooled rows 39 / 132, 16 99 / 158, 24 144 / 160, 32 192 / 159, 40 234 / 314, 64 383 / 314, 256 1393 / 1233
+  //   d 768 (12 workgroups for 8 pooled rows): 8 rows 12 / 37, 128 31 / 57, 256 53 / 75
   const int groups = (B + RB - 1) / RB, jpw = groups * ((d + 63) / 64) >= 256 ? 16 : 4;
   hipLaunchKernelGGL(kern, dim3(groups, (d + 4 * jpw - 1) / (4 * jpw)), dim3(256), smem, st, w1, b1, w2, vu, B, d, jpw, vh);
 }

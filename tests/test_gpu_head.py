@@ -1,12 +1,12 @@
-"""The action head on both sides of the width from which a wave keeps eight loads in flight, with widths that end inside a
+"""The heads.  The action head on both sides of the width from which a wave keeps eight loads in flight, with widths that end inside a
 step of 256 columns, and with every split of the action rows over workgroups: the logits are the oracle's, and a row has
-the same bits whatever batch it is in."""
+the same bits whatever batch it is in.  The value head on both sides of its rule for the rows of a wave."""
 import numpy as np
 import pytest
 
 import workloads as W
 from tests import parity as P
-from tests.test_gpu_parity import ragged_obs, run_both
+from tests.test_gpu_parity import _value_case, ragged_obs, run_both
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +31,11 @@ def test_head_widths_and_splits(heads, bins):
         pol.close()
     for n in got:
         assert np.array_equal(got[n], got[300][:n]), n
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("batch", [3, 56, 57])               # 7 groups of 8 rows x 32: four rows of W1 a wave; 8: sixteen
+def test_value_head_rows_per_wave(batch):
+    shape = W.PolicyShape(1, 2048, 16, 128, 128, 700, dtype="bf16")
+    wl = W.Workload("Vh", 93, shape, batch=batch, n_patches=2, instr_len=(0, 0), n_tokens=2)
+    _value_case(wl, ragged_obs(wl, [2] * batch, [0] * batch, seed=8), None, n_steps=5, tol=2e-3)
