@@ -251,8 +251,8 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
 //   for ALL outstanding LDS loads before any LDS read, so the reads are inline assembly and the waits explicit.
 // * The instruction: 16x16x32.  On real operands the matrix cores are limited by power, not issue: an MFMA-only loop on
-//   random activations and bf16-exact weights sustains 1.94 PFLOP/s with 16x16x32 (half the accumulator traffic per
-//   product) against 1.68 with 32x32x16.  In this kernel that is 2.59 ms instead of 2.85 (gate/up, 18560 x 22016 x 4096),
+//   weight bits (vla_probe) sustains 1.76 PFLOP/s with 16x16x32 (half the accumulator traffic per product) against 1.59
+//   with 32x32x16.  In this kernel that is 2.59 ms instead of 2.85 (gate/up, 18560 x 22016 x 4096),
 //   1.40 instead of 1.48 (down), 0.56 instead of 0.61 (o).
 // * A pass of 8-bit low terms (LO8) follows on 16x16x128: both k-steps of a slab are one product, so the two register
 //   buffers hold one slab and there is none to spare for the next.  Each register is refilled as soon as its last
