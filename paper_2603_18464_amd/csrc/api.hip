@@ -36,7 +36,7 @@ struct ArenaLayout {
   std::vector<LayerW> layers;
 };
 struct WorkLayout {
-  size_t x, hn, q, att, act, part, rope_cos, rope_sin, tok_seq, tok_pos, tok_src, last_row, seq_len,
+  size_t x, hn, q, att, act, part, norm_y, norm_sums, rope_cos, rope_sin, tok_seq, tok_pos, tok_src, last_row, seq_len,
       cu_patch, cu_instr, cur_ids, logits, vz, vml, vu, vh, ids2, tail, chunk_rows, chunk_logits, slot_map, range_flag,
       total;
 };
@@ -139,6 +139,8 @@ WorkLayout work_layout(const vla_config& c) {
   w.act = take(T * f * es * terms);
   const size_t widest = 3 * d > 2 * f ? 3 * d : 2 * f;
   w.part = take(c.dtype == VLA_BF16 ? (size_t)kMaxKSplit * part_rows(c) * widest * 4 : 0);
+  w.norm_y = take(c.dtype == VLA_BF16 ? (size_t)kNormRows * d * 4 : 0);
+  w.norm_sums = take(c.dtype == VLA_BF16 ? (size_t)kNormRows * (d / 16) * 4 : 0);
   w.rope_cos = take((size_t)c.max_seq * (c.head_dim / 2) * 4);
   w.rope_sin = take((size_t)c.max_seq * (c.head_dim / 2) * 4);
   w.tok_seq = take(T * 4);
@@ -431,6 +433,13 @@ inline f16* frag_rows(f16* base, int row0, int K) { return base + (size_t)(row0 
 // (nullptr when no layer is a two-term layer; single-term layers of a two-term configuration pass nullptr on)
 inline f16* frag_lo(const vla_config& c, f16* base, int K) { return two_term(c) ? base + max_rows(c) * (size_t)K : nullptr; }
 
+// Whether the decode products that read normalised rows normalise them themselves: up to 16 rows, and up to kNormRows of a
+// narrow model.  (Every workgroup reads the rows in float32, which from 17 rows on costs a wide model more than the two
+// launches it saves.)  us of a layer's four products, with the norm apart / inside: d 4096 1 row 91.7 / 85.7, 16 93.2 / 90.7,
+// 17 94.6 / 95.3, 32 97.3 / 106; d 2048 1 38.0 / 35.2, 16 39.3 / 37.9, 24 40.4 / 40.5, 32 41.6 / 43.8; d 768 1 20.2 / 17.0,
+// 16 21.1 / 18.8, 32 22.0 / 20.3.
+inline bool norm_in_gemm(const vla_config& c, int B) { return B <= 16 || (B <= kNormRows && c.d_model <= 1024); }
+
 // Decode step of the 16-bit path: split-K GEMMs whose partial planes span the whole batch, and one kernel after each
 // GEMM that sums the planes and applies the elementwise step for all rows.  Batches of up to kSkinnyMaxRows rows
 // use the weight-streaming kernel (every wave an independent stream; a 128-row accumulator tile is what a wave's
@@ -438,7 +447,8 @@ inline f16* frag_lo(const vla_config& c, f16* base, int K) { return two_term(c) 
 // the tiled kernel in chunks of 256 rows, split over K (activations shared through LDS, every weight read once per 256
 // rows); a remainder of at most 128 rows, and the matrices the tiled kernel does not take, go to the weight-streaming
 // kernel in chunks of 128 rows with the same number of planes (the later chunks find the matrix they re-read in
-// the 256 MB last-level cache).
+// the 256 MB last-level cache).  A few rows take five launches a layer instead of seven, with the same bits: the products
+// that read normalised rows normalise them, the products that add to the residual rows do so.
 int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
   const vla_config& c = ctx->cfg;
   const WorkLayout& w = ctx->wl;
@@ -470,13 +480,18 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     }
   };
   f16* const none = nullptr;
+  const bool norm = norm_in_gemm(c, B);
+  float *y = at<float>(ctx->work, w.norm_y), *sums = at<float>(ctx->work, w.norm_sums);
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);      // low-term planes only in two-term layers
     const bool two = two_term_layer(c, l), two_next = two_term_layer(c, l + 1);
     {
       ProfScope ps(ctx, FAM_GEMM_QKV_DECODE, st);
-      gemm(hn, two ? hn_lo : none, lw.w_qkv, 3 * d, d, ks_qkv);
+      if (norm)
+        skinny_norm_gemm(y, sums, c.rms_eps, two, at<f16>(ctx->arena, lw.w_qkv), part, B, 3 * d, d, ks_qkv, st);
+      else
+        gemm(hn, two ? hn_lo : none, lw.w_qkv, 3 * d, d, ks_qkv);
     }
     {
       // the attention kernel itself sums the QKV partials of its (sequence, head), applies RoPE and appends the
@@ -489,11 +504,20 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     }
     {
       ProfScope ps(ctx, FAM_GEMM_O_DECODE, st);
-      gemm(att, two ? att_lo : none, lw.w_o, d, d, ks_o);
-      reduce_resid_norm(part, ks_o, B, 0, B, d, x, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, hn, two ? hn_lo : none, 0,
-                        st);
+      if (norm) {
+        skinny_resid(att, two ? att_lo : none, at<f16>(ctx->arena, lw.w_o), x, at<float>(ctx->arena, lw.g_ffn), y, sums, B, d, d,
+                     ks_o, st);
+      } else {
+        gemm(att, two ? att_lo : none, lw.w_o, d, d, ks_o);
+        reduce_resid_norm(part, ks_o, B, 0, B, d, x, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, hn, two ? hn_lo : none, 0,
+                          st);
+      }
     }
-    {
+    if (norm) {
+      ProfScope ps(ctx, FAM_GEMM_GATEUP_DECODE, st);
+      skinny_norm_swiglu(y, sums, c.rms_eps, two, at<f16>(ctx->arena, lw.w_gu), act, two ? act_lo : none, B,
+                         f, d, st);
+    } else {
       ProfScope ps(ctx, FAM_GEMM_GATEUP_DECODE, st);
       // chunks of at most 128 rows finish the elementwise step inside the product; the tiled kernel's planes need a launch
       int r0 = 0;
@@ -509,8 +533,12 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     {
       ProfScope ps(ctx, FAM_GEMM_DOWN_DECODE, st);
       const float* next_gain = l + 1 < c.n_layers ? at<float>(ctx->arena, ctx->al.layers[l + 1].g_attn) : nullptr;
-      gemm(act, two ? act_lo : none, lw.w_down, d, f, ks_dn);
-      reduce_resid_norm(part, ks_dn, B, 0, B, d, x, next_gain, c.rms_eps, hn, two_next ? hn_lo : none, 0, st);
+      if (norm) {
+        skinny_resid(act, two ? act_lo : none, at<f16>(ctx->arena, lw.w_down), x, next_gain, y, sums, B, d, f, ks_dn, st);
+      } else {
+        gemm(act, two ? act_lo : none, lw.w_down, d, f, ks_dn);
+        reduce_resid_norm(part, ks_dn, B, 0, B, d, x, next_gain, c.rms_eps, hn, two_next ? hn_lo : none, 0, st);
+      }
     }
   }
   return VLA_OK;
@@ -762,7 +790,8 @@ int do_decode(vla_ctx* ctx, int32_t B, const int32_t* token_ids, float* logits, 
     f16* hn = at<f16>(ctx->work, w.hn);
     decode_begin<T>(token_ids, at<T>(ctx->arena, ctx->al.embed), c.vocab, at<int32_t>(ctx->work, w.seq_len), slot_map,
                     at<int32_t>(ctx->work, w.tok_seq), at<int32_t>(ctx->work, w.tok_pos), at<float>(ctx->work, w.x), B,
-                    c.d_model, half ? at<float>(ctx->arena, ctx->al.layers[0].g_attn) : nullptr, c.rms_eps, hn,
+                    c.d_model, half ? at<float>(ctx->arena, ctx->al.layers[0].g_attn) : nullptr, c.rms_eps,
+                    norm_in_gemm(c, B) ? at<float>(ctx->work, w.norm_y) : nullptr, at<float>(ctx->work, w.norm_sums), hn,
                     half && two_term_layer(c, 0) ? frag_lo(c, hn, c.d_model) : nullptr, st);
   }
   if (sizeof(T) == 2) run_layers_decode_f16(ctx, B, st);

@@ -182,6 +182,16 @@ void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // The gate/up product of at most kSkinnyMaxRows rows with its elementwise step, straight to fragments (K >= 128).
 void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
                    int K, hipStream_t st);
+// The same products for at most kNormRows rows that take the RMSNorm of their rows with them (two: as two terms), from y = x *
+// gain (float32, fragment order) and sums of squares [M][d / 16]; and the O / down product that adds to the residual rows x
+// [M, N] itself, with the sums of skinny_gemm with kgroups planes and reduce_resid_norm, and with a gain leaves y and sums.
+constexpr int kNormRows = 32;
+void skinny_norm_gemm(const float* y, const float* sums, float eps, bool two, const f16* Wp, float* part, int M, int N, int d,
+                      int kgroups, hipStream_t st);
+void skinny_norm_swiglu(const float* y, const float* sums, float eps, bool two, const f16* Wp, f16* act_frag, f16* act_frag_lo,
+                        int M, int f, int d, hipStream_t st);
+void skinny_resid(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums, int M,
+                  int N, int K, int kgroups, hipStream_t st);
 // The same product for up to 256 rows on the tiled kernel (256 rows x 256 or 64 columns a workgroup), split over `ksplit`
 // K slices (one partial plane each): activations go through LDS once per workgroup instead of once per wave, which is what
 // a large batch needs to stream every weight once at full rate.  Needs N % 256 == 0 and K % 64 == 0 (splitk_gemm_fits).
@@ -192,11 +202,11 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 void reduce_resid_norm(const float* part, int ksplit, int plane_rows, int prow0, int M, int d, float* x,
                        const float* gain, float eps, f16* hn_frag, f16* hn_frag_lo, int row0, hipStream_t st);
 // Start of a decode step: x rows from the embedding table, tok_seq / tok_pos of the step, lengths + 1, and with a gain the
-// first norm in fragment order.  slot_map: device [M] cache slot of each row, nullptr = identity.
+// first norm in fragment order, or with y != nullptr y and sums as above.  slot_map: device [M] cache slot of each row, nullptr = identity.
 template <class T>
 void decode_begin(const int32_t* ids, const T* embed, int vocab, int32_t* seq_len, const int32_t* slot_map,
-                  int32_t* tok_seq, int32_t* tok_pos, float* x, int M, int d, const float* gain, float eps, f16* hn_frag,
-                  f16* hn_frag_lo, hipStream_t st);
+                  int32_t* tok_seq, int32_t* tok_pos, float* x, int M, int d, const float* gain, float eps, float* y,
+                  float* sums, f16* hn_frag, f16* hn_frag_lo, hipStream_t st);
 void reduce_swiglu(const float* part, int ksplit, int plane_rows, int prow0, int M, int f, f16* act_frag,
                    f16* act_frag_lo, int row0, hipStream_t st);
 
