@@ -1,11 +1,10 @@
 // Causal attention against the KV cache: the float32 rows kernel, flash attention of the 16-bit prefill, and the decode
 // kernel of the 16-bit path.
 //
-// attention_rows (float32): one wave per (token, head).  Lanes first split the keys (each lane scores keys
-// lane, lane+64, ...), the softmax statistics are reduced across the wave, then lanes split the
-// head dimension and accumulate the probability-weighted values.  Keys/values of a (slot, head)
-// are contiguous [position][head_dim] rows in the cache.  A few dozen keys: bound by latency, so a key is read as
-// 16-byte pieces and the values of eight keys are requested together.
+// attention_rows (float32): one wave per (token, head).  Keys and values of a (slot, head) are contiguous
+// [position][head_dim] rows in the cache; HD / 4 lanes share a row, 16 bytes each, so an instruction reads 64 * 4 / HD whole
+// rows and a score is a butterfly over the lanes of its row.  A few dozen keys: bound by its chain of latencies, so the rows
+// of G instructions are requested together, and the first values with the keys, before there is a score.
 #include <type_traits>
 
 #include "common.h"
@@ -17,59 +16,71 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
     const float* __restrict__ q, const float* __restrict__ k_cache, const float* __restrict__ v_cache,
     const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos, float* __restrict__ out, int n_items,
     int n_heads, int max_seq) {
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // [4 waves][HD] queries, [4][max_seq] scores
+  extern __shared__ float smem[];                    // [4 waves][max_seq] scores
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int item = blockIdx.x * 4 + wave;            // (token, head)
   if (item >= n_items) return;                       // whole wave leaves; no block barrier is used
-  float* qs = smem + wave * HD;
-  float* sc = smem + 4 * HD + (size_t)wave * max_seq;
+  float* sc = smem + (size_t)wave * max_seq;
+  constexpr int LPR = HD / 4, RPI = 64 / LPR, G = 12;
+  const int c = lane % LPR, sub = lane / LPR;
   const int tok = item / n_heads, head = item - tok * n_heads;
   const int slot = tok_seq[tok], pos = tok_pos[tok];
-  const int ctx = pos + 1;                           // keys 0..pos
-  const float* qrow = q + (size_t)item * HD;
-  for (int i = lane; i < HD; i += 64) qs[i] = qrow[i];
-  const float* kbase = k_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
-  const float* vbase = v_cache + ((size_t)slot * n_heads + head) * max_seq * HD;
+  const f32x4 qv = *(const f32x4*)(q + (size_t)item * HD + c * 4);
+  const size_t blk = ((size_t)slot * n_heads + head) * max_seq * HD + c * 4;
+  const float *kbase = k_cache + blk, *vbase = v_cache + blk;
   const float scale = rsqrtf((float)HD);
-  __builtin_amdgcn_wave_barrier();
+  f32x4 kv[G], vv[G];
+  auto request = [&](f32x4 (&r)[G], const float* base, int key0) {
+#pragma unroll
+    for (int u = 0; u < G; ++u) r[u] = *(const f32x4*)(base + (size_t)min(key0 + u * RPI + sub, pos) * HD);   // keys 0..pos
+  };
+  request(kv, kbase, 0);
+  request(vv, vbase, 0);
+  __builtin_amdgcn_sched_barrier(0);
   float mx = -INFINITY;
-  for (int key = lane; key < ctx; key += 64) {
-    const float* kr = kbase + (size_t)key * HD;
-    float s = 0.f;
-#pragma unroll 8
-    for (int i = 0; i < HD; i += 4) {
-      const f32x4 kv = *(const f32x4*)(kr + i), qv = *(const f32x4*)(qs + i);
+  for (int key0 = 0; key0 <= pos; key0 += RPI * G) {
+    if (key0 > 0) request(kv, kbase, key0);
+    float s[G];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s = fmaf(qv[e], kv[e], s);
+    for (int u = 0; u < G; ++u) s[u] = fmaf(qv[3], kv[u][3], fmaf(qv[2], kv[u][2], fmaf(qv[1], kv[u][1], qv[0] * kv[u][0])));
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int u = 0; u < G; ++u) s[u] += __shfl_xor(s[u], o, 64);
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int key = key0 + u * RPI + sub;
+      s[u] *= scale;
+      mx = fmaxf(mx, s[u]);                                // (a clamped row repeats key pos: the same maximum)
+      if (c == 0 && key <= pos) sc[key] = s[u];
     }
-    s *= scale;
-    sc[key] = s;
-    mx = fmaxf(mx, s);
   }
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int key = lane; key < ctx; key += 64) {
-    const float p = __expf(sc[key] - mx);
-    sc[key] = p;
-    sum += p;
-  }
-  sum = wave_sum(sum);
+#pragma unroll
+  for (int o = 32; o >= LPR; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
   __builtin_amdgcn_wave_barrier();
-  const float inv = 1.0f / sum;
-  float* orow = out + (size_t)item * HD;
-  for (int i = lane; i < HD; i += 64) {
-    float acc = 0.f;
-    int key = 0;
-    for (; key + 8 <= ctx; key += 8) {
-      float v[8];
+  float sum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int key0 = 0; key0 <= pos; key0 += RPI * G) {
+    if (key0 > 0) request(vv, vbase, key0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = vbase[(size_t)(key + u) * HD + i];
+    for (int u = 0; u < G; ++u) {
+      const int key = key0 + u * RPI + sub;
+      if (key <= pos) {
+        const float p = __expf(sc[key] - mx);
+        sum += p;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc = fmaf(sc[key + u], v[u], acc);
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, vv[u][e], acc[e]);
+      }
     }
-    for (; key < ctx; ++key) acc = fmaf(sc[key], vbase[(size_t)key * HD + i], acc);
-    orow[i] = acc * inv;
   }
+#pragma unroll
+  for (int o = 32; o >= LPR; o >>= 1) {
+    sum += __shfl_xor(sum, o, 64);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+  }
+  const float inv = 1.0f / sum;
+  if (sub == 0) *(f32x4*)(out + (size_t)item * HD + c * 4) = acc * inv;
 }
 
 // ---- prefill: causal flash attention on the matrix cores --------------------------------------------
@@ -651,7 +662,7 @@ void attention_rows_f32(const float* q, const float* k_cache, const float* v_cac
                         hipStream_t st) {
   const int n_items = n_tok * n_heads;
   const int blocks = (n_items + 3) / 4;
-  const size_t smem = 4 * (size_t)(head_dim + max_seq) * sizeof(float);
+  const size_t smem = 4 * (size_t)max_seq * sizeof(float);
 #define VLA_ATTN_CASE(HD)                                                                                   \
   case HD:                                                                                                  \
     hipLaunchKernelGGL((attention_rows_kernel<HD>), dim3(blocks), dim3(256), smem, st, q, k_cache, v_cache, \

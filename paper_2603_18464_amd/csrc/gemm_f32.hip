@@ -9,35 +9,46 @@
 // reads from L2; the order of every sum is the same, so a row's bits do not depend on the batch it is in.
 // Policy step of the 2-layer model (4 sequences of 32 tokens, 7 tokens out): 3.18 ms with 64 x 64 tiles of scalar FMAs
 // (4 workgroups on N = 256, 33 to 78 us a launch) and the norms, rotation, SwiGLU and residual adds as launches of their
-// own (11 a layer); 0.41 ms with these (5 a layer).
+// own (11 a layer); 0.40 ms with these (5 a layer); 0.375 with what the epilogues read requested before the product and all
+// of a down projection's operands (11 k-steps a wave) in one round instead of two, and the attention's keys and values together.
 #include "common.h"
 
 namespace vla {
 
 // Columns of a tile: tile t covers W rows col(t) .. + 15 and, for kNT == 2, + second() .. + 15; store() gets element
-// (m, c) of them.  kNT == 2 pairs the columns an elementwise step needs together.
+// (m, c) of them.  kNT == 2 pairs the columns an elementwise step needs together.  What store() needs from memory is
+// requested by index() and fetch() before the product, behind the operands: at the end it would be one or two more
+// latencies of a launch that is made of them.
 struct F32Resid {
   static constexpr int kNT = 1;
+  struct Index {};
+  struct Fetched { float x; };
+  __device__ Index index(int) const { return {}; }
+  __device__ Fetched fetch(int m, int t, int c, const Index&) const { return {x[(size_t)m * ldx + min(t * 16 + c, n - 1)]}; }
   float* x;
   int ldx, n;
   __device__ int col(int t) const { return t * 16; }
   __device__ int second() const { return 0; }
   __device__ int last() const { return n - 1; }
-  __device__ void store(int m, int t, int c, const float (&v)[1]) const {
+  __device__ void store(int m, int t, int c, const float (&v)[1], const Index&, const Fetched& old) const {
     const int j = t * 16 + c;
-    if (j < n) x[(size_t)m * ldx + j] += v[0];
+    if (j < n) x[(size_t)m * ldx + j] = old.x + v[0];
   }
 };
 
 // W = [gate rows | up rows]: act[m][j] = silu(gate j) * up j
 struct F32Swiglu {
   static constexpr int kNT = 2;
+  struct Index {};
+  struct Fetched {};
+  __device__ Index index(int) const { return {}; }
+  __device__ Fetched fetch(int, int, int, const Index&) const { return {}; }
   float* act;
   int f;
   __device__ int col(int t) const { return t * 16; }
   __device__ int second() const { return f; }
   __device__ int last() const { return f - 1; }
-  __device__ void store(int m, int t, int c, const float (&v)[2]) const {
+  __device__ void store(int m, int t, int c, const float (&v)[2], const Index&, const Fetched&) const {
     const int j = t * 16 + c;
     if (j < f) act[(size_t)m * f + j] = v[0] / (1.0f + expf(-v[0])) * v[1];
   }
@@ -46,7 +57,14 @@ struct F32Swiglu {
 // W = [q | k | v] rows, head by head: tile t is 16 rotary pairs (i, i + head_dim/2) of one head of q, k or v
 struct F32Qkv {
   static constexpr int kNT = 2;
+  struct Index { int pos, slot; };
+  struct Fetched { float cs, sn; };
   RopeKv o;
+  __device__ Index index(int m) const { return {o.tok_pos[m], o.tok_seq[m]}; }
+  __device__ Fetched fetch(int, int t, int c, const Index& x) const {
+    const int u = t / tiles_per_head(), at = x.pos * (o.head_dim >> 1) + (t - u * tiles_per_head()) * 16 + c;
+    return {o.rope_cos[at], o.rope_sin[at]};
+  }
   __device__ int tiles_per_head() const { return o.head_dim >> 5; }
   __device__ int col(int t) const {
     const int u = t / tiles_per_head();
@@ -54,15 +72,14 @@ struct F32Qkv {
   }
   __device__ int second() const { return o.head_dim >> 1; }
   __device__ int last() const { return 3 * o.d_model - 1; }
-  __device__ void store(int m, int t, int c, const float (&v)[2]) const {
+  __device__ void store(int m, int t, int c, const float (&v)[2], const Index& x, const Fetched& f) const {
     const int u = t / tiles_per_head(), half = o.head_dim >> 1;
     const int i = (t - u * tiles_per_head()) * 16 + c, which = u / o.n_heads, head = u - which * o.n_heads;
-    const int pos = o.tok_pos[m];
     float a = v[0], b = v[1];
-    if (which < 2) rope_pair(v[0], v[1], o.rope_cos[pos * half + i], o.rope_sin[pos * half + i], a, b);
+    if (which < 2) rope_pair(v[0], v[1], f.cs, f.sn, a, b);
     float* dst = which == 0 ? (float*)o.q + (size_t)m * o.d_model + head * o.head_dim
                             : (float*)(which == 1 ? o.k_cache : o.v_cache) +
-                                  (((size_t)o.tok_seq[m] * o.n_heads + head) * o.max_seq + pos) * o.head_dim;
+                                  (((size_t)x.slot * o.n_heads + head) * o.max_seq + x.pos) * o.head_dim;
     dst[i] = a;
     dst[i + half] = b;
   }
@@ -75,7 +92,7 @@ struct F32Qkv {
 template <int MT, bool VEC, bool NORM, class Epi>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W,
                                                        const float* __restrict__ gain, float eps, int M, int K, int tiles, Epi epi) {
-  constexpr int NT = Epi::kNT, U = MT == 1 ? 6 : 4;        // k-steps (16 k) requested together
+  constexpr int NT = Epi::kNT, U = MT == 1 ? (NT == 1 ? 12 : 6) : 4;   // k-steps (16 k) requested together
   __shared__ float red[4][MT * NT][256];
   __shared__ float s_ss[4][MT * 16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -114,8 +131,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  for (int s0 = s_begin; s0 < s_end; s0 += U) {
-    f32x4 a[U][MT], w[U][NT], gn[NORM ? U : 1];
+  f32x4 a[U][MT], w[U][NT], gn[NORM ? U : 1];
+  auto request = [&](int s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (s0 + u < s_end) {                                // uniform across the wave
@@ -125,6 +142,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         for (int j = 0; j < NT; ++j) w[u][j] = load(w_row[j], s0 + u);
         if constexpr (NORM) gn[u] = load(gain, s0 + u);
       }
+  };
+  const int t = threadIdx.x, row = t >> 4, c = t & 15;     // the output element(s) of this thread
+  typename Epi::Index index[MT];
+  typename Epi::Fetched fetched[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) index[i] = epi.index(min(m0 + i * 16 + row, M - 1));
+  request(s_begin);
+#pragma unroll
+  for (int i = 0; i < MT; ++i) fetched[i] = epi.fetch(min(m0 + i * 16 + row, M - 1), tile, c, index[i]);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int s0 = s_begin; s0 < s_end; s0 += U) {
+    if (s0 > s_begin) request(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (s0 + u < s_end) {
@@ -158,7 +187,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
   }
   __syncthreads();
-  const int t = threadIdx.x, row = t >> 4, c = t & 15;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const int m = m0 + i * 16 + row;
@@ -172,7 +200,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
     for (int j = 0; j < NT; ++j)
       v[j] = ((red[0][i * NT + j][t] + red[1][i * NT + j][t]) + (red[2][i * NT + j][t] + red[3][i * NT + j][t])) * inv;
-    epi.store(m, tile, c, v);
+    epi.store(m, tile, c, v, index[i], fetched[i]);
   }
 }
 
