@@ -44,9 +44,7 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
 #pragma unroll
     for (int u = 0; u < G; ++u) s[u] = fmaf(qv[3], kv[u][3], fmaf(qv[2], kv[u][2], fmaf(qv[1], kv[u][1], qv[0] * kv[u][0])));
 #pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1)
-#pragma unroll
-      for (int u = 0; u < G; ++u) s[u] += __shfl_xor(s[u], o, 64);
+    for (int u = 0; u < G; ++u) s[u] = lanes_sum<1, LPR / 2>(s[u]);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const int key = key0 + u * RPI + sub;
@@ -55,8 +53,7 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
       if (c == 0 && key <= pos) sc[key] = s[u];
     }
   }
-#pragma unroll
-  for (int o = 32; o >= LPR; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  if constexpr (LPR < 64) mx = lanes_max<LPR, 32>(mx);
   __builtin_amdgcn_wave_barrier();
   float sum = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -73,11 +70,10 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
       }
     }
   }
+  if constexpr (LPR < 64) {
+    sum = lanes_sum<LPR, 32>(sum);
 #pragma unroll
-  for (int o = 32; o >= LPR; o >>= 1) {
-    sum += __shfl_xor(sum, o, 64);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+    for (int e = 0; e < 4; ++e) acc[e] = lanes_sum<LPR, 32>(acc[e]);
   }
   const float inv = 1.0f / sum;
   if (sub == 0) *(f32x4*)(out + (size_t)item * HD + c * 4) = acc * inv;
@@ -554,9 +550,7 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
       sc[u] = t;
     }
 #pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1)
-#pragma unroll
-      for (int u = 0; u < G; ++u) sc[u] += __shfl_xor(sc[u], o, 64);
+    for (int u = 0; u < G; ++u) sc[u] = lanes_sum<1, LPR / 2>(sc[u]);
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       sc[u] = row_of(it0 + u) < ctx ? sc[u] * scale : -INFINITY;   // uniform over the LPR lanes of a row
@@ -594,21 +588,16 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     }
   }
   // bring the lanes of the wave to a common maximum, then add the row groups
-  float mx = m_run;
-#pragma unroll
-  for (int o = 32; o >= LPR; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  const float mx = lanes_max<LPR, 32>(m_run);
   {
     const float f = m_run == -INFINITY ? 0.f : __expf(m_run - mx);
     lsum *= f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] *= f;
   }
+  lsum = lanes_sum<LPR, 32>(lsum);
 #pragma unroll
-  for (int o = 32; o >= LPR; o >>= 1) {
-    lsum += __shfl_xor(lsum, o, 64);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], o, 64);
-  }
+  for (int j = 0; j < 8; ++j) acc[j] = lanes_sum<LPR, 32>(acc[j]);
   if (sub == 0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) s_o[wave][c * 8 + j] = acc[j];

@@ -28,16 +28,59 @@ template <> __device__ __forceinline__ f16 from_f32<f16>(float v) { return (f16)
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16 from_f32<bf16>(float v) { return (bf16)v; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// ---- values across the lanes of a wave ------------------------------------------------------------------------
+// combine<LO, HI>(v, op): v combined over the lanes that differ in strides LO, 2 LO, .. HI, narrowest first, the result in all
+// of them.  In the vector unit: a step is one instruction behind the operand's, where a shuffle goes through the LDS and takes
+// some hundred cycles, and the kernels of a decode step are chains of such steps.  LO is 1, 8, 16 or 32 (a stride of 4 is
+// done by a mirror, which needs lanes that already agree in strides 1 and 2).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+#else
+  return v;
+#endif
+}
+constexpr int kQuad0 = 0x00, kQuad1 = 0x55, kQuad2 = 0xAA, kQuad3 = 0xFF;       // lane 0 .. 3 of a quad to all of it
+template <int STRIDE, class Op>
+__device__ __forceinline__ float combine_step(float v, Op op) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (STRIDE == 1) return op(v, dpp<0xB1>(v));                        // quad_perm 1 0 3 2
+  if constexpr (STRIDE == 2) return op(v, dpp<0x4E>(v));                        // quad_perm 2 3 0 1
+  if constexpr (STRIDE == 4) return op(v, dpp<0x141>(v));                       // row_half_mirror
+  if constexpr (STRIDE == 8) return op(v, dpp<0x128>(v));                       // row_ror 8
+  if constexpr (STRIDE >= 16) {                                                 // both halves of the pair in both its lanes
+    unsigned a = __builtin_bit_cast(unsigned, v), c = a;
+    asm("" : "+v"(c));                                     // (of a swap of a value with itself the compiler makes a copy)
+    const auto s = [&] {
+      if constexpr (STRIDE == 16) return __builtin_amdgcn_permlane16_swap(a, c, false, false);
+      else return __builtin_amdgcn_permlane32_swap(a, c, false, false);
+    }();
+    a = s[0];
+    c = s[1];
+    asm("" : "+v"(a), "+v"(c));                            // (... and takes its two results for one)
+    return op(__builtin_bit_cast(float, a), __builtin_bit_cast(float, c));
+  }
+#endif
   return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+template <int LO, int HI, class Op>
+__device__ __forceinline__ float combine(float v, Op op) {
+  static_assert(LO == 1 || LO >= 8, "see above");
+  if constexpr (LO <= 1 && HI >= 1) v = combine_step<1>(v, op);
+  if constexpr (LO <= 2 && HI >= 2) v = combine_step<2>(v, op);
+  if constexpr (LO <= 4 && HI >= 4) v = combine_step<4>(v, op);
+  if constexpr (LO <= 8 && HI >= 8) v = combine_step<8>(v, op);
+  if constexpr (LO <= 16 && HI >= 16) v = combine_step<16>(v, op);
+  if constexpr (LO <= 32 && HI >= 32) v = combine_step<32>(v, op);
   return v;
 }
+struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+template <int LO, int HI> __device__ __forceinline__ float lanes_sum(float v) { return combine<LO, HI>(v, Add()); }
+template <int LO, int HI> __device__ __forceinline__ float lanes_max(float v) { return combine<LO, HI>(v, Max()); }
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<1, 32>(v); }
+__device__ __forceinline__ float wave_max(float v) { return lanes_max<1, 32>(v); }
 
 // ---- kernel families timed by the profiling hooks ----------------------------------------------
 enum Family {

@@ -48,14 +48,13 @@ __device__ __forceinline__ void settle(f32x16 (&p)[MT], f32x16 (&q)[MT]) {
 // ---- RMS statistics of a float32 row ---------------------------------------------------------------------------
 // Every kernel of the decode path that normalises a row adds its squares in one order, so that the bits do not depend on
 // which of them a batch takes: pieces of four elements; groups of 16, (p0 + p1) + (p2 + p3); spans of 64, (g0 + g1) +
-// (g2 + g3); lane j of sixteen adds spans j, j + 16, ...; a butterfly over the sixteen, widest stride first.
+// (g2 + g3); lane j of sixteen adds spans j, j + 16, ...; a butterfly over the sixteen, narrowest stride first.
 __device__ __forceinline__ float sum4_squares(const f32x4& v) {
   return fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], v[0] * v[0])));
 }
 // ss: a lane's spans; lanes 16 i .. 16 i + 15 hold one row.
 __device__ __forceinline__ float norm_factor(float ss, int d, float eps) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  ss = lanes_sum<1, 8>(ss);
   return 1.0f / sqrtf(ss / (float)d + eps);
 }
 
@@ -599,11 +598,12 @@ __global__ __launch_bounds__(1024) void skinny_resid_kernel(const f16* __restric
     if (gain) {
       if (m < M) y[frag_index(m, n0 + c, N)] = v * g;
       f32x4 e;                                             // the four elements of this lane's piece
-#pragma unroll
-      for (int t = 0; t < 4; ++t) e[t] = __shfl(v, ((int)lane & ~3) + t, 64);
-      float ss = sum4_squares(e);
-      ss += __shfl_xor(ss, 4, 64);
-      ss += __shfl_xor(ss, 8, 64);
+      e[0] = dpp<kQuad0>(v);
+      e[1] = dpp<kQuad1>(v);
+      e[2] = dpp<kQuad2>(v);
+      e[3] = dpp<kQuad3>(v);
+      float ss = combine_step<4>(sum4_squares(e), Add());
+      ss = combine_step<8>(ss, Add());
       if (m < M && c == 0) sums[(size_t)m * (N >> 4) + blockIdx.x] = ss;
     }
   }
@@ -724,8 +724,7 @@ __global__ __launch_bounds__(1024) void reduce_resid_norm_kernel(const float* __
     }
     if (gain) {                                            // a span of 64 columns is 16 lanes
       float ss = i < d ? sum4_squares(v[it]) : 0.f;
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+      ss = lanes_sum<1, 8>(ss);
       if (i < d && (threadIdx.x & 15) == 0) red[i >> 6] = ss;
     }
   }
@@ -810,16 +809,14 @@ __global__ __launch_bounds__(256) void decode_begin_kernel(const int32_t* __rest
     }
     if (gain) {
       float ss = sum4_squares(v);
-      ss += __shfl_xor(ss, 1, 64);
-      ss += __shfl_xor(ss, 2, 64);
+      ss = lanes_sum<1, 2>(ss);
       if (y) {
         if (i < d) {
           *(f32x4*)(y + frag_index(m, i, d)) = v * *(const f32x4*)(gain + i);
           if ((threadIdx.x & 3) == 0) sums[(size_t)m * (d >> 4) + (i >> 4)] = ss;
         }
       } else {
-        ss += __shfl_xor(ss, 4, 64);
-        ss += __shfl_xor(ss, 8, 64);
+        ss = combine_step<8>(combine_step<4>(ss, Add()), Add());
         if (i < d && (threadIdx.x & 15) == 0) red[i >> 6] = ss;
       }
     }

@@ -180,9 +180,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 #pragma unroll
       for (int e = 0; e < 4; ++e) red[wave][i * NT + j][(4 * g + e) * 16 + r] = acc[i][j][e];
     if constexpr (NORM) {
-      float s = ss[i];
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
+      const float s = lanes_sum<16, 32>(ss[i]);
       if (g == 0) s_ss[wave][i * 16 + r] = s;
     }
   }

@@ -609,12 +609,9 @@ __global__ __launch_bounds__(64) void select_kernel(const float* __restrict__ lo
     if (s > best) { best = s; best_j = j; }      // strict: keeps the lowest index within a lane
     zmax = fmaxf(zmax, y);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ob = __shfl_xor(best, o, 64);
-    const int oj = __shfl_xor(best_j, o, 64);
-    if (ob > best || (ob == best && oj < best_j)) { best = ob; best_j = oj; }
-  }
+  // the lowest index among the lanes at the maximum: indices up to 1023 are exact in float32
+  const float top = wave_max(best);
+  best_j = -(int)wave_max(best == top && best_j < A ? -(float)best_j : -(float)A);
   if (best_j >= A) best_j = 0;                     // no lane saw a score above -inf
   zmax = wave_max(zmax);
   float se = 0.f;
