@@ -254,6 +254,11 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   weight bits (vla_probe) sustains 1.76 PFLOP/s with 16x16x32 (half the accumulator traffic per product) against 1.59
 //   with 32x32x16.  In this kernel that is 2.59 ms instead of 2.85 (gate/up, 18560 x 22016 x 4096),
 //   1.40 instead of 1.48 (down), 0.56 instead of 0.61 (o).
+// * DEEP: the fragments are read a whole slab ahead, for launches of at most 256 of the smallest tiles, where a k-step of four
+//   products a wave is shorter than the reads of the next one take.  With eight waves of 32x32 instead of four of 32x64 and
+//   four stages (whose number costs instructions where it is not a power of two) a slab of the 64x128 tile is 0.25 us instead
+//   of 0.33: 290 rows, N 768: K 2048 12.7 -> 9.6 us, K 768 7.3 -> 6.2; N 4096 K 4096 from the caches 25 -> 20, with weights
+//   from HBM 27 and 28 (K 11008 67 and 67).  Larger tiles gain nothing (128x256 at 290 and 2338 rows +-1 %).
 // * A pass of 8-bit low terms (LO8) follows on 16x16x128: both k-steps of a slab are one product, so the two register
 //   buffers hold one slab and there is none to spare for the next.  Each register is refilled as soon as its last
 //   product has issued instead: a slab runs as two halves of the wave's rows, the first half's A fragments are refilled
@@ -339,13 +344,18 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const 
 // depends on it.
 template <int MT, int NT>
 __device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
-  static_assert(MT * NT % 8 == 0, "whole groups of eight");
+  static_assert(MT * NT % 8 == 0 || MT * NT == 4, "whole groups of eight, or one of four");
 #if defined(__HIP_DEVICE_COMPILE__)
 #define VLA_ACC(j) "+v"(acc[(g + j) / NT][(g + j) % NT])
+  if constexpr (MT * NT == 4) {
+    constexpr int g = 0;
+    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3));
+  } else {
 #pragma unroll
-  for (int g = 0; g < MT * NT; g += 8)
-    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
-                 VLA_ACC(7));
+    for (int g = 0; g < MT * NT; g += 8)
+      asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
+                   VLA_ACC(7));
+  }
 #undef VLA_ACC
 #endif
 }
@@ -368,7 +378,7 @@ __device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a
 // SPLITK (with EpiPartial; one row of tiles, M <= BM): A is in the fragment order of the decode path
 // ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), tiles_m is the
 // number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, class Epi, bool LO8, bool SPLITK>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, class Epi, bool LO8, bool SPLITK>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16* __restrict__ A, int lda,
                                                                    const f16* __restrict__ Wp,
                                                                    const f16* __restrict__ W8, int M, int K, int Kw,
@@ -477,7 +487,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   }
   const unsigned w_b = lds0 + 2u * (unsigned)(A_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
 
-  f16x8 af[2][MT], bf[2][NT];
+  constexpr int NBUF = DEEP ? 2 * KS : 2;              // register buffers, a k-step each
+  f16x8 af[NBUF][MT], bf[NBUF][NT];
   constexpr int R = MT + NT, MF = MT * NT;             // reads and products of a k-step
   // fragment reads of k-step ss of the stage at byte offset so (block j of an operand in fragment order: 32 rows hold two
   // fragments)
@@ -501,50 +512,65 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
 #pragma unroll
     for (int j = 0; j < NT; ++j) hold(bf[f][j]);
   };
-  // One k-step of slab kt, its fragments in register buffer F: the MFMAs, and between them the reads of the next k-step
-  // (in the first three quarters, so that they have landed at the end).  In the last k-step of a slab the next one
-  // belongs to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes slab kt + S.
-  auto step = [&](int kt, auto F, auto SS) VLA_INLINE {
-    constexpr int f = decltype(F)::value, ss = decltype(SS)::value;
-    constexpr bool last = ss == KS - 1;
+  // One k-step of slab kt: the MFMAs, and between them fragment reads (in the first three quarters, so that they have
+  // landed at the end) and the loads of slab kt + S.
+  // Read ahead by a k-step: the k-steps alternate between two buffers, P is the slab's first one.  The reads of the last
+  // k-step belong to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes the loads.
+  // DEEP, read ahead by a slab: P is the half of the buffers slab kt is in, and all of this holds from its first k-step on.
+  auto step = [&](int kt, auto P, auto SS) VLA_INLINE {
+    constexpr int p = decltype(P)::value, ss = decltype(SS)::value;
+    constexpr bool last = ss == KS - 1, next = DEEP || last;        // next: the reads are of slab kt + 1
+    constexpr int f = DEEP ? p * KS + ss : (p + ss) & 1, g = DEEP ? (p ^ 1) * KS + ss : f ^ 1;
     constexpr int n_rd = MF * 3 / 4 > 0 ? MF * 3 / 4 : 1;
-    if constexpr (last) {
+    if constexpr (DEEP ? ss == 0 : last) {
       wait_vmcnt<(S - 2) * LPS>();
       __builtin_amdgcn_s_barrier();
     }
-    const unsigned so = (unsigned)((kt + (last ? 1 : 0)) % S) * (2u * STAGE_HALVES);
+    const unsigned so = (unsigned)((kt + (next ? 1 : 0)) % S) * (2u * STAGE_HALVES);
     static_for<MF>([&](auto I) VLA_INLINE {
       constexpr int i = decltype(I)::value, mt = i / NT, nt = i % NT;
       if constexpr (LO8) mfma_in_place(acc[mt][nt], af[f][mt], bf[f][nt]);
       else acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[f][mt], bf[f][nt], acc[mt][nt], 0, 0, 0);
       constexpr int r0 = i < n_rd ? i * R / n_rd : R, r1 = i < n_rd ? (i + 1) * R / n_rd : R;
       static_for<r1 - r0>([&](auto J) VLA_INLINE {
-        read_one(so, f ^ 1, std::integral_constant<int, last ? 0 : ss + 1>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
+        read_one(so, g, std::integral_constant<int, DEEP ? ss : (last ? 0 : ss + 1)>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
       });
-      if constexpr (last) {
-        constexpr int l0 = i * LPS / MF, l1 = (i + 1) * LPS / MF;
+      if constexpr (next) {
+        constexpr int at = DEEP ? ss * MF + i : i, of = DEEP ? KS * MF : MF;
+        constexpr int l0 = at * LPS / of, l1 = (at + 1) * LPS / of;
         static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_one(kt + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    arrived(f ^ 1);
+    if constexpr (!DEEP) arrived(g);
+    else if constexpr (last) static_for<KS>([&](auto J) VLA_INLINE { arrived((p ^ 1) * KS + decltype(J)::value); });
   };
-  auto slab = [&](int kt, auto F0) VLA_INLINE {                   // slab kt starts in register buffer F0
-    static_for<KS>([&](auto SS) VLA_INLINE { step(kt, std::integral_constant<int, (decltype(F0)::value + decltype(SS)::value) & 1>{}, SS); });
+  auto slab = [&](int kt, auto P) VLA_INLINE {
+    static_for<KS>([&](auto SS) VLA_INLINE { step(kt, P, SS); });
   };
   constexpr std::integral_constant<int, 0> c0{};
   constexpr std::integral_constant<int, 1> c1{};
-  constexpr std::integral_constant<int, KS & 1> cn{};  // buffer of an odd slab's first k-step
+  constexpr std::integral_constant<int, DEEP ? 1 : KS & 1> cn{};  // P of an odd slab
   static_for<S>([&](auto I) VLA_INLINE { static_for<LPS>([&](auto J) VLA_INLINE { issue_one(decltype(I)::value, J); }); });
   wait_vmcnt<(S - 1) * LPS>();
   __builtin_amdgcn_s_barrier();
-  static_for<R>([&](auto I) VLA_INLINE { read_one(0u, 0, c0, I); });
-  arrived(0);
+  static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE {
+    static_for<R>([&](auto I) VLA_INLINE { read_one(0u, decltype(SS)::value, SS, I); });
+  });
+  static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE { arrived(decltype(SS)::value); });
   const int KTh = LO8 ? KTw : KT;
   int kt = 0;
   if constexpr (LO8) {
     settle(acc);                                       // the zeros are written
-    for (; kt < KTh; ++kt) slab(kt, c0);
+    if constexpr (DEEP) {
+      for (; kt + 1 < KTh; kt += 2) {
+        slab(kt, c0);
+        slab(kt + 1, cn);
+      }
+      if (kt < KTh) slab(kt++, c0);
+    } else {
+      for (; kt < KTh; ++kt) slab(kt, c0);
+    }
     settle(acc);
     // Fragments of one slab, k-steps 0 and 1: variables of their own, read afresh, since the product wants the two in
     // adjacent registers and the loop above must not be bound by that.  Reads are issued in the order: first-half A
@@ -650,7 +676,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   }
 }
 
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, bool SPLITK, class Epi>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, bool LO8, bool SPLITK, class Epi>
 static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, int M, int K, int Kw, int tiles_m,
                          int tiles_n, const Epi& epi, hipStream_t st) {
   const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
@@ -658,7 +684,7 @@ static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, in
   constexpr bool pair = WN < Epi::kSpan;
   constexpr size_t stage = (size_t)WGM * WGN / (pair ? 2 : 1) * 32 * ((pair ? 2 : 1) * WN + 4) * sizeof(float);
   constexpr size_t smem = slabs > stage ? slabs : stage;
-  auto kern = gemm_f16_kernel<WGM, WGN, WM, WN, PK, S, OCC, Epi, LO8, SPLITK>;
+  auto kern = gemm_f16_kernel<WGM, WGN, WM, WN, PK, S, OCC, DEEP, Epi, LO8, SPLITK>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -666,9 +692,9 @@ static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, in
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, A, lda, Wp, W8, M, K, Kw, tiles_m, tiles_n, epi);
 }
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool LO8, class Epi>
+template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, bool LO8, class Epi>
 static void launch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  launch_tiles<WGM, WGN, WM, WN, PK, S, OCC, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
+  launch_tiles<WGM, WGN, WM, WN, PK, S, OCC, DEEP, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
                                                                (g.M + WGM * WM - 1) / (WGM * WM), g.N / (WGN * WN), epi, st);
 }
 
@@ -688,8 +714,8 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
   const int k = Afrag_lo ? 2 * K : K;
   // 256 columns a workgroup re-read the activations least, but a matrix of 4096 columns would occupy 64 compute units: 64
   // columns then.  256 rows, K = 4096 / 11008: 17 / 39 us (256 columns 46 / 83, two weight-streaming launches 45 / 72).
-  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 64, 2, 1, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
-  else launch_tiles<4, 2, 64, 32, 64, 4, 1, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
+  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 64, 2, 1, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
+  else launch_tiles<4, 2, 64, 32, 64, 4, 1, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -734,7 +760,8 @@ static TilePick pick_tile(int M, int N, int K) {
 
 // Rings are as deep as the LDS allows: cold weights take longer than two slabs to arrive (64x128 with 6 stages 28 and
 // 68 us for o and down at 290 rows, with 3 stages and two workgroups per compute unit 30 and 73), except where several
-// rounds of 64x128 tiles share the compute units.  256x256: 8 waves of 64x128, slabs of 64 k (half the barriers: gate/up
+// rounds of 64x128 tiles share the compute units, and except the eight-wave form of the first variant (four stages do; an
+// epilogue that needs 128 columns of a row together keeps the four waves and six stages the variant is named after).  256x256: 8 waves of 64x128, slabs of 64 k (half the barriers: gate/up
 // 363 against 371 us at 2338 rows, qkv 1399 against 1429 at 18560) once there are three rounds to hide the shorter
 // look-ahead, else and for the residual epilogue four stages of 32 (o 551 against 563 at 18560 rows, gate/up 81 against
 // 92 at 290).  With low terms always slabs of 64 k: one 128-deep product of the low-term pass.
@@ -755,17 +782,20 @@ template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr bool resid = std::is_same<Epi, EpiResid>::value;
   switch (gemm_f16_variant(g.M, g.N, g.K, LO8, resid)) {
-    case 0: launch<2, 2, 32, 64, 64, 6, 1, LO8>(g, epi, st); break;
-    case 1: launch<2, 2, 32, 64, 64, 3, 2, LO8>(g, epi, st); break;
-    case 2: launch<4, 2, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case 3: launch<2, 4, 32, 64, 64, 4, 1, LO8>(g, epi, st); break;
-    case 4: launch<2, 4, 64, 64, 64, 3, 1, LO8>(g, epi, st); break;
-    case 5: launch<2, 4, 96, 64, 64, 2, 1, LO8>(g, epi, st); break;
+    case 0:
+      if constexpr (Epi::kSpan <= 64) launch<2, 4, 32, 32, 64, 4, 1, true, LO8>(g, epi, st);
+      else launch<2, 2, 32, 64, 64, 6, 1, false, LO8>(g, epi, st);
+      break;
+    case 1: launch<2, 2, 32, 64, 64, 3, 2, false, LO8>(g, epi, st); break;
+    case 2: launch<4, 2, 32, 64, 64, 4, 1, false, LO8>(g, epi, st); break;
+    case 3: launch<2, 4, 32, 64, 64, 4, 1, false, LO8>(g, epi, st); break;
+    case 4: launch<2, 4, 64, 64, 64, 3, 1, false, LO8>(g, epi, st); break;
+    case 5: launch<2, 4, 96, 64, 64, 2, 1, false, LO8>(g, epi, st); break;
     case 6:
-      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 64, 2, 1, LO8>(g, epi, st);
+      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 64, 2, 1, false, LO8>(g, epi, st);
       break;
     default:
-      if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false>(g, epi, st);
+      if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false, false>(g, epi, st);
   }
 }
 template <class Epi>
