@@ -245,8 +245,13 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 // One kernel template for every size: a workgroup of WGM x WGN waves computes a BM x BN tile (a wave WM x WN of it).
 //
 // * Slabs of PK k of A and W go straight from global memory into LDS (global_load_lds_dwordx4: lane l of a wave
-//   instruction deposits its 16 bytes at the wave-uniform LDS base + 16*l), S slabs ahead of the MFMAs, through a
-//   ring of S stages; one barrier per slab publishes the landed slab and frees the one everybody has in registers.
+//   instruction deposits its 16 bytes at the wave-uniform LDS base + 16*l), S slabs of A and SW of W ahead of the MFMAs,
+//   through a ring of stages each; one barrier per slab publishes the landed slab and frees the one everybody has in
+//   registers.  A comes from the L2 and W, in a launch of few tiles, from HBM: where the 160 KiB do not hold another stage of
+//   both they hold a third one of W.  Against two stages of each: 192x256 at 290 rows 79 -> 62 us (qkv), 84 -> 68 (gate/up),
+//   191 -> 142 (down), at 18560 rows 1811 -> 1652, 2846 -> 2656, 1760 -> 1493; 256x256 at 290 rows 88 -> 75, 94 -> 82,
+//   212 -> 180, at 18560 1615 -> 1601, 2576 -> 2564, 1443 -> 1377, with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.
+// * SPREAD: the weights of a slab's second k-step are requested a k-step after the rest, so that the loads go out evenly.
 // * Fragments are double buffered in registers: while the MFMAs of one k-step run, the reads of the next
 //   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
 //   for ALL outstanding LDS loads before any LDS read, so the reads are inline assembly and the waits explicit.
@@ -360,15 +365,8 @@ __device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
 #endif
 }
 
-template <int PK>
-__device__ __forceinline__ int a_swizzle(int r) {
-  if constexpr (PK == 32) {
-    const int q = (r >> 2) & 3;
-    return ((q & 1) << 1) ^ ((q >> 1) * 3);            // 0, 2, 3, 1
-  } else {
-    return (r >> 1) & 7;
-  }
-}
+constexpr int PK = 64;                                 // k of a slab (a slab of low terms is one 128-deep product)
+__device__ __forceinline__ int a_swizzle(int r) { return (r >> 1) & 7; }
 
 template <class Epi> __device__ __forceinline__ const f16* epi_a_lo(const Epi&) { return nullptr; }
 __device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a_lo; }
@@ -378,20 +376,21 @@ __device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a
 // SPLITK (with EpiPartial; one row of tiles, M <= BM): A is in the fragment order of the decode path
 // ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), tiles_m is the
 // number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, class Epi, bool LO8, bool SPLITK>
+template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, class Epi, bool LO8, bool SPLITK>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16* __restrict__ A, int lda,
                                                                    const f16* __restrict__ Wp,
                                                                    const f16* __restrict__ W8, int M, int K, int Kw,
                                                                    int tiles_m, int tiles_n, Epi epi_in) {
-  static_assert(!LO8 || PK == 64, "a slab of low terms is one 128-deep product");
   constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / 16, NT = WN / 16;
   constexpr int KS = PK / 32, KS16 = PK / 16;          // k-steps of a slab; 16-k blocks of a slab
   constexpr int AP = BM * PK / 512 / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;   // KiB pieces per wave and slab
   static_assert(AP * NW * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
-  constexpr int A_HALVES = BM * PK, STAGE_HALVES = (BM + BN) * PK;
+  constexpr int A_HALVES = BM * PK, W_HALVES = BN * PK, W0_HALVES = S * A_HALVES;
+  static_assert(SW == S || SW == S + 1, "the counts of loads in flight below");
+  static_assert(!SPREAD || (WP % KS16 == 0 && SW == S + 1 && !DEEP && !LO8), "as counted below");
   constexpr int RPP = 512 / PK;                        // rows of A per piece
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  f16* lds = (f16*)smem;                               // [S][A slab | W slab]
+  f16* lds = (f16*)smem;                               // [S][A slab], [SW][W slab]
 
   // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a contiguous run of
   // tiles, walked in groups of GM row-tiles that share the same weight columns (4 and 8 measure alike for the small
@@ -425,7 +424,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   int KT = K / PK, KTw = Kw / PK;                      // slabs; of which the first KTw are high terms
   size_t kb0 = 0;                                      // first 16-k block of this workgroup's K range
   if constexpr (SPLITK) {
-    static_assert(PK == 64, "slices are cut in units of 64 k");
     const int u0 = (int)((long long)kz * KTw / tiles_m), u1 = (int)((long long)(kz + 1) * KTw / tiles_m);
     kb0 = (size_t)u0 * KS16;
     KTw = u1 - u0;
@@ -442,13 +440,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   // chunk's bits of swz(i * RPP) flipped, so two registers serve all pieces.
   const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)min(M - 1 - m0, BM - 1) * a_pitch;   // (fits 32 bits)
   const int r0 = wave * AP * RPP + lane / (PK / 8);
-  const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle<PK>(r0)) * 16u;
-  auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped)
+  const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle(r0)) * 16u;
+  auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped), A first
     constexpr int i = decltype(I)::value;
     const int ks = min(kt, KT - 1), kw = ks >= KTw ? ks - KTw : ks;
-    f16* base = lds + (kt % S) * STAGE_HALVES;
     if constexpr (i < AP) {
-      f16* dst = base + (wave * AP + i) * 512;
+      f16* dst = lds + (kt % S) * A_HALVES + (wave * AP + i) * 512;
       if constexpr (SPLITK) {
         const int j = wave * AP + i;                   // piece of the slab: block row j / KS16 (clamped to the rows
         const int rb = min(j / KS16, (M - 1) >> 5);    // that exist), 16-k block j % KS16
@@ -456,15 +453,21 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       } else {
         unsigned row = a_row;
         hold32(row);                                   // the offset is formed here, three instructions a load, and not kept
-        row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle<PK>(i * RPP) * 16));
+        row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle(i * RPP) * 16));
         load_to_lds_16(a_base, row, 2u * PK * (unsigned)ks, dst);
       }
     } else {
       const int j = wave * WP + i - AP;                // piece of the slab: block row j / KS16, 16-k block j % KS16
       const bool low = LO8 && ks >= KTw;
       const unsigned blk = (unsigned)(j / KS16 * KB16) * (low ? 512u : 1024u) + (unsigned)(j % KS16) * 1024u;
-      load_to_lds_16(low ? w8_base : w_base, lane16, blk + 1024u * KS16 * (unsigned)kw, base + A_HALVES + j * 512);
+      load_to_lds_16(low ? w8_base : w_base, lane16, blk + 1024u * KS16 * (unsigned)kw, lds + W0_HALVES + (kt % SW) * W_HALVES + j * 512);
     }
+  };
+
+  // x-th of a wave's weight pieces that hold the first (second) 32 k of the slab
+  constexpr auto half_piece = [](int x, bool second) { return AP + x / (KS16 / 2) * KS16 + x % (KS16 / 2) + (second ? KS16 / 2 : 0); };
+  auto issue_next = [&](int kt, auto I) VLA_INLINE {   // piece I of what takes the stages of slab kt
+    issue_one(decltype(I)::value < AP ? kt + S : kt + SW, I);
   };
 
   f32x4 acc[MT][NT];
@@ -483,24 +486,28 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   for (int s = 0; s < KS; ++s) {
     const int c = 4 * s + fgrp;                        // 16-byte chunk of the row
     if constexpr (SPLITK) a_k[s] = lds0 + (unsigned)(wm * (WM / 32) * KS16) * 1024u + in_block;
-    else a_k[s] = lds0 + 2u * (unsigned)(frow * PK + ((c ^ a_swizzle<PK>(frow)) << 3));
+    else a_k[s] = lds0 + 2u * (unsigned)(frow * PK + ((c ^ a_swizzle(frow)) << 3));
   }
-  const unsigned w_b = lds0 + 2u * (unsigned)(A_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
+  const unsigned w_b = lds0 + 2u * (unsigned)(W0_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
 
   constexpr int NBUF = DEEP ? 2 * KS : 2;              // register buffers, a k-step each
   f16x8 af[NBUF][MT], bf[NBUF][NT];
   constexpr int R = MT + NT, MF = MT * NT;             // reads and products of a k-step
-  // fragment reads of k-step ss of the stage at byte offset so (block j of an operand in fragment order: 32 rows hold two
+  struct Stages { unsigned a, b; };                    // byte offsets of a slab's stages
+  auto stages_of = [&](int kt) VLA_INLINE {
+    return Stages{(unsigned)(kt % S) * (2u * A_HALVES), (unsigned)(kt % SW) * (2u * W_HALVES)};
+  };
+  // fragment reads of k-step ss of the slab in stages so (block j of an operand in fragment order: 32 rows hold two
   // fragments)
-  auto read_a = [&](unsigned so, f16x8& dst, auto SS, auto J) VLA_INLINE {
+  auto read_a = [&](Stages so, f16x8& dst, auto SS, auto J) VLA_INLINE {
     constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
-    read_frag_asm<SPLITK ? (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256 : j * 16 * PK * 2>(dst, a_k[ss] + so);
+    read_frag_asm<SPLITK ? (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256 : j * 16 * PK * 2>(dst, a_k[ss] + so.a);
   };
-  auto read_b = [&](unsigned so, f16x8& dst, auto SS, auto J) VLA_INLINE {
+  auto read_b = [&](Stages so, f16x8& dst, auto SS, auto J) VLA_INLINE {
     constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
-    read_frag_asm<(j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256>(dst, w_b + so);
+    read_frag_asm<(j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256>(dst, w_b + so.b);
   };
-  auto read_one = [&](unsigned so, int f, auto SS, auto I) VLA_INLINE {   // I-th fragment read of a k-step
+  auto read_one = [&](Stages so, int f, auto SS, auto I) VLA_INLINE {   // I-th fragment read of a k-step
     constexpr int x = decltype(I)::value;
     if constexpr (x < MT) read_a(so, af[f][x], SS, I);
     else read_b(so, bf[f][x - MT], SS, std::integral_constant<int, x - MT>{});
@@ -523,10 +530,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     constexpr int f = DEEP ? p * KS + ss : (p + ss) & 1, g = DEEP ? (p ^ 1) * KS + ss : f ^ 1;
     constexpr int n_rd = MF * 3 / 4 > 0 ? MF * 3 / 4 : 1;
     if constexpr (DEEP ? ss == 0 : last) {
-      wait_vmcnt<(S - 2) * LPS>();
+      wait_vmcnt<(S - 2) * LPS + (SW - S) * WP>();
       __builtin_amdgcn_s_barrier();
     }
-    const unsigned so = (unsigned)((kt + (next ? 1 : 0)) % S) * (2u * STAGE_HALVES);
+    const Stages so = stages_of(kt + (next ? 1 : 0));
     static_for<MF>([&](auto I) VLA_INLINE {
       constexpr int i = decltype(I)::value, mt = i / NT, nt = i % NT;
       if constexpr (LO8) mfma_in_place(acc[mt][nt], af[f][mt], bf[f][nt]);
@@ -535,10 +542,17 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       static_for<r1 - r0>([&](auto J) VLA_INLINE {
         read_one(so, g, std::integral_constant<int, DEEP ? ss : (last ? 0 : ss + 1)>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
       });
-      if constexpr (next) {
+      if constexpr (SPREAD) {                          // last k-step: A and the first 32 k of W; the next one: the other 32 k
+        constexpr int n = last ? AP + WP / 2 : WP / 2, l0 = i * n / MF, l1 = (i + 1) * n / MF;
+        static_for<l1 - l0>([&](auto J) VLA_INLINE {
+          constexpr int x = l0 + decltype(J)::value;
+          if constexpr (last && x < AP) issue_next(kt, std::integral_constant<int, x>{});
+          else issue_next(last ? kt : kt - 1, std::integral_constant<int, half_piece(x - (last ? AP : 0), !last)>{});
+        });
+      } else if constexpr (next) {
         constexpr int at = DEEP ? ss * MF + i : i, of = DEEP ? KS * MF : MF;
         constexpr int l0 = at * LPS / of, l1 = (at + 1) * LPS / of;
-        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_one(kt + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
+        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_next(kt, std::integral_constant<int, l0 + decltype(J)::value>{}); });
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -550,12 +564,18 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   };
   constexpr std::integral_constant<int, 0> c0{};
   constexpr std::integral_constant<int, 1> c1{};
-  constexpr std::integral_constant<int, DEEP ? 1 : KS & 1> cn{};  // P of an odd slab
+  constexpr std::integral_constant<int, DEEP ? 1 : 0> cn{};       // P of an odd slab
   static_for<S>([&](auto I) VLA_INLINE { static_for<LPS>([&](auto J) VLA_INLINE { issue_one(decltype(I)::value, J); }); });
-  wait_vmcnt<(S - 1) * LPS>();
+  static_for<SW - S>([&](auto I) VLA_INLINE {
+    static_for<SPREAD ? WP / 2 : WP>([&](auto J) VLA_INLINE {
+      constexpr int j = decltype(J)::value;
+      issue_one(S + decltype(I)::value, std::integral_constant<int, SPREAD ? half_piece(j, false) : AP + j>{});
+    });
+  });
+  wait_vmcnt<(S - 1) * LPS + (SW - S) * (SPREAD ? WP / 2 : WP)>();
   __builtin_amdgcn_s_barrier();
   static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE {
-    static_for<R>([&](auto I) VLA_INLINE { read_one(0u, decltype(SS)::value, SS, I); });
+    static_for<R>([&](auto I) VLA_INLINE { read_one(stages_of(0), decltype(SS)::value, SS, I); });
   });
   static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE { arrived(decltype(SS)::value); });
   const int KTh = LO8 ? KTw : KT;
@@ -577,11 +597,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     // fragments, B fragments column by column, second-half A fragments.
     constexpr int H = MT / 2;
     f16x8 al[2][MT], bl[2][NT];
-    auto refill_a = [&](unsigned so, auto J) VLA_INLINE {
+    auto refill_a = [&](Stages so, auto J) VLA_INLINE {
       read_a(so, al[0][decltype(J)::value], c0, J);
       read_a(so, al[1][decltype(J)::value], c1, J);
     };
-    auto refill_b = [&](unsigned so, auto J) VLA_INLINE {
+    auto refill_b = [&](Stages so, auto J) VLA_INLINE {
       read_b(so, bl[0][decltype(J)::value], c0, J);
       read_b(so, bl[1][decltype(J)::value], c1, J);
     };
@@ -609,9 +629,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       wait_lds();
 #pragma unroll
       for (int i = H; i < MT; ++i) hold_a(i);
-      wait_vmcnt<(S - 2) * LPS>();                     // slab t + 1 has landed, slab t is in everybody's registers
+      wait_vmcnt<(S - 2) * LPS + (SW - S) * WP>();                     // slab t + 1 has landed, slab t is in everybody's registers
       __builtin_amdgcn_s_barrier();
-      const unsigned so = (unsigned)((t + 1) % S) * (2u * STAGE_HALVES);
+      const Stages so = stages_of(t + 1);
       static_for<NT>([&](auto NI) VLA_INLINE {         // rows of the second half
         constexpr int nt = decltype(NI)::value;
         static_for<MT - H>([&](auto MI) VLA_INLINE {
@@ -622,13 +642,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
           }
         });
         constexpr int l0 = nt * LPS / NT, l1 = (nt + 1) * LPS / NT;
-        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_one(t + S, std::integral_constant<int, l0 + decltype(J)::value>{}); });
+        static_for<l1 - l0>([&](auto J) VLA_INLINE { issue_next(t, std::integral_constant<int, l0 + decltype(J)::value>{}); });
         __builtin_amdgcn_sched_barrier(0);
       });
       refill_b(so, std::integral_constant<int, NT - 1>{});
       static_for<MT - H>([&](auto J) VLA_INLINE { refill_a(so, std::integral_constant<int, H + decltype(J)::value>{}); });
     };
-    const unsigned so0 = (unsigned)(kt % S) * (2u * STAGE_HALVES);
+    const Stages so0 = stages_of(kt);
     static_for<H>([&](auto J) VLA_INLINE { refill_a(so0, J); });
     static_for<NT>([&](auto J) VLA_INLINE { refill_b(so0, J); });
     static_for<MT - H>([&](auto J) VLA_INLINE { refill_a(so0, std::integral_constant<int, H + decltype(J)::value>{}); });
@@ -676,15 +696,15 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   }
 }
 
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, bool LO8, bool SPLITK, class Epi>
+template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, bool LO8, bool SPLITK, class Epi>
 static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, int M, int K, int Kw, int tiles_m,
                          int tiles_n, const Epi& epi, hipStream_t st) {
   const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
-  constexpr size_t slabs = (size_t)S * (WGM * WM + WGN * WN) * PK * sizeof(f16);
+  constexpr size_t slabs = ((size_t)S * WGM * WM + (size_t)SW * WGN * WN) * PK * sizeof(f16);
   constexpr bool pair = WN < Epi::kSpan;
   constexpr size_t stage = (size_t)WGM * WGN / (pair ? 2 : 1) * 32 * ((pair ? 2 : 1) * WN + 4) * sizeof(float);
   constexpr size_t smem = slabs > stage ? slabs : stage;
-  auto kern = gemm_f16_kernel<WGM, WGN, WM, WN, PK, S, OCC, DEEP, Epi, LO8, SPLITK>;
+  auto kern = gemm_f16_kernel<WGM, WGN, WM, WN, S, SW, OCC, DEEP, SPREAD, Epi, LO8, SPLITK>;
   static bool attr_set = false;
   if (!attr_set) {
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -692,9 +712,9 @@ static void launch_tiles(const f16* A, int lda, const f16* Wp, const f16* W8, in
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, st, A, lda, Wp, W8, M, K, Kw, tiles_m, tiles_n, epi);
 }
-template <int WGM, int WGN, int WM, int WN, int PK, int S, int OCC, bool DEEP, bool LO8, class Epi>
+template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, bool LO8, class Epi>
 static void launch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  launch_tiles<WGM, WGN, WM, WN, PK, S, OCC, DEEP, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
+  launch_tiles<WGM, WGN, WM, WN, S, SW, OCC, DEEP, SPREAD, LO8, false>(g.A, g.lda, g.Wp, g.W8, g.M, g.K, g.Kw,
                                                                (g.M + WGM * WM - 1) / (WGM * WM), g.N / (WGN * WN), epi, st);
 }
 
@@ -714,8 +734,8 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
   const int k = Afrag_lo ? 2 * K : K;
   // 256 columns a workgroup re-read the activations least, but a matrix of 4096 columns would occupy 64 compute units: 64
   // columns then.  256 rows, K = 4096 / 11008: 17 / 39 us (256 columns 46 / 83, two weight-streaming launches 45 / 72).
-  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 64, 2, 1, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
-  else launch_tiles<4, 2, 64, 32, 64, 4, 1, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
+  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 2, 3, 1, false, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
+  else launch_tiles<4, 2, 64, 32, 4, 4, 1, false, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -723,21 +743,21 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // what a workgroup takes on a chip that is not full (bound by the latency and rate of its LDS fills: fixed + per_k *
 // K / 1024), and the rate of a chip full of them (bound by power and the L2).  Full rounds of 256 workgroups cost the
 // larger of the two, the last partial round likewise for its share.  us at K = 4096 / 11008, and PFLOP/s:
-//   64x128 27.6 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 192x256
-//   63 / 155, 1.18; 256x256 76 / 185, 1.30.
+//   64x128 27.9 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 192x256
+//   59 / 143, 1.25; 256x256 73 / 180, 1.30.
 // The pick against the fastest of the six, each forced in turn (the four matrices of the 7B model at 64 to 18560 rows and
-// of the 12-layer one at 145 to 9216, single- and two-term, 160 products): 0.7 % slower in the median, 1.7 % in the mean,
-// up to 5 % in nine of ten.  us single-term, pick and others: 290 rows qkv 49 (64x256; 256x256 76), o 28 (64x128; 72),
-// down 68 (64x128; 178); 580 rows gate/up 111 (128x256; 256x256 161), down 85 (128x128; 185); 2338 rows gate/up 361
-// (256x256; 128x256 374), o 90 (192x256; 256x256 95); 9216 rows of d 768 gate/up 62 (192x256; 128x256 72).
-// Where it is off: gate/up at 290 rows 87 (192x256; 256x256 79), down at 2338 231 (256x256; 192x256 217) and at 4640 435
-// (192x256; 128x256 405), qkv and gate/up at 1740 by 5 to 7 %, two-term qkv at 870 149 (256x256; 192x256 128).  The model
-// has 192x256 too fast in a partial round (o at 2338 rows: 71 predicted).
+// of the 12-layer one at 64 to 18432, single- and two-term, 164 products): the same in 150 of them, 0.1 % slower in the
+// mean.  us single-term, pick and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
+// (64x128; 73), down 68 (64x128; 180); 580 rows gate/up 112 (128x256; 256x256 163), down 84 (128x128; 191); 870 rows qkv 78
+// (192x256; 256x256 90); 2338 rows gate/up 375 (256x256; 128x256 390), o 79 (192x256; 256x256 89), down 187 (192x256;
+// 256x256 212); 9216 rows of d 768 gate/up 62 (192x256; 128x256 69).
+// Where it is off: gate/up at 400 rows 92 (256x256 32-k; 64-k 89), o at 9280 301 (256x256; 128x256 292), qkv of d 768 at 64
+// rows 8.6 (64x128; 128x128 8.1).
 enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_192x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
 constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.9f, 5.9f, 0.68f}, {128, 128, 4.3f, 7.4f, 0.92f},
-                                         {64, 256, 6.8f, 9.3f, 0.80f}, {128, 256, 4.2f, 11.4f, 1.15f}, {192, 256, 8.0f, 13.7f, 1.18f},
-                                         {256, 256, 11.5f, 16.1f, 1.30f}};
+                                         {64, 256, 6.8f, 9.3f, 0.80f}, {128, 256, 4.2f, 11.4f, 1.15f}, {192, 256, 8.0f, 13.7f, 1.25f},
+                                         {256, 256, 10.9f, 16.1f, 1.30f}};
 struct TilePick { Tile tile; long long tiles; };
 static TilePick pick_tile(int M, int N, int K) {
   TilePick best{T_64x128, 0};
@@ -761,10 +781,12 @@ static TilePick pick_tile(int M, int N, int K) {
 // Rings are as deep as the LDS allows: cold weights take longer than two slabs to arrive (64x128 with 6 stages 28 and
 // 68 us for o and down at 290 rows, with 3 stages and two workgroups per compute unit 30 and 73), except where several
 // rounds of 64x128 tiles share the compute units, and except the eight-wave form of the first variant (four stages do; an
-// epilogue that needs 128 columns of a row together keeps the four waves and six stages the variant is named after).  256x256: 8 waves of 64x128, slabs of 64 k (half the barriers: gate/up
-// 363 against 371 us at 2338 rows, qkv 1399 against 1429 at 18560) once there are three rounds to hide the shorter
-// look-ahead, else and for the residual epilogue four stages of 32 (o 551 against 563 at 18560 rows, gate/up 81 against
-// 92 at 290).  With low terms always slabs of 64 k: one 128-deep product of the low-term pass.
+// epilogue that needs 128 columns of a row together keeps the four waves and six stages the variant is named after).
+// 256x256: 8 waves of 64x128; the residual epilogue and fewer than three rounds of tiles request the weights in halves of
+// 32 k (SPREAD: down 253 against 259 us at 3480 rows, 212 against 215 at 2338, 523 against 526 at 6960; o 89.0 against 89.7 at
+// 2338, 560 against 558 at 18560); the larger launches are the same either way (+-1 %).  Slabs of 32 k throughout, in four
+// stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at 2338 rows, 536 and 525 at 6960,
+// 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.
 const char* const kGemmF16Variants[kGemmF16VariantCount] = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256",
                                                             "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"};
 int gemm_f16_variant(int M, int N, int K, bool lo8, bool resid) {
@@ -783,19 +805,19 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr bool resid = std::is_same<Epi, EpiResid>::value;
   switch (gemm_f16_variant(g.M, g.N, g.K, LO8, resid)) {
     case 0:
-      if constexpr (Epi::kSpan <= 64) launch<2, 4, 32, 32, 64, 4, 1, true, LO8>(g, epi, st);
-      else launch<2, 2, 32, 64, 64, 6, 1, false, LO8>(g, epi, st);
+      if constexpr (Epi::kSpan <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
+      else launch<2, 2, 32, 64, 6, 6, 1, false, false, LO8>(g, epi, st);
       break;
-    case 1: launch<2, 2, 32, 64, 64, 3, 2, false, LO8>(g, epi, st); break;
-    case 2: launch<4, 2, 32, 64, 64, 4, 1, false, LO8>(g, epi, st); break;
-    case 3: launch<2, 4, 32, 64, 64, 4, 1, false, LO8>(g, epi, st); break;
-    case 4: launch<2, 4, 64, 64, 64, 3, 1, false, LO8>(g, epi, st); break;
-    case 5: launch<2, 4, 96, 64, 64, 2, 1, false, LO8>(g, epi, st); break;
+    case 1: launch<2, 2, 32, 64, 3, 3, 2, false, false, LO8>(g, epi, st); break;
+    case 2: launch<4, 2, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
+    case 3: launch<2, 4, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
+    case 4: launch<2, 4, 64, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
+    case 5: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
     case 6:
-      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 64, 2, 1, false, LO8>(g, epi, st);
+      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
       break;
     default:
-      if constexpr (!LO8) launch<4, 2, 64, 128, 32, 4, 1, false, false>(g, epi, st);
+      if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, false>(g, epi, st);
   }
 }
 template <class Epi>
