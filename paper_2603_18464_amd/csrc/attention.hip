@@ -417,8 +417,12 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
 // The query and the new key / value row of this (sequence, head) are not read from memory but formed here from
 // the split-K partial sums of the QKV GEMM (summed in plane order, RoPE applied; the query stays in float32, the
 // key / value row is rounded as the cache holds it); the new row is appended to the cache for the following steps
-// and used from LDS in this one.  The first two groups of cache rows are requested before that work, which needs none of
-// them, and every group's successor as soon as its registers are free.
+// and used from LDS in this one: a group that reaches past the cached rows takes it into its registers first.
+// One wave each forms the query, the key and the value, its partial sums and rotary factors requested before any
+// cache row (answers come back in the order of the requests, and the partial sums need no context length), the first two
+// groups of rows behind them and every group's successor as soon as its registers are free.  us a launch at one row and 290
+// positions: 12 heads of 64 5.95 -> 5.27 (low terms 6.7 -> 6.2), 32 heads of 128 8.2 -> 7.3 (10.0 -> 9.4), against one
+// wave that formed all three behind the requests of the cache rows and a branch a row for the new one.
 struct QkvPartials {
   const float* part;       // [ksplit][rows][3 * d_model]
   int ksplit, rows;
@@ -442,9 +446,11 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
   constexpr int G = TWO ? 3 : 4;         // instructions of a group (what the registers hold twice)
   __shared__ float s_m[NW], s_l[NW];
   __shared__ float s_o[NW][HD];
-  __shared__ __attribute__((aligned(16))) float s_q[HD], s_k[HD], s_v[HD];   // the new row, unrounded
+  __shared__ __attribute__((aligned(16))) float s_q[HD];               // the query, unrounded
+  __shared__ __attribute__((aligned(16))) f16 s_new[2][HD];            // the new key and value row, as the cache holds them
+  __shared__ __attribute__((aligned(8))) unsigned char s_new_lo[2][TWO ? HD : 8];
   const int b = blockIdx.x, head = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane / LPR, c = lane % LPR;          // row inside the instruction, 8-dim chunk
   const int ctx = tok_pos[b] + 1;                      // >= 2 in a decode step: the prefix holds a position
   const int slot = tok_seq[b];
@@ -462,7 +468,6 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
   auto row_of = [&](int it) { return (it * NW + wave) * RPI + sub; };
   auto request = [&](auto S, int it0) {
     constexpr int s = decltype(S)::value;
-    if (it0 >= n_it) return;                            // uniform
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const size_t off = (size_t)min(row_of(it0 + u), last_global) * HD + c * 8;
@@ -476,48 +481,62 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
   };
   constexpr std::integral_constant<int, 0> s0{};
   constexpr std::integral_constant<int, 1> s1{};
+  // waves 0, 1, 2: the new query, key, value; a lane has the rotary pair i, i + HD / 2 (HD 64: lanes 32.. repeat the others)
+  constexpr int HALF = HD / 2;
+  const int i = lane % HALF, pos = ctx - 1;
+  float p[kMaxKSplit][2];
+  float cs = 0.f, sn = 0.f;
+  if (wave < 3) {
+    const int c0 = wave * d_model + head * HD + i;
+#pragma unroll
+    for (int ks = 0; ks < kMaxKSplit; ++ks) {           // all planes in flight; planes past the last repeat it, unused
+      const float* pp = qp.part + ((size_t)min(ks, qp.ksplit - 1) * qp.rows + b) * 3 * (size_t)d_model;
+      p[ks][0] = pp[c0];
+      p[ks][1] = pp[c0 + HALF];
+    }
+    cs = qp.rope_cos[pos * HALF + i];
+    sn = qp.rope_sin[pos * HALF + i];
+  }
   request(s0, 0);
   request(s1, G);
-  {
-    constexpr int HALF = HD / 2;
-    if (threadIdx.x < HALF) {
-      const int i = threadIdx.x, c0 = head * HD + i, c1 = c0 + HALF, d = d_model, pos = ctx - 1;
-      const size_t N = 3 * (size_t)d;
-      const float cs = qp.rope_cos[pos * HALF + i], sn = qp.rope_sin[pos * HALF + i];
-      float p[kMaxKSplit][6];
+  if (wave < 3) {
+    float v0 = 0.f, v1 = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < kMaxKSplit; ++ks) {         // all planes in flight; planes past the last repeat it, unused
-        const float* pp = qp.part + ((size_t)min(ks, qp.ksplit - 1) * qp.rows + b) * N;
-        p[ks][0] = pp[c0]; p[ks][1] = pp[c1]; p[ks][2] = pp[d + c0]; p[ks][3] = pp[d + c1];
-        p[ks][4] = pp[2 * d + c0]; p[ks][5] = pp[2 * d + c1];
-      }
-      float v[6] = {};
-#pragma unroll
-      for (int ks = 0; ks < kMaxKSplit; ++ks)
-#pragma unroll
-        for (int j = 0; j < 6; ++j) v[j] = ks < qp.ksplit ? v[j] + p[ks][j] : v[j];
-      float q0, q1, k0f, k1f;
-      rope_pair(v[0], v[1], cs, sn, q0, q1);
-      rope_pair(v[2], v[3], cs, sn, k0f, k1f);
-      const f16 k0 = from_f32<f16>(k0f), k1 = from_f32<f16>(k1f);
-      const f16 v0 = from_f32<f16>(v[4]), v1 = from_f32<f16>(v[5]);
-      kb[(size_t)pos * HD + i] = k0; kb[(size_t)pos * HD + i + HALF] = k1;
-      vb[(size_t)pos * HD + i] = v0; vb[(size_t)pos * HD + i + HALF] = v1;
-      if constexpr (TWO) {
-        const int ke = pack_lo8(k0f - (float)k0, k1f - (float)k1, v[4] - (float)v0, v[5] - (float)v1);
-        kbl[(size_t)pos * HD + i] = (unsigned char)(ke & 0xff); kbl[(size_t)pos * HD + i + HALF] = (unsigned char)((ke >> 8) & 0xff);
-        vbl[(size_t)pos * HD + i] = (unsigned char)((ke >> 16) & 0xff); vbl[(size_t)pos * HD + i + HALF] = (unsigned char)((ke >> 24) & 0xff);
-        // this step uses exactly what later steps will read back: hi + lo
-        s_q[i] = q0; s_q[i + HALF] = q1;
-        s_k[i] = (float)k0 + unpack_lo8(ke, 0); s_k[i + HALF] = (float)k1 + unpack_lo8(ke, 1);
-        s_v[i] = (float)v0 + unpack_lo8(ke, 2); s_v[i + HALF] = (float)v1 + unpack_lo8(ke, 3);
+    for (int ks = 0; ks < kMaxKSplit; ++ks) {
+      v0 = ks < qp.ksplit ? v0 + p[ks][0] : v0;
+      v1 = ks < qp.ksplit ? v1 + p[ks][1] : v1;
+    }
+    if (wave < 2) {
+      float r0, r1;
+      rope_pair(v0, v1, cs, sn, r0, r1);
+      v0 = r0;
+      v1 = r1;
+    }
+    if (lane < HALF) {
+      if (wave == 0) {                                  // the query never leaves float32
+        s_q[i] = v0;
+        s_q[i + HALF] = v1;
       } else {
-        s_q[i] = q0; s_q[i + HALF] = q1;      // the query never leaves float32
-        s_k[i] = (float)k0; s_k[i + HALF] = (float)k1; s_v[i] = (float)v0; s_v[i + HALF] = (float)v1;
+        const size_t at = (size_t)pos * HD + i;
+        const f16 h0 = from_f32<f16>(v0), h1 = from_f32<f16>(v1);
+        f16* rows = wave == 1 ? kb : vb;
+        rows[at] = h0;
+        rows[at + HALF] = h1;
+        s_new[wave - 1][i] = h0;
+        s_new[wave - 1][i + HALF] = h1;
+        if constexpr (TWO) {
+          const int e = pack_lo8(v0 - (float)h0, v1 - (float)h1, 0.f, 0.f);
+          const unsigned char e0 = (unsigned char)(e & 0xff), e1 = (unsigned char)((e >> 8) & 0xff);
+          unsigned char* rows_lo = wave == 1 ? kbl : vbl;
+          rows_lo[at] = e0;
+          rows_lo[at + HALF] = e1;
+          s_new_lo[wave - 1][i] = e0;
+          s_new_lo[wave - 1][i + HALF] = e1;
+        }
       }
     }
-    __syncthreads();
   }
+  __syncthreads();
   float qf[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) qf[j] = s_q[c * 8 + j];
@@ -532,20 +551,32 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     constexpr int s = decltype(S)::value;
     float sc[G];
     float m_new = m_run;
+    if (((it0 + G - 1) * NW + wave + 1) * RPI > ctx - 1) {         // (uniform) rows the cache did not hold: the new one and,
+      const f16x8 kn = *(const f16x8*)&s_new[0][c * 8], vn = *(const f16x8*)&s_new[1][c * 8];   // masked below, those past it
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const bool in = row_of(it0 + u) > last_global;
+        kv[s][u] = in ? kn : kv[s][u];
+        vv[s][u] = in ? vn : vv[s][u];
+      }
+      if constexpr (TWO) {
+        const i32x2 kln = *(const i32x2*)&s_new_lo[0][c * 8], vln = *(const i32x2*)&s_new_lo[1][c * 8];
+#pragma unroll
+        for (int u = 0; u < G; ++u) {
+          const bool in = row_of(it0 + u) > last_global;
+          kl[s][u] = in ? kln : kl[s][u];
+          vl[s][u] = in ? vln : vl[s][u];
+        }
+      }
+    }
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const int row = row_of(it0 + u);
       float t = 0.f;
-      if (row > last_global) {                               // the new row, from LDS
 #pragma unroll
-        for (int j = 0; j < 8; ++j) t = fmaf(qf[j], s_k[c * 8 + j], t);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float kf = (float)kv[s][u][j];
-          if constexpr (TWO) kf += unpack_lo8(kl[s][u][j >> 2], j & 3);
-          t = fmaf(qf[j], kf, t);
-        }
+      for (int j = 0; j < 8; ++j) {
+        float kf = (float)kv[s][u][j];
+        if constexpr (TWO) kf += unpack_lo8(kl[s][u][j >> 2], j & 3);
+        t = fmaf(qf[j], kf, t);
       }
       sc[u] = t;
     }
@@ -566,25 +597,20 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     for (int u = 0; u < G; ++u) {
       const float p = __expf(sc[u] - m_use);
       lsum += p;
-      if (row_of(it0 + u) > last_global) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = fmaf(p, s_v[c * 8 + j], acc[j]);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float vf = (float)vv[s][u][j];
-          if constexpr (TWO) vf += unpack_lo8(vl[s][u][j >> 2], j & 3);
-          acc[j] = fmaf(p, vf, acc[j]);
-        }
+      for (int j = 0; j < 8; ++j) {
+        float vf = (float)vv[s][u][j];
+        if constexpr (TWO) vf += unpack_lo8(vl[s][u][j >> 2], j & 3);
+        acc[j] = fmaf(p, vf, acc[j]);
       }
     }
   };
   for (int it0 = 0; it0 < n_it; it0 += 2 * G) {
     consume(s0, it0);
-    request(s0, it0 + 2 * G);
-    if (it0 + G < n_it) {                                          // uniform
+    if (it0 + 2 * G < n_it) request(s0, it0 + 2 * G);              // uniform
+    if (it0 + G < n_it) {
       consume(s1, it0 + G);
-      request(s1, it0 + 3 * G);
+      if (it0 + 3 * G < n_it) request(s1, it0 + 3 * G);
     }
   }
   // bring the lanes of the wave to a common maximum, then add the row groups
@@ -605,7 +631,7 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
   }
   __syncthreads();
   if (threadIdx.x < HD) {
-    const int i = threadIdx.x;
+    const int col = threadIdx.x;
     float m = s_m[0];
 #pragma unroll
     for (int w = 1; w < NW; ++w) m = fmaxf(m, s_m[w]);
@@ -614,9 +640,9 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     for (int w = 0; w < NW; ++w) {
       const float f = s_m[w] == -INFINITY ? 0.f : __expf(s_m[w] - m);
       l += s_l[w] * f;
-      o += s_o[w][i] * f;
+      o += s_o[w][col] * f;
     }
-    const int k = head * HD + i;
+    const int k = head * HD + col;
     const size_t at = ((size_t)(b >> 5) * (d_model >> 4) + (k >> 4)) * 512 + ((b & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
     const float r = o / l;
     const f16 r16 = from_f32<f16>(r);
