@@ -787,6 +787,8 @@ static TilePick pick_tile(int M, int N, int K) {
 // 2338, 560 against 558 at 18560); the larger launches are the same either way (+-1 %).  Slabs of 32 k throughout, in four
 // stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at 2338 rows, 536 and 525 at 6960,
 // 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.
+// The single-term QKV product of heads of 128 keeps two stages of each operand in its large launches: 1404 us, against 1435
+// with a third one of the weights and 1423 with SPREAD (18560 rows, 7B, among the other kernels of a policy step).
 const char* const kGemmF16Variants[kGemmF16VariantCount] = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256",
                                                             "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"};
 int gemm_f16_variant(int M, int N, int K, bool lo8, bool resid) {
@@ -814,7 +816,8 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
     case 4: launch<2, 4, 64, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
     case 5: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
     case 6:
-      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
+      if constexpr (!LO8 && Epi::kSpan == 128) launch<4, 2, 64, 128, 2, 2, 1, false, false, LO8>(g, epi, st);
+      else if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
       break;
     default:
       if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, false>(g, epi, st);
