@@ -433,12 +433,22 @@ inline f16* frag_rows(f16* base, int row0, int K) { return base + (size_t)(row0 
 // (nullptr when no layer is a two-term layer; single-term layers of a two-term configuration pass nullptr on)
 inline f16* frag_lo(const vla_config& c, f16* base, int K) { return two_term(c) ? base + max_rows(c) * (size_t)K : nullptr; }
 
-// Whether the decode products that read normalised rows normalise them themselves: up to 16 rows, and up to kNormRows of a
-// narrow model.  (Every workgroup reads the rows in float32, which from 17 rows on costs a wide model more than the two
-// launches it saves.)  us of a layer's four products, with the norm apart / inside: d 4096 1 row 91.7 / 85.7, 16 93.2 / 90.7,
-// 17 94.6 / 95.3, 32 97.3 / 106; d 2048 1 38.0 / 35.2, 16 39.3 / 37.9, 24 40.4 / 40.5, 32 41.6 / 43.8; d 768 1 20.2 / 17.0,
-// 16 21.1 / 18.8, 32 22.0 / 20.3.
-inline bool norm_in_gemm(const vla_config& c, int B) { return B <= 16 || (B <= kNormRows && c.d_model <= 1024); }
+// Whether the products of decode layer l that read normalised rows normalise them themselves, and with them the down product
+// of the layer before adds to the residual rows (l = n_layers: that product alone).  Up to 16 rows, and up to kNormRows of a
+// narrow model: every workgroup reads the rows in float32, which from 17 rows on costs a wide model more than the two launches
+// it saves.  And as long as the down product is not bound by its activations: a workgroup reads all of them for 16 columns
+// (skinny_gemm_kernel: for 64), rows x d_ffn x terms elements; twice as many where d / 16 workgroups fill the 256 compute
+// units in whole rounds.  us of a layer, the norm apart / inside less the norm apart (two-term layers behind the semicolon):
+//   d 768 f 2048, 1 row -2.4; -2.4, 16 -3.3; -2.6, 32 -2.1; -1.0.  d 1024 f 5504, 8 rows -3.3; -1.9, 16 -2.9; -1.4, 17 -1.7;
+//   +0.5, 32 -0.5; +2.0.  d 1024 f 11008, 8 rows -2.3; -1.0, 16 -0.1; +1.9, 17 +2.9; +6.5, 32 +5.8; +10.5.  d 2048 f 11008, 8
+//   rows -2.5; -1.1, 16 -0.1; +1.1, 17 +2.7; +5.4.  d 2048 f 16384, 8 rows -1.5; +1.8, 16 +0.7; +4.9.  d 4096 f 11008, 8 rows
+//   -5.8; -4.6, 12 -5.1; -2.6, 16 -1.9; +0.2, 17 +1.7; +3.2.  d 4096 f 22016, 8 rows -6.4; -4.1, 12 -5.3; +0.8, 16 -2.3; +3.9.
+//   d 5120 f 13824, 8 rows -0.7; +1.7, 12 +2.5; +7.3.  d 8192 f 22016, 8 rows -11.8; -8.5, 12 -9.4; 0.0, 16 -0.5; +8.9.
+inline bool norm_in_gemm(const vla_config& c, int B, int l) {
+  if (B > (c.d_model <= 1024 ? kNormRows : 16)) return false;
+  const int terms = two_term_layer(c, l - 1) ? 2 : 1, budget = c.d_model % 4096 == 0 ? 49152 : 24576;
+  return l == 0 || (long long)c.d_ffn * terms * ((B + 7) / 8) <= budget;
+}
 
 // Decode step of the 16-bit path: split-K GEMMs whose partial planes span the whole batch, and one kernel after each
 // GEMM that sums the planes and applies the elementwise step for all rows.  Batches of up to kSkinnyMaxRows rows
@@ -480,12 +490,12 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     }
   };
   f16* const none = nullptr;
-  const bool norm = norm_in_gemm(c, B);
   float *y = at<float>(ctx->work, w.norm_y), *sums = at<float>(ctx->work, w.norm_sums);
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);      // low-term planes only in two-term layers
     const bool two = two_term_layer(c, l), two_next = two_term_layer(c, l + 1);
+    const bool norm = norm_in_gemm(c, B, l), norm_next = norm_in_gemm(c, B, l + 1);
     {
       ProfScope ps(ctx, FAM_GEMM_QKV_DECODE, st);
       if (norm)
@@ -533,7 +543,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
     {
       ProfScope ps(ctx, FAM_GEMM_DOWN_DECODE, st);
       const float* next_gain = l + 1 < c.n_layers ? at<float>(ctx->arena, ctx->al.layers[l + 1].g_attn) : nullptr;
-      if (norm) {
+      if (norm_next) {
         skinny_resid(act, two ? act_lo : none, at<f16>(ctx->arena, lw.w_down), x, next_gain, y, sums, B, d, f, ks_dn, st);
       } else {
         gemm(act, two ? act_lo : none, lw.w_down, d, f, ks_dn);
@@ -791,7 +801,7 @@ int do_decode(vla_ctx* ctx, int32_t B, const int32_t* token_ids, float* logits, 
     decode_begin<T>(token_ids, at<T>(ctx->arena, ctx->al.embed), c.vocab, at<int32_t>(ctx->work, w.seq_len), slot_map,
                     at<int32_t>(ctx->work, w.tok_seq), at<int32_t>(ctx->work, w.tok_pos), at<float>(ctx->work, w.x), B,
                     c.d_model, half ? at<float>(ctx->arena, ctx->al.layers[0].g_attn) : nullptr, c.rms_eps,
-                    norm_in_gemm(c, B) ? at<float>(ctx->work, w.norm_y) : nullptr, at<float>(ctx->work, w.norm_sums), hn,
+                    norm_in_gemm(c, B, 0) ? at<float>(ctx->work, w.norm_y) : nullptr, at<float>(ctx->work, w.norm_sums), hn,
                     half && two_term_layer(c, 0) ? frag_lo(c, hn, c.d_model) : nullptr, st);
   }
   if (sizeof(T) == 2) run_layers_decode_f16(ctx, B, st);
