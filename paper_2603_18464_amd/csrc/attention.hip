@@ -419,10 +419,11 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
 // key / value row is rounded as the cache holds it); the new row is appended to the cache for the following steps
 // and used from LDS in this one: a group that reaches past the cached rows takes it into its registers first.
 // One wave each forms the query, the key and the value, its partial sums and rotary factors requested before any
-// cache row (answers come back in the order of the requests, and the partial sums need no context length), the first two
-// groups of rows behind them and every group's successor as soon as its registers are free.  us a launch at one row and 290
-// positions: 12 heads of 64 5.95 -> 5.27 (low terms 6.7 -> 6.2), 32 heads of 128 8.2 -> 7.3 (10.0 -> 9.4), against one
-// wave that formed all three behind the requests of the cache rows and a branch a row for the new one.
+// cache row (answers come back in the order of the requests, and the partial sums need no context length), behind them the
+// first group of rows and, of a context that has one, the second, and every group's successor as soon as its registers are
+// free.  us a launch at one row and 290 positions: 12 heads of 64 5.95 -> 5.27 (low terms 6.7 -> 6.2), 32 heads of 128 8.2 ->
+// 7.3 (10.0 -> 9.4), against one wave that formed all three behind the requests of the cache rows and a branch a row for the
+// new one.
 struct QkvPartials {
   const float* part;       // [ksplit][rows][3 * d_model]
   int ksplit, rows;
@@ -497,49 +498,61 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     cs = qp.rope_cos[pos * HALF + i];
     sn = qp.rope_sin[pos * HALF + i];
   }
-  request(s0, 0);
-  request(s1, G);
-  if (wave < 3) {
-    float v0 = 0.f, v1 = 0.f;
+  float qf[8];
+  auto new_row = [&]() __attribute__((always_inline)) {   // forms and stores the new row, and leaves this lane's part of the query
+    if (wave < 3) {
+      float v0 = p[0][0], v1 = p[0][1];
 #pragma unroll
-    for (int ks = 0; ks < kMaxKSplit; ++ks) {
-      v0 = ks < qp.ksplit ? v0 + p[ks][0] : v0;
-      v1 = ks < qp.ksplit ? v1 + p[ks][1] : v1;
-    }
-    if (wave < 2) {
-      float r0, r1;
-      rope_pair(v0, v1, cs, sn, r0, r1);
-      v0 = r0;
-      v1 = r1;
-    }
-    if (lane < HALF) {
-      if (wave == 0) {                                  // the query never leaves float32
-        s_q[i] = v0;
-        s_q[i + HALF] = v1;
-      } else {
-        const size_t at = (size_t)pos * HD + i;
-        const f16 h0 = from_f32<f16>(v0), h1 = from_f32<f16>(v1);
-        f16* rows = wave == 1 ? kb : vb;
-        rows[at] = h0;
-        rows[at + HALF] = h1;
-        s_new[wave - 1][i] = h0;
-        s_new[wave - 1][i + HALF] = h1;
-        if constexpr (TWO) {
-          const int e = pack_lo8(v0 - (float)h0, v1 - (float)h1, 0.f, 0.f);
-          const unsigned char e0 = (unsigned char)(e & 0xff), e1 = (unsigned char)((e >> 8) & 0xff);
-          unsigned char* rows_lo = wave == 1 ? kbl : vbl;
-          rows_lo[at] = e0;
-          rows_lo[at + HALF] = e1;
-          s_new_lo[wave - 1][i] = e0;
-          s_new_lo[wave - 1][i + HALF] = e1;
+      for (int ks = 1; ks < kMaxKSplit; ++ks) {
+        v0 = ks < qp.ksplit ? v0 + p[ks][0] : v0;
+        v1 = ks < qp.ksplit ? v1 + p[ks][1] : v1;
+      }
+      if (wave < 2) {
+        float r0, r1;
+        rope_pair(v0, v1, cs, sn, r0, r1);
+        v0 = r0;
+        v1 = r1;
+      }
+      if (lane < HALF) {
+        if (wave == 0) {                                // the query never leaves float32
+          s_q[i] = v0;
+          s_q[i + HALF] = v1;
+        } else {
+          const size_t at = (size_t)pos * HD + i;
+          const f16 h0 = from_f32<f16>(v0), h1 = from_f32<f16>(v1);
+          f16* rows = wave == 1 ? kb : vb;
+          rows[at] = h0;
+          rows[at + HALF] = h1;
+          s_new[wave - 1][i] = h0;
+          s_new[wave - 1][i + HALF] = h1;
+          if constexpr (TWO) {
+            const int e = pack_lo8(v0 - (float)h0, v1 - (float)h1, 0.f, 0.f);
+            const unsigned char e0 = (unsigned char)(e & 0xff), e1 = (unsigned char)((e >> 8) & 0xff);
+            unsigned char* rows_lo = wave == 1 ? kbl : vbl;
+            rows_lo[at] = e0;
+            rows_lo[at + HALF] = e1;
+            s_new_lo[wave - 1][i] = e0;
+            s_new_lo[wave - 1][i + HALF] = e1;
+          }
         }
       }
     }
-  }
-  __syncthreads();
-  float qf[8];
+    __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 8; ++j) qf[j] = s_q[c * 8 + j];
+    for (int j = 0; j < 8; ++j) qf[j] = s_q[c * 8 + j];
+  };
+  // A context that one group covers has no second one: its requests, for the last row again and again, would make 74 us of 256
+  // sequences of 60 (32 heads of 64, low terms) 88.  The branches meet behind the new row, the short one with nothing in flight,
+  // so that the waits that follow count on the second group's requests (without that the first group waits for both: 1 % of a
+  // launch at 290 positions, 5 % of some).
+  request(s0, 0);
+  if (__builtin_expect(n_it > G, 1)) {                  // uniform
+    request(s1, G);
+    new_row();
+  } else {
+    new_row();
+    __builtin_amdgcn_s_waitcnt(0x0f70);                 // vmcnt(0), for the compiler to see
+  }
   const float scale = rsqrtf((float)HD);
 
   // One pass with a running maximum per lane: the key rows and the value rows of a group are requested together, so
