@@ -4,7 +4,10 @@
 // attention_rows (float32): one wave per (token, head).  Keys and values of a (slot, head) are contiguous
 // [position][head_dim] rows in the cache; HD / 4 lanes share a row, 16 bytes each, so an instruction reads 64 * 4 / HD whole
 // rows and a score is a butterfly over the lanes of its row.  A few dozen keys: bound by its chain of latencies, so the rows
-// of G instructions are requested together, and the first values with the keys, before there is a score.
+// of two groups of G instructions are in flight, a group requested again as soon as its registers are free, and the first
+// values with the keys, before there is a score.  Groups by a context's use of them: six instructions, four where these are
+// eight rows each.  us a decode step of two layers of d 512, groups of twelve one after the other / these: one sequence of
+// 1000 keys, heads of 64 154 / 128, of 256 438 / 307; a prefill of 64 prefixes of 33, heads of 32, 604 / 568.
 #include <type_traits>
 
 #include "common.h"
@@ -17,11 +20,11 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
     const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos, float* __restrict__ out, int n_items,
     int n_heads, int max_seq) {
   extern __shared__ float smem[];                    // [4 waves][max_seq] scores
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int item = blockIdx.x * 4 + wave;            // (token, head)
   if (item >= n_items) return;                       // whole wave leaves; no block barrier is used
   float* sc = smem + (size_t)wave * max_seq;
-  constexpr int LPR = HD / 4, RPI = 64 / LPR, G = 12;
+  constexpr int LPR = HD / 4, RPI = 64 / LPR, G = HD == 32 ? 4 : 6, STEP = G * RPI;
   const int c = lane % LPR, sub = lane / LPR;
   const int tok = item / n_heads, head = item - tok * n_heads;
   const int slot = tok_seq[tok], pos = tok_pos[tok];
@@ -29,20 +32,17 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
   const size_t blk = ((size_t)slot * n_heads + head) * max_seq * HD + c * 4;
   const float *kbase = k_cache + blk, *vbase = v_cache + blk;
   const float scale = rsqrtf((float)HD);
-  f32x4 kv[G], vv[G];
+  f32x4 kv[2][G], vv[2][G];
   auto request = [&](f32x4 (&r)[G], const float* base, int key0) {
 #pragma unroll
     for (int u = 0; u < G; ++u) r[u] = *(const f32x4*)(base + (size_t)min(key0 + u * RPI + sub, pos) * HD);   // keys 0..pos
   };
-  request(kv, kbase, 0);
-  request(vv, vbase, 0);
-  __builtin_amdgcn_sched_barrier(0);
-  float mx = -INFINITY;
-  for (int key0 = 0; key0 <= pos; key0 += RPI * G) {
-    if (key0 > 0) request(kv, kbase, key0);
+  float mx = -INFINITY, sum = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto scores = [&](const f32x4 (&k)[G], int key0) __attribute__((always_inline)) {
     float s[G];
 #pragma unroll
-    for (int u = 0; u < G; ++u) s[u] = fmaf(qv[3], kv[u][3], fmaf(qv[2], kv[u][2], fmaf(qv[1], kv[u][1], qv[0] * kv[u][0])));
+    for (int u = 0; u < G; ++u) s[u] = fmaf(qv[3], k[u][3], fmaf(qv[2], k[u][2], fmaf(qv[1], k[u][1], qv[0] * k[u][0])));
 #pragma unroll
     for (int u = 0; u < G; ++u) s[u] = lanes_sum<1, LPR / 2>(s[u]);
 #pragma unroll
@@ -52,13 +52,8 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
       mx = fmaxf(mx, s[u]);                                // (a clamped row repeats key pos: the same maximum)
       if (c == 0 && key <= pos) sc[key] = s[u];
     }
-  }
-  if constexpr (LPR < 64) mx = lanes_max<LPR, 32>(mx);
-  __builtin_amdgcn_wave_barrier();
-  float sum = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int key0 = 0; key0 <= pos; key0 += RPI * G) {
-    if (key0 > 0) request(vv, vbase, key0);
+  };
+  auto values = [&](const f32x4 (&v)[G], int key0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const int key = key0 + u * RPI + sub;
@@ -66,10 +61,31 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
         const float p = __expf(sc[key] - mx);
         sum += p;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, vv[u][e], acc[e]);
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(p, v[u][e], acc[e]);
       }
     }
-  }
+  };
+  // one pass over the rows; the first two groups are requested
+  auto pass = [&](f32x4 (&r)[2][G], const float* base, auto&& consume) __attribute__((always_inline)) {
+    int key0 = 0;
+    for (; key0 + 2 * STEP <= pos; key0 += 2 * STEP) {
+      consume(r[0], key0);
+      request(r[0], base, key0 + 2 * STEP);
+      consume(r[1], key0 + STEP);
+      request(r[1], base, key0 + 3 * STEP);
+    }
+    consume(r[0], key0);
+    if (key0 + STEP <= pos) consume(r[1], key0 + STEP);
+  };
+  request(kv[0], kbase, 0);
+  request(kv[1], kbase, STEP);
+  request(vv[0], vbase, 0);
+  request(vv[1], vbase, STEP);
+  __builtin_amdgcn_sched_barrier(0);
+  pass(kv, kbase, scores);
+  if constexpr (LPR < 64) mx = lanes_max<LPR, 32>(mx);
+  __builtin_amdgcn_wave_barrier();
+  pass(vv, vbase, values);
   if constexpr (LPR < 64) {
     sum = lanes_sum<LPR, 32>(sum);
 #pragma unroll
