@@ -22,9 +22,10 @@ extern "C" {
 int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);
 
 /* Which variant of the prefill GEMM a product [rows, k] x [n, k]^T takes ("128x256", ...): a static text, "" for sizes
- * the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer; resid: the output projection and
- * the down projection (0: the QKV and gate/up products). */
-const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t resid);
+ * the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer; span: 32 for the output projection
+ * and the down projection, 64 for gate/up and for the QKV product of heads of 64, 128 for that of heads of 128 (the columns
+ * of a row that the product's last step needs together). */
+const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
 /* Timing hooks for the benchmark: duration of the launches of one kernel family, measured with
  * HIP events recorded on the launch stream around each launch.  vla_prof_enable(ctx, mask) clears

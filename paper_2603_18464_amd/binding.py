@@ -283,8 +283,8 @@ def vla_probe(ctx, kind: int, stream: int = 0) -> float:
     return v.value
 
 
-def vla_gemm_variant(rows: int, n: int, k: int, two_term: bool, resid: bool) -> str:
-    return lib().vla_gemm_variant(rows, n, k, int(two_term), int(resid)).decode()
+def vla_gemm_variant(rows: int, n: int, k: int, two_term: bool, span: int) -> str:
+    return lib().vla_gemm_variant(rows, n, k, int(two_term), span).decode()
 
 
 def vla_prof_enable(ctx, mask: int) -> None:

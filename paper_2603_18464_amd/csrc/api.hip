@@ -1515,11 +1515,11 @@ int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream) {
   return VLA_OK;
 }
 
-const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t resid) {
-  if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64) return "";
+const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span) {
+  if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64 || (span != 32 && span != 64 && span != 128)) return "";
   const bool low8 = lo8(two_term != 0, k);
   const int pitch = two_pitch(two_term != 0, k);
-  return kGemmF16Variants[gemm_f16_variant(rows, n, pitch, low8, resid != 0)];
+  return kGemmF16Variants[gemm_f16_variant(rows, n, pitch, k, low8, span)];
 }
 
 int vla_prof_enable(vla_ctx* ctx, int32_t mask) {

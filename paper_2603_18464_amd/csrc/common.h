@@ -178,11 +178,11 @@ void gemm_f16_swiglu(const GemmF16& g, f16* act, int ldact, int lo_mode, hipStre
 void gemm_f16_qkv(const GemmF16& g, const RopeKv& o, hipStream_t st);               // RoPE + cache
 // range_flag: device int, bits are OR-ed in when a weight cannot be re-encoded exactly (see pack_weight_kernel);
 // dst8 != nullptr: also the 8-bit copy fp8(w * 16) for 8-bit low terms (K % 64 == 0)
-// The variant of the kernel a launch takes (an index into the names), by the product's size, whether it has slabs of 8-bit
-// low terms (K then counts both: 1.5 * Kw), and whether its epilogue is the residual add.
-constexpr int kGemmF16VariantCount = 8;
-extern const char* const kGemmF16Variants[kGemmF16VariantCount];
-int gemm_f16_variant(int M, int N, int K, bool lo8, bool resid);
+// The variant of the kernel a launch takes (an index into the names), by the product's size (Kw: its contraction; K: that and
+// its low terms, 1.5 or 2 * Kw), whether it has slabs of 8-bit low terms, and its epilogue: the columns of a row that this needs
+// together, 32 (residual add), 64 (gate/up, QKV of heads of 64) or 128 (QKV of heads of 128).
+extern const char* const kGemmF16Variants[];
+int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span);
 void pack_weight_f16(const bf16* src, int rows, int K, f16* dst, unsigned char* dst8, int row0, int interleave_mode,
                      int* range_flag, hipStream_t st);
 

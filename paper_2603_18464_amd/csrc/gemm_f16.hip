@@ -250,7 +250,8 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   registers.  A comes from the L2 and W, in a launch of few tiles, from HBM: where the 160 KiB do not hold another stage of
 //   both they hold a third one of W.  Against two stages of each: 192x256 at 290 rows 79 -> 62 us (qkv), 84 -> 68 (gate/up),
 //   191 -> 142 (down), at 18560 rows 1811 -> 1652, 2846 -> 2656, 1760 -> 1493; 256x256 at 290 rows 88 -> 75, 94 -> 82,
-//   212 -> 180, at 18560 1615 -> 1601, 2576 -> 2564, 1443 -> 1377, with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.
+//   212 -> 180, at 18560 rows down 1443 -> 1377 and with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.  (Single-term
+//   256x256 launches of many tiles keep two of each where the weights stay in the caches: see the tile choice.)
 // * SPREAD: the weights of a slab's second k-step are requested a k-step after the rest, so that the loads go out evenly.
 // * Fragments are double buffered in registers: while the MFMAs of one k-step run, the reads of the next
 //   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     for (int j = 0; j < NT; ++j) hold(bf[f][j]);
   };
   // One k-step of slab kt: the MFMAs, and between them fragment reads (in the first three quarters, so that they have
-  // landed at the end) and the loads of slab kt + S.
+  // landed at the end) and the loads that take slab kt's stages (A of slab kt + S, W of slab kt + SW).
   // Read ahead by a k-step: the k-steps alternate between two buffers, P is the slab's first one.  The reads of the last
   // k-step belong to slab kt + 1, which must have landed, and slab kt is in everybody's registers: its stage takes the loads.
   // DEEP, read ahead by a slab: P is the half of the buffers slab kt is in, and all of this holds from its first k-step on.
@@ -748,14 +749,18 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // larger of the two, the last partial round likewise for its share.  us at K = 4096 / 11008, and PFLOP/s:
 //   64x128 27.9 / 67.6, 0.68; 128x128 33.8 / 83.6, 0.92; 64x256 44 / 107, 0.80; 128x256 50 / 128, 1.15; 192x256
 //   59 / 143, 1.25; 256x256 73 / 180, 1.30.
-// The pick against the fastest of the six, each forced in turn (the four matrices of the 7B model at 64 to 18560 rows and
-// of the 12-layer one at 64 to 18432, single- and two-term, 164 products): the same in 150 of them, 0.1 % slower in the
-// mean.  us single-term, pick and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
+// The constants of the last two are a little above these times (62.8 / 155, 75.3 / 184): they stand for every width, and in a
+// model of matrices that come from the caches the third weight stage gives these tiles less.  Over 1084 products (the four
+// matrices of models of d 256 to 5120 at 64 to 37120 rows, single- and two-term, each tile forced in turn) the pick is the
+// fastest in 1015 and 0.30 % slower in the mean; constants that meet the two columns make it 0.38 %, and 0.57 instead of 0.19 %
+// over the 7B matrices among them; the best of a search over both tiles' constants 0.25 %.
+// us single-term, pick and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
 // (64x128; 73), down 68 (64x128; 180); 580 rows gate/up 112 (128x256; 256x256 163), down 84 (128x128; 191); 870 rows qkv 78
-// (192x256; 256x256 90); 2338 rows gate/up 375 (256x256; 128x256 390), o 79 (192x256; 256x256 89), down 187 (192x256;
-// 256x256 212); 9216 rows of d 768 gate/up 62 (192x256; 128x256 69).
-// Where it is off: gate/up at 400 rows 92 (256x256 32-k; 64-k 89), o at 9280 301 (256x256; 128x256 292), qkv of d 768 at 64
-// rows 8.6 (64x128; 128x128 8.1).
+// (192x256; 256x256 90); 2320 rows gate/up 378 (256x256; 128x256 389), o 86 (192x256; 256x256 101), down 197 (192x256;
+// 256x256 236); 9216 rows of d 768 gate/up 62 (192x256; 128x256 69).
+// Where it is off most: qkv at 580 rows of d 5120 116 (256x256; 192x256 99), gate/up at 13920 rows of d 768 112 (128x256;
+// 256x256 102), down at 3480 rows of d 3072 184 (256x256; 192x256 159), the matrices of d 512 and less at 7000 rows and more by
+// 4 to 20 %, qkv at 37120 rows of d 1536 515 (192x256; 256x256 486).
 enum Tile { T_64x128, T_128x128, T_64x256, T_128x256, T_192x256, T_256x256, T_COUNT };
 struct TileCost { int bm, bn; float fixed, per_k, rate; };
 constexpr TileCost kTileCost[T_COUNT] = {{64, 128, 3.9f, 5.9f, 0.68f}, {128, 128, 4.3f, 7.4f, 0.92f},
@@ -782,48 +787,65 @@ static TilePick pick_tile(int M, int N, int K) {
 }
 
 // Rings are as deep as the LDS allows: cold weights take longer than two slabs to arrive (64x128 with 6 stages 28 and
-// 68 us for o and down at 290 rows, with 3 stages and two workgroups per compute unit 30 and 73), except where several
-// rounds of 64x128 tiles share the compute units, and except the eight-wave form of the first variant (four stages do; an
-// epilogue that needs 128 columns of a row together keeps the four waves and six stages the variant is named after).
-// 256x256: 8 waves of 64x128; the residual epilogue and fewer than three rounds of tiles request the weights in halves of
-// 32 k (SPREAD: down 253 against 259 us at 3480 rows, 212 against 215 at 2338, 523 against 526 at 6960; o 89.0 against 89.7 at
-// 2338, 560 against 558 at 18560); the larger launches are the same either way (+-1 %).  Slabs of 32 k throughout, in four
-// stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at 2338 rows, 536 and 525 at 6960,
-// 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.
-// The single-term QKV product of heads of 128 keeps two stages of each operand in its large launches: 1404 us, against 1435
-// with a third one of the weights and 1423 with SPREAD (18560 rows, 7B, among the other kernels of a policy step).
-const char* const kGemmF16Variants[kGemmF16VariantCount] = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256",
-                                                            "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"};
-int gemm_f16_variant(int M, int N, int K, bool lo8, bool resid) {
+// 68 us for o and down at 290 rows, with 3 stages and two workgroups per compute unit 30 and 73), except
+// * where several rounds of 64x128 tiles share the compute units (3 stages, two workgroups), and in the eight-wave form of a
+//   launch of few of them, whose four stages do; an epilogue that needs 128 columns of a row together (span 128) cannot have
+//   that form's wave tiles of 32 columns and keeps four waves and six stages;
+// * 256x256, eight waves of 64x128: a third weight stage does nothing for a single-term launch of three rounds and more
+//   whose weights stay in the caches between the tile rows that read them, and costs 1 to 3 % there (a stage's offset is no
+//   power of two, and the chip is bound by power).  The line lies where the weights and half of the activations reach
+//   215 MB of the 256 MB last-level cache.  Three stages over two, weights and activations in MB: gate/up 45 + 76 (d 2048,
+//   18560 rows) +1.7 %, 90 + 152 +1.8, 101 + 114 (d 3072) +2.0, 134 + 152 +1.1, 180 + 19 (7B, 2320 rows) +2.4, 180 + 38 +1.4 and
+//   -0.3, 151 + 152 -0.4, 180 + 76 -1.3, 180 + 152 -1.8, 201 + 76 -3.3, 268 + 38 -4.0; qkv 57 + 228 +2.8, 101 + 152 (7B, 18560
+//   rows) +1.8 to +2.7, 101 + 304 +0.9, 127 + 171 -0.5, 157 + 190 -2.3, 226 + 114 -6.2; heads of 64 as heads of 128.  The
+//   epilogue that adds to the residual rows always gains (-1 to -4 %), and so do low terms (0 to -6 %);
+// * the residual epilogue and launches of fewer than three rounds request the weights in halves of 32 k (SPREAD: down 253
+//   against 259 us at 3480 rows, 212 against 215 at 2338, 523 against 526 at 6960; o 89.0 against 89.7 at 2338, 560 against 558
+//   at 18560); the larger launches are the same either way (+-1 %).
+// (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
+// 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
+enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_192x256, V_256x256, V_256x256_W3, V_256x256_SPREAD, V_COUNT };
+const char* const kGemmF16Variants[] = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
+                                        "192x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
+static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
+int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
   const TilePick p = pick_tile(M, N, K);
   switch (p.tile) {
-    case T_64x128: return p.tiles <= 256 ? 0 : 1;
-    case T_128x128: return 2;
-    case T_64x256: return 3;
-    case T_128x256: return 4;
-    case T_192x256: return 5;
-    default: return lo8 || (!resid && p.tiles >= 768) ? 6 : 7;
+    case T_64x128: return p.tiles > 256 ? V_64x128_ROUNDS : span <= 64 ? V_64x128_8W : V_64x128;
+    case T_128x128: return V_128x128;
+    case T_64x256: return V_64x256;
+    case T_128x256: return V_128x256;
+    case T_192x256: return V_192x256;
+    default: break;
   }
+  if (lo8) return V_256x256_W3;
+  if (span == EpiResid::kSpan || p.tiles < 768) return V_256x256_SPREAD;
+  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
 }
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  constexpr bool resid = std::is_same<Epi, EpiResid>::value;
-  switch (gemm_f16_variant(g.M, g.N, g.K, LO8, resid)) {
-    case 0:
-      if constexpr (Epi::kSpan <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
-      else launch<2, 2, 32, 64, 6, 6, 1, false, false, LO8>(g, epi, st);
+  constexpr int span = Epi::kSpan;
+  constexpr bool resid = span == EpiResid::kSpan;
+  switch (gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span)) {
+    case V_64x128_8W:
+      if constexpr (span <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
       break;
-    case 1: launch<2, 2, 32, 64, 3, 3, 2, false, false, LO8>(g, epi, st); break;
-    case 2: launch<4, 2, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
-    case 3: launch<2, 4, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
-    case 4: launch<2, 4, 64, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
-    case 5: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
-    case 6:
-      if constexpr (!LO8 && Epi::kSpan == 128) launch<4, 2, 64, 128, 2, 2, 1, false, false, LO8>(g, epi, st);
-      else if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
+    case V_64x128:
+      if constexpr (span > 64) launch<2, 2, 32, 64, 6, 6, 1, false, false, LO8>(g, epi, st);
+      break;
+    case V_64x128_ROUNDS: launch<2, 2, 32, 64, 3, 3, 2, false, false, LO8>(g, epi, st); break;
+    case V_128x128: launch<4, 2, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
+    case V_64x256: launch<2, 4, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
+    case V_128x256: launch<2, 4, 64, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
+    case V_192x256: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
+    case V_256x256:
+      if constexpr (!LO8 && !resid) launch<4, 2, 64, 128, 2, 2, 1, false, false, LO8>(g, epi, st);
+      break;
+    case V_256x256_W3:
+      if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
       break;
     default:
-      if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, false>(g, epi, st);
+      if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, LO8>(g, epi, st);
   }
 }
 template <class Epi>

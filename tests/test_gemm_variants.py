@@ -11,36 +11,57 @@ from paper_2603_18464_amd.binding import vla_gemm_variant
 from tests import parity as P
 from tests.test_gpu_parity import ragged_obs
 
-ALL = {"64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "192x256", "256x256 64-k slabs", "256x256 32-k slabs"}
-# Not reached: three stages need more than 256 of the smallest tiles to be the fastest choice, which takes a wide matrix of
-# a short contraction (gate/up only); 32-k slabs have no room for 8-bit low terms, 64-k ones are not for the residual add.
-REACHED = {(two, epi): ALL - ({"64x128 3 stages"} if epi != "gate/up" else set())
-           for two in (False, True) for epi in ("qkv", "gate/up", "resid")}
-REACHED[False, "resid"] -= {"256x256 64-k slabs"}
-REACHED[True, "qkv"] -= {"256x256 32-k slabs"}
-REACHED[True, "gate/up"] -= {"256x256 32-k slabs"}
+ALL = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "192x256", "256x256",
+       "256x256 3 weight stages", "256x256 spread"}
+SPAN = {"resid": 32, "gate/up": 64, "qkv64": 64, "qkv128": 128}
+# Not reached: of the forms of a launch of few 64x128 tiles each epilogue has one; three stages need more than 256 of these
+# tiles to be the fastest choice, which takes a wide matrix of a short contraction (gate/up only); 8-bit low terms have one
+# form of 256x256 and the residual add another (with low terms it has both: those of a d_ffn that is an odd multiple of 64 are
+# halves).
+REACHED = {(two, epi): ALL - {"64x128 8 waves" if epi == "qkv128" else "64x128 6 stages"}
+           - ({"64x128 3 stages"} if epi != "gate/up" else set())
+           - ({"256x256"} if two or epi == "resid" else set())
+           - ({"256x256 3 weight stages"} if epi == "resid" and not two else set())
+           - ({"256x256 spread"} if two and epi != "resid" else set())
+           for two in (False, True) for epi in SPAN}
+# A single-term product with three weight stages has a matrix of 100 MB or more.  Here for heads of 64; the 7B workloads run
+# the other two (gate/up from 7000 rows on, heads of 128 from 28 000 on).
+BY_7B = [("gate/up", 64 * 290, 22016), ("qkv128", 256 * 290, 12288)]
+for epi, _, _ in BY_7B:
+    REACHED[False, epi] -= {"256x256 3 weight stages"}
 
 # (d_model, d_ffn, head_dim, rows): three layers, the first two-term, the last one partly on the rows of the head only
 CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 64, 64, [2881, 4100, 6000]),
          (128, 2048, 128, [1100, 2300]), (512, 2048, 64, [3500]), (1536, 64, 128, [8000]), (128, 16448, 64, [64]),
          (1024, 64, 64, [1300]), (2048, 704, 128, [8000]), (512, 4096, 128, [6000]), (1280, 2816, 128, [700]),
-         (3072, 64, 128, [400, 1300])]
+         (3072, 64, 128, [400, 1300]), (1280, 64, 64, [1088]), (2048, 64, 64, [8000]), (5632, 64, 64, [4500])]
 
 
-def launches(d, f, rows):
+def launches(d, f, hd, rows):
     for two in (False, True):
-        for epi, n, k in (("qkv", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-            yield (two, epi), vla_gemm_variant(rows, n, k, two, epi == "resid")
+        for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
+            yield (two, epi), vla_gemm_variant(rows, n, k, two, SPAN[epi])
 
 
 def test_the_cases_reach_every_variant():
     reached = {key: set() for key in REACHED}
-    for d, f, _, rows_list in CASES:
+    for d, f, hd, rows_list in CASES:
         for rows in rows_list:
-            for key, variant in launches(d, f, rows):
+            for key, variant in launches(d, f, hd, rows):
                 reached[key].add(variant)
     assert reached == REACHED
-    assert vla_gemm_variant(64, 100, 128, False, False) == ""
+    for epi, rows, n in BY_7B:
+        assert vla_gemm_variant(rows, n, 4096, False, SPAN[epi]) == "256x256 3 weight stages"
+    assert vla_gemm_variant(64, 100, 128, False, 32) == vla_gemm_variant(64, 128, 128, False, 1) == ""
+
+
+def test_the_third_weight_stage_goes_by_the_bytes_that_are_read_again():
+    """The same tile, with two stages where weights and half of the activations stay below 215 MB: whatever the epilogue."""
+    for span in (64, 128):
+        for rows, n, k, third in ((18560, 12288, 4096, False), (18560, 22016, 4096, True), (2320, 22016, 4096, False),
+                                  (18560, 11008, 2048, False), (18560, 49152, 2048, True), (9280, 18432, 6144, True)):
+            want = "256x256 3 weight stages" if third else "256x256"
+            assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
 
 
 @pytest.mark.gpu
