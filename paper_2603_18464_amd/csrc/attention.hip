@@ -706,7 +706,7 @@ void attention_rows_f32(const float* q, const float* k_cache, const float* v_cac
                         hipStream_t st) {
   const int n_items = n_tok * n_heads;
   const int blocks = (n_items + 3) / 4;
-  const size_t smem = 4 * (size_t)max_seq * sizeof(float);
+  const size_t smem = attention_rows_lds(max_seq);
 #define VLA_ATTN_CASE(HD)                                                                                   \
   case HD:                                                                                                  \
     hipLaunchKernelGGL((attention_rows_kernel<HD>), dim3(blocks), dim3(256), smem, st, q, k_cache, v_cache, \

@@ -198,7 +198,8 @@ void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float
 template <class T>
 void assemble_prefix(const T* patch_emb, const int32_t* instr_ids, const T* embed,
                      const int32_t* tok_src, float* x, int T_tokens, int d, int vocab, hipStream_t st);
-// Attention: one query row per (token, head) against the cache.
+// Attention: one query row per (token, head) against the cache; its LDS holds the scores of four of them.
+inline size_t attention_rows_lds(int max_seq) { return 4 * (size_t)max_seq * sizeof(float); }
 void attention_rows_f32(const float* q, const float* k_cache, const float* v_cache, const int32_t* tok_seq,
                         const int32_t* tok_pos, float* out, int n_tok, int n_heads, int head_dim, int max_seq,
                         hipStream_t st);

@@ -65,6 +65,15 @@ def test_config_validation_and_sizes():
             B.vla_query_sizes(bad)
 
 
+def test_float32_length_limit_is_what_the_scores_take():
+    """64 KiB hold the scores of four waves: 4096 positions each, one of which keeps the cache's pitch odd, for every head size."""
+    for hd in (32, 64, 128, 256):
+        shape = W.PolicyShape(2, 256, 256 // hd, hd, 96, 300, n_action_bins=40, dtype="f32")
+        B.vla_query_sizes(B.make_config(shape, 1, 4095, 64))
+        with pytest.raises(B.VlaError):
+            B.vla_query_sizes(B.make_config(shape, 1, 4096, 64))
+
+
 def test_null_arguments_and_unbound_state():
     L = B.lib()
     assert L.vla_create(None, None) == -1
