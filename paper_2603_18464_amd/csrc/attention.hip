@@ -426,8 +426,8 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
 // HBM-bound at large batches, bound by its chain of latencies at small ones: the keys and values of a (slot, head) are
 // one contiguous [position][HD] block each, and the kernel streams them once with 16-byte-per-lane loads (a wave
 // instruction covers 64*16/(2*HD) whole rows).  One workgroup = 8 waves per (sequence, head); wave w takes every 8th
-// group of rows.  A lane owns 8 head dimensions of one row at a time: scores are reduced across the HD/8 lanes of a row
-// with shuffles, the probability-weighted values stay in 8 per-lane accumulators, and the partial softmax
+// group of rows.  A lane owns 8 head dimensions of one row at a time: scores are added up over the HD/8 lanes of a row
+// in the vector unit, the probability-weighted values stay in 8 per-lane accumulators, and the partial softmax
 // statistics and outputs of the waves are merged through LDS at the end.
 //
 // The query and the new key / value row of this (sequence, head) are not read from memory but formed here from

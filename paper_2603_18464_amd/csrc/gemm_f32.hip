@@ -9,8 +9,9 @@
 // reads from L2; the order of every sum is the same, so a row's bits do not depend on the batch it is in.
 // Policy step of the 2-layer model (4 sequences of 32 tokens, 7 tokens out): 3.18 ms with 64 x 64 tiles of scalar FMAs
 // (4 workgroups on N = 256, 33 to 78 us a launch) and the norms, rotation, SwiGLU and residual adds as launches of their
-// own (11 a layer); 0.40 ms with these (5 a layer); 0.375 with what the epilogues read requested before the product and all
-// of a down projection's operands (11 k-steps a wave) in one round instead of two, and the attention's keys and values together.
+// own (11 a layer); 0.40 ms with these (5 a layer); 0.36 with what the epilogues read requested before the product and all
+// of a down projection's operands (11 k-steps a wave) in one round instead of two, the attention's keys and values together and
+// lane sums in the vector unit.
 #include "common.h"
 
 namespace vla {
