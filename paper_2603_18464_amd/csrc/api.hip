@@ -438,7 +438,7 @@ inline f16* frag_lo(const vla_config& c, f16* base, int K) { return two_term(c) 
 // narrow model: every workgroup reads the rows in float32, which from 17 rows on costs a wide model more than the two launches
 // it saves.  And as long as the down product is not bound by its activations: a workgroup reads all of them for 16 columns
 // (skinny_gemm_kernel: for 64), rows x d_ffn x terms elements; twice as many where d / 16 workgroups fill the 256 compute
-// units in whole rounds.  us of a layer, the norm apart / inside less the norm apart (two-term layers behind the semicolon):
+// units in whole rounds.  us of a decode layer with the norm inside less those with it apart (behind the semicolon: two-term):
 //   d 768 f 2048, 1 row -2.4; -2.4, 16 -3.3; -2.6, 32 -2.1; -1.0.  d 1024 f 5504, 8 rows -3.3; -1.9, 16 -2.9; -1.4, 17 -1.7;
 //   +0.5, 32 -0.5; +2.0.  d 1024 f 11008, 8 rows -2.3; -1.0, 16 -0.1; +1.9, 17 +2.9; +6.5, 32 +5.8; +10.5.  d 2048 f 11008, 8
 //   rows -2.5; -1.1, 16 -0.1; +1.1, 17 +2.7; +5.4.  d 2048 f 16384, 8 rows -1.5; +1.8, 16 +0.7; +4.9.  d 4096 f 11008, 8 rows
