@@ -27,6 +27,10 @@ int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);
  * of a row that the product's last step needs together). */
 const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
+/* Rows of the tiles that this product's launch runs: the variant's, but where it has 192 or 256 of them 160, 192, 224 or 256,
+ * whichever leaves the last round of tiles fullest.  0 for sizes the 16-bit path does not have.  Host only. */
+int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term);
+
 /* Timing hooks for the benchmark: duration of the launches of one kernel family, measured with
  * HIP events recorded on the launch stream around each launch.  vla_prof_enable(ctx, mask) clears
  * what was collected and then times the families whose bit (1 << index) is set in mask (0 = off).

@@ -1522,6 +1522,11 @@ const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_ter
   return kGemmF16Variants[gemm_f16_variant(rows, n, pitch, k, low8, span)];
 }
 
+int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term) {
+  if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64) return 0;
+  return gemm_f16_tile_rows(rows, n, two_pitch(two_term != 0, k));
+}
+
 int vla_prof_enable(vla_ctx* ctx, int32_t mask) {
   if (!ctx) return VLA_E_NULL;
   for (auto& v : ctx->prof) {

@@ -350,17 +350,17 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const 
 // depends on it.
 template <int MT, int NT>
 __device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
-  static_assert(MT * NT % 8 == 0 || MT * NT == 4, "whole groups of eight, or one of four");
+  static_assert(MT * NT % 4 == 0, "whole groups of eight, and one of four");
 #if defined(__HIP_DEVICE_COMPILE__)
 #define VLA_ACC(j) "+v"(acc[(g + j) / NT][(g + j) % NT])
-  if constexpr (MT * NT == 4) {
-    constexpr int g = 0;
-    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3));
-  } else {
+  constexpr int EIGHTS = MT * NT / 8 * 8;
 #pragma unroll
-    for (int g = 0; g < MT * NT; g += 8)
-      asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
-                   VLA_ACC(7));
+  for (int g = 0; g < EIGHTS; g += 8)
+    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
+                 VLA_ACC(7));
+  if constexpr (EIGHTS < MT * NT) {
+    constexpr int g = EIGHTS;
+    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3));
   }
 #undef VLA_ACC
 #endif
@@ -384,8 +384,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
                                                                    int tiles_m, int tiles_n, Epi epi_in) {
   constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / 16, NT = WN / 16;
   constexpr int KS = PK / 32, KS16 = PK / 16;          // k-steps of a slab; 16-k blocks of a slab
-  constexpr int AP = BM * PK / 512 / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;   // KiB pieces per wave and slab
-  static_assert(AP * NW * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
+  // KiB pieces per wave and slab.  Where those of A do not divide among the waves (REST of them are left for the last round),
+  // piece i of a wave is piece i * NW + wave of the slab, and the last round's are loaded by several waves: the same bytes to
+  // the same place, so that every wave counts the same loads.
+  constexpr int A_ALL = BM * PK / 512, AP = (A_ALL + NW - 1) / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;
+  constexpr int REST = A_ALL % NW;
+  static_assert(A_ALL * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
+  static_assert(REST == 0 || (REST % 2 == 0 && NW % 2 == 0 && !SPLITK), "all pieces of a wave have the same swizzle then");
   // Rings of one depth are one ring of [A slab | W slab], with one offset a stage (two rings: 128x256 tiles 0.6 % slower,
   // 128x128 0.3 %); else they follow one another.
   constexpr int A_HALVES = BM * PK, W_HALVES = BN * PK, A_STAGE = A_HALVES + (SW == S ? W_HALVES : 0);
@@ -443,13 +448,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   // Rows of A: piece i of a wave holds rows r0 + i * RPP (clamped to the last one), whose swizzle is that of r0 with the
   // chunk's bits of swz(i * RPP) flipped, so two registers serve all pieces.
   const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)min(M - 1 - m0, BM - 1) * a_pitch;   // (fits 32 bits)
-  const int r0 = wave * AP * RPP + lane / (PK / 8);
+  const int r0 = wave * (REST ? 1 : AP) * RPP + lane / (PK / 8);
+  const unsigned a_back = REST ? (unsigned)(wave - wave % (REST ? REST : 1)) : 0u;    // pieces a wave's last one is moved back by
   const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle(r0)) * 16u;
   auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped), A first
     constexpr int i = decltype(I)::value;
     const int ks = min(kt, KT - 1), kw = ks >= KTw ? ks - KTw : ks;
     if constexpr (i < AP) {
-      f16* dst = lds + (kt % S) * A_STAGE + (wave * AP + i) * 512;
+      f16* dst = lds + (kt % S) * A_STAGE + (REST ? i * NW + wave - (i == AP - 1 ? (int)a_back : 0) : wave * AP + i) * 512;
       if constexpr (SPLITK) {
         const int j = wave * AP + i;                   // piece of the slab: block row j / KS16 (clamped to the rows
         const int rb = min(j / KS16, (M - 1) >> 5);    // that exist), 16-k block j % KS16
@@ -457,7 +463,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       } else {
         unsigned row = a_row;
         hold32(row);                                   // the offset is formed here, three instructions a load, and not kept
-        row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle(i * RPP) * 16));
+        if constexpr (REST) row = min(row + (unsigned)(i * NW * RPP - (i == AP - 1 ? (int)a_back * RPP : 0)) * a_pitch, a_last) + a_chunk;
+        else row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle(i * RPP) * 16));
         load_to_lds_16(a_base, row, 2u * PK * (unsigned)ks, dst);
       }
     } else {
@@ -698,6 +705,17 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     epi.template consume<COLS, PITCH, ROWS>(tile + side * ROWS * PITCH, m0 + wm * WM + mb * 32 + side * ROWS,
                                             n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
   }
+  if constexpr (MT % 2 != 0) {                         // the last 16 rows
+    if constexpr (PAIR) __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        tile[(4 * (lane >> 4) + e) * PITCH + side * WN + nt * 16 + (lane & 15)] = acc[MT - 1][nt][e];
+    if constexpr (PAIR) __syncthreads();
+    epi.template consume<COLS, PITCH, ROWS / 2>(tile + side * (ROWS / 2) * PITCH, m0 + wm * WM + (MT - 1) * 16 + side * (ROWS / 2),
+                                                n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
+  }
 }
 
 template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, bool LO8, bool SPLITK, class Epi>
@@ -808,6 +826,11 @@ enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_12
 const char* const kGemmF16Variants[] = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
                                         "192x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
 static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
+static Variant form_of_256(int M, int N, int Kw, long long tiles, bool lo8, int span) {
+  if (lo8) return V_256x256_W3;
+  if (span == EpiResid::kSpan || tiles < 768) return V_256x256_SPREAD;
+  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
+}
 int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
   const TilePick p = pick_tile(M, N, K);
   switch (p.tile) {
@@ -816,17 +839,41 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
     case T_64x256: return V_64x256;
     case T_128x256: return V_128x256;
     case T_192x256: return V_192x256;
-    default: break;
+    default: return form_of_256(M, N, Kw, p.tiles, lo8, span);
   }
-  if (lo8) return V_256x256_W3;
-  if (span == EpiResid::kSpan || p.tiles < 768) return V_256x256_SPREAD;
-  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
 }
+
+// Rows of the tiles a launch runs.  Where the model picks 192 or 256 rows, the rounds are balanced: the last one costs a whole
+// tile's time however few workgroups it has, and that is proportional to a tile's rows + 90 (a slab of weights, the fill and the
+// end of a tile cost the same for each), so of 160, 192, 224 and 256 rows those are taken that need the least rounds x (rows +
+// 90), if that is 2.5 % less than the model's.  us with the model's rows / these, 7B: 780 rows qkv 80 / 73, gate/up 143 / 132;
+// 2208 rows gate/up 361 / 330, down 180 / 173, o 77.7 / 74.9; 2368 rows gate/up 364 / 343, down 185 / 181; 4100 rows down
+// 368 / 340, o 154 / 142, qkv 370 / 350; 6960 rows down 509 / 488, o 213 / 204; 9400 rows down 762 / 705; 14000 rows down 1032 / 978;
+// with low terms 5 to 10 % likewise.  Over 149 products of the 7B shape (290 to 28000 rows) 2.7 % less in the mean and none
+// slower; over 90 of d 768 and 2048 2.3 % less, the worst o at 18432 rows of d 768 39.4 / 40.1 (bound by the residual rows).
+int gemm_f16_tile_rows(int M, int N, int K) {
+  const TileCost& model = kTileCost[pick_tile(M, N, K).tile];
+  if (model.bm < 192) return model.bm;
+  auto cost = [&](int rows) { return (((long long)(M + rows - 1) / rows * (N / 256) + 255) / 256) * (rows + 90); };
+  int best = model.bm;
+  for (int rows = 160; rows <= 256; rows += 32)
+    if (cost(rows) < cost(best) && 40 * cost(rows) < 39 * cost(model.bm)) best = rows;
+  return best;
+}
+
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr int span = Epi::kSpan;
   constexpr bool resid = span == EpiResid::kSpan;
-  switch (gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span)) {
+  int v = gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span);
+  if (v >= V_192x256) {
+    const int rows = gemm_f16_tile_rows(g.M, g.N, g.K);
+    if (rows == 160) return launch<2, 4, 80, 64, 3, 3, 1, false, false, LO8>(g, epi, st);
+    if (rows == 224) return launch<2, 4, 112, 64, 2, 3, 1, false, false, LO8>(g, epi, st);
+    if (rows == 192) v = V_192x256;
+    else if (v == V_192x256) v = form_of_256(g.M, g.N, g.Kw, (long long)((g.M + 255) / 256) * (g.N / 256), LO8, span);
+  }
+  switch (v) {
     case V_64x128_8W:
       if constexpr (span <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
       break;
