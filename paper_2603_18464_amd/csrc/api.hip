@@ -450,6 +450,23 @@ inline bool norm_in_gemm(const vla_config& c, int B, int l) {
   return l == 0 || (long long)c.d_ffn * terms * ((B + 7) / 8) <= budget;
 }
 
+// What a decode step reads comes again in the next one.  Of weights and cached positions (all rows together) the last-level
+// cache holds over a step what fits; when both do not, everything that passes through it normally pushes the rest out before
+// its turn.  The weights stay if they fit, and the keys and values then, or if they alone are too many, are read as data that
+// does not come again.  kLastLevelKeep: a little under 256 MB.  us a decode step, normal / once, weights and keys and values in
+// MB: 12 layers of d 768 170 + 11 280 / 289 (normal), 170 + 85 317 / 302, 170 + 171 366 / 326, 170 + 342 466 / 431; 16 layers 227 +
+// 14 393 / 392; d 2048 16 layers, 1600 + 1200 1077 / 1065, + 3800 2115 / 2042; 8 layers of the 7B shape, 3200 + 80 equal, + 610
+// 1017 / 1003, + 5000 2285 / 2180, + 5700 3155 / 3055.
+constexpr long long kLastLevelKeep = 245'000'000;
+long long layer_weight_bytes(const vla_config& c) {
+  return 2LL * c.n_layers * c.d_model * (4LL * c.d_model + 3LL * c.d_ffn);
+}
+bool kv_read_once(const vla_config& c, long long positions) {
+  const long long weights = layer_weight_bytes(c);
+  const long long kv = positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
+  return weights <= kLastLevelKeep ? weights + kv > kLastLevelKeep : kv > kLastLevelKeep;
+}
+
 // Decode step of the 16-bit path: split-K GEMMs whose partial planes span the whole batch, and one kernel after each
 // GEMM that sums the planes and applies the elementwise step for all rows.  Batches of up to kSkinnyMaxRows rows
 // use the weight-streaming kernel (every wave an independent stream; a 128-row accumulator tile is what a wave's
@@ -459,7 +476,7 @@ inline bool norm_in_gemm(const vla_config& c, int B, int l) {
 // kernel in chunks of 128 rows with the same number of planes (the later chunks find the matrix they re-read in
 // the 256 MB last-level cache).  A few rows take five launches a layer instead of seven, with the same bits: the products
 // that read normalised rows normalise them, the products that add to the residual rows do so.
-int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
+int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positions) {
   const vla_config& c = ctx->cfg;
   const WorkLayout& w = ctx->wl;
   const int d = c.d_model, f = c.d_ffn;
@@ -491,6 +508,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
   };
   f16* const none = nullptr;
   float *y = at<float>(ctx->work, w.norm_y), *sums = at<float>(ctx->work, w.norm_sums);
+  const bool kv_once = kv_read_once(c, positions);
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);      // low-term planes only in two-term layers
@@ -510,7 +528,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st) {
       decode_attention_fused(part, ks_qkv, B, rk.rope_cos, rk.rope_sin, (f16*)rk.k_cache, (f16*)rk.v_cache,
                              (unsigned char*)rk.k_lo, (unsigned char*)rk.v_lo, rk.tok_seq, rk.tok_pos, att, two ? att_lo : none, B, d,
                              c.n_heads, c.head_dim,
-                             kv_pitch(c), st);
+                             kv_pitch(c), kv_once, st);
     }
     {
       ProfScope ps(ctx, FAM_GEMM_O_DECODE, st);
@@ -804,7 +822,9 @@ int do_decode(vla_ctx* ctx, int32_t B, const int32_t* token_ids, float* logits, 
                     norm_in_gemm(c, B, 0) ? at<float>(ctx->work, w.norm_y) : nullptr, at<float>(ctx->work, w.norm_sums), hn,
                     half && two_term_layer(c, 0) ? frag_lo(c, hn, c.d_model) : nullptr, st);
   }
-  if (sizeof(T) == 2) run_layers_decode_f16(ctx, B, st);
+  long long positions = 0;
+  for (int b = 0; b < B; ++b) positions += ctx->len[slots ? slots[b] : b];
+  if (sizeof(T) == 2) run_layers_decode_f16(ctx, B, st, positions);
   else run_layers_f32(ctx, B, true, st);
   if (logits) run_head<T>(ctx, B, nullptr, logits, ld_logits, st);
   HIP_TRY(ctx, hipGetLastError());

@@ -450,7 +450,9 @@ struct QkvPartials {
 // TWO (two-term mode): the cache holds every key / value as a half-precision high term plus a one-byte low term
 // (k_lo / v_lo, same indexing, bf8(16 * lo)); both are streamed and added in float32; the output is written as hi
 // and lo fragments (out_frag_lo).
-template <int HD, bool TWO>
+// ONCE: the step's keys, values and weights together do not stay in the 256 MB last-level cache until the next step (see
+// kv_read_once), so the rows are requested as data that is not read again.  They then leave the caches to what is.
+template <int HD, bool TWO, bool ONCE>
 __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
     f16* __restrict__ k_cache, f16* __restrict__ v_cache,
     unsigned char* __restrict__ k_lo, unsigned char* __restrict__ v_lo, const int32_t* __restrict__ tok_seq,
@@ -488,11 +490,11 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
 #pragma unroll
     for (int u = 0; u < G; ++u) {
       const size_t off = (size_t)min(row_of(it0 + u), last_global) * HD + c * 8;
-      kv[s][u] = *(const f16x8*)(kb + off);
-      vv[s][u] = *(const f16x8*)(vb + off);
+      kv[s][u] = load_once<ONCE>((const f16x8*)(kb + off));
+      vv[s][u] = load_once<ONCE>((const f16x8*)(vb + off));
       if constexpr (TWO) {
-        kl[s][u] = *(const i32x2*)(kbl + off);
-        vl[s][u] = *(const i32x2*)(vbl + off);
+        kl[s][u] = load_once<ONCE>((const i32x2*)(kbl + off));
+        vl[s][u] = load_once<ONCE>((const i32x2*)(vbl + off));
       }
     }
   };
@@ -685,12 +687,17 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
 void decode_attention_fused(const float* part, int ksplit, int part_rows, const float* rope_cos, const float* rope_sin,
                             f16* k_cache, f16* v_cache, unsigned char* k_lo, unsigned char* v_lo, const int32_t* tok_seq,
                             const int32_t* tok_pos, f16* out_frag, f16* out_frag_lo, int B, int d_model, int n_heads,
-                            int head_dim, int max_seq, hipStream_t st) {
+                            int head_dim, int max_seq, bool kv_once, hipStream_t st) {
   const dim3 grid(B, n_heads);
   const QkvPartials qp{part, ksplit, part_rows, rope_cos, rope_sin};
-#define VLA_DEC_ATT(HDV, TWOV)                                                                                     \
-  hipLaunchKernelGGL((decode_attention_kernel<HDV, TWOV>), grid, dim3(512), 0, st, k_cache, v_cache,              \
+#define VLA_DEC_ATT_ONCE(HDV, TWOV, ONCEV)                                                                         \
+  hipLaunchKernelGGL((decode_attention_kernel<HDV, TWOV, ONCEV>), grid, dim3(512), 0, st, k_cache, v_cache,       \
                      k_lo, v_lo, tok_seq, tok_pos, out_frag, out_frag_lo, d_model, n_heads, max_seq, qp)
+#define VLA_DEC_ATT(HDV, TWOV)                      \
+  do {                                              \
+    if (kv_once) VLA_DEC_ATT_ONCE(HDV, TWOV, true); \
+    else VLA_DEC_ATT_ONCE(HDV, TWOV, false);        \
+  } while (0)
   if (k_lo) {
     if (head_dim == 128) VLA_DEC_ATT(128, true);
     else VLA_DEC_ATT(64, true);
@@ -699,6 +706,7 @@ void decode_attention_fused(const float* part, int ksplit, int part_rows, const 
     else VLA_DEC_ATT(64, false);
   }
 #undef VLA_DEC_ATT
+#undef VLA_DEC_ATT_ONCE
 }
 
 void attention_rows_f32(const float* q, const float* k_cache, const float* v_cache, const int32_t* tok_seq,

@@ -171,6 +171,13 @@ __device__ __forceinline__ void rope_pair(float lo, float hi, float cs, float sn
   b = __fmaf_rn(hi, cs, __fmul_rn(lo, sn));
 }
 
+// *p, and with ONCE as data that is not read again before the caches have turned over: it is the first to leave them.
+template <bool ONCE, class V>
+__device__ __forceinline__ V load_once(const V* p) {
+  if constexpr (ONCE) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 // C = A * W^T with fused epilogues (f16 MFMA, fp32 accumulation).
 void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st);           // x += C
 // silu(gate)*up; lo_mode 1: also half-precision low terms at column f + j; 2: 8-bit low terms, bytes behind the f halves
@@ -257,10 +264,11 @@ void reduce_swiglu(const float* part, int ksplit, int plane_rows, int prow0, int
 
 // Decode attention of the 16-bit path (one query per row of the step); output in fragment order.  k_lo / v_lo
 // != nullptr: two-term mode (low terms of the cache, output also as low-term fragments out_frag_lo).
+// kv_once: the cached rows do not stay in the last-level cache until the next step reads them.
 void decode_attention_fused(const float* part, int ksplit, int part_rows, const float* rope_cos, const float* rope_sin,
                             f16* k_cache, f16* v_cache, unsigned char* k_lo, unsigned char* v_lo, const int32_t* tok_seq,
                             const int32_t* tok_pos, f16* out_frag, f16* out_frag_lo, int B, int d_model, int n_heads,
-                            int head_dim, int max_seq, hipStream_t st);
+                            int head_dim, int max_seq, bool kv_once, hipStream_t st);
 
 // Action head: final RMSNorm + action rows of the LM head -> logits [B, A] float32.
 template <class T>
