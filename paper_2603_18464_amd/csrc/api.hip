@@ -461,6 +461,12 @@ constexpr long long kLastLevelKeep = 245'000'000;
 long long layer_weight_bytes(const vla_config& c) {
   return 2LL * c.n_layers * c.d_model * (4LL * c.d_model + 3LL * c.d_ffn);
 }
+// The decode products likewise, where the weights alone are too many (and one launch takes all rows: a matrix read chunk by
+// chunk comes again).  What gains most is what the weights then leave in the cache: the keys and values of a few sequences, the
+// partial planes, the rows.  us a decode step, normal / once: 6 layers of the 7B shape, 1 row 608 / 562, 4 rows 649 / 606, 16 rows
+// 737 / 711, 32 rows 904 / 891, 64 rows 1289 / 1274, 128 rows 2106 / 2077; 5 of d 5120 at 1 row 742 / 684; 16 of d 2048 754 /
+// 719; 24 of d 768 (340 MB) 631 / 596, 20 (283 MB) 514 / 500, 16 (227 MB) 393 / 402, 12 (170 MB) 280 / 305 (normal).
+bool weights_read_once(const vla_config& c) { return layer_weight_bytes(c) > kLastLevelKeep; }
 bool kv_read_once(const vla_config& c, long long positions) {
   const long long weights = layer_weight_bytes(c);
   const long long kv = positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
@@ -486,6 +492,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
   f16* act = at<f16>(ctx->work, w.act);
   f16 *hn_lo = frag_lo(c, hn, d), *att_lo = frag_lo(c, att, d), *act_lo = frag_lo(c, act, f);
   float* part = ctx->part_override ? ctx->part_override : at<float>(ctx->work, w.part);
+  const bool w_once = weights_read_once(c);
   // the tiled split-K kernel takes the chunks of more than 128 rows
   auto tiled = [&](int N, int K) { return B > kSkinnyMaxRows && splitk_gemm_fits(256, N, K); };
   auto planes = [&](int N, int K) { return tiled(N, K) ? splitk_ksplit(N, K) : skinny_ksplit(N, K); };
@@ -503,7 +510,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
     for (int r0 = tiled(N, K) ? gemm_tiled(a, a_lo, w_off, N, K, ks) : 0; r0 < B; r0 += kSkinnyMaxRows) {
       const int m = B - r0 < kSkinnyMaxRows ? B - r0 : kSkinnyMaxRows;
       skinny_gemm(frag_rows(a, r0, K), a_lo ? frag_rows(a_lo, r0, K) : nullptr, at<f16>(ctx->arena, w_off), part, m, N, K,
-                  ks, B, r0, st);
+                  ks, B, r0, w_once && B <= kSkinnyMaxRows, st);
     }
   };
   f16* const none = nullptr;
@@ -517,7 +524,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
     {
       ProfScope ps(ctx, FAM_GEMM_QKV_DECODE, st);
       if (norm)
-        skinny_norm_gemm(y, sums, c.rms_eps, two, at<f16>(ctx->arena, lw.w_qkv), part, B, 3 * d, d, ks_qkv, st);
+        skinny_norm_gemm(y, sums, c.rms_eps, two, at<f16>(ctx->arena, lw.w_qkv), part, B, 3 * d, d, ks_qkv, w_once, st);
       else
         gemm(hn, two ? hn_lo : none, lw.w_qkv, 3 * d, d, ks_qkv);
     }
@@ -534,7 +541,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
       ProfScope ps(ctx, FAM_GEMM_O_DECODE, st);
       if (norm) {
         skinny_resid(att, two ? att_lo : none, at<f16>(ctx->arena, lw.w_o), x, at<float>(ctx->arena, lw.g_ffn), y, sums, B, d, d,
-                     ks_o, st);
+                     ks_o, w_once, st);
       } else {
         gemm(att, two ? att_lo : none, lw.w_o, d, d, ks_o);
         reduce_resid_norm(part, ks_o, B, 0, B, d, x, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, hn, two ? hn_lo : none, 0,
@@ -544,7 +551,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
     if (norm) {
       ProfScope ps(ctx, FAM_GEMM_GATEUP_DECODE, st);
       skinny_norm_swiglu(y, sums, c.rms_eps, two, at<f16>(ctx->arena, lw.w_gu), act, two ? act_lo : none, B,
-                         f, d, st);
+                         f, d, w_once, st);
     } else {
       ProfScope ps(ctx, FAM_GEMM_GATEUP_DECODE, st);
       // chunks of at most 128 rows finish the elementwise step inside the product; the tiled kernel's planes need a launch
@@ -556,13 +563,13 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
       for (; r0 < B; r0 += kSkinnyMaxRows)
         skinny_swiglu(frag_rows(hn, r0, d), two ? frag_rows(hn_lo, r0, d) : none, at<f16>(ctx->arena, lw.w_gu),
                       frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : none,
-                      B - r0 < kSkinnyMaxRows ? B - r0 : kSkinnyMaxRows, f, d, st);
+                      B - r0 < kSkinnyMaxRows ? B - r0 : kSkinnyMaxRows, f, d, w_once && B <= kSkinnyMaxRows, st);
     }
     {
       ProfScope ps(ctx, FAM_GEMM_DOWN_DECODE, st);
       const float* next_gain = l + 1 < c.n_layers ? at<float>(ctx->arena, ctx->al.layers[l + 1].g_attn) : nullptr;
       if (norm_next) {
-        skinny_resid(act, two ? act_lo : none, at<f16>(ctx->arena, lw.w_down), x, next_gain, y, sums, B, d, f, ks_dn, st);
+        skinny_resid(act, two ? act_lo : none, at<f16>(ctx->arena, lw.w_down), x, next_gain, y, sums, B, d, f, ks_dn, w_once, st);
       } else {
         gemm(act, two ? act_lo : none, lw.w_down, d, f, ks_dn);
         reduce_resid_norm(part, ks_dn, B, 0, B, d, x, next_gain, c.rms_eps, hn, two_next ? hn_lo : none, 0, st);
@@ -598,17 +605,18 @@ void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_nee
                                         (two ? max_rows(c) * (size_t)f * sizeof(f16) : 0) +
                                         align_up(pad32 * f * sizeof(f16)));
   const int ks_o = skinny_ksplit(d, d), ks_dn = skinny_ksplit(d, f);
+  const bool w_once = weights_read_once(c) && n_need <= kSkinnyMaxRows;
   const int chunk = (int)(part_rows(c) < (size_t)kSkinnyMaxRows ? part_rows(c) : (size_t)kSkinnyMaxRows);
   gather_tail(att, two_pitch(two, d), lo8(two, d), x, need, n_need, d, att_frag, att_frag_lo, x_c, st);
   for (int r0 = 0; r0 < n_need; r0 += chunk) {
     const int m = n_need - r0 < chunk ? n_need - r0 : chunk;
     skinny_gemm(frag_rows(att_frag, r0, d), two ? frag_rows(att_frag_lo, r0, d) : nullptr, at<f16>(ctx->arena, lw.w_o),
-                part, m, d, d, ks_o, m, 0, st);
+                part, m, d, d, ks_o, m, 0, w_once, st);
     reduce_resid_norm(part, ks_o, m, 0, m, d, x_c, at<float>(ctx->arena, lw.g_ffn), c.rms_eps, hn, hn_lo, r0, st);
     skinny_swiglu(frag_rows(hn, r0, d), two ? frag_rows(hn_lo, r0, d) : nullptr, at<f16>(ctx->arena, lw.w_gu),
-                  frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : nullptr, m, f, d, st);
+                  frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : nullptr, m, f, d, w_once, st);
     skinny_gemm(frag_rows(act, r0, f), two ? frag_rows(act_lo, r0, f) : nullptr, at<f16>(ctx->arena, lw.w_down), part, m, d,
-                f, ks_dn, m, 0, st);
+                f, ks_dn, m, 0, w_once, st);
     reduce_resid_norm(part, ks_dn, m, 0, m, d, x_c, nullptr, c.rms_eps, hn, nullptr, r0, st);
   }
   scatter_tail(x_c, need, n_need, d, x, st);

@@ -229,21 +229,22 @@ int skinny_ksplit(int N, int K);
 constexpr int kSkinnyMaxRows = 128;   // most rows of one weight-streaming GEMM launch
 // Two-term mode: *_lo arguments hold the low terms f16(a - f16(a)) in the same fragment order (nullptr: single-term).
 // The M rows of a launch are rows prow0 .. prow0 + M - 1 of partial planes of plane_rows rows each.
+// w_once: the weights do not stay in the caches until they are read again.
 void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int ksplit,
-                 int plane_rows, int prow0, hipStream_t st);
+                 int plane_rows, int prow0, bool w_once, hipStream_t st);
 // The gate/up product of at most kSkinnyMaxRows rows with its elementwise step, straight to fragments (K >= 128).
 void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
-                   int K, hipStream_t st);
+                   int K, bool w_once, hipStream_t st);
 // The same products for at most kNormRows rows that take the RMSNorm of their rows with them (two: as two terms), from y = x *
 // gain (float32, fragment order) and sums of squares [M][d / 16]; and the O / down product that adds to the residual rows x
 // [M, N] itself, with the sums of skinny_gemm with kgroups planes and reduce_resid_norm, and with a gain leaves y and sums.
 constexpr int kNormRows = 32;
 void skinny_norm_gemm(const float* y, const float* sums, float eps, bool two, const f16* Wp, float* part, int M, int N, int d,
-                      int kgroups, hipStream_t st);
+                      int kgroups, bool w_once, hipStream_t st);
 void skinny_norm_swiglu(const float* y, const float* sums, float eps, bool two, const f16* Wp, f16* act_frag, f16* act_frag_lo,
-                        int M, int f, int d, hipStream_t st);
+                        int M, int f, int d, bool w_once, hipStream_t st);
 void skinny_resid(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums, int M,
-                  int N, int K, int kgroups, hipStream_t st);
+                  int N, int K, int kgroups, bool w_once, hipStream_t st);
 // The same product for up to 256 rows on the tiled kernel (256 rows x 256 or 64 columns a workgroup), split over `ksplit`
 // K slices (one partial plane each): activations go through LDS once per workgroup instead of once per wave, which is what
 // a large batch needs to stream every weight once at full rate.  Needs N % 256 == 0 and K % 64 == 0 (splitk_gemm_fits).

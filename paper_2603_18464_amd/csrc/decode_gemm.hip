@@ -13,6 +13,8 @@
 //     workgroup add their partial tiles through LDS; one plane part[kg][M][N] is written per group and
 //     the following reduce kernel adds the planes in a fixed order (deterministic) and applies the
 //     layer's elementwise step: RoPE + KV append, residual add + RMSNorm for the next GEMM, or SwiGLU.
+#include <type_traits>
+
 #include "common.h"
 
 namespace vla {
@@ -43,6 +45,16 @@ __device__ __forceinline__ void settle(f32x16 (&p)[MT], f32x16 (&q)[MT]) {
   else VLA_SETTLE("+v"(p[0]), "+v"(q[0]), "+v"(p[1]), "+v"(q[1]), "+v"(p[2]), "+v"(q[2]), "+v"(p[3]), "+v"(q[3]));
 #undef VLA_SETTLE
 #endif
+}
+
+// launch(two, once) with the flags as compile-time values.  once: the weights are read as data that does not come again (see
+// weights_read_once).
+template <class F>
+static void by_flags(bool two, bool once, F&& launch) {
+  if (two && once) launch(std::true_type{}, std::true_type{});
+  else if (two) launch(std::true_type{}, std::false_type{});
+  else if (once) launch(std::false_type{}, std::true_type{});
+  else launch(std::false_type{}, std::false_type{});
 }
 
 // ---- RMS statistics of a float32 row ---------------------------------------------------------------------------
@@ -78,7 +90,7 @@ __device__ __forceinline__ float norm_scaled(float y, float factor) {
 // used for the hi and the lo activation fragments (weights are read once, the MFMA work doubles).
 // D: ring depth.  Rows of A past M - 1 are read from row M - 1: their results are not used, and a few rows then cost the
 // L2 a few lines per fragment instead of sixteen.
-template <int MT, int D, bool TWO>
+template <int MT, int D, bool TWO, bool ONCE>
 __device__ __forceinline__ void stream_slice(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
                                              const f16* __restrict__ Wp, int nbp, int kb_begin, int kb_end, int KB16,
                                              int M, f32x16 (&acc0)[MT], f32x16 (&acc1)[MT]) {
@@ -110,8 +122,8 @@ __device__ __forceinline__ void stream_slice(const f16* __restrict__ Af, const f
   constexpr int NA = TWO ? 2 * MT : MT;                    // activation fragments per k-step: hi (then lo)
   f16x8 wq[D][2], aq[D][NA];
   auto load_stage = [&](int s, size_t kb) {
-    wq[s][0] = *(const f16x8*)(w0 + kb * 512 + at_lane);
-    wq[s][1] = *(const f16x8*)(w1 + kb * 512 + at_lane);
+    wq[s][0] = load_once<ONCE>((const f16x8*)(w0 + kb * 512 + at_lane));
+    wq[s][1] = load_once<ONCE>((const f16x8*)(w1 + kb * 512 + at_lane));
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const size_t at = ((size_t)mt * KB16 + kb) * 512;
@@ -185,7 +197,7 @@ __device__ __forceinline__ int acc_at(int m, int c) {
 }
 
 // Output rows: the M rows of this launch are rows row0 .. row0 + M - 1 of planes of plane_rows rows each.
-template <int MT, int D, bool TWO>
+template <int MT, int D, bool TWO, bool ONCE>
 __global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_kernel(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
                                                           const f16* __restrict__ Wp, float* __restrict__ part, int M,
                                                           int N, int K, int kgroups, int plane_rows, int row0) {
@@ -204,7 +216,7 @@ __global__ __launch_bounds__(256, (MT <= 2 || !TWO) ? 2 : 1) void skinny_gemm_ke
   // two arrays (one per 32-column block) rather than one: the compiler splits an array into scalars only up to a
   // bounded number of accesses, and an unsplit accumulator array would live in scratch memory
   f32x16 acc0[MT], acc1[MT];
-  stream_slice<MT, D, TWO>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
+  stream_slice<MT, D, TWO, ONCE>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
   if (wave >= 2) put_acc<MT>(red, wave - 2, acc0, acc1);
   __syncthreads();
   if (wave < 2) add_acc<MT>(red, wave, acc0, acc1);         // w0 += w2, w1 += w3
@@ -268,7 +280,7 @@ __device__ __forceinline__ void swiglu_finish(float* red, int wave, f32x16 (&acc
 // Two workgroups per compute unit up to 32 rows, and with single-term operands up to 64 (the register budget behind the
 // ring depths): all 344 of the 7B matrix are then resident at once.  From 65 rows on the LDS (96 or 128 KiB) holds one,
 // and 344 of them are two rounds on 256 compute units: single-term 45.5 us at 64 rows, 66.7 at 128.
-template <int MT, int D, bool TWO>
+template <int MT, int D, bool TWO, bool ONCE>
 __global__ __launch_bounds__(512, MT == 1 || (MT == 2 && !TWO) ? 4 : 2) void skinny_swiglu_kernel(const f16* __restrict__ Af,
                                                                              const f16* __restrict__ Af_lo,
                                                                              const f16* __restrict__ Wp,
@@ -281,19 +293,19 @@ __global__ __launch_bounds__(512, MT == 1 || (MT == 2 && !TWO) ? 4 : 2) void ski
   const int kb_begin = (int)((long long)wave * KB16 / 8);
   const int kb_end = (int)((long long)(wave + 1) * KB16 / 8);      // non-empty: K >= 128
   f32x16 acc0[MT], acc1[MT];
-  stream_slice<MT, D, TWO>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
+  stream_slice<MT, D, TWO, ONCE>(Af, Af_lo, Wp, nbp, kb_begin, kb_end, KB16, M, acc0, acc1);
   swiglu_finish<MT>(red, wave, acc0, acc1, act_frag, act_frag_lo, M, f, nbp);
 }
 
 // M <= kSkinnyMaxRows rows (fragment blocks start at the first of them); Wp: the fused gate/up matrix [2 f, K].
 // act_frag_lo may be given with single-term operands and the other way round.
 void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* act_frag, f16* act_frag_lo, int M, int f,
-                   int K, hipStream_t st) {
+                   int K, bool w_once, hipStream_t st) {
   const dim3 grid(f / 32), block(512);
   const int MT = (M + 31) / 32;
-#define VLA_SKINNY_LAUNCH(MTV, DV, TWOV)                                                                          \
+#define VLA_SKINNY_LAUNCH(MTV, DV, TWOV, ONCEV)                                                                   \
   {                                                                                                               \
-    auto kern = skinny_swiglu_kernel<MTV, DV, TWOV>;                                                              \
+    auto kern = skinny_swiglu_kernel<MTV, DV, TWOV, ONCEV>;                                                       \
     constexpr size_t smem = (size_t)4 * MTV * 32 * 64 * sizeof(float);                                            \
     static bool attr_set = false;                                                                                 \
     if (!attr_set) {                                                                                              \
@@ -302,10 +314,12 @@ void skinny_swiglu(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, f16* ac
     }                                                                                                             \
     hipLaunchKernelGGL(kern, grid, block, smem, st, Afrag, Afrag_lo, Wp, act_frag, act_frag_lo, M, f, K);         \
   }
-#define VLA_SKINNY_CASE(MTV, DV, DV2)                  \
-  case MTV:                                            \
-    if (Afrag_lo) VLA_SKINNY_LAUNCH(MTV, DV2, true)    \
-    else VLA_SKINNY_LAUNCH(MTV, DV, false)             \
+#define VLA_SKINNY_CASE(MTV, DV, DV2)                            \
+  case MTV:                                                      \
+    if (Afrag_lo && w_once) VLA_SKINNY_LAUNCH(MTV, DV2, true, true) \
+    else if (Afrag_lo) VLA_SKINNY_LAUNCH(MTV, DV2, true, false)  \
+    else if (w_once) VLA_SKINNY_LAUNCH(MTV, DV, false, true)     \
+    else VLA_SKINNY_LAUNCH(MTV, DV, false, false)                \
     break;
   switch (MT) {
     VLA_SKINNY_CASE(1, 6, 4)
@@ -372,7 +386,7 @@ __device__ __forceinline__ float row_factor(const NormRows& in, float* factors, 
 
 // stream_slice for at most 32 rows that are normalised on the way: a lane's eight elements of a k-block are read as float32,
 // scaled by its row's factor and rounded.  D: ring depth.
-template <int D, bool TWO>
+template <int D, bool TWO, bool ONCE>
 __device__ __forceinline__ void norm_stream_slice(const NormRows& in, const f16* __restrict__ Wp, int nbp, int kb_begin,
                                                   int kb_end, float* factors, f32x16& acc0, f32x16& acc1) {
   const unsigned lane = threadIdx.x & 63, at_lane = lane * 8;
@@ -390,8 +404,8 @@ __device__ __forceinline__ void norm_stream_slice(const NormRows& in, const f16*
   f32x4 yq[D][2];
   auto load_stage = [&](int s, int i) {
     const size_t at = kb_of(i) * 512;
-    wq[s][0] = *(const f16x8*)(w0 + at + at_lane);
-    wq[s][1] = *(const f16x8*)(w1 + at + at_lane);
+    wq[s][0] = load_once<ONCE>((const f16x8*)(w0 + at + at_lane));
+    wq[s][1] = load_once<ONCE>((const f16x8*)(w1 + at + at_lane));
     yq[s][0] = *(const f32x4*)(in.y + at + at_row);
     yq[s][1] = *(const f32x4*)(in.y + at + at_row + 4);
   };
@@ -437,7 +451,7 @@ __device__ __forceinline__ void norm_stream_slice(const NormRows& in, const f16*
 }
 
 // skinny_gemm_kernel for at most 32 rows with the norm of its rows in front.
-template <int D, bool TWO>
+template <int D, bool TWO, bool ONCE>
 __global__ __launch_bounds__(256, 2) void skinny_norm_gemm_kernel(NormRows in, const f16* __restrict__ Wp,
                                                                   float* __restrict__ part, int N, int kgroups) {
   __shared__ float red[2 * 32 * 64];
@@ -447,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void skinny_norm_gemm_kernel(NormRows in, c
   const int nbp = blockIdx.x % NP, kg = blockIdx.x / NP;
   const int slices = 4 * kgroups, sl = 4 * kg + wave;
   f32x16 acc0[1], acc1[1];
-  norm_stream_slice<D, TWO>(in, Wp, nbp, (int)((long long)sl * KB16 / slices), (int)((long long)(sl + 1) * KB16 / slices),
+  norm_stream_slice<D, TWO, ONCE>(in, Wp, nbp, (int)((long long)sl * KB16 / slices), (int)((long long)(sl + 1) * KB16 / slices),
                                factors, acc0[0], acc1[0]);
   if (wave >= 2) put_acc<1>(red, wave - 2, acc0, acc1);
   __syncthreads();
@@ -465,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void skinny_norm_gemm_kernel(NormRows in, c
 }
 
 // skinny_swiglu_kernel for at most 32 rows with the norm of its rows in front.  Two workgroups per compute unit.
-template <int D, bool TWO>
+template <int D, bool TWO, bool ONCE>
 __global__ __launch_bounds__(512, 4) void skinny_norm_swiglu_kernel(NormRows in, const f16* __restrict__ Wp,
                                                                     f16* __restrict__ act_frag, f16* __restrict__ act_frag_lo,
                                                                     int f) {
@@ -474,7 +488,7 @@ __global__ __launch_bounds__(512, 4) void skinny_norm_swiglu_kernel(NormRows in,
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KB16 = in.d >> 4;
   f32x16 acc0[1], acc1[1];
-  norm_stream_slice<D, TWO>(in, Wp, blockIdx.x, (int)((long long)wave * KB16 / 8), (int)((long long)(wave + 1) * KB16 / 8),
+  norm_stream_slice<D, TWO, ONCE>(in, Wp, blockIdx.x, (int)((long long)wave * KB16 / 8), (int)((long long)(wave + 1) * KB16 / 8),
                                factors, acc0[0], acc1[0]);
   swiglu_finish<1>(red, wave, acc0, acc1, act_frag, act_frag_lo, in.M, f, blockIdx.x);
 }
@@ -507,7 +521,7 @@ __device__ __forceinline__ f16x8 odd_sixteens(const f16x8& v) {
 // the planes and the reduce kernel: N 4096 K 4096 8.7 / 12.4, K 11008 17.4 / 20.4, N 768 K 768 3.4 / 5.9, K 2048 4.4 / 6.4; at
 // 32 rows 10.8 / 12.9, 22.8 / 21.4, 3.7 / 6.8, 5.1 / 7.1.
 // D: pairs of k-blocks in flight a wave.
-template <int D, bool TWO, bool FEW>
+template <int D, bool TWO, bool FEW, bool ONCE>
 __global__ __launch_bounds__(1024) void skinny_resid_kernel(const f16* __restrict__ Af, const f16* __restrict__ Af_lo,
                                                             const f16* __restrict__ Wp, float* __restrict__ x,
                                                             const float* __restrict__ gain, float* __restrict__ y,
@@ -539,7 +553,7 @@ __global__ __launch_bounds__(1024) void skinny_resid_kernel(const f16* __restric
   f16x8 wq[D], aq[D][FEW ? 1 : 2], al[TWO ? D : 1][FEW ? 1 : 2];
   auto load_pair = [&](int s, int p) {
     const unsigned at = kb_at(2 * p + odd);
-    wq[s] = *(const f16x8*)(w0 + at + at_w);
+    wq[s] = load_once<ONCE>((const f16x8*)(w0 + at + at_w));
 #pragma unroll
     for (int h = 0; h < (FEW ? 1 : 2); ++h) {
       const unsigned k = (FEW ? at : kb_at(2 * p + h)) + at_a;
@@ -610,31 +624,40 @@ __global__ __launch_bounds__(1024) void skinny_resid_kernel(const f16* __restric
 }
 
 void skinny_norm_gemm(const float* y, const float* sums, float eps, bool two, const f16* Wp, float* part, int M, int N, int d,
-                      int kgroups, hipStream_t st) {
+                      int kgroups, bool w_once, hipStream_t st) {
   const NormRows in{y, sums, eps, M, d};
   const dim3 grid((N / 64) * kgroups), block(256);
-  if (two) hipLaunchKernelGGL((skinny_norm_gemm_kernel<6, true>), grid, block, 0, st, in, Wp, part, N, kgroups);
-  else hipLaunchKernelGGL((skinny_norm_gemm_kernel<6, false>), grid, block, 0, st, in, Wp, part, N, kgroups);
+  auto launch = [&](auto TWO, auto ONCE) {
+    hipLaunchKernelGGL((skinny_norm_gemm_kernel<6, decltype(TWO)::value, decltype(ONCE)::value>), grid, block, 0, st, in, Wp, part,
+                       N, kgroups);
+  };
+  by_flags(two, w_once, launch);
 }
 void skinny_norm_swiglu(const float* y, const float* sums, float eps, bool two, const f16* Wp, f16* act_frag, f16* act_frag_lo,
-                        int M, int f, int d, hipStream_t st) {
+                        int M, int f, int d, bool w_once, hipStream_t st) {
   const NormRows in{y, sums, eps, M, d};
   const dim3 grid(f / 32), block(512);
-  if (two) hipLaunchKernelGGL((skinny_norm_swiglu_kernel<3, true>), grid, block, 0, st, in, Wp, act_frag, act_frag_lo, f);
-  else hipLaunchKernelGGL((skinny_norm_swiglu_kernel<3, false>), grid, block, 0, st, in, Wp, act_frag, act_frag_lo, f);
+  auto launch = [&](auto TWO, auto ONCE) {
+    hipLaunchKernelGGL((skinny_norm_swiglu_kernel<3, decltype(TWO)::value, decltype(ONCE)::value>), grid, block, 0, st, in, Wp,
+                       act_frag, act_frag_lo, f);
+  };
+  by_flags(two, w_once, launch);
 }
 template <int D, bool TWO, bool FEW>
-static void launch_resid(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums,
+static void launch_resid(bool w_once, const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums,
                          int M, int N, int K, int kgroups, hipStream_t st) {
-  hipLaunchKernelGGL((skinny_resid_kernel<D, TWO, FEW>), dim3(N / 16), dim3(256 * kgroups),
-                     (size_t)4 * kgroups * 16 * 64 * sizeof(float), st, Afrag, Afrag_lo, Wp, x, gain, y, sums, M, N, K);
+  auto launch = [&](auto, auto ONCE) {
+    hipLaunchKernelGGL((skinny_resid_kernel<D, TWO, FEW, decltype(ONCE)::value>), dim3(N / 16), dim3(256 * kgroups),
+                       (size_t)4 * kgroups * 16 * 64 * sizeof(float), st, Afrag, Afrag_lo, Wp, x, gain, y, sums, M, N, K);
+  };
+  by_flags(false, w_once, launch);
 }
 // Slices of up to eight k-blocks (the products of a small model) take two pairs in flight, which start sooner: N 768 K 768
 // 3.3 us with two, 3.5 with four, K 2048 4.3 and 4.5; others four (three where the registers hold 32 rows of both terms).
 void skinny_resid(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums, int M,
-                  int N, int K, int kgroups, hipStream_t st) {
+                  int N, int K, int kgroups, bool w_once, hipStream_t st) {
   const bool brief = K / 16 <= 4 * kgroups * 8;
-#define VLA_RESID(D, TWO, FEW) launch_resid<D, TWO, FEW>(Afrag, Afrag_lo, Wp, x, gain, y, sums, M, N, K, kgroups, st)
+#define VLA_RESID(D, TWO, FEW) launch_resid<D, TWO, FEW>(w_once, Afrag, Afrag_lo, Wp, x, gain, y, sums, M, N, K, kgroups, st)
   if (M <= 16) {
     if (Afrag_lo) { if (brief) VLA_RESID(2, true, true); else VLA_RESID(4, true, true); }
     else { if (brief) VLA_RESID(2, false, true); else VLA_RESID(4, false, true); }
@@ -660,13 +683,16 @@ int skinny_ksplit(int N, int K) {
 
 // M <= kSkinnyMaxRows rows (fragment blocks Afrag / Afrag_lo start at the first of them); Afrag_lo != nullptr: two-term.
 void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* part, int M, int N, int K, int kgroups,
-                 int plane_rows, int row0, hipStream_t st) {
+                 int plane_rows, int row0, bool w_once, hipStream_t st) {
+  // (read once, matrices in MB, 32 to 64 rows: 14 11.4 -> 12.0 us, 25 12.5 -> 13.2 and 14.6 -> 15.6, 34 19.1 -> 19.9, 56 18.9 ->
+  // 18.7, 90 32.2 -> 30.4, 101 34.6 -> 33.9, 141 60.4 -> 56.5)
+  w_once = w_once && 2LL * N * K >= 64'000'000;
   const dim3 grid((N / 64) * kgroups), block(256);
   const int MT = (M + 31) / 32;
   const size_t smem = (size_t)2 * MT * 32 * 64 * sizeof(float);
-#define VLA_SKINNY_LAUNCH(MTV, DV, TWOV)                                                                          \
+#define VLA_SKINNY_LAUNCH(MTV, DV, TWOV, ONCEV)                                                                   \
   {                                                                                                               \
-    auto kern = skinny_gemm_kernel<MTV, DV, TWOV>;                                                                \
+    auto kern = skinny_gemm_kernel<MTV, DV, TWOV, ONCEV>;                                                         \
     static bool attr_set = false;                                                                                 \
     if (!attr_set) {                                                                                              \
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);        \
@@ -674,10 +700,12 @@ void skinny_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
     }                                                                                                             \
     hipLaunchKernelGGL(kern, grid, block, smem, st, Afrag, Afrag_lo, Wp, part, M, N, K, kgroups, plane_rows, row0); \
   }
-#define VLA_SKINNY_CASE(MTV, DV, DV2)                  \
-  case MTV:                                            \
-    if (Afrag_lo) VLA_SKINNY_LAUNCH(MTV, DV2, true)    \
-    else VLA_SKINNY_LAUNCH(MTV, DV, false)             \
+#define VLA_SKINNY_CASE(MTV, DV, DV2)                            \
+  case MTV:                                                      \
+    if (Afrag_lo && w_once) VLA_SKINNY_LAUNCH(MTV, DV2, true, true) \
+    else if (Afrag_lo) VLA_SKINNY_LAUNCH(MTV, DV2, true, false)  \
+    else if (w_once) VLA_SKINNY_LAUNCH(MTV, DV, false, true)     \
+    else VLA_SKINNY_LAUNCH(MTV, DV, false, false)                \
     break;
   switch (MT) {     // ring depth: as deep as the registers allow (weights 2 + activations MT or 2 MT fragments per stage)
     VLA_SKINNY_CASE(1, 8, 6)

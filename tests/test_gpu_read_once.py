@@ -33,3 +33,40 @@ def test_the_same_bits_on_both_sides(hd, fast, batches):
         assert (2 * layers * d * (4 * d + 3 * 192) + kv > KEEP) == (B == batches[1])
     assert np.isfinite(got[0]).all()
     assert np.array_equal(got[0], got[1][:batches[0]])
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("hd,d,f,two_layers", [(128, 4096, 9728, 1), (64, 4096, 9728, 4), (128, 128, 192, 1)])
+def test_weights_read_once(hd, d, f, two_layers):
+    """Weights that outgrow the last-level cache: a decode step's rows have the same bits in batches of every form of its
+    products (normalising ones, those with planes above and below the size that takes part, one to four blocks of rows), which
+    are the oracle's.  The small model reads its weights as ever."""
+    from oracle import vla_oracle as O
+    from paper_2603_18464_amd import VlaPolicy
+    shape = W.PolicyShape(2, d, d // hd, hd, f, 600, n_action_bins=40, dtype="bf16")
+    weights = W.make_weights(shape, 5)
+    assert (2 * 2 * d * (4 * d + 3 * f) > KEEP) == (d == 4096)
+    wl = W.Workload("Rw", 98, shape, batch=3, n_patches=9, instr_len=(0, 0), n_tokens=2)
+    few = ragged_obs(wl, [9, 4, 7], [0] * 3, seed=22)
+    pol = VlaPolicy(shape, 128, 16, 128 * 9, two_term_layers=two_layers)
+    pol.load_weights(weights)
+    ref = None
+    for B in (3, 17, 33, 70, 128):
+        reps = [b % 3 for b in range(B)]
+        cu = few["cu_patch"]
+        obs = {"patch_emb": np.concatenate([few["patch_emb"][cu[r]:cu[r + 1]] for r in reps]),
+               "cu_patch": np.concatenate([[0], np.cumsum([cu[r + 1] - cu[r] for r in reps])]).astype(np.int32),
+               "instr_ids": few["instr_ids"], "cu_instr": np.zeros(B + 1, dtype=np.int32)}
+        dev = P.device_inputs(pol, obs)
+        out = pol.policy_step(dev["patch_emb"], obs["cu_patch"], dev["instr_ids"], obs["cu_instr"], 2, want_logits=True)
+        got = out["logits"].cpu().numpy()
+        if ref is None:
+            ref = got
+            ora = O.OraclePolicy(shape, weights).policy_step(P.split_obs(few, range(3))[0], P.split_obs(few, range(3))[1], 2, mode="cached")
+            assert np.abs(ref[:, 0] - ora["logits"][:, 0]).max() <= P.tolerances(wl)["logit"]
+            same = out["tokens"].cpu().numpy()[:, 0] == ora["tokens"][:, 0]
+            assert same.any()                              # the step behind an equal token is comparable
+            assert np.abs(ref[same, 1] - ora["logits"][same, 1]).max() <= P.tolerances(wl)["logit"]
+        for b in range(B):
+            assert np.array_equal(got[b], ref[b % 3]), (B, b)
+    pol.close()
