@@ -279,7 +279,7 @@ __device__ __forceinline__ void swiglu_finish(float* red, int wave, f32x16 (&acc
 // launch behind it.  Eight waves, slice w each.
 // Two workgroups per compute unit up to 32 rows, and with single-term operands up to 64 (the register budget behind the
 // ring depths): all 344 of the 7B matrix are then resident at once.  From 65 rows on the LDS (96 or 128 KiB) holds one,
-// and 344 of them are two rounds on 256 compute units: single-term 45.5 us at 64 rows, 66.7 at 128.
+// and 344 of them are two rounds on 256 compute units: single-term 45.5 us at 64 rows (43.5 with ONCE), 66.7 at 128.
 template <int MT, int D, bool TWO, bool ONCE>
 __global__ __launch_bounds__(512, MT == 1 || (MT == 2 && !TWO) ? 4 : 2) void skinny_swiglu_kernel(const f16* __restrict__ Af,
                                                                              const f16* __restrict__ Af_lo,
