@@ -440,12 +440,33 @@ void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache
 // free.  us a launch at one row and 290 positions: 12 heads of 64 5.95 -> 5.27 (low terms 6.7 -> 6.2), 32 heads of 128 8.2 ->
 // 7.3 (10.0 -> 9.4), against one wave that formed all three behind the requests of the cache rows and a branch a row for the
 // new one.
+//
+// Rows past the cached ones are not requested: the loads are bounded by a buffer descriptor of the group's rows that exist.
+// Clamped to the last row they cost little while its line stays in the L1; read as data that does not come again it does not
+// stay, and with blocks of about a power of two bytes the last rows of all of them lie on a few channels.  us a step of 4 layers
+// of d 2048 (heads of 64, single-term) at 512 sequences, normal and clamped / once and clamped / once and bounded: 60 positions in
+// blocks of 127 1169 / 1578 / 1140, 100 in blocks of 127 1276 / 1542 / 1229, 60 in blocks of 201 1149 / 1138 / 1126; normal and
+// bounded is as normal and clamped (+-1 %).  A row's low terms are requested with its high ones: behind those of the whole group
+// they made a step of two-term layers at 256 sequences of 300 and 500 positions 5 and 9 % longer.
 struct QkvPartials {
   const float* part;       // [ksplit][rows][3 * d_model]
   int ksplit, rows;
   const float* rope_cos;   // [max_seq, HD/2]
   const float* rope_sin;
 };
+
+// Elements from `at` on of the first `rows` rows of ROW elements behind base (uniform, as rows is); zeros, and no request, for
+// those of later rows.  ONCE: as data that is not read again.
+template <class V, bool ONCE, int ROW, class E>
+__device__ __forceinline__ V load_row(const E* base, int rows, unsigned at) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, rows * (int)(ROW * sizeof(E)), 0x00027000);
+  if constexpr (sizeof(V) == 16) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at * sizeof(E), 0, ONCE ? 2 : 0));
+  else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rsrc, at * sizeof(E), 0, ONCE ? 2 : 0));
+#else
+  return V{};
+#endif
+}
 
 // TWO (two-term mode): the cache holds every key / value as a half-precision high term plus a one-byte low term
 // (k_lo / v_lo, same indexing, bf8(16 * lo)); both are streamed and added in float32; the output is written as hi
@@ -487,14 +508,19 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
   auto row_of = [&](int it) { return (it * NW + wave) * RPI + sub; };
   auto request = [&](auto S, int it0) {
     constexpr int s = decltype(S)::value;
+    const int r0 = it0 * NW * RPI, rows = min(ctx - 1 - r0, G * NW * RPI);   // uniform; rows >= 0: it0 < n_it
+    const size_t from = (size_t)r0 * HD;
+    unsigned at0 = (unsigned)row_of(0) * HD + c * 8;
+    hold32(at0);                                       // the offsets are formed here, an addition a load, and not kept
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      const size_t off = (size_t)min(row_of(it0 + u), last_global) * HD + c * 8;
-      kv[s][u] = load_once<ONCE>((const f16x8*)(kb + off));
-      vv[s][u] = load_once<ONCE>((const f16x8*)(vb + off));
+      const unsigned at = at0 + u * NW * RPI * HD;
+      kv[s][u] = load_row<f16x8, ONCE, HD>(kb + from, rows, at);
+      vv[s][u] = load_row<f16x8, ONCE, HD>(vb + from, rows, at);
       if constexpr (TWO) {
-        kl[s][u] = load_once<ONCE>((const i32x2*)(kbl + off));
-        vl[s][u] = load_once<ONCE>((const i32x2*)(vbl + off));
+        kl[s][u] = load_row<i32x2, ONCE, HD>(kbl + from, rows, at);
+        vl[s][u] = load_row<i32x2, ONCE, HD>(vbl + from, rows, at);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -559,8 +585,8 @@ __global__ __launch_bounds__(512, 4) void decode_attention_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) qf[j] = s_q[c * 8 + j];
   };
-  // A context that one group covers has no second one: its requests, for the last row again and again, would make 74 us of 256
-  // sequences of 60 (32 heads of 64, low terms) 88.  The branches meet behind the new row, the short one with nothing in flight,
+  // A context that one group covers has no second one (its requests, clamped to the last row, made 74 us of 256 sequences of 60
+  // positions, 32 heads of 64, low terms, 88).  The branches meet behind the new row, the short one with nothing in flight,
   // so that the waits that follow count on the second group's requests (without that the first group waits for both: 1 % of a
   // launch at 290 positions, 5 % of some).
   request(s0, 0);

@@ -178,6 +178,13 @@ __device__ __forceinline__ V load_once(const V* p) {
   else return *p;
 }
 
+// Keeps what is computed from v from being computed ahead of a loop and kept in registers.
+__device__ __forceinline__ void hold32(unsigned& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+}
+
 // C = A * W^T with fused epilogues (f16 MFMA, fp32 accumulation).
 void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st);           // x += C
 // silu(gate)*up; lo_mode 1: also half-precision low terms at column f + j; 2: 8-bit low terms, bytes behind the f halves

@@ -317,12 +317,6 @@ __device__ __forceinline__ void hold(f16x8& v) {
   asm volatile("" : "+v"(v));
 #endif
 }
-// Keeps what is computed from v from being computed ahead of a loop and kept in registers.
-__device__ __forceinline__ void hold32(unsigned& v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(v));
-#endif
-}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
 #if defined(__HIP_DEVICE_COMPILE__)

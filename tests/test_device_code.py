@@ -230,6 +230,16 @@ def test_float32_rows_that_are_not_aligned_are_loaded_16_bytes_at_a_time(built):
         assert ops.count("global_load_dwordx4") >= 12, name
 
 
+def test_decode_attention_requests_only_rows_that_exist(built):
+    """About time as well: rows past the context, clamped to its last row, made steps of short contexts up to 35 % longer where
+    they are read as data that does not come again.  Loads bounded by a descriptor make no request for them."""
+    kernels = {n: [ins[1] for ins in code] for n, code in built.items() if "decode_attention_kernelI" in n}
+    assert len(kernels) == 8                                          # head size, low terms, read once
+    for name, ops in kernels.items():
+        assert ops.count("buffer_load_dwordx4") >= 24, name
+        assert not {"global_load_dwordx2", "global_load_dwordx4", "flat_load_dwordx2", "flat_load_dwordx4"} & set(ops), name
+
+
 def test_the_ceiling_probe_runs_the_instruction_of_the_prefill_gemm(built):
     """A ceiling measured with another instruction is no ceiling: 32x32x16 sustains less than 16x16x32."""
     def products(name, part):
