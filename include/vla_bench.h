@@ -31,6 +31,11 @@ const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_ter
  * whichever leaves the last round of tiles fullest.  0 for sizes the 16-bit path does not have.  Host only. */
 int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term);
 
+/* What a decode step of `rows` sequences with `positions` cached positions (all of them together) reads as data that does not
+ * come again: bit 0 the weights (products that leave partial sums for the next launch: only matrices of 64 MB and more), bit 1
+ * the keys and values.  0 on the float32 path, for a NULL context and for sizes that no step has.  Host only. */
+int32_t vla_decode_reads_once(vla_ctx* ctx, int32_t rows, int64_t positions);
+
 /* Timing hooks for the benchmark: duration of the launches of one kernel family, measured with
  * HIP events recorded on the launch stream around each launch.  vla_prof_enable(ctx, mask) clears
  * what was collected and then times the families whose bit (1 << index) is set in mask (0 = off).

@@ -467,10 +467,17 @@ long long layer_weight_bytes(const vla_config& c) {
 // 737 / 711, 32 rows 904 / 891, 64 rows 1289 / 1274, 128 rows 2106 / 2077; 5 of d 5120 at 1 row 742 / 684; 16 of d 2048 754 /
 // 719; 24 of d 768 (340 MB) 631 / 596, 20 (283 MB) 514 / 500, 16 (227 MB) 393 / 402, 12 (170 MB) 280 / 305 (normal).
 bool weights_read_once(const vla_config& c) { return layer_weight_bytes(c) > kLastLevelKeep; }
-bool kv_read_once(const vla_config& c, long long positions) {
+// Above kSkinnyMaxRows rows the weights are read normally however many they are, and what passes the cache with them pushes the
+// rest out either way.  Narrow models of short contexts then lose a little by reading keys and values once.  % of a step, 129 / 256
+// / 512 rows: 24 layers of d 768 (340 MB) 60 positions +1.1 / +2.7 / +1.8, 100 +1.3 / +2.7 / +1.7, 180 +0.2 / +0.1 / -0.9, 220 -0.8 /
+// -0.6 / -1.9, 300 -2.2 / -3.0 / -4.5; 16 of d 1024 100 +2.0 / +1.9 / 0.0, 220 -0.3 / -1.1 / -2.9; 10 of d 1536 60 +1.2 / +0.6 /
+// -0.4, 220 -0.9 / -2.2 / -4.1; 4 of d 2048 60 +0.2 / -0.3 / -2.4; 3 of d 4096 60 -1.2 / -1.9 / -2.8.  Up to kSkinnyMaxRows, with the
+// weights read once, every one of these gains (-0.4 to -9.8; 10 of d 1536 +0.6 at worst).
+bool kv_read_once(const vla_config& c, int rows, long long positions) {
   const long long weights = layer_weight_bytes(c);
   const long long kv = positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
-  return weights <= kLastLevelKeep ? weights + kv > kLastLevelKeep : kv > kLastLevelKeep;
+  if (weights <= kLastLevelKeep) return weights + kv > kLastLevelKeep;
+  return kv > kLastLevelKeep && (rows <= kSkinnyMaxRows || c.d_model >= 2048 || positions >= 192LL * rows);
 }
 
 // Decode step of the 16-bit path: split-K GEMMs whose partial planes span the whole batch, and one kernel after each
@@ -515,7 +522,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
   };
   f16* const none = nullptr;
   float *y = at<float>(ctx->work, w.norm_y), *sums = at<float>(ctx->work, w.norm_sums);
-  const bool kv_once = kv_read_once(c, positions);
+  const bool kv_once = kv_read_once(c, B, positions);
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerW& lw = ctx->al.layers[l];
     const RopeKv rk = layer_rope_kv(ctx, l);      // low-term planes only in two-term layers
@@ -1553,6 +1560,11 @@ const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_ter
 int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term) {
   if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64) return 0;
   return gemm_f16_tile_rows(rows, n, two_pitch(two_term != 0, k));
+}
+
+int32_t vla_decode_reads_once(vla_ctx* ctx, int32_t rows, int64_t positions) {
+  if (!ctx || ctx->cfg.dtype != VLA_BF16 || rows <= 0 || positions < 0) return 0;
+  return (rows <= kSkinnyMaxRows && weights_read_once(ctx->cfg) ? 1 : 0) | (kv_read_once(ctx->cfg, rows, positions) ? 2 : 0);
 }
 
 int vla_prof_enable(vla_ctx* ctx, int32_t mask) {

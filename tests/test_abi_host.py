@@ -94,6 +94,29 @@ def test_null_arguments_and_unbound_state():
     B.vla_destroy(ctx)
 
 
+WEIGHTS_ONCE, KV_ONCE = 1, 2
+
+
+def reads_once(layers, d, f, hd, rows, positions):
+    ctx = B.vla_create(B.make_config(W.PolicyShape(layers, d, d // hd, hd, f, 600, dtype="bf16"), 1, 64, 64, precision=B.VLA_PREC_FAST))
+    got = B.vla_decode_reads_once(ctx, rows, rows * positions)
+    B.vla_destroy(ctx)
+    return got
+
+
+def test_keys_and_values_of_short_contexts_are_read_normally_where_the_weights_are():
+    """Weights that outgrow the last-level cache are read normally above 128 rows; keys and values of narrow models and contexts
+    of less than 192 positions then too (read once: steps up to 2.7 % longer)."""
+    for layers, d, f, hd in ((24, 768, 2048, 64), (60, 512, 1408, 64), (16, 1024, 2816, 128), (10, 1536, 4096, 64)):
+        assert reads_once(layers, d, f, hd, 256, 100) == reads_once(layers, d, f, hd, 256, 191) == 0
+        assert reads_once(layers, d, f, hd, 256, 192) == reads_once(layers, d, f, hd, 129, 300) == KV_ONCE
+        assert reads_once(layers, d, f, hd, 128, 140) == WEIGHTS_ONCE | KV_ONCE
+    assert reads_once(8, 2048, 5504, 128, 256, 60) == reads_once(32, 4096, 11008, 128, 129, 60) == KV_ONCE
+    assert reads_once(12, 768, 2048, 64, 256, 60) == KV_ONCE                # weights that stay (170 MB)
+    assert reads_once(12, 768, 2048, 64, 1, 290) == reads_once(12, 768, 2048, 64, 0, 290) == 0
+    assert B.vla_decode_reads_once(None, 1, 1) == 0
+
+
 def test_serving_state_transitions_on_the_host():
     """Drain / update state machine (Appendix "High-Performance NCCL-based Weight Synchronization"): the
     transitions that touch no device state."""
