@@ -297,7 +297,7 @@ const char* kFamilyNames[FAM_COUNT] = {"gemm_qkv_prefill", "gemm_o_prefill", "ge
 template <class T> T* at(char* base, size_t off) { return reinterpret_cast<T*>(base + off); }
 
 // ---- one pass over the layers for `rows` packed tokens (prefill: all prefix tokens; decode: B) ------
-void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_need, hipStream_t st);
+void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_need, int rows, hipStream_t st);
 
 RopeKv layer_rope_kv(vla_ctx* ctx, int l) {
   const vla_config& c = ctx->cfg;
@@ -363,7 +363,7 @@ int run_layers_f16(vla_ctx* ctx, int rows, hipStream_t st, const int32_t* need, 
     const bool fits = pad32 <= max_rows(c) &&
                       align_up(pad32 * f * sizeof(f16)) + (size_t)n_need * d * 4 <= max_rows(c) * (size_t)f * sizeof(f16);
     if (l == c.n_layers - 1 && need && n_need > 0 && (size_t)n_need * 2 <= (size_t)rows && fits) {
-      run_tail_f16(ctx, lw, need, n_need, st);
+      run_tail_f16(ctx, lw, need, n_need, rows, st);
       break;
     }
     {
@@ -461,12 +461,24 @@ constexpr long long kLastLevelKeep = 245'000'000;
 long long layer_weight_bytes(const vla_config& c) {
   return 2LL * c.n_layers * c.d_model * (4LL * c.d_model + 3LL * c.d_ffn);
 }
+long long kv_step_bytes(const vla_config& c, long long positions) {
+  return positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
+}
 // The decode products likewise, where the weights alone are too many (and one launch takes all rows: a matrix read chunk by
 // chunk comes again).  What gains most is what the weights then leave in the cache: the keys and values of a few sequences, the
 // partial planes, the rows.  us a decode step, normal / once: 6 layers of the 7B shape, 1 row 608 / 562, 4 rows 649 / 606, 16 rows
 // 737 / 711, 32 rows 904 / 891, 64 rows 1289 / 1274, 128 rows 2106 / 2077; 5 of d 5120 at 1 row 742 / 684; 16 of d 2048 754 /
-// 719; 24 of d 768 (340 MB) 631 / 596, 20 (283 MB) 514 / 500, 16 (227 MB) 393 / 402, 12 (170 MB) 280 / 305 (normal).
-bool weights_read_once(const vla_config& c) { return layer_weight_bytes(c) > kLastLevelKeep; }
+// 719; 24 of d 768 (340 MB) 631 / 596, 20 (283 MB) 514 / 500, 16 (227 MB) 393 / 402, 12 (170 MB) 280 / 305 (normal); 24 of d 768 at
+// 32 rows 786 / 765, 64 rows 1033 / 966, 128 rows 1397 / 1362 (from 64 rows on with the keys and values).
+// Weights a little above the line still come again in part when the step reads little else (kStepKeep).  % of a step, weights +
+// keys and values in MB: 18 layers of d 768 255 + 5 +2.3, + 10 +0.7, + 20 -1.5, + 40 -2.8; 10 of d 1024 257 + 4 +2.1, + 30 -0.5, + 52
+// -4.4; 40 of d 512 257 + 7 +1.6, + 30 -3.1; 5 of d 1536 262 + 6 +2.7, + 22 +1.9, + 45 +0.7, + 78 -2.3, 283 + 3 -3.5; 19 of d 768 269 +
+// 5 -0.3, + 21 -2.6.
+constexpr long long kStepKeep = 285'000'000;
+bool weights_read_once(const vla_config& c, long long positions) {
+  const long long weights = layer_weight_bytes(c);
+  return weights > kLastLevelKeep && weights + kv_step_bytes(c, positions) > kStepKeep;
+}
 // Above kSkinnyMaxRows rows the weights are read normally however many they are, and what passes the cache with them pushes the
 // rest out either way.  Narrow models of short contexts then lose a little by reading keys and values once.  % of a step, 129 / 256
 // / 512 rows: 24 layers of d 768 (340 MB) 60 positions +1.1 / +2.7 / +1.8, 100 +1.3 / +2.7 / +1.7, 180 +0.2 / +0.1 / -0.9, 220 -0.8 /
@@ -474,8 +486,7 @@ bool weights_read_once(const vla_config& c) { return layer_weight_bytes(c) > kLa
 // -0.4, 220 -0.9 / -2.2 / -4.1; 4 of d 2048 60 +0.2 / -0.3 / -2.4; 3 of d 4096 60 -1.2 / -1.9 / -2.8.  Up to kSkinnyMaxRows, with the
 // weights read once, every one of these gains (-0.4 to -9.8; 10 of d 1536 +0.6 at worst).
 bool kv_read_once(const vla_config& c, int rows, long long positions) {
-  const long long weights = layer_weight_bytes(c);
-  const long long kv = positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
+  const long long weights = layer_weight_bytes(c), kv = kv_step_bytes(c, positions);
   if (weights <= kLastLevelKeep) return weights + kv > kLastLevelKeep;
   return kv > kLastLevelKeep && (rows <= kSkinnyMaxRows || c.d_model >= 2048 || positions >= 192LL * rows);
 }
@@ -499,7 +510,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
   f16* act = at<f16>(ctx->work, w.act);
   f16 *hn_lo = frag_lo(c, hn, d), *att_lo = frag_lo(c, att, d), *act_lo = frag_lo(c, act, f);
   float* part = ctx->part_override ? ctx->part_override : at<float>(ctx->work, w.part);
-  const bool w_once = weights_read_once(c);
+  const bool w_once = weights_read_once(c, positions);
   // the tiled split-K kernel takes the chunks of more than 128 rows
   auto tiled = [&](int N, int K) { return B > kSkinnyMaxRows && splitk_gemm_fits(256, N, K); };
   auto planes = [&](int N, int K) { return tiled(N, K) ? splitk_ksplit(N, K) : skinny_ksplit(N, K); };
@@ -589,7 +600,7 @@ int run_layers_decode_f16(vla_ctx* ctx, int B, hipStream_t st, long long positio
 // Output projection and feed-forward of one layer for n_need compact rows with the weight-streaming GEMMs.
 // Buffers that are dead at this point of the last prefill layer hold the compact set: q -> attention output in
 // fragment order, hn -> normalised rows, act -> SwiGLU output followed by the float32 residual rows.
-void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_need, hipStream_t st) {
+void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_need, int rows, hipStream_t st) {
   const vla_config& c = ctx->cfg;
   const WorkLayout& w = ctx->wl;
   const int d = c.d_model, f = c.d_ffn;
@@ -612,7 +623,7 @@ void run_tail_f16(vla_ctx* ctx, const LayerW& lw, const int32_t* need, int n_nee
                                         (two ? max_rows(c) * (size_t)f * sizeof(f16) : 0) +
                                         align_up(pad32 * f * sizeof(f16)));
   const int ks_o = skinny_ksplit(d, d), ks_dn = skinny_ksplit(d, f);
-  const bool w_once = weights_read_once(c) && n_need <= kSkinnyMaxRows;
+  const bool w_once = weights_read_once(c, rows) && n_need <= kSkinnyMaxRows;
   const int chunk = (int)(part_rows(c) < (size_t)kSkinnyMaxRows ? part_rows(c) : (size_t)kSkinnyMaxRows);
   gather_tail(att, two_pitch(two, d), lo8(two, d), x, need, n_need, d, att_frag, att_frag_lo, x_c, st);
   for (int r0 = 0; r0 < n_need; r0 += chunk) {
@@ -1564,7 +1575,7 @@ int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term)
 
 int32_t vla_decode_reads_once(vla_ctx* ctx, int32_t rows, int64_t positions) {
   if (!ctx || ctx->cfg.dtype != VLA_BF16 || rows <= 0 || positions < 0) return 0;
-  return (rows <= kSkinnyMaxRows && weights_read_once(ctx->cfg) ? 1 : 0) | (kv_read_once(ctx->cfg, rows, positions) ? 2 : 0);
+  return (rows <= kSkinnyMaxRows && weights_read_once(ctx->cfg, positions) ? 1 : 0) | (kv_read_once(ctx->cfg, rows, positions) ? 2 : 0);
 }
 
 int vla_prof_enable(vla_ctx* ctx, int32_t mask) {

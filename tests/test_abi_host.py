@@ -117,6 +117,16 @@ def test_keys_and_values_of_short_contexts_are_read_normally_where_the_weights_a
     assert B.vla_decode_reads_once(None, 1, 1) == 0
 
 
+def test_weights_a_little_above_the_cache_are_read_normally_by_a_step_that_reads_little_else():
+    """Weights of 245 MB and more are read once only if the step reads 285 MB together with its keys and values (below, steps of
+    one or two sequences were up to 3 % longer)."""
+    for layers, d, f, rows, positions, want in ((18, 768, 2048, 1, 64, 0), (18, 768, 2048, 16, 64, WEIGHTS_ONCE),
+                                                (10, 1024, 2816, 1, 64, 0), (5, 1536, 3648, 2, 64, 0),
+                                                (5, 1536, 4096, 1, 256, WEIGHTS_ONCE), (17, 768, 2048, 8, 64, KV_ONCE),
+                                                (24, 768, 2048, 1, 2, WEIGHTS_ONCE), (32, 4096, 11008, 1, 290, WEIGHTS_ONCE)):
+        assert reads_once(layers, d, f, 64, rows, positions) == want, (layers, d, f, rows)
+
+
 def test_serving_state_transitions_on_the_host():
     """Drain / update state machine (Appendix "High-Performance NCCL-based Weight Synchronization"): the
     transitions that touch no device state."""
