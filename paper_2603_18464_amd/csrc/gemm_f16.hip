@@ -816,26 +816,11 @@ static TilePick pick_tile(int M, int N, int K) {
 //   at 18560); the larger launches are the same either way (+-1 %).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
-enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_192x256, V_256x256, V_256x256_W3, V_256x256_SPREAD, V_COUNT };
+enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
+               V_256x256_W3, V_256x256_SPREAD, V_COUNT };
 const char* const kGemmF16Variants[] = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
-                                        "192x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
+                                        "160x256", "192x256", "224x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
 static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
-static Variant form_of_256(int M, int N, int Kw, long long tiles, bool lo8, int span) {
-  if (lo8) return V_256x256_W3;
-  if (span == EpiResid::kSpan || tiles < 768) return V_256x256_SPREAD;
-  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
-}
-int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
-  const TilePick p = pick_tile(M, N, K);
-  switch (p.tile) {
-    case T_64x128: return p.tiles > 256 ? V_64x128_ROUNDS : span <= 64 ? V_64x128_8W : V_64x128;
-    case T_128x128: return V_128x128;
-    case T_64x256: return V_64x256;
-    case T_128x256: return V_128x256;
-    case T_192x256: return V_192x256;
-    default: return form_of_256(M, N, Kw, p.tiles, lo8, span);
-  }
-}
 
 // Rows of the tiles a launch runs.  Where the model picks 192 or 256 rows, the rounds are balanced: the last one costs a whole
 // tile's time however few workgroups it has, and that is proportional to a tile's rows + 90 (a slab of weights, the fill and the
@@ -845,29 +830,41 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
 // 368 / 340, o 154 / 142, qkv 370 / 350; 6960 rows down 509 / 488, o 213 / 204; 9400 rows down 762 / 705; 14000 rows down 1032 / 978;
 // with low terms 5 to 10 % likewise.  Over 149 products of the 7B shape (290 to 28000 rows) 2.7 % less in the mean and none
 // slower; over 90 of d 768 and 2048 2.3 % less, the worst o at 18432 rows of d 768 39.4 / 40.1 (bound by the residual rows).
-int gemm_f16_tile_rows(int M, int N, int K) {
-  const TileCost& model = kTileCost[pick_tile(M, N, K).tile];
-  if (model.bm < 192) return model.bm;
+static int tile_rows(const TilePick& pick, int M, int N) {
+  const int picked = kTileCost[pick.tile].bm;
+  if (picked < 192) return picked;
   auto cost = [&](int rows) { return (((long long)(M + rows - 1) / rows * (N / 256) + 255) / 256) * (rows + 90); };
-  int best = model.bm;
+  int best = picked;
   for (int rows = 160; rows <= 256; rows += 32)
-    if (cost(rows) < cost(best) && 40 * cost(rows) < 39 * cost(model.bm)) best = rows;
+    if (cost(rows) < cost(best) && 40 * cost(rows) < 39 * cost(picked)) best = rows;
   return best;
+}
+int gemm_f16_tile_rows(int M, int N, int K) { return tile_rows(pick_tile(M, N, K), M, N); }
+int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
+  const TilePick p = pick_tile(M, N, K);
+  switch (p.tile) {
+    case T_64x128: return p.tiles > 256 ? V_64x128_ROUNDS : span <= 64 ? V_64x128_8W : V_64x128;
+    case T_128x128: return V_128x128;
+    case T_64x256: return V_64x256;
+    case T_128x256: return V_128x256;
+    default: break;
+  }
+  switch (tile_rows(p, M, N)) {
+    case 160: return V_160x256;
+    case 192: return V_192x256;
+    case 224: return V_224x256;
+    default: break;
+  }
+  if (lo8) return V_256x256_W3;
+  if (span == EpiResid::kSpan || (long long)((M + 255) / 256) * (N / 256) < 768) return V_256x256_SPREAD;
+  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
 }
 
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr int span = Epi::kSpan;
   constexpr bool resid = span == EpiResid::kSpan;
-  int v = gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span);
-  if (v >= V_192x256) {
-    const int rows = gemm_f16_tile_rows(g.M, g.N, g.K);
-    if (rows == 160) return launch<2, 4, 80, 64, 3, 3, 1, false, false, LO8>(g, epi, st);
-    if (rows == 224) return launch<2, 4, 112, 64, 2, 3, 1, false, false, LO8>(g, epi, st);
-    if (rows == 192) v = V_192x256;
-    else if (v == V_192x256) v = form_of_256(g.M, g.N, g.Kw, (long long)((g.M + 255) / 256) * (g.N / 256), LO8, span);
-  }
-  switch (v) {
+  switch (gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span)) {
     case V_64x128_8W:
       if constexpr (span <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
       break;
@@ -878,7 +875,9 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
     case V_128x128: launch<4, 2, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
     case V_64x256: launch<2, 4, 32, 64, 4, 4, 1, false, false, LO8>(g, epi, st); break;
     case V_128x256: launch<2, 4, 64, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
+    case V_160x256: launch<2, 4, 80, 64, 3, 3, 1, false, false, LO8>(g, epi, st); break;
     case V_192x256: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
+    case V_224x256: launch<2, 4, 112, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
     case V_256x256:
       if constexpr (!LO8 && !resid) launch<4, 2, 64, 128, 2, 2, 1, false, false, LO8>(g, epi, st);
       break;

@@ -7,12 +7,12 @@ import pytest
 
 import workloads as W
 from oracle import vla_oracle as O
-from paper_2603_18464_amd.binding import vla_gemm_variant
+from paper_2603_18464_amd.binding import vla_gemm_tile_rows, vla_gemm_variant
 from tests import parity as P
 from tests.test_gpu_parity import ragged_obs
 
-ALL = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "192x256", "256x256",
-       "256x256 3 weight stages", "256x256 spread"}
+ALL = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "160x256", "192x256", "224x256",
+       "256x256", "256x256 3 weight stages", "256x256 spread"}
 SPAN = {"resid": 32, "gate/up": 64, "qkv64": 64, "qkv128": 128}
 # Not reached: of the forms of a launch of few 64x128 tiles each epilogue has one; three stages need more than 256 of these
 # tiles to be the fastest choice, which takes a wide matrix of a short contraction (gate/up only); 8-bit low terms have one
@@ -35,6 +35,8 @@ CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 6
          (128, 2048, 128, [1100, 2300]), (512, 2048, 64, [3500]), (1536, 64, 128, [8000]), (128, 16448, 64, [64]),
          (1024, 64, 64, [1300]), (2048, 704, 128, [8000]), (512, 4096, 128, [6000]), (1280, 2816, 128, [700]),
          (3072, 64, 128, [400, 1300]), (1280, 64, 64, [1088]), (2048, 64, 64, [8000]), (5632, 64, 64, [4500])]
+# (in test_gpu_gemm_balanced.py)
+BALANCED = [(768, 1024, 64, [5200]), (1280, 1024, 64, [8000]), (768, 64, 128, [7000])]
 
 
 def launches(d, f, hd, rows):
@@ -45,7 +47,7 @@ def launches(d, f, hd, rows):
 
 def test_the_cases_reach_every_variant():
     reached = {key: set() for key in REACHED}
-    for d, f, hd, rows_list in CASES:
+    for d, f, hd, rows_list in CASES + BALANCED:
         for rows in rows_list:
             for key, variant in launches(d, f, hd, rows):
                 reached[key].add(variant)
@@ -55,10 +57,22 @@ def test_the_cases_reach_every_variant():
     assert vla_gemm_variant(64, 100, 128, False, 32) == vla_gemm_variant(64, 128, 128, False, 1) == ""
 
 
+def test_the_variant_is_what_the_launch_runs():
+    """Where the rounds are balanced the launch runs other tiles than the cost model picks: the name is that of the launch."""
+    for rows, n, k, span, want in ((2320, 22016, 4096, 64, "224x256"), (2208, 22016, 4096, 64, "160x256"), (290, 22016, 4096, 64, "160x256"),
+                                   (4100, 12288, 4096, 128, "160x256"), (10533, 22016, 4096, 64, "256x256 3 weight stages"),
+                                   (2320, 4096, 4096, 32, "160x256"), (18560, 4096, 11008, 32, "256x256 spread")):
+        assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
+    for n, k, span in ((12288, 4096, 128), (22016, 4096, 64), (4096, 11008, 32), (2304, 768, 64), (768, 2048, 32)):
+        for rows in range(1, 30000, 173):
+            for two in (False, True):
+                assert vla_gemm_variant(rows, n, k, two, span).startswith(f"{vla_gemm_tile_rows(rows, n, k, two)}x")
+
+
 def test_the_third_weight_stage_goes_by_the_bytes_that_are_read_again():
     """The same tile, with two stages where weights and half of the activations stay below 215 MB: whatever the epilogue."""
     for span in (64, 128):
-        for rows, n, k, third in ((18560, 12288, 4096, False), (18560, 22016, 4096, True), (2320, 22016, 4096, False),
+        for rows, n, k, third in ((18560, 12288, 4096, False), (18560, 22016, 4096, True), (2560, 22016, 4096, False),
                                   (18560, 11008, 2048, False), (18560, 49152, 2048, True), (9280, 18432, 6144, True)):
             want = "256x256 3 weight stages" if third else "256x256"
             assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
