@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as W
+from paper_2603_18464_amd.binding import vla_decode_reads_once
 from tests import parity as P
 from tests.test_gpu_parity import ragged_obs
 
@@ -35,28 +36,23 @@ def test_the_same_bits_on_both_sides(hd, fast, batches):
     assert np.array_equal(got[0], got[1][:batches[0]])
 
 
-@pytest.mark.timeout(300)
-@pytest.mark.parametrize("hd,d,f,two_layers", [(128, 4096, 9728, 1), (64, 4096, 9728, 4), (128, 128, 192, 1)])
-def test_weights_read_once(hd, d, f, two_layers):
-    """Weights that outgrow the last-level cache: a decode step's rows have the same bits in batches of every form of its
-    products (normalising ones, those with planes above and below the size that takes part, one to four blocks of rows), which
-    are the oracle's.  The small model reads its weights as ever."""
+def rows_have_the_same_bits(shape, two_layers, batches, once):
+    """A decode step's rows in every batch, which are the oracle's."""
     from oracle import vla_oracle as O
     from paper_2603_18464_amd import VlaPolicy
-    shape = W.PolicyShape(2, d, d // hd, hd, f, 600, n_action_bins=40, dtype="bf16")
     weights = W.make_weights(shape, 5)
-    assert (2 * 2 * d * (4 * d + 3 * f) > KEEP) == (d == 4096)
     wl = W.Workload("Rw", 98, shape, batch=3, n_patches=9, instr_len=(0, 0), n_tokens=2)
     few = ragged_obs(wl, [9, 4, 7], [0] * 3, seed=22)
-    pol = VlaPolicy(shape, 128, 16, 128 * 9, two_term_layers=two_layers)
+    pol = VlaPolicy(shape, max(batches), 16, max(batches) * 9, two_term_layers=two_layers)
     pol.load_weights(weights)
     ref = None
-    for B in (3, 17, 33, 70, 128):
+    for B in batches:
         reps = [b % 3 for b in range(B)]
         cu = few["cu_patch"]
         obs = {"patch_emb": np.concatenate([few["patch_emb"][cu[r]:cu[r + 1]] for r in reps]),
                "cu_patch": np.concatenate([[0], np.cumsum([cu[r + 1] - cu[r] for r in reps])]).astype(np.int32),
                "instr_ids": few["instr_ids"], "cu_instr": np.zeros(B + 1, dtype=np.int32)}
+        assert vla_decode_reads_once(pol.ctx, B, int(obs["cu_patch"][-1])) == once
         dev = P.device_inputs(pol, obs)
         out = pol.policy_step(dev["patch_emb"], obs["cu_patch"], dev["instr_ids"], obs["cu_instr"], 2, want_logits=True)
         got = out["logits"].cpu().numpy()
@@ -70,3 +66,23 @@ def test_weights_read_once(hd, d, f, two_layers):
         for b in range(B):
             assert np.array_equal(got[b], ref[b % 3]), (B, b)
     pol.close()
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("hd,d,f,two_layers", [(128, 4096, 9728, 1), (64, 4096, 9728, 4), (128, 128, 192, 1)])
+def test_weights_read_once(hd, d, f, two_layers):
+    """Weights that outgrow the last-level cache: a decode step's rows have the same bits in batches of every form of its
+    products (normalising ones, those with planes above and below the size that takes part, one to four blocks of rows), which
+    are the oracle's.  The small model reads its weights as ever."""
+    shape = W.PolicyShape(2, d, d // hd, hd, f, 600, n_action_bins=40, dtype="bf16")
+    assert (2 * 2 * d * (4 * d + 3 * f) > KEEP) == (d == 4096)
+    rows_have_the_same_bits(shape, two_layers, (3, 17, 33, 70, 128), once=int(d == 4096))
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("layers,f,hd", [(14, 2048, 64), (9, 4096, 128)])
+def test_weights_of_a_narrow_deep_model_read_once(layers, f, hd):
+    """Up to 32 rows of a narrow model all products normalise their rows or add to the residual ones: with short slices (f 2048)
+    and long ones, with and without low terms, up to 16 rows and above."""
+    shape = W.PolicyShape(layers, 1024, 1024 // hd, hd, f, 600, n_action_bins=40, dtype="bf16")
+    rows_have_the_same_bits(shape, 2, (3, 1, 16, 17, 24, 32, 33, 128), once=1)
