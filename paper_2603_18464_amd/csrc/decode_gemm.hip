@@ -646,11 +646,9 @@ void skinny_norm_swiglu(const float* y, const float* sums, float eps, bool two, 
 template <int D, bool TWO, bool FEW>
 static void launch_resid(bool w_once, const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* x, const float* gain, float* y, float* sums,
                          int M, int N, int K, int kgroups, hipStream_t st) {
-  auto launch = [&](auto, auto ONCE) {
-    hipLaunchKernelGGL((skinny_resid_kernel<D, TWO, FEW, decltype(ONCE)::value>), dim3(N / 16), dim3(256 * kgroups),
-                       (size_t)4 * kgroups * 16 * 64 * sizeof(float), st, Afrag, Afrag_lo, Wp, x, gain, y, sums, M, N, K);
-  };
-  by_flags(false, w_once, launch);
+  auto kern = w_once ? skinny_resid_kernel<D, TWO, FEW, true> : skinny_resid_kernel<D, TWO, FEW, false>;
+  hipLaunchKernelGGL(kern, dim3(N / 16), dim3(256 * kgroups), (size_t)4 * kgroups * 16 * 64 * sizeof(float), st, Afrag, Afrag_lo, Wp, x,
+                     gain, y, sums, M, N, K);
 }
 // Slices of up to eight k-blocks (the products of a small model) take two pairs in flight, which start sooner: N 768 K 768
 // 3.3 us with two, 3.5 with four, K 2048 4.3 and 4.5; others four (three where the registers hold 32 rows of both terms).
