@@ -453,7 +453,9 @@ inline bool norm_in_gemm(const vla_config& c, int B, int l) {
 // What a decode step reads comes again in the next one.  Of weights and cached positions (all rows together) the last-level
 // cache holds over a step what fits; when both do not, everything that passes through it normally pushes the rest out before
 // its turn.  The weights stay if they fit, and the keys and values then, or if they alone are too many, are read as data that
-// does not come again.  kLastLevelKeep: a little under 256 MB.  us a decode step, normal / once, weights and keys and values in
+// does not come again.  (Seen in the counters: as many read requests leave the L2, and what is read normally is answered sooner:
+// the weights of 12 layers of d 768 at 32 rows after 710 instead of 1131 cycles in gate/up, the keys and values of the 7B shape at
+// one row after 733 instead of 1192.)  kLastLevelKeep: a little under 256 MB.  us a decode step, normal / once, weights and keys and values in
 // MB: 12 layers of d 768 170 + 11 280 / 289 (normal), 170 + 85 317 / 302, 170 + 171 366 / 326, 170 + 342 466 / 431; 16 layers 227 +
 // 14 393 / 392; d 2048 16 layers, 1600 + 1200 1077 / 1065, + 3800 2115 / 2042; 8 layers of the 7B shape, 3200 + 80 equal, + 610
 // 1017 / 1003, + 5000 2285 / 2180, + 5700 3155 / 3055.
@@ -465,7 +467,8 @@ long long kv_step_bytes(const vla_config& c, long long positions) {
   return positions * c.d_model * (4LL * c.n_layers + 2LL * two_term_layers(c));
 }
 // The decode products likewise, where the weights alone are too many (and one launch takes all rows: a matrix read chunk by
-// chunk comes again).  What gains most is what the weights then leave in the cache: the keys and values of a few sequences, the
+// chunk comes again; of the products that leave planes to the next launch only matrices of 64 MB and more, see skinny_gemm).  What
+// gains most is what the weights then leave in the cache: the keys and values of a few sequences, the
 // partial planes, the rows.  us a decode step, normal / once: 6 layers of the 7B shape, 1 row 608 / 562, 4 rows 649 / 606, 16 rows
 // 737 / 711, 32 rows 904 / 891, 64 rows 1289 / 1274, 128 rows 2106 / 2077; 5 of d 5120 at 1 row 742 / 684; 16 of d 2048 754 /
 // 719; 24 of d 768 (340 MB) 631 / 596, 20 (283 MB) 514 / 500, 16 (227 MB) 393 / 402, 12 (170 MB) 280 / 305 (normal); 24 of d 768 at

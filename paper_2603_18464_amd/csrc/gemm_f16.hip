@@ -380,7 +380,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   constexpr int KS = PK / 32, KS16 = PK / 16;          // k-steps of a slab; 16-k blocks of a slab
   // KiB pieces per wave and slab.  Where those of A do not divide among the waves (REST of them are left for the last round),
   // piece i of a wave is piece i * NW + wave of the slab, and the last round's are loaded by several waves: the same bytes to
-  // the same place, so that every wave counts the same loads.
+  // the same place, so that every wave counts the same loads (160 rows: 56 pieces a slab for 52, 224 rows: 64 for 60; what the
+  // four cost has not been timed apart).
   constexpr int A_ALL = BM * PK / 512, AP = (A_ALL + NW - 1) / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;
   constexpr int REST = A_ALL % NW;
   static_assert(A_ALL * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
@@ -397,7 +398,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
 
   // XCD-aware tile order: consecutive workgroup ids land on different XCDs, so give each XCD a contiguous run of
   // tiles, walked in groups of GM row-tiles that share the same weight columns (4 and 8 measure alike for the small
-  // tiles; the 256-row tile is 4 % slower with 8 at 18560 rows, where the L2 then holds too few weight columns).
+  // tiles and for those of 224 rows, 26 products within +-1.2 % and one 2.4 % better with 8; the 256-row tile is 4 % slower with 8
+  // at 18560 rows, where the L2 then holds too few weight columns).
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = gridDim.x >> 3;
   const int pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -766,7 +768,7 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
 // matrices of models of d 256 to 5120 at 64 to 37120 rows, single- and two-term, each tile forced in turn) the pick is the
 // fastest in 1015 and 0.30 % slower in the mean; constants that meet the two columns make it 0.38 %, and 0.57 instead of 0.19 %
 // over the 7B matrices among them; the best of a search over both tiles' constants 0.25 %.
-// us single-term, pick and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
+// us single-term, the model's pick (192 and 256 rows are balanced afterwards, tile_rows) and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
 // (64x128; 73), down 68 (64x128; 180); 580 rows gate/up 112 (128x256; 256x256 163), down 84 (128x128; 191); 870 rows qkv 78
 // (192x256; 256x256 90); 2320 rows gate/up 378 (256x256; 128x256 389), o 86 (192x256; 256x256 101), down 197 (192x256;
 // 256x256 236); 9216 rows of d 768 gate/up 62 (192x256; 128x256 69).
@@ -811,9 +813,10 @@ static TilePick pick_tile(int M, int N, int K) {
 //   -0.3, 151 + 152 -0.4, 180 + 76 -1.3, 180 + 152 -1.8, 201 + 76 -3.3, 268 + 38 -4.0; qkv 57 + 228 +2.8, 101 + 152 (7B, 18560
 //   rows) +1.8 to +2.7, 101 + 304 +0.9, 127 + 171 -0.5, 157 + 190 -2.3, 226 + 114 -6.2; heads of 64 as heads of 128.  The
 //   epilogue that adds to the residual rows always gains (-1 to -4 %), and so do low terms (0 to -6 %);
-// * the residual epilogue and launches of fewer than three rounds request the weights in halves of 32 k (SPREAD: down 253
-//   against 259 us at 3480 rows, 212 against 215 at 2338, 523 against 526 at 6960; o 89.0 against 89.7 at 2338, 560 against 558
-//   at 18560); the larger launches are the same either way (+-1 %).
+// * the residual epilogue and launches of fewer than three rounds request the weights in halves of 32 k (SPREAD: gate/up 293
+//   against 298 us at 1800 rows, qkv 200 against 201 at 2368, down 517 against 520 at 7424 and 811 against 817 at 12000, 1346
+//   against 1342 at 18560; o 214.5 against 215.5 at 7424, 337 against 336 at 12000, 556 against 548 at 18560); the larger launches
+//   are the same either way (+-1 %).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
 enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
@@ -828,8 +831,9 @@ static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each"
 // 90), if that is 2.5 % less than the model's.  us with the model's rows / these, 7B: 780 rows qkv 80 / 73, gate/up 143 / 132;
 // 2208 rows gate/up 361 / 330, down 180 / 173, o 77.7 / 74.9; 2368 rows gate/up 364 / 343, down 185 / 181; 4100 rows down
 // 368 / 340, o 154 / 142, qkv 370 / 350; 6960 rows down 509 / 488, o 213 / 204; 9400 rows down 762 / 705; 14000 rows down 1032 / 978;
-// with low terms 5 to 10 % likewise.  Over 149 products of the 7B shape (290 to 28000 rows) 2.7 % less in the mean and none
-// slower; over 90 of d 768 and 2048 2.3 % less, the worst o at 18432 rows of d 768 39.4 / 40.1 (bound by the residual rows).
+// with low terms 5 to 10 % likewise.  Over the 354 products that it changes among those of d 768 to 5120 at 290 to 23200 rows,
+// with and without low terms, 5.2 % less in the mean; the worst are qkv with low terms at 9280 rows of d 3072, 644 / 650, and
+// without at 1450, 76.5 / 77.2.
 static int tile_rows(const TilePick& pick, int M, int N) {
   const int picked = kTileCost[pick.tile].bm;
   if (picked < 192) return picked;
