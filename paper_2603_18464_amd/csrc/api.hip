@@ -133,10 +133,11 @@ WorkLayout work_layout(const vla_config& c) {
   auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
   const size_t terms = two_term(c) ? 2 : 1;      // two-term layers: rows [hi | lo], or a second set of fragment blocks
   w.x = take(T * d * 4);
-  w.hn = take(T * d * es * terms);
+  const size_t T32 = c.dtype == VLA_BF16 ? (T + 31) / 32 * 32 : T;   // operands of the prefill products come in blocks of 32 rows
+  w.hn = take(T32 * d * es * terms);
   w.q = take(T * d * es * terms);
-  w.att = take(T * d * es * terms);
-  w.act = take(T * f * es * terms);
+  w.att = take(T32 * d * es * terms);
+  w.act = take(T32 * f * es * terms);
   const size_t widest = 3 * d > 2 * f ? 3 * d : 2 * f;
   w.part = take(c.dtype == VLA_BF16 ? (size_t)kMaxKSplit * part_rows(c) * widest * 4 : 0);
   w.norm_y = take(c.dtype == VLA_BF16 ? (size_t)kNormRows * d * 4 : 0);

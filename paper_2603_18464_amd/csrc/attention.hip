@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256, !TWO && HD == 64 ? 4 : 2) void flash_prefill_k
   l_run += __shfl_xor(l_run, 32, 64);
   if (qpos >= 0) {
     const float inv = 1.0f / l_run;
-    f16* orow = out + (size_t)(row0 + qpos) * ldo + head * HD;
+    const int m = row0 + qpos;                             // rows of fragment order, 16 bytes apart: an instruction writes 512 in a row
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -387,13 +387,13 @@ __global__ __launch_bounds__(256, !TWO && HD == 64 ? 4 : 2) void flash_prefill_k
           e[r] = v - (float)w[r];
           we[r] = from_f32<f16>(e[r]);
         }
-        *(f16x4*)(orow + dt * 32 + 8 * i + 4 * half) = w;
+        const int k = head * HD + dt * 32 + 8 * i + 4 * half;
+        *(f16x4*)(out + act_index(m, k, ldo)) = w;
         if constexpr (TWO) {
-          if (out_lo8)                                     // 8-bit low terms: bytes behind the row's lo_off high terms
-            *(int*)((unsigned char*)(out + (size_t)(row0 + qpos) * ldo + lo_off) + head * HD + dt * 32 + 8 * i + 4 * half) =
-                pack_lo8(e[0], e[1], e[2], e[3]);
+          if (out_lo8)                                     // 8-bit low terms, behind the lo_off high terms
+            *(int*)((unsigned char*)out + act_lo8_index(m, k, ldo, lo_off)) = pack_lo8(e[0], e[1], e[2], e[3]);
           else
-            *(f16x4*)(orow + lo_off + dt * 32 + 8 * i + 4 * half) = we;
+            *(f16x4*)(out + act_index(m, lo_off + k, ldo)) = we;
         }
       }
   }

@@ -127,12 +127,23 @@ struct RopeKv {
 constexpr float kWeightScale = 256.0f;
 constexpr int kMaxKSplit = 4;   // most partial planes (groups of 4 K slices) a decode GEMM writes
 
+// Element (m, k) of an operand of ld halves a row in MFMA fragment order: blocks of 32 rows, in each [k / 16][lane][8] where lane
+// l holds row l & 31 and k = 8 * (l >> 5) .. + 7.  32 rows of 64 k are 4 KiB, so a slab of a product is loaded in pieces of
+// one KiB, and rows that follow one another lie 16 bytes apart, so a kernel that holds many of them writes whole lines.
+__device__ __forceinline__ size_t act_index(int m, int k, int ld) {
+  return (size_t)(m >> 5) * 32 * ld + (size_t)(k >> 4) * 512 + ((m & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+}
+// Byte of its 8-bit low terms: they follow the Kw high terms of a block, [k / 32][lane][16], lane l: row l & 31, k = 16 * (l >> 5) ..
+__device__ __forceinline__ size_t act_lo8_index(int m, int k, int ld, int Kw) {
+  return (size_t)(m >> 5) * 64 * ld + (size_t)64 * Kw + (size_t)(k >> 5) * 1024 + ((m & 31) + 32 * ((k >> 4) & 1)) * 16 + (k & 15);
+}
+
 // Two-term activations: a value a is carried as hi = f16(a) and lo = f16(a - hi) (together about 22 significant
-// bits).  Row-major operands keep them side by side, A = [hi | lo] with K = 2 * Kw columns; since the weights
+// bits).  Operands keep them side by side, A = [hi | lo] with K = 2 * Kw columns; since the weights
 // are exact, A * W^T = hi * W^T + lo * W^T is one contraction over 2 * Kw in which the weight index wraps.
 struct GemmF16 {
-  const f16* A;    // [M, K] row-major activations
-  int lda;
+  const f16* A;    // [M, K] activations in fragment order, allocated to a multiple of 32 rows (see act_index)
+  int lda;         // halves a row
   const f16* Wp;   // [N, Kw] weights * kWeightScale in MFMA fragment order (see pack_weight_f16)
   int M, N, K;     // K = Kw (single-term A), 2 * Kw (two-term A, half-precision low terms) or, with W8, 1.5 * Kw
   int Kw;          //   (two-term A whose low terms are bytes: row = [hi: Kw halves | lo8: Kw bytes]; Kw % 128 == 0)

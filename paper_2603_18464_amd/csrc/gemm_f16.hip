@@ -2,7 +2,9 @@
 // work fused into the epilogue (residual add; SwiGLU; rotary embedding + KV-cache write).
 //
 // Operand layouts
-//   A   row-major [M, lda] f16 (activations produced by this library).
+//   A   [M, K] f16 in fragment order like the weights, lda halves a row: blocks of 32 rows, in each its slabs of 64 k (4 KiB: four
+//       blocks of 16 k), behind those of the high terms those of the low ones (act_index, act_lo8_index).  A row-major A costs
+//       the same bytes as 128-byte pieces of eight rows an instruction instead of one KiB, and an address a lane.
 //   Wp  weights (bf16 at the boundary, re-encoded exactly as f16 * kWeightScale) repacked once at
 //       load time into MFMA fragment order: the 32x16 block
 //       (rows n0..n0+31, k0..k0+15) is stored as 64 lanes x 8 halves = 1 KiB, lane l holding
@@ -85,38 +87,40 @@ struct EpiSwiglu {
   f16* act;
   int ld;
   int f;        // number of outputs per row
-  int lo_mode;  // 0: single-term; 1: half-precision low terms at act[m][f + j]; 2: bytes at ((char*)&act[m][f])[j]
+  int lo_mode;  // 0: single-term; 1: half-precision low terms of output j at column f + j; 2: bytes (act_lo8_index)
+  // A lane finishes eight outputs of a row, 16 bytes of a fragment; the lanes of an instruction are 32 (16) rows by 2 (4) such.
   template <int COLS, int PITCH, int ROWS>
   __device__ __forceinline__ void consume(const float* tile, int m_base, int nb, int lane, int M) const {
-    typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-    constexpr int LPR = COLS / 8, RPI = 64 / LPR;
-    const int rs = lane / LPR, q = lane % LPR, jb = q >> 3, c4 = (q & 7) * 4;
+    typedef __attribute__((ext_vector_type(2))) int i32x2;
+    constexpr int PIECES = COLS / 16, PPI = 64 / ROWS;     // of a row; of a row and instruction
+    static_assert(PIECES % PPI == 0, "whole instructions");
+    const int r = lane % ROWS, m = m_base + r;
 #pragma unroll
-    for (int it = 0; it < ROWS / RPI; ++it) {
-      const int r = it * RPI + rs, m = m_base + r;
-      const f32x4 g = *(const f32x4*)(tile + r * PITCH + jb * 64 + c4);
-      const f32x4 u = *(const f32x4*)(tile + r * PITCH + jb * 64 + 32 + c4);
-      f16x4 o;
-      float a[4];
+    for (int it = 0; it < PIECES / PPI; ++it) {
+      const int p = it * PPI + lane / ROWS, c = (p >> 2) * 64 + (p & 3) * 8, k = nb / 2 + p * 8;
+      float a[8], e[8];
+      f16x8 o;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        a[j] = swiglu_scaled(g[j], u[j]);
-        o[j] = from_f32<f16>(a[j]);
+      for (int h = 0; h < 2; ++h) {
+        const f32x4 g = *(const f32x4*)(tile + r * PITCH + c + 4 * h);
+        const f32x4 u = *(const f32x4*)(tile + r * PITCH + c + 32 + 4 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[4 * h + j] = swiglu_scaled(g[j], u[j]);
       }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = from_f32<f16>(a[j]);
       if (m < M) {
-        f16* row = act + (size_t)m * ld;
-        *(f16x4*)(row + nb / 2 + jb * 32 + c4) = o;
+        *(f16x8*)(act + act_index(m, k, ld)) = o;
         if (lo_mode != 0) {                  // (uniform) low terms only where the layer carries them
-          float e[4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) e[j] = a[j] - (float)o[j];
+          for (int j = 0; j < 8; ++j) e[j] = a[j] - (float)o[j];
           if (lo_mode == 1) {
-            f16x4 oe;
+            f16x8 oe;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) oe[j] = from_f32<f16>(e[j]);
-            *(f16x4*)(row + f + nb / 2 + jb * 32 + c4) = oe;
+            for (int j = 0; j < 8; ++j) oe[j] = from_f32<f16>(e[j]);
+            *(f16x8*)(act + act_index(m, f + k, ld)) = oe;
           } else {
-            *(int*)((unsigned char*)(row + f) + nb / 2 + jb * 32 + c4) = pack_lo8(e[0], e[1], e[2], e[3]);
+            *(i32x2*)((unsigned char*)act + act_lo8_index(m, k, ld, f)) = i32x2{pack_lo8(e[0], e[1], e[2], e[3]), pack_lo8(e[4], e[5], e[6], e[7])};
           }
         }
       }
@@ -273,10 +277,7 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   Against 4 waves of 128x128 with 32x32x16 and 32x32x64 the 7B policy step of 64 takes 244.5 instead of 247.5 ms (its
 //   4 two-term layers are a sixth of it), of 8 54.0 instead of 54.2, the 12-layer model's of 32 6.24 instead of 6.29;
 //   with 128x256 tiles at every size 247.9, 54.3 and 6.22.
-// * A slab layout: rows of PK halves; chunk c (16 bytes) of row r sits in slot c ^ swz(r).  The LDS serves a 16-byte
-//   read in groups of 16 lanes, {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} of each half-wave pair, so a group of the
-//   16x16 reads mixes two chunk columns; swz is chosen so that such a group covers all 64 banks (plain (r >> 2) & 3
-//   for 64-byte rows costs a two-way conflict there).  The weight slab is in fragment order and needs no swizzle.
+// * Both slabs are in fragment order, so that a load is one KiB from one place and a read of the LDS has no bank conflicts.
 // * Every variant runs the same sequence of MFMAs per output element (k ascending, one chain), so a sequence's bits do
 //   not depend on which tile its batch selects.
 
@@ -334,49 +335,53 @@ __device__ __forceinline__ void static_for(F&& f) {
 // products of the first separate source and result registers, and the 256 of a wave run out (12 spilled, reloaded in
 // the loop with a wait for every load in flight).  The compiler does not know the latency of the statement: settle()
 // before anything but another of these touches the accumulators.
+// AGPR: the accumulators are in the accumulation half of the register file (a wave of 128x128 has 256 of them, which is all of
+// it; left to itself the compiler moves them back and forth).
+template <bool AGPR>
 __device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const f16x8& b) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+  if constexpr (AGPR) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 #endif
 }
-// The wait on both sides of a run of such products (8 issue slots behind a product, 2 in front of one; 32 given), eight
-// accumulators a statement.  It takes them and gives them back, so whatever reads them, register copies included,
-// depends on it.
-template <int MT, int NT>
+// The wait on both sides of a run of such products (8 issue slots behind a product, 2 in front of one; 32 given), four
+// accumulators a statement, in the first of them.  They take the accumulators and give them back, so whatever reads them,
+// register copies included, depends on it.
+template <bool AGPR, int MT, int NT>
 __device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
-  static_assert(MT * NT % 4 == 0, "whole groups of eight, and one of four");
+  static_assert(MT * NT % 4 == 0, "whole groups of four");
 #if defined(__HIP_DEVICE_COMPILE__)
-#define VLA_ACC(j) "+v"(acc[(g + j) / NT][(g + j) % NT])
-  constexpr int EIGHTS = MT * NT / 8 * 8;
-#pragma unroll
-  for (int g = 0; g < EIGHTS; g += 8)
-    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3), VLA_ACC(4), VLA_ACC(5), VLA_ACC(6),
-                 VLA_ACC(7));
-  if constexpr (EIGHTS < MT * NT) {
-    constexpr int g = EIGHTS;
-    asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(0), VLA_ACC(1), VLA_ACC(2), VLA_ACC(3));
-  }
+#define VLA_ACC(c, j) "+" c(acc[(g + j) / NT][(g + j) % NT])
+#define VLA_SETTLE4(nops, c) asm volatile(nops : VLA_ACC(c, 0), VLA_ACC(c, 1), VLA_ACC(c, 2), VLA_ACC(c, 3))
+  static_for<MT * NT / 4>([&](auto G) VLA_INLINE {
+    constexpr int g = 4 * decltype(G)::value;
+    if constexpr (AGPR && g == 0) VLA_SETTLE4("s_nop 15\n\ts_nop 15", "a");
+    else if constexpr (AGPR) VLA_SETTLE4("", "a");
+    else if constexpr (g == 0) VLA_SETTLE4("s_nop 15\n\ts_nop 15", "v");
+    else VLA_SETTLE4("", "v");
+  });
+#undef VLA_SETTLE4
 #undef VLA_ACC
 #endif
 }
 
 constexpr int PK = 64;                                 // k of a slab (a slab of low terms is one 128-deep product)
-__device__ __forceinline__ int a_swizzle(int r) { return (r >> 1) & 7; }
 
 template <class Epi> __device__ __forceinline__ const f16* epi_a_lo(const Epi&) { return nullptr; }
 __device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a_lo; }
 
 // LO8: the launch has slabs of 8-bit low terms (W8 != nullptr): K == 1.5 * Kw, A row = [hi: Kw halves | lo8: Kw bytes].
 // Otherwise K == Kw, or K == 2 * Kw (half-precision low terms behind the high terms: the weight slabs wrap).
-// SPLITK (with EpiPartial; one row of tiles, M <= BM): A is in the fragment order of the decode path
-// ([m/32][k/16][lane][8], the low terms of two-term operands in a second buffer of the same order), tiles_m is the
-// number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
+// SPLITK (with EpiPartial; one row of tiles, M <= BM): the low terms of two-term operands are in a second buffer of the order of
+// the first, tiles_m is the number of K slices, and workgroup (tile column tn, slice kz) accumulates slice kz of K only.
 template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, class Epi, bool LO8, bool SPLITK>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16* __restrict__ A, int lda,
                                                                    const f16* __restrict__ Wp,
                                                                    const f16* __restrict__ W8, int M, int K, int Kw,
                                                                    int tiles_m, int tiles_n, Epi epi_in) {
   constexpr int NW = WGM * WGN, BM = WGM * WM, BN = WGN * WN, MT = WM / 16, NT = WN / 16;
+  constexpr bool AGPR = MT * NT == 64;
+  static_assert(!AGPR || !LO8, "the products of low terms leave their accumulators to the compiler");
   constexpr int KS = PK / 32, KS16 = PK / 16;          // k-steps of a slab; 16-k blocks of a slab
   // KiB pieces per wave and slab.  Where those of A do not divide among the waves (REST of them are left for the last round),
   // piece i of a wave is piece i * NW + wave of the slab, and the last round's are loaded by several waves: the same bytes to
@@ -385,14 +390,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   constexpr int A_ALL = BM * PK / 512, AP = (A_ALL + NW - 1) / NW, WP = BN * PK / 512 / NW, LPS = AP + WP;
   constexpr int REST = A_ALL % NW;
   static_assert(A_ALL * 512 == BM * PK && WP * NW * 512 == BN * PK, "slab must divide among the waves");
-  static_assert(REST == 0 || (REST % 2 == 0 && NW % 2 == 0 && !SPLITK), "all pieces of a wave have the same swizzle then");
+  static_assert(BM % 32 == 0, "whole blocks of A");
   // Rings of one depth are one ring of [A slab | W slab], with one offset a stage (two rings: 128x256 tiles 0.6 % slower,
   // 128x128 0.3 %); else they follow one another.
   constexpr int A_HALVES = BM * PK, W_HALVES = BN * PK, A_STAGE = A_HALVES + (SW == S ? W_HALVES : 0);
   constexpr int W_STAGE = SW == S ? A_STAGE : W_HALVES, W0_HALVES = SW == S ? A_HALVES : S * A_HALVES;
   static_assert(SW == S || SW == S + 1, "the counts of loads in flight below");
-  static_assert(!SPREAD || (WP % KS16 == 0 && SW == S + 1 && !DEEP && !LO8), "as counted below");
-  constexpr int RPP = 512 / PK;                        // rows of A per piece
+  static_assert(!SPREAD || (SW == S + 1 && !DEEP && !LO8), "as counted below");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   f16* lds = (f16*)smem;                               // [S][A slab | W slab], or [S][A slab], [SW][W slab]
 
@@ -437,32 +441,21 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   }
 
   const unsigned lane16 = (unsigned)lane * 16u;        // lane offset in an operand in fragment order
-  const f16* a_base = SPLITK ? A + kb0 * 512 : A + (size_t)m0 * lda;
+  const f16* a_base = A + (size_t)m0 * lda + kb0 * 512;
   const f16* a_lo_base = SPLITK && epi_a_lo(epi) ? epi_a_lo(epi) + kb0 * 512 : a_base;
   const f16* w_base = Wp + ((size_t)(n0 / 32) * KB16 + kb0) * 512;
   const f16* w8_base = LO8 ? W8 + (size_t)(n0 / 32) * KB16 * 256 : w_base;
-  // Rows of A: piece i of a wave holds rows r0 + i * RPP (clamped to the last one), whose swizzle is that of r0 with the
-  // chunk's bits of swz(i * RPP) flipped, so two registers serve all pieces.
-  const unsigned a_pitch = 2u * (unsigned)lda, a_last = (unsigned)min(M - 1 - m0, BM - 1) * a_pitch;   // (fits 32 bits)
-  const int r0 = wave * (REST ? 1 : AP) * RPP + lane / (PK / 8);
-  const unsigned a_back = REST ? (unsigned)(wave - wave % (REST ? REST : 1)) : 0u;    // pieces a wave's last one is moved back by
-  const unsigned a_row = (unsigned)r0 * a_pitch, a_chunk = (unsigned)((lane % (PK / 8)) ^ a_swizzle(r0)) * 16u;
+  const unsigned a_block = 64u * (unsigned)lda;        // bytes of a block of 32 rows of A
+  const int a_last = (M - 1 - m0) >> 5;                // last block there is (a launch's rows are allocated in whole blocks)
+  const int a_back = REST ? wave - wave % (REST ? REST : 1) : 0;     // pieces a wave's last one is moved back by
   auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped), A first
     constexpr int i = decltype(I)::value;
     const int ks = min(kt, KT - 1), kw = ks >= KTw ? ks - KTw : ks;
-    if constexpr (i < AP) {
-      f16* dst = lds + (kt % S) * A_STAGE + (REST ? i * NW + wave - (i == AP - 1 ? (int)a_back : 0) : wave * AP + i) * 512;
-      if constexpr (SPLITK) {
-        const int j = wave * AP + i;                   // piece of the slab: block row j / KS16 (clamped to the rows
-        const int rb = min(j / KS16, (M - 1) >> 5);    // that exist), 16-k block j % KS16
-        load_to_lds_16(ks >= KTw ? a_lo_base : a_base, lane16, 1024u * (unsigned)(rb * KB16 + j % KS16 + kw * KS16), dst);
-      } else {
-        unsigned row = a_row;
-        hold32(row);                                   // the offset is formed here, three instructions a load, and not kept
-        if constexpr (REST) row = min(row + (unsigned)(i * NW * RPP - (i == AP - 1 ? (int)a_back * RPP : 0)) * a_pitch, a_last) + a_chunk;
-        else row = min(row + (unsigned)(i * RPP) * a_pitch, a_last) + (a_chunk ^ (unsigned)(a_swizzle(i * RPP) * 16));
-        load_to_lds_16(a_base, row, 2u * PK * (unsigned)ks, dst);
-      }
+    if constexpr (i < AP) {                            // piece j of the slab: block row j / KS16 (clamped), 16-k block j % KS16
+      const int j = REST ? i * NW + wave - (i == AP - 1 ? a_back : 0) : wave * AP + i;
+      const unsigned blk = (unsigned)min(j / KS16, a_last) * a_block + (unsigned)(j % KS16) * 1024u;
+      const bool low = SPLITK && ks >= KTw;
+      load_to_lds_16(low ? a_lo_base : a_base, lane16, blk + 1024u * KS16 * (unsigned)(SPLITK ? kw : ks), lds + (kt % S) * A_STAGE + j * 512);
     } else {
       const int j = wave * WP + i - AP;                // piece of the slab: block row j / KS16, 16-k block j % KS16
       const bool low = LO8 && ks >= KTw;
@@ -471,8 +464,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     }
   };
 
-  // x-th of a wave's weight pieces that hold the first (second) 32 k of the slab
-  constexpr auto half_piece = [](int x, bool second) { return AP + x / (KS16 / 2) * KS16 + x % (KS16 / 2) + (second ? KS16 / 2 : 0); };
   auto issue_next = [&](int kt, auto I) VLA_INLINE {   // piece I of what takes the stages of slab kt
     issue_one(decltype(I)::value < AP ? kt + S : kt + SW, I);
   };
@@ -486,15 +477,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   // LDS byte addresses of this lane's fragments inside stage 0.  A lane of a fragment is (row l % 16, k group
   // l / 16 of 8 k); in fragment order its 16 bytes are at 16 * (row & 31) + 512 * (group & 1) of 16-k block group / 2.
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char*)smem);
-  const int frow = wm * WM + (lane & 15), fgrp = lane >> 4;
+  const int fgrp = lane >> 4;
   const unsigned in_block = (unsigned)(fgrp >> 1) * 1024u + (unsigned)(fgrp & 1) * 512u + (unsigned)(lane & 15) * 16u;
-  unsigned a_k[KS];
-#pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const int c = 4 * s + fgrp;                        // 16-byte chunk of the row
-    if constexpr (SPLITK) a_k[s] = lds0 + (unsigned)(wm * (WM / 32) * KS16) * 1024u + in_block;
-    else a_k[s] = lds0 + 2u * (unsigned)(frow * PK + ((c ^ a_swizzle(frow)) << 3));
-  }
+  // first fragment of A of this wave, and what is added for every second one: of wave tiles of an odd number of fragments the
+  // second begins in the middle of a block
+  const int a_frag = wm * MT;
+  const unsigned a_even = lds0 + (unsigned)(a_frag >> 1) * (KS16 * 1024u) + (unsigned)(a_frag & 1) * 256u + in_block;
+  const unsigned a_odd = MT % 2 ? a_even + (a_frag & 1 ? KS16 * 1024u - 512u : 0u) : a_even;
   const unsigned w_b = lds0 + 2u * (unsigned)(W0_HALVES + wn * (WN / 32) * KS16 * 512) + in_block;
 
   constexpr int NBUF = DEEP ? 2 * KS : 2;              // register buffers, a k-step each
@@ -508,7 +497,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   // fragments)
   auto read_a = [&](Stages so, f16x8& dst, auto SS, auto J) VLA_INLINE {
     constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
-    read_frag_asm<SPLITK ? (j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256 : j * 16 * PK * 2>(dst, a_k[ss] + so.a);
+    read_frag_asm<(j / 2 * KS16 + 2 * ss) * 1024 + (j & 1) * 256>(dst, (j & 1 ? a_odd : a_even) + so.a);
   };
   auto read_b = [&](Stages so, f16x8& dst, auto SS, auto J) VLA_INLINE {
     constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
@@ -543,18 +532,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     const Stages so = stages_of(kt + (next ? 1 : 0));
     static_for<MF>([&](auto I) VLA_INLINE {
       constexpr int i = decltype(I)::value, mt = i / NT, nt = i % NT;
-      if constexpr (LO8) mfma_in_place(acc[mt][nt], af[f][mt], bf[f][nt]);
+      if constexpr (LO8 || AGPR) mfma_in_place<AGPR>(acc[mt][nt], af[f][mt], bf[f][nt]);
       else acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[f][mt], bf[f][nt], acc[mt][nt], 0, 0, 0);
       constexpr int r0 = i < n_rd ? i * R / n_rd : R, r1 = i < n_rd ? (i + 1) * R / n_rd : R;
       static_for<r1 - r0>([&](auto J) VLA_INLINE {
         read_one(so, g, std::integral_constant<int, DEEP ? ss : (last ? 0 : ss + 1)>{}, std::integral_constant<int, r0 + decltype(J)::value>{});
       });
-      if constexpr (SPREAD) {                          // last k-step: A and the first 32 k of W; the next one: the other 32 k
-        constexpr int n = last ? AP + WP / 2 : WP / 2, l0 = i * n / MF, l1 = (i + 1) * n / MF;
+      if constexpr (SPREAD) {                          // last k-step: A; the next one: W
+        constexpr int n = last ? AP : WP, l0 = i * n / MF, l1 = (i + 1) * n / MF;
         static_for<l1 - l0>([&](auto J) VLA_INLINE {
-          constexpr int x = l0 + decltype(J)::value;
-          if constexpr (last && x < AP) issue_next(kt, std::integral_constant<int, x>{});
-          else issue_next(last ? kt : kt - 1, std::integral_constant<int, half_piece(x - (last ? AP : 0), !last)>{});
+          issue_next(last ? kt : kt - 1, std::integral_constant<int, (last ? 0 : AP) + l0 + decltype(J)::value>{});
         });
       } else if constexpr (next) {
         constexpr int at = DEEP ? ss * MF + i : i, of = DEEP ? KS * MF : MF;
@@ -573,13 +560,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   constexpr std::integral_constant<int, 1> c1{};
   constexpr std::integral_constant<int, DEEP ? 1 : 0> cn{};       // P of an odd slab
   static_for<S>([&](auto I) VLA_INLINE { static_for<LPS>([&](auto J) VLA_INLINE { issue_one(decltype(I)::value, J); }); });
-  static_for<SW - S>([&](auto I) VLA_INLINE {
-    static_for<SPREAD ? WP / 2 : WP>([&](auto J) VLA_INLINE {
-      constexpr int j = decltype(J)::value;
-      issue_one(S + decltype(I)::value, std::integral_constant<int, SPREAD ? half_piece(j, false) : AP + j>{});
+  if constexpr (!SPREAD)
+    static_for<SW - S>([&](auto I) VLA_INLINE {
+      static_for<WP>([&](auto J) VLA_INLINE { issue_one(S + decltype(I)::value, std::integral_constant<int, AP + decltype(J)::value>{}); });
     });
-  });
-  wait_vmcnt<(S - 1) * LPS + (SW - S) * (SPREAD ? WP / 2 : WP)>();
+  wait_vmcnt<(S - 1) * LPS + (SPREAD ? 0 : (SW - S) * WP)>();
   __builtin_amdgcn_s_barrier();
   static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE {
     static_for<R>([&](auto I) VLA_INLINE { read_one(stages_of(0), decltype(SS)::value, SS, I); });
@@ -587,8 +572,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   static_for<DEEP ? KS : 1>([&](auto SS) VLA_INLINE { arrived(decltype(SS)::value); });
   const int KTh = LO8 ? KTw : KT;
   int kt = 0;
+  if constexpr (LO8 || AGPR) settle<AGPR>(acc);        // the zeros are written
   if constexpr (LO8) {
-    settle(acc);                                       // the zeros are written
     if constexpr (DEEP) {
       for (; kt + 1 < KTh; kt += 2) {
         slab(kt, c0);
@@ -598,7 +583,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     } else {
       for (; kt < KTh; ++kt) slab(kt, c0);
     }
-    settle(acc);
+    settle<AGPR>(acc);
     // Fragments of one slab, k-steps 0 and 1: variables of their own, read afresh, since the product wants the two in
     // adjacent registers and the loop above must not be bound by that.  Reads are issued in the order: first-half A
     // fragments, B fragments column by column, second-half A fragments.
@@ -675,6 +660,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
     }
     if (kt < KTh) slab(kt, c0);
   }
+  if constexpr (AGPR) settle<AGPR>(acc);
   wait_vmcnt<0>();                                     // the clamped tail loads still target this workgroup's LDS
   __syncthreads();                                     // every wave is done with the slabs: LDS becomes epilogue staging
 
@@ -752,8 +738,8 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
   const int k = Afrag_lo ? 2 * K : K;
   // 256 columns a workgroup re-read the activations least, but a matrix of 4096 columns would occupy 64 compute units: 64
   // columns then.  256 rows, K = 4096 / 11008: 17 / 39 us (256 columns 46 / 83, two weight-streaming launches 45 / 72).
-  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 2, 3, 1, false, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
-  else launch_tiles<4, 2, 64, 32, 4, 4, 1, false, false, false, true>(Afrag, 0, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
+  if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 2, 3, 1, false, false, false, true>(Afrag, K, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
+  else launch_tiles<4, 2, 64, 32, 4, 4, 1, false, false, false, true>(Afrag, K, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -889,7 +875,8 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
       if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
       break;
     default:
-      if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, LO8>(g, epi, st);
+      if constexpr (!LO8 && resid) launch<2, 2, 128, 128, 2, 3, 1, false, true, LO8>(g, epi, st);
+      else if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, LO8>(g, epi, st);
   }
 }
 template <class Epi>

@@ -118,26 +118,21 @@ __global__ __launch_bounds__(256) void gather_tail_kernel(const f16* __restrict_
                                                           const int32_t* __restrict__ need, int d,
                                                           f16* __restrict__ att_frag, f16* __restrict__ att_frag_lo,
                                                           float* __restrict__ x_c) {
+  typedef __attribute__((ext_vector_type(2))) int i32x2;
   const int i = blockIdx.x, src = need[i];
-  const u32x4* arow = (const u32x4*)(att + (size_t)src * ld_att);
-  u32x4* ablk = (u32x4*)(att_frag + (size_t)(i >> 5) * (d >> 4) * 512);
-  for (int kc = threadIdx.x; kc < (d >> 3); kc += blockDim.x)
-    ablk[(size_t)(kc >> 1) * 64 + (i & 31) + 32 * (kc & 1)] = arow[kc];
-  if (att_frag_lo) {                       // two-term rows [hi | lo]: the low terms follow at column d
-    u32x4* lblk = (u32x4*)(att_frag_lo + (size_t)(i >> 5) * (d >> 4) * 512);
-    if (lo8) {                             // ... as bytes: widened to half precision (exact)
-      const int* lrow = (const int*)(att + (size_t)src * ld_att + d);
-      for (int kc = threadIdx.x; kc < (d >> 3); kc += blockDim.x) {
-        const int w0 = lrow[2 * kc], w1 = lrow[2 * kc + 1];
+  for (int k = threadIdx.x * 8; k < d; k += blockDim.x * 8) {
+    const size_t to = act_index(i, k, d);
+    *(u32x4*)(att_frag + to) = *(const u32x4*)(att + act_index(src, k, ld_att));
+    if (att_frag_lo) {
+      if (lo8) {                             // low terms as bytes: widened to half precision (exact)
+        const i32x2 w = *(const i32x2*)((const unsigned char*)att + act_lo8_index(src, k, ld_att, d));
         f16x8 h;
-        h[0] = (f16)unpack_lo8(w0, 0); h[1] = (f16)unpack_lo8(w0, 1); h[2] = (f16)unpack_lo8(w0, 2); h[3] = (f16)unpack_lo8(w0, 3);
-        h[4] = (f16)unpack_lo8(w1, 0); h[5] = (f16)unpack_lo8(w1, 1); h[6] = (f16)unpack_lo8(w1, 2); h[7] = (f16)unpack_lo8(w1, 3);
-        lblk[(size_t)(kc >> 1) * 64 + (i & 31) + 32 * (kc & 1)] = __builtin_bit_cast(u32x4, h);
+        h[0] = (f16)unpack_lo8(w[0], 0); h[1] = (f16)unpack_lo8(w[0], 1); h[2] = (f16)unpack_lo8(w[0], 2); h[3] = (f16)unpack_lo8(w[0], 3);
+        h[4] = (f16)unpack_lo8(w[1], 0); h[5] = (f16)unpack_lo8(w[1], 1); h[6] = (f16)unpack_lo8(w[1], 2); h[7] = (f16)unpack_lo8(w[1], 3);
+        *(f16x8*)(att_frag_lo + to) = h;
+      } else {
+        *(u32x4*)(att_frag_lo + to) = *(const u32x4*)(att + act_index(src, d + k, ld_att));
       }
-    } else {
-      const u32x4* lrow = (const u32x4*)(att + (size_t)src * ld_att + d);
-      for (int kc = threadIdx.x; kc < (d >> 3); kc += blockDim.x)
-        lblk[(size_t)(kc >> 1) * 64 + (i & 31) + 32 * (kc & 1)] = lrow[kc];
     }
   }
   const f32x4* xr = (const f32x4*)(x + (size_t)src * d);
@@ -252,7 +247,7 @@ void score_rows(const float* logits, int rows, int A, float temperature, const i
 }
 
 // ---- RMSNorm ----------------------------------------------------------------------------------------
-// out[r, :] = x[row, :] * gain / sqrt(mean(x^2) + eps), statistics in float32; one workgroup per row.
+// out[r, :] = x[row, :] * gain / sqrt(mean(x^2) + eps), statistics in float32.
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
   v = wave_sum(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -262,54 +257,129 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gain,
-                                                      f16* __restrict__ out, int d, float eps, int ldo, int lo_mode) {
+// A barrier that orders the LDS alone: __syncthreads() would wait for the stores to global memory as well.
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
+}
+// The rows of a prefill, to fragment order: ROWS rows a workgroup, WPR waves each, HELD pieces of 256 elements a wave in registers
+// between the two passes.  Bound by HBM, few rows by latency.  The 16-byte pieces of a row lie 512 bytes apart, those of the
+// workgroup's rows side by side: the output goes through LDS, SPAN columns at a time, and leaves as segments of 16 * ROWS bytes, a
+// block's 32 rows from one XCD, whose L2 puts the lines together.  ONCE: the rows outgrow the last-level cache and are read as
+// data that does not come again, which leaves the lines in the L2 until they are whole.
+// us, one row a workgroup to rows of d / this: d 4096 290 rows 3.6 / 4.3, 2338 12.4 / 13.8, 7104 29.9 / 33.4, 18560 81 / 80 (93
+// without ONCE); d 768 288 rows 2.6 / 2.7, 9216 10.5 / 9.1.
+template <int ROWS, int WPR, int HELD, bool ONCE>
+__global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gain,
+                                                                  f16* __restrict__ out, int rows, int d, float eps, int ldo, int lo_mode) {
   typedef __attribute__((ext_vector_type(4))) f16 f16x4;
-  __shared__ float red[4];
-  const int r = blockIdx.x;
-  const float* row = x + (size_t)r * d;
-  constexpr int kHeld = 8;                 // float4 per thread kept in registers: rows up to 8192 wide are read once
-  f32x4 held[kHeld];
-  float ss = 0.f;
+  constexpr int SP = HELD < 4 ? HELD : 4, STEP = WPR * 256, SPAN = SP * STEP, NT = ROWS * WPR * 64;
+  constexpr int PITCH = SPAN + 16;                         // (spreads the rows of a read over the banks)
+  __shared__ __attribute__((aligned(16))) f16 s_hi[ROWS][PITCH];
+  __shared__ __attribute__((aligned(16))) f16 s_lo[ROWS][PITCH];     // or bytes, SPAN + 32 a row
+  unsigned char* s_lo8 = (unsigned char*)s_lo;
+  const int r0 = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * ROWS;
+  if (r0 >= rows) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) / WPR;
+  const int c0 = (threadIdx.x % (WPR * 64)) * 4;
+  const float* row = x + (size_t)min(r0 + wave, rows - 1) * d;
+  f32x4 held[HELD];
 #pragma unroll
-  for (int it = 0; it < kHeld; ++it) {
-    const int i = threadIdx.x * 4 + it * 1024;
-    held[it] = i < d ? *(const f32x4*)(row + i) : f32x4{0.f, 0.f, 0.f, 0.f};
-    ss += held[it][0] * held[it][0] + held[it][1] * held[it][1] + held[it][2] * held[it][2] + held[it][3] * held[it][3];
+  for (int it = 0; it < HELD; ++it) held[it] = c0 + it * STEP < d ? load_once<ONCE>((const f32x4*)(row + c0 + it * STEP)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 g[SP];
+  auto gains = [&](int k0) {                               // of the next span
+#pragma unroll
+    for (int i = 0; i < SP; ++i)
+      if (k0 + c0 + i * STEP < d) g[i] = *(const f32x4*)(gain + k0 + c0 + i * STEP);
+  };
+  gains(0);
+  // Whatever the form, the squares are added in one order: of a lane's pieces of 256 elements those of one number modulo four in a
+  // sum, (s0 + s1) + (s2 + s3), a butterfly over the lanes.
+  static_assert(4 % WPR == 0 && HELD % (4 / WPR) == 0, "a wave has the pieces of 4 / WPR of the sums");
+  constexpr int NS = 4 / WPR;
+  float ss[NS] = {};
+  auto squares = [&](const f32x4& v, int s) { ss[s] += fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], v[0] * v[0]))); };
+#pragma unroll
+  for (int it = 0; it < HELD; ++it) squares(held[it], it % NS);
+  for (int k = c0 + HELD * STEP; k < d; k += NS * STEP)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (k + s * STEP < d) squares(*(const f32x4*)(row + k + s * STEP), s);
+  float sum;
+  if constexpr (WPR == 1) {
+    sum = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+  } else {
+    __shared__ float s_sum[ROWS][4][64];                   // (sum s is that of wave s % WPR)
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % WPR;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) s_sum[wave][s * WPR + w][lane] = ss[s];
+    lds_barrier();
+    sum = (s_sum[wave][0][lane] + s_sum[wave][1][lane]) + (s_sum[wave][2][lane] + s_sum[wave][3][lane]);
   }
-  for (int i = threadIdx.x * 4 + kHeld * 1024; i < d; i += 1024) {
-    const f32x4 v = *(const f32x4*)(row + i);
-    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-  }
-  ss = block_sum_256(ss, red);
-  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  f16* o = out + (size_t)r * ldo;
-  // lo_mode 1 (two-term output): the low terms go to column d + i; 2: as bytes behind the d high terms
-  auto emit = [&](int i, const f32x4& v) {
-    const f32x4 g = *(const f32x4*)(gain + i);
+  sum = wave_sum(sum);
+  const float inv = 1.0f / sqrtf(sum / (float)d + eps);
+  auto put = [&](int c, const f32x4& v, const f32x4& g) {  // columns c .. + 3 of the span
     f16x4 q, qe;
     float e[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float h = v[j] * inv * g[j];
+      float h = v[j] * inv * g[j];
+      asm("" : "+v"(h));                                   // the product is rounded here, in every form
       q[j] = from_f32<f16>(h);
       e[j] = h - to_f32(q[j]);
       qe[j] = from_f32<f16>(e[j]);
     }
-    *(f16x4*)(o + i) = q;
-    if (lo_mode == 1) *(f16x4*)(o + d + i) = qe;
-    if (lo_mode == 2) *(int*)((unsigned char*)(o + d) + i) = pack_lo8(e[0], e[1], e[2], e[3]);
+    *(f16x4*)&s_hi[wave][c] = q;
+    if (lo_mode == 1) *(f16x4*)&s_lo[wave][c] = qe;
+    if (lo_mode == 2) *(int*)(s_lo8 + wave * (SPAN + 32) + c) = pack_lo8(e[0], e[1], e[2], e[3]);
+  };
+  // the rows of a span, side by side; low terms of lo_mode 1 go to column d + k, of 2 as bytes behind the block's high terms
+  auto leave = [&](int k0) {
+    lds_barrier();
+    const int n = min(d - k0, SPAN), m = r0 + threadIdx.x % ROWS;
+    const f16 *hi = s_hi[threadIdx.x % ROWS], *lo = s_lo[threadIdx.x % ROWS];
+    const unsigned char* lo8 = s_lo8 + threadIdx.x % ROWS * (SPAN + 32);
+    if (m < rows) {
+      for (int c = threadIdx.x / ROWS * 8; c < n; c += NT / ROWS * 8) {
+        *(u32x4*)(out + act_index(m, k0 + c, ldo)) = *(const u32x4*)(hi + c);
+        if (lo_mode == 1) *(u32x4*)(out + act_index(m, d + k0 + c, ldo)) = *(const u32x4*)(lo + c);
+      }
+      if (lo_mode == 2)
+        for (int c = threadIdx.x / ROWS * 16; c < n; c += NT / ROWS * 16) *(u32x4*)((unsigned char*)out + act_lo8_index(m, k0 + c, ldo, d)) = *(const u32x4*)(lo8 + c);
+    }
+    lds_barrier();
   };
 #pragma unroll
-  for (int it = 0; it < kHeld; ++it) {
-    const int i = threadIdx.x * 4 + it * 1024;
-    if (i < d) emit(i, held[it]);
+  for (int sp = 0; sp < HELD / SP; ++sp) {
+    if (sp * SPAN < d) {                                   // (uniform)
+#pragma unroll
+      for (int i = 0; i < SP; ++i)
+        if (sp * SPAN + c0 + i * STEP < d) put(c0 + i * STEP, held[sp * SP + i], g[i]);
+      gains((sp + 1) * SPAN);
+      leave(sp * SPAN);
+    }
   }
-  for (int i = threadIdx.x * 4 + kHeld * 1024; i < d; i += 1024) emit(i, *(const f32x4*)(row + i));
+  for (int k0 = HELD * STEP; k0 < d; k0 += SPAN) {
+    for (int c = c0; c < SPAN && k0 + c < d; c += STEP) put(c, *(const f32x4*)(row + k0 + c), *(const f32x4*)(gain + k0 + c));
+    leave(k0);
+  }
 }
+// Up to some 1400 rows more of them a compute unit cost less than more of their waves.
 void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float eps, int lo_mode, hipStream_t st) {
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, st, x, gain, out, d, eps,
-                     lo_mode == 1 ? 2 * d : (lo_mode == 2 ? d + d / 2 : d), lo_mode);
+  const int ldo = lo_mode == 1 ? 2 * d : (lo_mode == 2 ? d + d / 2 : d);
+  auto launch = [&](auto kern, int r, int wpr) {
+    hipLaunchKernelGGL(kern, dim3(((rows + r - 1) / r + 7) / 8 * 8), dim3(r * wpr * 64), 0, st, x, gain, out, rows, d, eps, ldo, lo_mode);
+  };
+  const bool once = (size_t)rows * d * sizeof(float) > 245'000'000;
+  if (d <= 1024) {
+    if (rows <= 600) launch(rmsnorm_kernel<2, 2, 2, false>, 2, 2);
+    else launch(rmsnorm_kernel<4, 1, 4, false>, 4, 1);
+  } else {
+    if (rows <= 1400) launch(rmsnorm_kernel<2, 4, 4, false>, 2, 4);
+    else if (once) launch(rmsnorm_kernel<4, 2, 8, true>, 4, 2);
+    else launch(rmsnorm_kernel<4, 2, 8, false>, 4, 2);
+  }
 }
 
 // ---- action head ------------------------------------------------------------------------------------
