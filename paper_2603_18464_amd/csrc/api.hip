@@ -1574,7 +1574,7 @@ const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_ter
 
 int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term) {
   if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64) return 0;
-  return gemm_f16_tile_rows(rows, n, two_pitch(two_term != 0, k));
+  return gemm_f16_tile_rows(rows, n, two_pitch(two_term != 0, k), k);
 }
 
 int32_t vla_decode_reads_once(vla_ctx* ctx, int32_t rows, int64_t positions) {

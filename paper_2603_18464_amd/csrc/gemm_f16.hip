@@ -344,22 +344,30 @@ __device__ __forceinline__ void mfma_in_place(f32x4& acc, const f16x8& a, const 
   else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 #endif
 }
-// The wait on both sides of a run of such products (8 issue slots behind a product, 2 in front of one; 32 given), four
-// accumulators a statement, in the first of them.  They take the accumulators and give them back, so whatever reads them,
-// register copies included, depends on it.
+// The wait on both sides of a run of such products (8 issue slots behind a product, 2 in front of one; 32 given), eight
+// accumulators a statement.  It takes them and gives them back, so whatever reads them, register copies included,
+// depends on it.
 template <bool AGPR, int MT, int NT>
 __device__ __forceinline__ void settle(f32x4 (&acc)[MT][NT]) {
-  static_assert(MT * NT % 4 == 0, "whole groups of four");
+  static_assert(MT * NT % 4 == 0, "whole groups of eight, and one of four");
 #if defined(__HIP_DEVICE_COMPILE__)
 #define VLA_ACC(c, j) "+" c(acc[(g + j) / NT][(g + j) % NT])
-#define VLA_SETTLE4(nops, c) asm volatile(nops : VLA_ACC(c, 0), VLA_ACC(c, 1), VLA_ACC(c, 2), VLA_ACC(c, 3))
-  static_for<MT * NT / 4>([&](auto G) VLA_INLINE {
-    constexpr int g = 4 * decltype(G)::value;
-    if constexpr (AGPR && g == 0) VLA_SETTLE4("s_nop 15\n\ts_nop 15", "a");
-    else if constexpr (AGPR) VLA_SETTLE4("", "a");
-    else if constexpr (g == 0) VLA_SETTLE4("s_nop 15\n\ts_nop 15", "v");
-    else VLA_SETTLE4("", "v");
-  });
+#define VLA_SETTLE4(c) asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(c, 0), VLA_ACC(c, 1), VLA_ACC(c, 2), VLA_ACC(c, 3))
+#define VLA_SETTLE8(c)                                                                                                            \
+  asm volatile("s_nop 15\n\ts_nop 15" : VLA_ACC(c, 0), VLA_ACC(c, 1), VLA_ACC(c, 2), VLA_ACC(c, 3), VLA_ACC(c, 4), VLA_ACC(c, 5), \
+               VLA_ACC(c, 6), VLA_ACC(c, 7))
+  constexpr int EIGHTS = MT * NT / 8 * 8;
+#pragma unroll
+  for (int g = 0; g < EIGHTS; g += 8) {
+    if constexpr (AGPR) VLA_SETTLE8("a");
+    else VLA_SETTLE8("v");
+  }
+  if constexpr (EIGHTS < MT * NT) {
+    constexpr int g = EIGHTS;
+    if constexpr (AGPR) VLA_SETTLE4("a");
+    else VLA_SETTLE4("v");
+  }
+#undef VLA_SETTLE8
 #undef VLA_SETTLE4
 #undef VLA_ACC
 #endif
@@ -369,6 +377,47 @@ constexpr int PK = 64;                                 // k of a slab (a slab of
 
 template <class Epi> __device__ __forceinline__ const f16* epi_a_lo(const Epi&) { return nullptr; }
 __device__ __forceinline__ const f16* epi_a_lo(const EpiPartial& e) { return e.a_lo; }
+
+// The accumulators of a wave's 16 MT x 16 NT, rows m_wave .. and column group wn of a tile's columns n0 .., through LDS to the
+// epilogue.
+template <int MT, int NT, int WGN, class Epi>
+__device__ __forceinline__ void store_tile(f32x4 (&acc)[MT][NT], const Epi& epi, unsigned char* smem, int wave, int wn, int lane,
+                                           int m_wave, int n0, int M) {
+  // The pitch keeps the stores of a 32-row group conflict free: the four row groups a store instruction covers start 16
+  // banks apart.
+  constexpr bool PAIR = 16 * NT < Epi::kSpan;               // two waves side by side share a staging tile
+  static_assert(!PAIR || (WGN % 2 == 0 && 32 * NT >= Epi::kSpan), "an epilogue's span is one or two wave tiles");
+  constexpr int COLS = PAIR ? 32 * NT : 16 * NT, PITCH = COLS + 4, ROWS = PAIR ? 16 : 32;
+  float* tile = (float*)smem + (PAIR ? wave >> 1 : wave) * 32 * PITCH;
+  const int side = PAIR ? wn & 1 : 0;
+#pragma unroll
+  for (int mb = 0; mb < MT / 2; ++mb) {
+    if constexpr (PAIR) {
+      if (mb > 0) __syncthreads();                     // the partner has read the previous rows
+    }
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          tile[(mi * 16 + 4 * (lane >> 4) + e) * PITCH + side * 16 * NT + nt * 16 + (lane & 15)] = acc[mb * 2 + mi][nt][e];
+    if constexpr (PAIR) __syncthreads();
+    epi.template consume<COLS, PITCH, ROWS>(tile + side * ROWS * PITCH, m_wave + mb * 32 + side * ROWS,
+                                            n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
+  }
+  if constexpr (MT % 2 != 0) {                         // the last 16 rows
+    if constexpr (PAIR) __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        tile[(4 * (lane >> 4) + e) * PITCH + side * 16 * NT + nt * 16 + (lane & 15)] = acc[MT - 1][nt][e];
+    if constexpr (PAIR) __syncthreads();
+    epi.template consume<COLS, PITCH, ROWS / 2>(tile + side * (ROWS / 2) * PITCH, m_wave + (MT - 1) * 16 + side * (ROWS / 2),
+                                                n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
+  }
+}
 
 // LO8: the launch has slabs of 8-bit low terms (W8 != nullptr): K == 1.5 * Kw, A row = [hi: Kw halves | lo8: Kw bytes].
 // Otherwise K == Kw, or K == 2 * Kw (half-precision low terms behind the high terms: the weight slabs wrap).
@@ -664,40 +713,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   wait_vmcnt<0>();                                     // the clamped tail loads still target this workgroup's LDS
   __syncthreads();                                     // every wave is done with the slabs: LDS becomes epilogue staging
 
-  // The pitch keeps the stores of a 32-row group conflict free: the four row groups a store instruction covers start 16
-  // banks apart.
-  constexpr bool PAIR = WN < Epi::kSpan;               // two waves side by side share a staging tile
-  static_assert(!PAIR || (WGN % 2 == 0 && 2 * WN >= Epi::kSpan), "an epilogue's span is one or two wave tiles");
-  constexpr int COLS = PAIR ? 2 * WN : WN, PITCH = COLS + 4, ROWS = PAIR ? 16 : 32;
-  float* tile = (float*)smem + (PAIR ? wave >> 1 : wave) * 32 * PITCH;
-  const int side = PAIR ? wn & 1 : 0;
-#pragma unroll
-  for (int mb = 0; mb < WM / 32; ++mb) {
-    if constexpr (PAIR) {
-      if (mb > 0) __syncthreads();                     // the partner has read the previous rows
-    }
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          tile[(mi * 16 + 4 * (lane >> 4) + e) * PITCH + side * WN + nt * 16 + (lane & 15)] = acc[mb * 2 + mi][nt][e];
-    if constexpr (PAIR) __syncthreads();
-    epi.template consume<COLS, PITCH, ROWS>(tile + side * ROWS * PITCH, m0 + wm * WM + mb * 32 + side * ROWS,
-                                            n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
-  }
-  if constexpr (MT % 2 != 0) {                         // the last 16 rows
-    if constexpr (PAIR) __syncthreads();
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        tile[(4 * (lane >> 4) + e) * PITCH + side * WN + nt * 16 + (lane & 15)] = acc[MT - 1][nt][e];
-    if constexpr (PAIR) __syncthreads();
-    epi.template consume<COLS, PITCH, ROWS / 2>(tile + side * (ROWS / 2) * PITCH, m0 + wm * WM + (MT - 1) * 16 + side * (ROWS / 2),
-                                                n0 + (PAIR ? wn >> 1 : wn) * COLS, lane, M);
-  }
+  store_tile<MT, NT, WGN>(acc, epi, smem, wave, wn, lane, m0 + wm * WM, n0, M);
 }
 
 template <int WGM, int WGN, int WM, int WN, int S, int SW, int OCC, bool DEEP, bool SPREAD, bool LO8, bool SPLITK, class Epi>
@@ -740,6 +756,177 @@ void splitk_gemm(const f16* Afrag, const f16* Afrag_lo, const f16* Wp, float* pa
   // columns then.  256 rows, K = 4096 / 11008: 17 / 39 us (256 columns 46 / 83, two weight-streaming launches 45 / 72).
   if (N / 256 * ksplit >= 128) launch_tiles<4, 2, 64, 128, 2, 3, 1, false, false, false, true>(Afrag, K, Wp, no8, M, k, K, ksplit, N / 256, epi, st);
   else launch_tiles<4, 2, 64, 32, 4, 4, 1, false, false, false, true>(Afrag, K, Wp, no8, M, k, K, ksplit, N / 64, epi, st);
+}
+
+
+// ---- few rows ---------------------------------------------------------------------------------------------------
+// x += A * W^T of a few hundred rows.  A compute unit has some 64 KiB of loads in flight, which come back in order: where its
+// weights come from HBM (1.1 us) it takes in 58 GB/s whatever the depth of its rings, activations that are in the L2 included.
+// So a tile is 64 columns (four waves of 16 MT x 16), which shares the products out over the most compute units, and with `ahead`
+// a workgroup more for each 64 columns does nothing but read their weights, which the workgroups of the row tiles, on the same
+// XCD, then find in its L2.  A wave's weights go straight to its registers, four U k-steps ahead, A in slabs of 128 k through S
+// stages of LDS, in pieces of a fragment (16 rows x 32 k, one KiB, which half a block of fragment order makes as well), and its
+// fragments are read two k-steps ahead.  The sequence of products per element is that of gemm_f16_kernel.
+// us, that kernel's 64x128 tiles / this without / with reading ahead, cold weights, N 4096: 230 rows K 4096 26.2 / 22.1 / 17.2,
+// K 11008 69.9 / 54.9 / 40.9; 165 rows K 11008 70.5 / 41.0 / 34.9; with low terms 290 rows 99.9 / 76 / 68; N 768, 290 rows (weights
+// from the last-level cache) K 768 5.8 / 4.1, K 2048 9.9 / 6.4, with low terms 7.9 / 4.7 and 14.8 / 8.5.
+// (More stages, 16 or 32 k-steps of weights ahead, waves of their own for the loads of A: 53 to 55 us of the 54.9.  Reading ahead
+// beside the tiles of gemm_f16_kernel does little for QKV and gate/up: 128x256 at 290 rows 57 -> 54, 160x256 70 -> 70.)
+template <int MT, int S, int U, bool LO8>
+__global__ __launch_bounds__(256, 1) void gemm_few_kernel(const f16* __restrict__ A, int lda, const f16* __restrict__ Wp,
+                                                          const f16* __restrict__ W8, int M, int Kw, int tiles_m, int tiles_n,
+                                                          int ahead, EpiResid epi) {
+  constexpr int D = 4 * U, AP = MT, STAGE = MT * 4 * 1024;           // weight fragments and pieces of A of a wave; bytes of a stage
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // the row tiles of 64 columns one after the other: their weights come to one L2
+  const int pid = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int per_n = tiles_m + ahead;
+  if (pid >= per_n * tiles_n) return;
+  const int tn = pid / per_n, tm = pid - tn * per_n - ahead, m0 = max(tm, 0) * 16 * MT, n0 = tn * 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KTh = Kw / 128, KT = LO8 ? KTh + Kw / 256 : KTh;         // slabs of high terms, and with the low ones (256 k each)
+  // a lane's 16 bytes of a fragment: row lane % 16, k group lane / 16 of 8 k
+  const unsigned in_block = (unsigned)(lane >> 5) * 1024u + (unsigned)((lane >> 4) & 1) * 512u + (unsigned)(lane & 15) * 16u;
+  const f16* a_base = A + (size_t)(m0 >> 5) * 32 * lda;
+  const unsigned a_block = 64u * (unsigned)lda;
+  const int h0 = (m0 >> 4) & 1, h_last = ((M - 1) >> 4) - ((m0 >> 5) << 1);     // half blocks, from the tile's first block on
+  auto issue_a = [&](int kt, unsigned stage, auto I) VLA_INLINE {    // a wave's k-step of the slab, fragment I
+    constexpr int i = decltype(I)::value;
+    const int h = min(i + h0, h_last);
+    const unsigned off = (unsigned)(h >> 1) * a_block + (unsigned)(h & 1) * 256u + (unsigned)wave * 2048u + 8192u * (unsigned)min(kt, KT - 1);
+    load_to_lds_16(a_base, in_block, off, (f16*)(smem + stage + (i * 4 + wave) * 1024));
+  };
+  const int blk = (n0 >> 5) + (wave >> 1);
+  const f16* w_base = Wp + (size_t)blk * Kw * 32 + (wave & 1) * 128;
+  const f16* w8_base = LO8 ? W8 + (size_t)blk * Kw * 16 + (wave & 1) * 128 : w_base;
+  f16x8 wq[D];
+  auto load_w = [&](const f16* base, int q, int n, int s) VLA_INLINE {         // k-step q of n (clamped)
+#if defined(__HIP_DEVICE_COMPILE__)
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00027000);
+    wq[s] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, in_block, 2048u * (unsigned)min(q, n - 1), 0));
+#endif
+  };
+  f32x4 acc[MT][1];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const unsigned a_rd = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char*)smem) + (unsigned)lane * 16u;
+  f16x8 af[4][MT];                                     // fragments of a slab's k-steps
+  auto read_a = [&](unsigned so, auto SS, auto J) VLA_INLINE {
+    constexpr int ss = decltype(SS)::value, j = decltype(J)::value;
+    read_frag_asm<(j * 4 + ss) * 1024>(af[ss][j], a_rd + so);
+  };
+  auto hold_all = [&](int ss) VLA_INLINE {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) hold(af[ss][i]);
+  };
+  // Loads newer than those of the next slab when it is waited for, at least: A of the S - 2 slabs behind it, and the weights of the
+  // k-steps since, which are 4 S - 5 where it was requested in the fourth k-step of the slab S - 1 before this one, and in the
+  // first slabs, whose A was requested in front of all weights, D + 2 and more.
+  auto next_landed = [&]() VLA_INLINE {                // and this slab is in everybody's registers
+    wait_lds();
+    wait_vmcnt<(S - 2) * AP + (4 * S - 6 < D + 2 ? 4 * S - 6 : D + 2)>();
+    __builtin_amdgcn_s_barrier();
+  };
+  static_assert((S - 1) * AP + D <= 63, "the counter of loads in flight");
+  constexpr int BAR = MT / 2;                          // product of the third k-step in front of which the barrier stands
+  auto step = [&](int kt, unsigned so, unsigned nx, auto SS, auto RS) VLA_INLINE {
+    constexpr int ss = decltype(SS)::value, s = decltype(RS)::value;
+    wait_lds<MT>();                                    // read two k-steps ago; newer: the last one's reads
+    hold_all(ss);
+    static_for<MT>([&](auto I) VLA_INLINE {
+      constexpr int i = decltype(I)::value;
+      if constexpr (ss == 2 && i == BAR) next_landed();
+      acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[ss][i], wq[s], acc[i][0], 0, 0, 0);
+      constexpr int f0 = ss == 2 ? BAR : 0, x0 = i < f0 ? 0 : (i - f0) * MT / (MT - f0), x1 = i < f0 ? 0 : (i - f0 + 1) * MT / (MT - f0);
+      static_for<x1 - x0>([&](auto J) VLA_INLINE {
+        read_a(ss >= 2 ? nx : so, std::integral_constant<int, (ss + 2) & 3>{}, std::integral_constant<int, x0 + decltype(J)::value>{});
+      });
+      if constexpr (ss == 3) issue_a(kt + S, so, I);   // (its stage is free behind the barrier)
+      if constexpr (i == MT - 1) load_w(w_base, kt * 4 + ss + D, 4 * KTh, s);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  if (tm < 0) {                                        // reads the columns' weights into the L2
+    auto pass = [&](const f16* base, int n) VLA_INLINE {
+      static_for<D>([&](auto I) VLA_INLINE { load_w(base, decltype(I)::value, n, decltype(I)::value); });
+      for (int q = D; q < n + D; q += D)
+        static_for<D>([&](auto I) VLA_INLINE {
+          hold(wq[decltype(I)::value]);
+          if (q < n) load_w(base, q + decltype(I)::value, n, decltype(I)::value);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    pass(w_base, 4 * KTh);
+    if constexpr (LO8) pass(w8_base, 2 * KTh);
+    return;
+  }
+  static_for<S>([&](auto I) VLA_INLINE { static_for<AP>([&](auto J) VLA_INLINE { issue_a(decltype(I)::value, decltype(I)::value * STAGE, J); }); });
+  __builtin_amdgcn_sched_barrier(0);                   // (the counts of loads in flight rely on this order)
+  static_for<D>([&](auto I) VLA_INLINE { load_w(w_base, decltype(I)::value, 4 * KTh, decltype(I)::value); });
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vmcnt<(S - 1) * AP + D>();
+  __builtin_amdgcn_s_barrier();
+  static_for<MT>([&](auto J) VLA_INLINE { read_a(0, std::integral_constant<int, 0>{}, J); });
+  static_for<MT>([&](auto J) VLA_INLINE { read_a(0, std::integral_constant<int, 1>{}, J); });
+  unsigned so = 0;
+  auto after = [&](unsigned o) VLA_INLINE { return o + STAGE == STAGE * S ? 0u : o + STAGE; };
+  auto slab = [&](int kt, auto X) VLA_INLINE {
+    const unsigned nx = after(so);
+    static_for<4>([&](auto SS) VLA_INLINE { step(kt, so, nx, SS, std::integral_constant<int, 4 * decltype(X)::value + decltype(SS)::value>{}); });
+    so = nx;
+  };
+  int kt = 0;
+  for (; kt + U <= KTh; kt += U) static_for<U>([&](auto X) VLA_INLINE { slab(kt + decltype(X)::value, X); });
+  const int rest = KTh - kt;
+  static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < rest) slab(kt + decltype(X)::value, X); });
+  if constexpr (LO8) {                                 // a product takes two pieces of A and of W: 128 k of low terms
+    static_for<D>([&](auto I) VLA_INLINE { load_w(w8_base, decltype(I)::value, 2 * KTh, decltype(I)::value); });
+    auto low_slab = [&](int t, int q0, auto X) VLA_INLINE {
+      const unsigned nx = after(so);
+      static_for<2>([&](auto PR) VLA_INLINE {
+        constexpr int pr = decltype(PR)::value, s = 4 * decltype(X)::value + 2 * pr;
+        if constexpr (pr == 1) next_landed();
+        else wait_lds();
+        hold_all(2 * pr);
+        hold_all(2 * pr + 1);
+        static_for<MT>([&](auto I) VLA_INLINE {
+          constexpr int i = decltype(I)::value;
+          acc[i][0] = mfma_lo8(af[2 * pr][i], af[2 * pr + 1][i], wq[s], wq[s + 1], acc[i][0]);
+          read_a(pr ? nx : so, std::integral_constant<int, 2 - 2 * pr>{}, I);
+          read_a(pr ? nx : so, std::integral_constant<int, 3 - 2 * pr>{}, I);
+          if constexpr (pr == 1) issue_a(t + S, so, I);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        load_w(w8_base, q0 + 2 * pr + D, 2 * KTh, s);
+        load_w(w8_base, q0 + 2 * pr + 1 + D, 2 * KTh, s + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      so = nx;
+    };
+    int q0 = 0;
+    for (kt = KTh; kt + U <= KT; kt += U, q0 += D)
+      static_for<U>([&](auto X) VLA_INLINE { low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X); });
+    const int last = KT - kt;
+    static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < last) low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X); });
+  }
+  wait_lds();                                          // the reads ahead of the end, and the clamped loads, before the LDS is staging
+  static_for<4>([&](auto SS) VLA_INLINE { hold_all(decltype(SS)::value); });
+  wait_vmcnt<0>();
+  __syncthreads();
+  store_tile<MT, 1, 4>(acc, epi, smem, wave, wave, lane, m0, n0, M);
+}
+template <int MT, int S, bool LO8>
+static void launch_few(const GemmF16& g, int ahead, const EpiResid& epi, hipStream_t st) {
+  const int tiles_m = (g.M + 16 * MT - 1) / (16 * MT), tiles_n = g.N / 64;
+  constexpr size_t smem = (size_t)S * MT * 4096;
+  auto kern = gemm_few_kernel<MT, S, 4, LO8>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3(((tiles_m + ahead) * tiles_n + 7) / 8 * 8), dim3(256), smem, st, g.A, g.lda, g.Wp, g.W8, g.M, g.Kw, tiles_m,
+                     tiles_n, ahead, epi);
 }
 
 // ---- tile choice ------------------------------------------------------------------------------------------------
@@ -805,9 +992,9 @@ static TilePick pick_tile(int M, int N, int K) {
 //   are the same either way (+-1 %).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
-enum Variant { V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
+enum Variant { V_32x64, V_48x64, V_64x64, V_80x64, V_96x64, V_112x64, V_128x64, V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
                V_256x256_W3, V_256x256_SPREAD, V_COUNT };
-const char* const kGemmF16Variants[] = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
+const char* const kGemmF16Variants[] = {"32x64", "48x64", "64x64", "80x64", "96x64", "112x64", "128x64", "64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
                                         "160x256", "192x256", "224x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
 static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
 
@@ -829,8 +1016,29 @@ static int tile_rows(const TilePick& pick, int M, int N) {
     if (cost(rows) < cost(best) && 40 * cost(rows) < 39 * cost(picked)) best = rows;
   return best;
 }
-int gemm_f16_tile_rows(int M, int N, int K) { return tile_rows(pick_tile(M, N, K), M, N); }
+// gemm_few_kernel's tiles where a launch runs them (rows 0: it does not): residual adds (no wider than their contraction, which
+// gate/up and QKV products of these sizes are) of whole slabs.  The tiles are the lowest that leave the weights of every 64 columns
+// a workgroup of their own on a chip of 256 (a last tile of a fragment's rows is as good), and if none do, the lowest that fit.
+// Above 384 rows the tiles of gemm_f16_kernel are as good (480 rows of N 4096, K 11008 69 and 66 us, 580 87 and 88); where one
+// tile holds all rows and the columns are many, reading ahead only doubles the reads (80 rows of N 8192 40 us, without 33).
+struct FewTiles { int rows, ahead; };
+static FewTiles few_tiles(int M, int N, int K, int Kw) {
+  const bool lo8 = 2 * K == 3 * Kw;
+  if (N > Kw || N < 512 || M > 384 || (K != Kw && !lo8) || Kw % (lo8 ? 256 : 128)) return {0, 0};
+  for (int ahead = 1; ahead >= 0; --ahead)
+    for (int rows = 32; rows <= (ahead ? 128 : 96); rows += 16) {
+      const int tiles = (M + rows - 1) / rows, brief = ahead && tiles > 1 && (M - 1) % rows < 16;
+      if ((tiles + ahead - brief) * (N / 64) <= 256 && (!ahead || tiles > 1 || N <= 4096)) return {rows, ahead - brief};
+    }
+  return {0, 0};
+}
+int gemm_f16_tile_rows(int M, int N, int K, int Kw) {
+  const int few = few_tiles(M, N, K, Kw).rows;
+  return few ? few : tile_rows(pick_tile(M, N, K), M, N);
+}
 int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
+  const int few = span == EpiResid::kSpan ? few_tiles(M, N, K, Kw).rows : 0;
+  if (few) return V_32x64 + few / 16 - 2;
   const TilePick p = pick_tile(M, N, K);
   switch (p.tile) {
     case T_64x128: return p.tiles > 256 ? V_64x128_ROUNDS : span <= 64 ? V_64x128_8W : V_64x128;
@@ -854,7 +1062,21 @@ template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr int span = Epi::kSpan;
   constexpr bool resid = span == EpiResid::kSpan;
-  switch (gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span)) {
+  const int variant = gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span);
+  if constexpr (resid) {
+    const int ahead = few_tiles(g.M, g.N, g.K, g.Kw).ahead;
+    switch (variant) {
+      case V_32x64: return launch_few<2, 8, LO8>(g, ahead, epi, st);
+      case V_48x64: return launch_few<3, 6, LO8>(g, ahead, epi, st);
+      case V_64x64: return launch_few<4, 5, LO8>(g, ahead, epi, st);
+      case V_80x64: return launch_few<5, 4, LO8>(g, ahead, epi, st);
+      case V_96x64: return launch_few<6, 4, LO8>(g, ahead, epi, st);
+      case V_112x64: return launch_few<7, 4, LO8>(g, ahead, epi, st);
+      case V_128x64: return launch_few<8, 4, LO8>(g, ahead, epi, st);
+      default: break;
+    }
+  }
+  switch (variant) {
     case V_64x128_8W:
       if constexpr (span <= 64) launch<2, 4, 32, 32, 4, 4, 1, true, false, LO8>(g, epi, st);
       break;
