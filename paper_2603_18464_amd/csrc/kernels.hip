@@ -295,37 +295,39 @@ __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* _
   };
   gains(0);
   // Whatever the form, the squares are added in one order: of a lane's pieces of 256 elements those of one number modulo four in a
-  // sum, (s0 + s1) + (s2 + s3), a butterfly over the lanes.
+  // sum, a butterfly over the lanes for each of the four, ((s0 + s1) + s2) + s3.
   static_assert(4 % WPR == 0 && HELD % (4 / WPR) == 0, "a wave has the pieces of 4 / WPR of the sums");
   constexpr int NS = 4 / WPR;
   float ss[NS] = {};
-  auto squares = [&](const f32x4& v, int s) { ss[s] += fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[1], v[1], v[0] * v[0]))); };
+  auto squares = [&](const f32x4& v, int s) { ss[s] += fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[0], v[0], v[1] * v[1]))); };
 #pragma unroll
   for (int it = 0; it < HELD; ++it) squares(held[it], it % NS);
   for (int k = c0 + HELD * STEP; k < d; k += NS * STEP)
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (k + s * STEP < d) squares(*(const f32x4*)(row + k + s * STEP), s);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) ss[s] = wave_sum(ss[s]);
   float sum;
   if constexpr (WPR == 1) {
-    sum = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    sum = ((ss[0] + ss[1]) + ss[2]) + ss[3];
   } else {
-    __shared__ float s_sum[ROWS][4][64];                   // (sum s is that of wave s % WPR)
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % WPR;
+    __shared__ float s_sum[ROWS][4];                       // (sum s is that of wave s % WPR)
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % WPR;
+    if ((threadIdx.x & 63) == 0) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) s_sum[wave][s * WPR + w][lane] = ss[s];
+      for (int s = 0; s < NS; ++s) s_sum[wave][s * WPR + w] = ss[s];
+    }
     lds_barrier();
-    sum = (s_sum[wave][0][lane] + s_sum[wave][1][lane]) + (s_sum[wave][2][lane] + s_sum[wave][3][lane]);
+    sum = ((s_sum[wave][0] + s_sum[wave][1]) + s_sum[wave][2]) + s_sum[wave][3];
   }
-  sum = wave_sum(sum);
   const float inv = 1.0f / sqrtf(sum / (float)d + eps);
   auto put = [&](int c, const f32x4& v, const f32x4& g) {  // columns c .. + 3 of the span
     f16x4 q, qe;
     float e[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float h = v[j] * inv * g[j];
-      asm("" : "+v"(h));                                   // the product is rounded here, in every form
+      const float h = v[j] * inv * g[j];
       q[j] = from_f32<f16>(h);
       e[j] = h - to_f32(q[j]);
       qe[j] = from_f32<f16>(e[j]);
