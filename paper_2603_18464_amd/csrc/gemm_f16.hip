@@ -1007,10 +1007,13 @@ static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each"
 // with low terms 5 to 10 % likewise.  Over the 354 products that it changes among those of d 768 to 5120 at 290 to 23200 rows,
 // with and without low terms, 5.2 % less in the mean; the worst are qkv with low terms at 9280 rows of d 3072, 644 / 650, and
 // without at 1450, 76.5 / 77.2.
+static long long rounds_cost(int M, int N, int rows) {
+  return (((long long)(M + rows - 1) / rows * (N / 256) + 255) / 256) * (rows + 90);
+}
 static int tile_rows(const TilePick& pick, int M, int N) {
   const int picked = kTileCost[pick.tile].bm;
   if (picked < 192) return picked;
-  auto cost = [&](int rows) { return (((long long)(M + rows - 1) / rows * (N / 256) + 255) / 256) * (rows + 90); };
+  auto cost = [&](int rows) { return rounds_cost(M, N, rows); };
   int best = picked;
   for (int rows = 160; rows <= 256; rows += 32)
     if (cost(rows) < cost(best) && 40 * cost(rows) < 39 * cost(picked)) best = rows;
@@ -1058,6 +1061,37 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
   return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
 }
 
+// Rows that go into a first launch of whole rounds where the rest of them costs less in a launch of its own, with lower tiles,
+// than as the last round of all: 0 where it does not.  The second launch costs some 5 us (its own, and the end of the first's
+// last round), and the two have to come to 2.5 % less.  us from the first launch's
+// start to the last one's end, 7B, 18560 rows (73 x 16 tiles of 256 rows: 4.56 rounds; now four whole ones, and 14 x 16 tiles of 160),
+// before the 128x128 waves, with them, and in two launches: down 1311, 1269, 1217; o 537, 530, 515.
+static int first_rows(int M, int N, int K) {
+  const auto cost_of = [&](int rows) -> long long {        // 0: not a launch of such tiles
+    const TilePick p = pick_tile(rows, N, K);
+    return kTileCost[p.tile].bm < 192 ? 0 : rounds_cost(rows, N, tile_rows(p, rows, N));
+  };
+  const long long one = cost_of(M);
+  if (one <= 2 * 346) return 0;                            // (a round of 256 rows and another)
+  const float us_per_cost = (kTileCost[T_256x256].fixed + kTileCost[T_256x256].per_k * (float)K / 1024.0f) / 346.0f;
+  const long long launch = (long long)(5.0f / us_per_cost);
+  long long best = one * 39 / 40;
+  int first = 0;
+  for (int rows = 160; rows <= 256; rows += 32) {
+    const int rounds = (int)(((long long)(M / rows) * (N / 256)) / 256);           // whole ones there are
+    for (int r = rounds; r > 0 && r > rounds - 2; --r) {
+      const int m = (int)((long long)r * 256 / (N / 256)) * rows;
+      if (m <= 0 || m >= M) continue;
+      const long long a = cost_of(m), b = cost_of(M - m);
+      if (a && b && a + b + launch < best) {
+        best = a + b + launch;
+        first = m;
+      }
+    }
+  }
+  return first;
+}
+
 template <bool LO8, class Epi>
 static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr int span = Epi::kSpan;
@@ -1101,10 +1135,33 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
       else if constexpr (!LO8) launch<4, 2, 64, 128, 2, 3, 1, false, true, LO8>(g, epi, st);
   }
 }
+// An epilogue for rows m .. of its operands (m a multiple of 32).
+static EpiResid rows_from(const EpiResid& e, int m) { return EpiResid{e.x + (size_t)m * e.ldx, e.ldx}; }
+static EpiSwiglu rows_from(const EpiSwiglu& e, int m) { return EpiSwiglu{e.act + (size_t)m * e.ld, e.ld, e.f, e.lo_mode}; }
+template <int HD>
+static EpiQkv<HD> rows_from(EpiQkv<HD> e, int m) {
+  e.o.q = (f16*)e.o.q + (size_t)m * e.o.ldq;
+  e.o.tok_seq += m;
+  e.o.tok_pos += m;
+  return e;
+}
 template <class Epi>
-static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
+static void dispatch_whole(const GemmF16& g, const Epi& epi, hipStream_t st) {
   if (g.W8) dispatch_lo<true>(g, epi, st);
   else dispatch_lo<false>(g, epi, st);
+}
+template <class Epi>
+static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
+  if (const int m = first_rows(g.M, g.N, g.K)) {
+    GemmF16 a = g, b = g;
+    a.M = m;
+    b.M = g.M - m;
+    b.A += (size_t)m * g.lda;
+    dispatch_whole(a, epi, st);
+    dispatch_whole(b, rows_from(epi, m), st);
+  } else {
+    dispatch_whole(g, epi, st);
+  }
 }
 
 void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st) { dispatch(g, EpiResid{x, ldx}, st); }
