@@ -109,12 +109,13 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(
 //                  16 arranged so that a lane's 8 keys are contiguous.
 // Bound by latency: a workgroup lives for three key tiles on average (prefixes of 290) and starts with two dependent
 // rounds of loads.  Per layer, 64 prefixes of 290, 32 heads of 128: 169 us with a head's tiles on one XCD (180 with them
-// dealt over three), 32 prefixes, 12 heads of 64: 20.6 us with four workgroups per compute unit (23.0 with two).
+// dealt over three), 32 prefixes, 12 heads of 64: 20.6 us with four workgroups per compute unit (23.0 with two); with the output in
+// fragment order, where a store of 32 rows is 512 bytes in a row instead of 64 pieces of 8, 155 and 19.4 (low terms 369 -> 340).
 // TWO (two-term mode): queries, keys and values each come as hi + lo terms (the low terms of the queries in half
 // precision at column lo_off of the same rows, those of the cache as bytes, lo8 = bf8(16 * lo), in k_lo / v_lo
 // with the cache's indexing; they are widened exactly to half precision while the tile is staged), the
 // scores are K_hi Q_hi + K_lo Q_hi + K_hi Q_lo, the output sum takes V_hi + V_lo, and the output rows are written
-// as [hi | lo] as well.  The staging tiles double, so one workgroup runs per compute unit instead of two.
+// with both terms as well.  The staging tiles double, so one workgroup runs per compute unit instead of two.
 // The LDS serves a 16-byte read in groups of 16 lanes that here are 16 keys whose numbers differ in their low four bits:
 // the swizzle puts their chunks in 16 different slots of the 64 banks (two rows of 64 dimensions share the banks).
 template <int HD>
@@ -400,8 +401,7 @@ __global__ __launch_bounds__(256, !TWO && HD == 64 ? 4 : 2) void flash_prefill_k
 }
 
 // k_lo / v_lo != nullptr selects the two-term kernel: q rows are [hi | lo] of pitch ldq with the low terms at
-// column lo_off = d_model, and so are the output rows (pitch ldo), unless out_lo8 asks for 8-bit low terms (bytes
-// behind the d_model high terms of each row).
+// column lo_off = d_model, and so the output (fragment order, ldo halves a row), unless out_lo8 asks for 8-bit low terms.
 void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache, const unsigned char* k_lo,
                    const unsigned char* v_lo, const int32_t* cu_patch, const int32_t* cu_instr, const int32_t* slot_map,
                    f16* out, int ldo, bool out_lo8, int B, int max_len, int n_heads, int head_dim, int max_seq,

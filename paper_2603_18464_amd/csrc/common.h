@@ -220,7 +220,7 @@ void gemm_f32_resid(const float* A, const float* W, float* x, int M, int d, int 
 
 // Row-wise kernels.
 void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float eps,
-             int lo_mode /* 0: rows of d; 1: [hi | lo] of 2 d; 2: [hi | lo8] of 1.5 d */, hipStream_t st);
+             int lo_mode /* out in fragment order, 0: rows of d; 1: [hi | lo] of 2 d; 2: [hi | lo8] of 1.5 d */, hipStream_t st);
 template <class T>
 void assemble_prefix(const T* patch_emb, const int32_t* instr_ids, const T* embed,
                      const int32_t* tok_src, float* x, int T_tokens, int d, int vocab, hipStream_t st);
@@ -234,7 +234,7 @@ void attention_rows_f32(const float* q, const float* k_cache, const float* v_cac
 // cu_patch / cu_instr are the device copies of the cumulative offsets; max_len = longest prefix; slot_map
 // (device, [B], or nullptr for the identity) gives the cache slot of each sequence of the call.
 // k_lo / v_lo (low terms of the cache) != nullptr: two-term mode, q rows are [hi | lo] with the low terms at column
-// d_model, and so are the output rows, or (out_lo8) [hi | 8-bit low terms].
+// d_model; the output is in fragment order (act_index, ldo halves a row), low terms at column d_model too, or (out_lo8) as bytes.
 void flash_prefill(const f16* q, int ldq, const f16* k_cache, const f16* v_cache, const unsigned char* k_lo,
                    const unsigned char* v_lo, const int32_t* cu_patch, const int32_t* cu_instr, const int32_t* slot_map,
                    f16* out, int ldo, bool out_lo8, int B, int max_len, int n_heads, int head_dim, int max_seq,
@@ -307,8 +307,8 @@ void value_finish(const float* vz, const float* vml, const T* step_emb, int n_st
                   float* values, hipStream_t st);
 
 // Last prefill layer, compact rows: gather attention output (to fragment order) and residual rows, scatter back.
-// att_frag_lo != nullptr: att rows are [hi | lo] (pitch ld_att; lo8: the low terms are bytes), the low terms go to
-// att_frag_lo as half precision
+// att_frag_lo != nullptr: att (fragment order, ld_att halves a row) has low terms (lo8: bytes), which go to att_frag_lo as half
+// precision
 void gather_tail(const f16* att, int ld_att, bool lo8, const float* x, const int32_t* need, int n, int d,
                  f16* att_frag, f16* att_frag_lo, float* x_c, hipStream_t st);
 void scatter_tail(const float* x_c, const int32_t* need, int n, int d, float* x, hipStream_t st);

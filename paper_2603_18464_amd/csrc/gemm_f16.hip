@@ -256,7 +256,17 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   191 -> 142 (down), at 18560 rows 1811 -> 1652, 2846 -> 2656, 1760 -> 1493; 256x256 at 290 rows 88 -> 75, 94 -> 82,
 //   212 -> 180, at 18560 rows down 1443 -> 1377 and with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.  (Single-term
 //   256x256 launches of many tiles keep two of each where the weights stay in the caches: see the tile choice.)
-// * SPREAD: the weights of a slab's second k-step are requested a k-step after the rest, so that the loads go out evenly.
+// * SPREAD: the weights of a slab are requested a k-step after its activations, so that the loads go out evenly.
+// * Both slabs are in fragment order, so that a load is one KiB from one place, with a scalar offset, and a read of the LDS has no
+//   bank conflicts.  A row-major A took an address a lane and eight pieces of 128 bytes a load: us, 18560 rows, that / this,
+//   gate/up 2450 / 2372, down 1336 / 1314, o 548 / 535, with low terms 4 % (gate/up) and 2.5 % (qkv) less, qkv +-1 %; 2338 rows
+//   gate/up 346 / 336, down 176 / 173.  On operands of zeros, where the clock does not drop, 1834 / 1741, 1113 / 977, 465 / 434:
+//   most of what it saves goes into the power limit.
+// * Four waves of 128x128 for the residual add's 256x256 tiles: a third fewer reads of the LDS than eight of 64x128, down 1314 ->
+//   1269, o 535 -> 530.  The accumulators are the 256 registers of the accumulation half.  With the other epilogues and with low
+//   terms, which two waves a SIMD cover better, gate/up 2372 -> 2450, qkv 1388 -> 1441, qkv with low terms 2190 -> 2349.
+// * What bounds the large launches: without the loads of the main loop gate/up takes 2120 of 2546 us (row-major A), without its
+//   reads of the LDS too 1568; barriers cost nothing; how the loads are spread over the k-steps makes no difference.
 // * Fragments are double buffered in registers: while the MFMAs of one k-step run, the reads of the next
 //   are in flight, slotted one by one between the MFMAs.  The compiler cannot tell the stages apart and would wait
 //   for ALL outstanding LDS loads before any LDS read, so the reads are inline assembly and the waits explicit.
@@ -277,7 +287,6 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   Against 4 waves of 128x128 with 32x32x16 and 32x32x64 the 7B policy step of 64 takes 244.5 instead of 247.5 ms (its
 //   4 two-term layers are a sixth of it), of 8 54.0 instead of 54.2, the 12-layer model's of 32 6.24 instead of 6.29;
 //   with 128x256 tiles at every size 247.9, 54.3 and 6.22.
-// * Both slabs are in fragment order, so that a load is one KiB from one place and a read of the LDS has no bank conflicts.
 // * Every variant runs the same sequence of MFMAs per output element (k ascending, one chain), so a sequence's bits do
 //   not depend on which tile its batch selects.
 
@@ -986,10 +995,8 @@ static TilePick pick_tile(int M, int N, int K) {
 //   -0.3, 151 + 152 -0.4, 180 + 76 -1.3, 180 + 152 -1.8, 201 + 76 -3.3, 268 + 38 -4.0; qkv 57 + 228 +2.8, 101 + 152 (7B, 18560
 //   rows) +1.8 to +2.7, 101 + 304 +0.9, 127 + 171 -0.5, 157 + 190 -2.3, 226 + 114 -6.2; heads of 64 as heads of 128.  The
 //   epilogue that adds to the residual rows always gains (-1 to -4 %), and so do low terms (0 to -6 %);
-// * the residual epilogue and launches of fewer than three rounds request the weights in halves of 32 k (SPREAD: gate/up 293
-//   against 298 us at 1800 rows, qkv 200 against 201 at 2368, down 517 against 520 at 7424 and 811 against 817 at 12000, 1346
-//   against 1342 at 18560; o 214.5 against 215.5 at 7424, 337 against 336 at 12000, 556 against 548 at 18560); the larger launches
-//   are the same either way (+-1 %).
+// * the residual epilogue (four waves of 128x128) and launches of fewer than three rounds request the weights a k-step after the
+//   activations (SPREAD, 18560 rows down 1337 against 1348 us, o 590 against 595; gate/up and qkv the same either way, +-1 %).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
 enum Variant { V_32x64, V_48x64, V_64x64, V_80x64, V_96x64, V_112x64, V_128x64, V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
