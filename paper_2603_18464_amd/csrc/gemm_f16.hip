@@ -830,28 +830,33 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(const f16* __restrict_
   };
   // Loads newer than those of the next slab when it is waited for, at least: A of the S - 2 slabs behind it, and the weights of the
   // k-steps since, which are 4 S - 5 where it was requested in the fourth k-step of the slab S - 1 before this one, and in the
-  // first slabs, whose A was requested in front of all weights, D + 2 and more.
-  auto next_landed = [&]() VLA_INLINE {                // and this slab is in everybody's registers
+  // first slabs, whose A was requested in front of all weights, D + 2 and more.  To the compiler the weights are ordinary loads,
+  // which it moves to where they are used and drops where they are not: only those count that a turn of the main loop leaves to
+  // the next one, and those in front of it, which it always takes.  Slabs behind the loop (number T, -1: in it) request none, so
+  // that 2 and 4 a slab fewer are in flight, and those of low terms behind theirs, which may be the only ones, count none.
+  constexpr int W_LOOP = 4 * S - 6 < D + 2 ? 4 * S - 6 : D + 2;
+  auto next_landed = [&](auto W) VLA_INLINE {          // W: weights among them; and this slab is in everybody's registers
     wait_lds();
-    wait_vmcnt<(S - 2) * AP + (4 * S - 6 < D + 2 ? 4 * S - 6 : D + 2)>();
+    wait_vmcnt<(S - 2) * AP + decltype(W)::value>();
     __builtin_amdgcn_s_barrier();
   };
   static_assert((S - 1) * AP + D <= 63, "the counter of loads in flight");
   constexpr int BAR = MT / 2;                          // product of the third k-step in front of which the barrier stands
-  auto step = [&](int kt, unsigned so, unsigned nx, auto SS, auto RS) VLA_INLINE {
-    constexpr int ss = decltype(SS)::value, s = decltype(RS)::value;
+  auto step = [&](int kt, unsigned so, unsigned nx, auto SS, auto RS, auto T) VLA_INLINE {
+    constexpr int ss = decltype(SS)::value, s = decltype(RS)::value, tail = decltype(T)::value;
+    constexpr int newer = tail < 0 ? W_LOOP : 4 * S - 8 - 4 * tail;
     wait_lds<MT>();                                    // read two k-steps ago; newer: the last one's reads
     hold_all(ss);
     static_for<MT>([&](auto I) VLA_INLINE {
       constexpr int i = decltype(I)::value;
-      if constexpr (ss == 2 && i == BAR) next_landed();
+      if constexpr (ss == 2 && i == BAR) next_landed(std::integral_constant<int, (newer > 0 ? newer : 0)>{});
       acc[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[ss][i], wq[s], acc[i][0], 0, 0, 0);
       constexpr int f0 = ss == 2 ? BAR : 0, x0 = i < f0 ? 0 : (i - f0) * MT / (MT - f0), x1 = i < f0 ? 0 : (i - f0 + 1) * MT / (MT - f0);
       static_for<x1 - x0>([&](auto J) VLA_INLINE {
         read_a(ss >= 2 ? nx : so, std::integral_constant<int, (ss + 2) & 3>{}, std::integral_constant<int, x0 + decltype(J)::value>{});
       });
       if constexpr (ss == 3) issue_a(kt + S, so, I);   // (its stage is free behind the barrier)
-      if constexpr (i == MT - 1) load_w(w_base, kt * 4 + ss + D, 4 * KTh, s);
+      if constexpr (i == MT - 1 && tail < 0) load_w(w_base, kt * 4 + ss + D, 4 * KTh, s);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -869,8 +874,10 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(const f16* __restrict_
     if constexpr (LO8) pass(w8_base, 2 * KTh);
     return;
   }
-  static_for<S>([&](auto I) VLA_INLINE { static_for<AP>([&](auto J) VLA_INLINE { issue_a(decltype(I)::value, decltype(I)::value * STAGE, J); }); });
-  __builtin_amdgcn_sched_barrier(0);                   // (the counts of loads in flight rely on this order)
+  static_for<S>([&](auto I) VLA_INLINE {
+    static_for<AP>([&](auto J) VLA_INLINE { issue_a(decltype(I)::value, decltype(I)::value * STAGE, J); });
+    __builtin_amdgcn_sched_barrier(0);                 // (the counts of loads in flight rely on this order)
+  });
   static_for<D>([&](auto I) VLA_INLINE { load_w(w_base, decltype(I)::value, 4 * KTh, decltype(I)::value); });
   __builtin_amdgcn_sched_barrier(0);
   wait_vmcnt<(S - 1) * AP + D>();
@@ -879,22 +886,26 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(const f16* __restrict_
   static_for<MT>([&](auto J) VLA_INLINE { read_a(0, std::integral_constant<int, 1>{}, J); });
   unsigned so = 0;
   auto after = [&](unsigned o) VLA_INLINE { return o + STAGE == STAGE * S ? 0u : o + STAGE; };
-  auto slab = [&](int kt, auto X) VLA_INLINE {
+  auto slab = [&](int kt, auto X, auto T) VLA_INLINE {
     const unsigned nx = after(so);
-    static_for<4>([&](auto SS) VLA_INLINE { step(kt, so, nx, SS, std::integral_constant<int, 4 * decltype(X)::value + decltype(SS)::value>{}); });
+    static_for<4>([&](auto SS) VLA_INLINE { step(kt, so, nx, SS, std::integral_constant<int, 4 * decltype(X)::value + decltype(SS)::value>{}, T); });
     so = nx;
   };
   int kt = 0;
-  for (; kt + U <= KTh; kt += U) static_for<U>([&](auto X) VLA_INLINE { slab(kt + decltype(X)::value, X); });
+  do {                                                 // (at least U slabs: few_tiles)
+    static_for<U>([&](auto X) VLA_INLINE { slab(kt + decltype(X)::value, X, std::integral_constant<int, -1>{}); });
+    kt += U;
+  } while (kt + U <= KTh);
   const int rest = KTh - kt;
-  static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < rest) slab(kt + decltype(X)::value, X); });
+  static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < rest) slab(kt + decltype(X)::value, X, X); });
   if constexpr (LO8) {                                 // a product takes two pieces of A and of W: 128 k of low terms
     static_for<D>([&](auto I) VLA_INLINE { load_w(w8_base, decltype(I)::value, 2 * KTh, decltype(I)::value); });
-    auto low_slab = [&](int t, int q0, auto X) VLA_INLINE {
+    auto low_slab = [&](int t, int q0, auto X, auto LOOP) VLA_INLINE {
+      constexpr bool loop = decltype(LOOP)::value;
       const unsigned nx = after(so);
       static_for<2>([&](auto PR) VLA_INLINE {
         constexpr int pr = decltype(PR)::value, s = 4 * decltype(X)::value + 2 * pr;
-        if constexpr (pr == 1) next_landed();
+        if constexpr (pr == 1) next_landed(std::integral_constant<int, loop ? W_LOOP : 0>{});
         else wait_lds();
         hold_all(2 * pr);
         hold_all(2 * pr + 1);
@@ -906,17 +917,19 @@ __global__ __launch_bounds__(256, 1) void gemm_few_kernel(const f16* __restrict_
           if constexpr (pr == 1) issue_a(t + S, so, I);
           __builtin_amdgcn_sched_barrier(0);
         });
-        load_w(w8_base, q0 + 2 * pr + D, 2 * KTh, s);
-        load_w(w8_base, q0 + 2 * pr + 1 + D, 2 * KTh, s + 1);
+        if constexpr (loop) {
+          load_w(w8_base, q0 + 2 * pr + D, 2 * KTh, s);
+          load_w(w8_base, q0 + 2 * pr + 1 + D, 2 * KTh, s + 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
       so = nx;
     };
     int q0 = 0;
     for (kt = KTh; kt + U <= KT; kt += U, q0 += D)
-      static_for<U>([&](auto X) VLA_INLINE { low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X); });
+      static_for<U>([&](auto X) VLA_INLINE { low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X, std::true_type{}); });
     const int last = KT - kt;
-    static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < last) low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X); });
+    static_for<U - 1>([&](auto X) VLA_INLINE { if ((int)decltype(X)::value < last) low_slab(kt + decltype(X)::value, q0 + 4 * decltype(X)::value, X, std::false_type{}); });
   }
   wait_lds();                                          // the reads ahead of the end, and the clamped loads, before the LDS is staging
   static_for<4>([&](auto SS) VLA_INLINE { hold_all(decltype(SS)::value); });
