@@ -21,17 +21,21 @@ extern "C" {
  * Best of three timed runs after a warm-up. */
 int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);
 
-/* Which variant of the prefill GEMM the launch of a product [rows, k] x [n, k]^T runs ("128x256", ...: rows x columns of a tile,
- * and its form where there are several): a static text, "" for sizes the 16-bit path does not have.  Host only.  two_term:
- * operands of a two-term layer; span: 32 for the output projection and the down projection, 64 for gate/up and for the QKV
+/* Rows of the first launch of a prefill product [rows, k] x [n, k]^T that takes two, one of whole rounds of tiles and one of the
+ * rest; 0 where it takes one, and for sizes the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer. */
+int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term);
+
+/* Which variant of the prefill GEMM a launch over `rows` rows of such a product runs ("128x256", ...: rows x columns of a tile,
+ * and its form where there are several): a static text, "" for sizes the 16-bit path does not have.  Of a product of two launches
+ * ask for the rows of each.  Host only.  span: 32 for the output projection and the down projection, 64 for gate/up and for the QKV
  * product of heads of 64, 128 for that of heads of 128 (the columns of a row that the product's last step needs together). */
 const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
-/* Rows of the tiles that this product's launch runs: 32 to 128 for residual adds of up to 384 rows, which products no wider than
+/* Rows of the tiles that this launch runs: 32 to 128 for residual adds of up to 384 rows, which products no wider than
  * their contraction are taken for (tiles of 64 columns).  Where the cost model picks tiles of 192 or 256 rows, of 160, 192, 224 and
  * 256 those are taken that need the least rounds of 256 workgroups x (rows + 90), if that is 2.5 % less than the model's.  0 for
  * sizes the 16-bit path does not have.  Host only. */
-int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term);
+int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
 /* What a decode step of `rows` sequences with `positions` cached positions (all of them together) reads as data that does not
  * come again: bit 0 the weights (products that leave partial sums for the next launch: only matrices of 64 MB and more), bit 1

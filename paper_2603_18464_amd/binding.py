@@ -19,7 +19,8 @@ EXPORTS = ["vla_create", "vla_destroy", "vla_last_error", "vla_query_sizes", "vl
            "vla_load_value_head", "vla_policy_step_value",
            "vla_policy_step_parallel", "vla_score_tokens",
            "vla_prefill_slots", "vla_decode_slots", "vla_release_slots",
-           "vla_probe", "vla_gemm_variant", "vla_gemm_tile_rows", "vla_decode_reads_once",
+           "vla_probe", "vla_gemm_variant", "vla_gemm_tile_rows", "vla_gemm_first_rows",
+           "vla_decode_reads_once",
            "vla_batcher_create", "vla_batcher_destroy", "vla_batcher_push", "vla_batcher_size",
            "vla_batcher_deadline", "vla_batcher_poll",
            "vla_get_state", "vla_drain_begin", "vla_update_begin", "vla_update_tensors", "vla_update_commit",
@@ -94,7 +95,8 @@ def lib() -> C.CDLL:
         L.vla_probe.argtypes = [vp, i32, C.POINTER(C.c_double), vp]
         L.vla_gemm_variant.argtypes = [i32] * 5
         L.vla_gemm_variant.restype = C.c_char_p
-        L.vla_gemm_tile_rows.argtypes = [i32] * 4
+        L.vla_gemm_tile_rows.argtypes = [i32] * 5
+        L.vla_gemm_first_rows.argtypes = [i32] * 4
         L.vla_decode_reads_once.argtypes = [vp, i32, C.c_int64]
         L.vla_batcher_create.argtypes = [i32, C.c_double, C.c_int64, C.POINTER(vp)]
         L.vla_batcher_destroy.argtypes = [vp]
@@ -289,8 +291,12 @@ def vla_gemm_variant(rows: int, n: int, k: int, two_term: bool, span: int) -> st
     return lib().vla_gemm_variant(rows, n, k, int(two_term), span).decode()
 
 
-def vla_gemm_tile_rows(rows: int, n: int, k: int, two_term: bool) -> int:
-    return lib().vla_gemm_tile_rows(rows, n, k, int(two_term))
+def vla_gemm_tile_rows(rows: int, n: int, k: int, two_term: bool, span: int) -> int:
+    return lib().vla_gemm_tile_rows(rows, n, k, int(two_term), span)
+
+
+def vla_gemm_first_rows(rows: int, n: int, k: int, two_term: bool) -> int:
+    return lib().vla_gemm_first_rows(rows, n, k, int(two_term))
 
 
 def vla_decode_reads_once(ctx, rows: int, positions: int) -> int:

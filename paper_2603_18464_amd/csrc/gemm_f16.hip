@@ -1055,8 +1055,8 @@ static FewTiles few_tiles(int M, int N, int K, int Kw) {
     }
   return {0, 0};
 }
-int gemm_f16_tile_rows(int M, int N, int K, int Kw) {
-  const int few = few_tiles(M, N, K, Kw).rows;
+int gemm_f16_tile_rows(int M, int N, int K, int Kw, int span) {
+  const int few = span == EpiResid::kSpan ? few_tiles(M, N, K, Kw).rows : 0;
   return few ? few : tile_rows(pick_tile(M, N, K), M, N);
 }
 int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
@@ -1086,7 +1086,7 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
 // last round), and the two have to come to 2.5 % less.  us from the first launch's
 // start to the last one's end, 7B, 18560 rows (73 x 16 tiles of 256 rows: 4.56 rounds; now four whole ones, and 14 x 16 tiles of 160),
 // before the 128x128 waves, with them, and in two launches: down 1311, 1269, 1217; o 537, 530, 515.
-static int first_rows(int M, int N, int K) {
+int gemm_f16_first_rows(int M, int N, int K) {
   const auto cost_of = [&](int rows) -> long long {        // 0: not a launch of such tiles
     const TilePick p = pick_tile(rows, N, K);
     return kTileCost[p.tile].bm < 192 ? 0 : rounds_cost(rows, N, tile_rows(p, rows, N));
@@ -1172,7 +1172,7 @@ static void dispatch_whole(const GemmF16& g, const Epi& epi, hipStream_t st) {
 }
 template <class Epi>
 static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  if (const int m = first_rows(g.M, g.N, g.K)) {
+  if (const int m = gemm_f16_first_rows(g.M, g.N, g.K)) {
     GemmF16 a = g, b = g;
     a.M = m;
     b.M = g.M - m;

@@ -7,7 +7,7 @@ import pytest
 
 import workloads as W
 from oracle import vla_oracle as O
-from paper_2603_18464_amd.binding import vla_gemm_tile_rows, vla_gemm_variant
+from paper_2603_18464_amd.binding import vla_gemm_first_rows, vla_gemm_tile_rows, vla_gemm_variant
 from tests import parity as P
 from tests.test_gpu_parity import ragged_obs
 
@@ -39,10 +39,17 @@ CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 6
 BALANCED = [(768, 1024, 64, [5200]), (1280, 1024, 64, [8000]), (768, 64, 128, [7000])]
 
 
+def parts(rows, n, k, two):
+    """Rows of each launch of a product."""
+    first = vla_gemm_first_rows(rows, n, k, two)
+    return [first, rows - first] if first else [rows]
+
+
 def launches(d, f, hd, rows):
     for two in (False, True):
         for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-            yield (two, epi), vla_gemm_variant(rows, n, k, two, SPAN[epi])
+            for m in parts(rows, n, k, two):
+                yield (two, epi), vla_gemm_variant(m, n, k, two, SPAN[epi])
 
 
 def test_the_cases_reach_every_variant():
@@ -58,15 +65,23 @@ def test_the_cases_reach_every_variant():
 
 
 def test_the_variant_is_what_the_launch_runs():
-    """Where the rounds are balanced the launch runs other tiles than the cost model picks: the name is that of the launch."""
+    """Where the rounds are balanced the launch runs other tiles than the cost model picks: the name is that of the launch.  Where
+    a product takes two launches each has one."""
     for rows, n, k, span, want in ((2320, 22016, 4096, 64, "224x256"), (2208, 22016, 4096, 64, "160x256"), (290, 22016, 4096, 64, "160x256"),
                                    (4100, 12288, 4096, 128, "160x256"), (10533, 22016, 4096, 64, "256x256 3 weight stages"),
-                                   (2320, 4096, 4096, 32, "160x256"), (18560, 4096, 11008, 32, "256x256 spread")):
+                                   (2320, 4096, 4096, 32, "160x256")):
         assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
+    for rows, n, k, span, want in ((18560, 4096, 11008, 32, [(16384, "256x256 spread"), (2176, "160x256")]),
+                                   (9280, 4096, 4096, 32, [(6144, "192x256"), (3136, "224x256")])):
+        assert [(m, vla_gemm_variant(m, n, k, False, span)) for m in parts(rows, n, k, False)] == want, (rows, n, k)
     for n, k, span in ((12288, 4096, 128), (22016, 4096, 64), (4096, 11008, 32), (2304, 768, 64), (768, 2048, 32)):
         for rows in range(1, 30000, 173):
             for two in (False, True):
-                assert vla_gemm_variant(rows, n, k, two, span).startswith(f"{vla_gemm_tile_rows(rows, n, k, two)}x")
+                for m in parts(rows, n, k, two):
+                    assert 0 < m <= rows and vla_gemm_variant(m, n, k, two, span).startswith(f"{vla_gemm_tile_rows(m, n, k, two, span)}x")
+    assert vla_gemm_tile_rows(300, 512, 768, False, 32) == 32           # of an epilogue that the few-row kernel has, and of one
+    assert vla_gemm_tile_rows(300, 512, 768, False, 64) == 64           # that it does not have
+    assert vla_gemm_first_rows(18560, 4000, 4096, False) == vla_gemm_first_rows(0, 4096, 4096, False) == 0
 
 
 def test_the_third_weight_stage_goes_by_the_bytes_that_are_read_again():

@@ -23,13 +23,14 @@ def test_the_cases_reach_every_height():
         for rows in rows_list:
             for two in (False, True):
                 for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-                    height = vla_gemm_tile_rows(rows, n, k, two)
-                    reached.add((two, epi, height))
-                    if height == 256:
-                        reached.add((two, epi, vla_gemm_variant(rows, n, k, two, V.SPAN[epi])))
+                    for m in V.parts(rows, n, k, two):
+                        height = vla_gemm_tile_rows(m, n, k, two, V.SPAN[epi])
+                        reached.add((two, epi, height))
+                        if height == 256:
+                            reached.add((two, epi, vla_gemm_variant(m, n, k, two, V.SPAN[epi])))
     assert {(two, epi, h) for two in (False, True) for epi in V.SPAN for h in HEIGHTS} <= reached
     assert {(False, epi, "256x256 spread") for epi in V.SPAN} <= reached
-    assert vla_gemm_tile_rows(64, 100, 128, False) == vla_gemm_tile_rows(0, 128, 128, False) == 0
+    assert vla_gemm_tile_rows(64, 100, 128, False, 32) == vla_gemm_tile_rows(0, 128, 128, False, 32) == vla_gemm_tile_rows(64, 128, 128, False, 1) == 0
 
 
 def test_the_height_needs_the_least_rounds_times_rows():
@@ -39,7 +40,7 @@ def test_the_height_needs_the_least_rounds_times_rows():
     for n, k in ((12288, 4096), (4096, 4096), (22016, 4096), (4096, 11008), (2304, 768), (768, 2048)):
         for m in range(33, 40000, 271):
             for two in (False, True):
-                rows, costs = vla_gemm_tile_rows(m, n, k, two), {h: cost(m, n, h) for h in HEIGHTS}
+                rows, costs = vla_gemm_tile_rows(m, n, k, two, 64), {h: cost(m, n, h) for h in HEIGHTS}
                 if not vla_gemm_variant(m, n, k, two, 64).startswith(tuple(f"{h}x256" for h in HEIGHTS)):
                     assert rows < 160                     # the model's choice, 64 or 128 rows
                     continue
@@ -60,7 +61,8 @@ def test_the_copies_reach_both_new_heights():
     for d, f, hd, n in COPIES:
         for two in (False, True):
             for epi, cols, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-                reached.add((two and k % 128 == 0, epi, vla_gemm_tile_rows(33 * n, cols, k, two)))
+                for m in V.parts(33 * n, cols, k, two):
+                    reached.add((two and k % 128 == 0, epi, vla_gemm_tile_rows(m, cols, k, two, V.SPAN[epi])))
     assert {(low8, epi, h) for low8 in (False, True) for epi in V.SPAN for h in (160, 224)} <= reached
 
 

@@ -25,7 +25,7 @@ def test_which_products_take_the_small_tiles():
     for (m, n, k, two, span), is_few in few.items():
         if is_few:                                        # residual adds of whole slabs, no wider than their contraction
             assert span == 32 and m <= 384 and 512 <= n <= k and k % (256 if two else 128) == 0
-            assert vla_gemm_variant(m, n, k, two, span) == f"{vla_gemm_tile_rows(m, n, k, two)}x64"
+            assert vla_gemm_variant(m, n, k, two, span) == f"{vla_gemm_tile_rows(m, n, k, two, span)}x64"
         elif span == 32 and m <= 384 and 512 <= n <= min(k, 4096) and k % 256 == 0:
             raise AssertionError((m, n, k, two))
     assert few[384, 8192, 32768, False, 32] is False      # more tiles than the chip has compute units
