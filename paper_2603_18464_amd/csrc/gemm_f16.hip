@@ -1012,10 +1012,17 @@ static TilePick pick_tile(int M, int N, int K) {
 //   activations (SPREAD, 18560 rows down 1337 against 1348 us, o 590 against 595; gate/up and qkv the same either way, +-1 %).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
-enum Variant { V_32x64, V_48x64, V_64x64, V_80x64, V_96x64, V_112x64, V_128x64, V_64x128_8W, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256, V_224x256, V_256x256,
-               V_256x256_W3, V_256x256_SPREAD, V_COUNT };
-const char* const kGemmF16Variants[] = {"32x64", "48x64", "64x64", "80x64", "96x64", "112x64", "128x64", "64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256",
-                                        "160x256", "192x256", "224x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
+constexpr int kFewHeights = 7;                            // gemm_few_kernel's tiles: 32, 48, ... 128 rows
+enum Variant {
+  V_FEW, V_FEW_AHEAD = V_FEW + kFewHeights,              // (the first of each; ahead: with workgroups that read the weights ahead)
+  V_64x128_8W = V_FEW_AHEAD + kFewHeights, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256,
+  V_224x256, V_256x256, V_256x256_W3, V_256x256_SPREAD, V_COUNT
+};
+const char* const kGemmF16Variants[] = {
+    "32x64", "48x64", "64x64", "80x64", "96x64", "112x64", "128x64",
+    "32x64 ahead", "48x64 ahead", "64x64 ahead", "80x64 ahead", "96x64 ahead", "112x64 ahead", "128x64 ahead",
+    "64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "160x256", "192x256",
+    "224x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
 static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
 
 // Rows of the tiles a launch runs.  Where the model picks 192 or 256 rows, the rounds are balanced: the last one costs a whole
@@ -1060,8 +1067,8 @@ int gemm_f16_tile_rows(int M, int N, int K, int Kw, int span) {
   return few ? few : tile_rows(pick_tile(M, N, K), M, N);
 }
 int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
-  const int few = span == EpiResid::kSpan ? few_tiles(M, N, K, Kw).rows : 0;
-  if (few) return V_32x64 + few / 16 - 2;
+  const FewTiles few = span == EpiResid::kSpan ? few_tiles(M, N, K, Kw) : FewTiles{0, 0};
+  if (few.rows) return (few.ahead ? V_FEW_AHEAD : V_FEW) + few.rows / 16 - 2;
   const TilePick p = pick_tile(M, N, K);
   switch (p.tile) {
     case T_64x128: return p.tiles > 256 ? V_64x128_ROUNDS : span <= 64 ? V_64x128_8W : V_64x128;
@@ -1118,15 +1125,15 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
   constexpr bool resid = span == EpiResid::kSpan;
   const int variant = gemm_f16_variant(g.M, g.N, g.K, g.Kw, LO8, span);
   if constexpr (resid) {
-    const int ahead = few_tiles(g.M, g.N, g.K, g.Kw).ahead;
-    switch (variant) {
-      case V_32x64: return launch_few<2, 8, LO8>(g, ahead, epi, st);
-      case V_48x64: return launch_few<3, 6, LO8>(g, ahead, epi, st);
-      case V_64x64: return launch_few<4, 5, LO8>(g, ahead, epi, st);
-      case V_80x64: return launch_few<5, 4, LO8>(g, ahead, epi, st);
-      case V_96x64: return launch_few<6, 4, LO8>(g, ahead, epi, st);
-      case V_112x64: return launch_few<7, 4, LO8>(g, ahead, epi, st);
-      case V_128x64: return launch_few<8, 4, LO8>(g, ahead, epi, st);
+    const int ahead = variant >= V_FEW_AHEAD;
+    switch (variant - (ahead ? V_FEW_AHEAD : V_FEW)) {
+      case 0: return launch_few<2, 8, LO8>(g, ahead, epi, st);
+      case 1: return launch_few<3, 6, LO8>(g, ahead, epi, st);
+      case 2: return launch_few<4, 5, LO8>(g, ahead, epi, st);
+      case 3: return launch_few<5, 4, LO8>(g, ahead, epi, st);
+      case 4: return launch_few<6, 4, LO8>(g, ahead, epi, st);
+      case 5: return launch_few<7, 4, LO8>(g, ahead, epi, st);
+      case 6: return launch_few<8, 4, LO8>(g, ahead, epi, st);
       default: break;
     }
   }
