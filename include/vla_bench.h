@@ -31,8 +31,8 @@ int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term
  * product of heads of 64, 128 for that of heads of 128 (the columns of a row that the product's last step needs together). */
 const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
-/* Rows of the tiles that this launch runs: 32 to 128 for residual adds of up to 384 rows, which products no wider than
- * their contraction are taken for (tiles of 64 columns).  Where the cost model picks tiles of 192 or 256 rows, of 160, 192, 224 and
+/* Rows of the tiles that this launch runs: 32 to 128 for residual adds of rows x (n + 1200) <= 2^21, of products no wider
+ * than their contraction (tiles of 64 columns).  Where the cost model picks tiles of 192 or 256 rows, of 160, 192, 224 and
  * 256 those are taken that need the least rounds of 256 workgroups x (rows + 90), if that is 2.5 % less than the model's.  0 for
  * sizes the 16-bit path does not have.  Host only. */
 int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);

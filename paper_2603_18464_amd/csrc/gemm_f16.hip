@@ -1049,12 +1049,17 @@ static int tile_rows(const TilePick& pick, int M, int N) {
 // gemm_few_kernel's tiles where a launch runs them (rows 0: it does not): residual adds (no wider than their contraction, which
 // gate/up and QKV products of these sizes are) of whole slabs.  The tiles are the lowest that leave the weights of every 64 columns
 // a workgroup of their own on a chip of 256 (a last tile of a fragment's rows is as good), and if none do, the lowest that fit.
-// Above 384 rows the tiles of gemm_f16_kernel are as good (480 rows of N 4096, K 11008 69 and 66 us, 580 87 and 88); where one
-// tile holds all rows and the columns are many, reading ahead only doubles the reads (80 rows of N 8192 40 us, without 33).
+// The line: rows x (columns + 1200) up to 2^21, from where gemm_f16_kernel's launch fills as many compute units with tiles that
+// read less.  us, that kernel / this: N 512 K 1536 870 rows 8.5 / 5.4, 1224 K 2048 10.0 / 10.3; N 768 K 768 580 rows 5.8 / 4.1,
+// 1065 6.4 / 5.5, 1450 6.5 / 6.4, K 2048 580 9.9 / 6.5, 1065 10.9 / 10.6, 1450 11.4 / 12.9; N 1536 K 4096 700 rows 24.4 / 19.2;
+// N 2048 K 5632 580 rows 35 / 27, 870 36 / 34; N 4096 K 11008 385 rows 68 / 64, 480 71 / 73, 580 88 / 90.  Over 498 products
+// between 385 rows and the line (N 512 to 4096, K of one to eight N, with and without low terms) 1.38 times as fast in the mean;
+// the worst N 1536 K 1536 at 766 rows, 0.97, and the above at 1224, 0.97.
+// Where one tile holds all rows and the columns are many, reading ahead only doubles the reads (80 rows of N 8192 40 us, without 33).
 struct FewTiles { int rows, ahead; };
 static FewTiles few_tiles(int M, int N, int K, int Kw) {
   const bool lo8 = 2 * K == 3 * Kw;
-  if (N > Kw || N < 512 || M > 384 || (K != Kw && !lo8) || Kw % (lo8 ? 256 : 128)) return {0, 0};
+  if (N > Kw || N < 512 || (long long)M * (N + 1200) > 1 << 21 || (K != Kw && !lo8) || Kw % (lo8 ? 256 : 128)) return {0, 0};
   for (int ahead = 1; ahead >= 0; --ahead)
     for (int rows = 32; rows <= (ahead ? 128 : 96); rows += 16) {
       const int tiles = (M + rows - 1) / rows, brief = ahead && tiles > 1 && (M - 1) % rows < 16;

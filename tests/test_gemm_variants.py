@@ -57,7 +57,8 @@ def test_the_cases_reach_every_variant():
     for d, f, hd, rows_list in CASES + BALANCED:
         for rows in rows_list:
             for key, variant in launches(d, f, hd, rows):
-                reached[key].add(variant)
+                if not variant.split()[0].endswith("x64"):    # (test_gpu_gemm_few.py has the few-row tiles)
+                    reached[key].add(variant)
     assert reached == REACHED
     for epi, rows, n in BY_7B:
         assert vla_gemm_variant(rows, n, 4096, False, SPAN[epi]) == "256x256 3 weight stages"

@@ -6,12 +6,13 @@ import pytest
 from paper_2603_18464_amd.binding import vla_gemm_tile_rows, vla_gemm_variant
 from tests import test_gemm_variants as V
 
-# (d_model, d_ffn, head_dim, rows): 33 rows alone and in batches; the last of a row are past the few-row tiles
-CASES = [(512, 2816, 64, [34, 48, 64, 65, 384, 385]), (768, 2048, 64, [47, 290, 1300]),
-         (3072, 64, 128, [49, 97, 128, 165, 192, 230, 290, 384, 400]), (4096, 64, 128, [289, 290, 320, 384, 700]),
-         (640, 1280, 64, [384, 385]), (896, 1024, 64, [386])]
+# (d_model, d_ffn, head_dim, rows): 33 rows alone and in batches, the last of which takes the tiled kernel
+CASES = [(512, 2816, 64, [34, 48, 64, 65, 385, 900, 1224, 1225]), (768, 2048, 64, [47, 290, 700, 1065, 1066]),
+         (3072, 64, 128, [49, 97, 128, 165, 192, 230, 290, 384, 490, 491]), (4096, 64, 128, [289, 290, 320, 384, 700]),
+         (640, 1280, 64, [384, 1200]), (896, 1024, 64, [386, 1100])]
 # heights without a workgroup that reads ahead, where the last tile has sixteen rows at most
-BRIEF = [(2048, 64, 128, [337]), (2560, 64, 64, [321]), (2816, 64, 128, [321]), (3328, 64, 128, [337]), (4352, 64, 128, [257])]
+BRIEF = [(2048, 64, 128, [337, 700]), (2560, 64, 64, [321, 600]), (2816, 64, 128, [321, 560]), (3328, 64, 128, [337, 500]),
+         (4352, 64, 128, [257, 400])]
 HEIGHTS = {f"{rows}x64" for rows in range(32, 129, 16)}
 FORMS = HEIGHTS | {name + " ahead" for name in HEIGHTS}
 
@@ -31,12 +32,12 @@ def test_the_cases_reach_every_form():
 
 
 def takes(m, n, k, two):
-    return 512 <= n <= k and k % (256 if two else 128) == 0 and m <= 384
+    return 512 <= n <= k and k % (256 if two else 128) == 0 and m * (n + 1200) <= 2 ** 21
 
 
 def test_which_products_take_the_small_tiles():
     few = {(m, n, k, two, span): vla_gemm_variant(m, n, k, two, span)
-           for m in (1, 33, 384, 385, 2000) for n in (384, 512, 768, 1024, 2048, 4096, 8192, 16384, 32768)
+           for m in (1, 33, 384, 385, 480, 640, 900, 1065, 1066, 2000) for n in (384, 512, 768, 1024, 2048, 4096, 8192, 16384, 32768)
            for k in (64, 128, 192, 768, 896, 4096, 32768) for two in (False, True) for span in (32, 64, 128)}
     for (m, n, k, two, span), name in few.items():
         if name in FORMS:                                 # residual adds of whole slabs, no wider than their contraction
@@ -44,6 +45,7 @@ def test_which_products_take_the_small_tiles():
             assert name.startswith(f"{vla_gemm_tile_rows(m, n, k, two, span)}x64")
         elif span == 32 and takes(m, n, k, two) and n <= 4096:
             raise AssertionError((m, n, k, two))
+    assert few[1065, 768, 768, False, 32] in FORMS and few[1066, 768, 768, False, 32] not in FORMS
     assert few[384, 8192, 32768, False, 32] not in FORMS  # more tiles than the chip has compute units
 
 
