@@ -266,18 +266,18 @@ __device__ __forceinline__ void lds_barrier() {
 // The rows of a prefill, to fragment order: ROWS rows a workgroup, WPR waves each, HELD pieces of 256 elements a wave in registers
 // between the two passes.  Bound by HBM, few rows by latency.  The 16-byte pieces of a row lie 512 bytes apart, those of the
 // workgroup's rows side by side: the output goes through LDS, SPAN columns at a time, and leaves as segments of 16 * ROWS bytes, a
-// block's 32 rows from one XCD, whose L2 puts the lines together.  ONCE: the rows outgrow the last-level cache and are read as
-// data that does not come again, which leaves the lines in the L2 until they are whole.
-// us, one row a workgroup to rows of d / this: d 4096 290 rows 3.6 / 4.3, 2338 12.4 / 13.8, 7104 29.9 / 33.4, 18560 81 / 80 (93
-// without ONCE); d 768 288 rows 2.6 / 2.7, 9216 10.5 / 9.1.
+// block's 32 rows from one XCD, whose L2 puts the lines together.  One row a workgroup (few rows) leaves as it is, in the 8
+// bytes of a lane.  ONCE: the rows outgrow the last-level cache and are read as data that does not come again, which leaves the
+// lines in the L2 until they are whole.
 template <int ROWS, int WPR, int HELD, bool ONCE>
 __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* __restrict__ x, const float* __restrict__ gain,
                                                                   f16* __restrict__ out, int rows, int d, float eps, int ldo, int lo_mode) {
   typedef __attribute__((ext_vector_type(4))) f16 f16x4;
   constexpr int SP = HELD < 4 ? HELD : 4, STEP = WPR * 256, SPAN = SP * STEP, NT = ROWS * WPR * 64;
   constexpr int PITCH = SPAN + 16;                         // (spreads the rows of a read over the banks)
-  __shared__ __attribute__((aligned(16))) f16 s_hi[ROWS][PITCH];
-  __shared__ __attribute__((aligned(16))) f16 s_lo[ROWS][PITCH];     // or bytes, SPAN + 32 a row
+  constexpr bool DIRECT = ROWS == 1;                       // a lane's four columns go out as they are
+  __shared__ __attribute__((aligned(16))) f16 s_hi[DIRECT ? 1 : ROWS][DIRECT ? 8 : PITCH];
+  __shared__ __attribute__((aligned(16))) f16 s_lo[DIRECT ? 1 : ROWS][DIRECT ? 8 : PITCH];     // or bytes, SPAN + 32 a row
   unsigned char* s_lo8 = (unsigned char*)s_lo;
   const int r0 = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * ROWS;
   if (r0 >= rows) return;
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* _
     sum = ((s_sum[wave][0] + s_sum[wave][1]) + s_sum[wave][2]) + s_sum[wave][3];
   }
   const float inv = 1.0f / sqrtf(sum / (float)d + eps);
-  auto put = [&](int c, const f32x4& v, const f32x4& g) {  // columns c .. + 3 of the span
+  auto put = [&](int k0, int c, const f32x4& v, const f32x4& g) {      // columns c .. + 3 of the span at k0
     f16x4 q, qe;
     float e[4];
 #pragma unroll
@@ -332,12 +332,19 @@ __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* _
       e[j] = h - to_f32(q[j]);
       qe[j] = from_f32<f16>(e[j]);
     }
-    *(f16x4*)&s_hi[wave][c] = q;
-    if (lo_mode == 1) *(f16x4*)&s_lo[wave][c] = qe;
-    if (lo_mode == 2) *(int*)(s_lo8 + wave * (SPAN + 32) + c) = pack_lo8(e[0], e[1], e[2], e[3]);
+    if constexpr (DIRECT) {
+      *(f16x4*)(out + act_index(r0, k0 + c, ldo)) = q;
+      if (lo_mode == 1) *(f16x4*)(out + act_index(r0, d + k0 + c, ldo)) = qe;
+      if (lo_mode == 2) *(int*)((unsigned char*)out + act_lo8_index(r0, k0 + c, ldo, d)) = pack_lo8(e[0], e[1], e[2], e[3]);
+    } else {
+      *(f16x4*)&s_hi[wave][c] = q;
+      if (lo_mode == 1) *(f16x4*)&s_lo[wave][c] = qe;
+      if (lo_mode == 2) *(int*)(s_lo8 + wave * (SPAN + 32) + c) = pack_lo8(e[0], e[1], e[2], e[3]);
+    }
   };
   // the rows of a span, side by side; low terms of lo_mode 1 go to column d + k, of 2 as bytes behind the block's high terms
   auto leave = [&](int k0) {
+    if constexpr (DIRECT) return;
     lds_barrier();
     const int n = min(d - k0, SPAN), m = r0 + threadIdx.x % ROWS;
     const f16 *hi = s_hi[threadIdx.x % ROWS], *lo = s_lo[threadIdx.x % ROWS];
@@ -357,17 +364,25 @@ __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* _
     if (sp * SPAN < d) {                                   // (uniform)
 #pragma unroll
       for (int i = 0; i < SP; ++i)
-        if (sp * SPAN + c0 + i * STEP < d) put(c0 + i * STEP, held[sp * SP + i], g[i]);
+        if (sp * SPAN + c0 + i * STEP < d) put(sp * SPAN, c0 + i * STEP, held[sp * SP + i], g[i]);
       gains((sp + 1) * SPAN);
       leave(sp * SPAN);
     }
   }
   for (int k0 = HELD * STEP; k0 < d; k0 += SPAN) {
-    for (int c = c0; c < SPAN && k0 + c < d; c += STEP) put(c, *(const f32x4*)(row + k0 + c), *(const f32x4*)(gain + k0 + c));
+    for (int c = c0; c < SPAN && k0 + c < d; c += STEP) put(k0, c, *(const f32x4*)(row + k0 + c), *(const f32x4*)(gain + k0 + c));
     leave(k0);
   }
 }
-// Up to some 1400 rows more of them a compute unit cost less than more of their waves.
+// us, rows of d by one workgroup a row / these forms (4096 columns in registers at most / these, where rows are wider):
+//   d 768   288 rows 2.4 / 2.4, 580 2.5 / 2.5, 870 2.7 / 2.7, 1400 3.1 / 3.0, 2500 4.1 / 3.7, 9280 9.7 / 8.6; with low terms 580 rows
+//           2.6 / 2.7, 870 2.8 / 2.9, 1400 3.3 / 3.2
+//   d 4096  288 rows 3.2 / 3.5, 580 3.7 / 4.6, 1400 5.6 / 6.6, 2500 11.3 / 12.6, 9280 33.8 / 35.6, 18560 79 / 80 (93 without ONCE);
+//           with low terms 288 3.5 / 4.1, 1400 6.9 / 8.8, 9280 39 to 41 / 41 to 46, 18560 92 / 91: what fragment order costs here is a
+//           tenth of what the products that read it gain
+//   d 5120  288 rows 3.5 / 4.0 (4.5), 2000 10.8 / 12.7, 4640 22.6 / 25.0 (26.5), 18560 100 / 102 (100), with low terms 118 / 125 (152)
+//   d 8192  288 rows 4.7 / 5.3 (6.1), 1400 12.8 / 14.2 (15.0), 4640 34 / 37 (45), 9280 84 / 83 (101), with low terms 99 / 100 (135)
+// One row a workgroup wins while a compute unit has three or four of them (two where a row is four pieces a wave).
 void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float eps, int lo_mode, hipStream_t st) {
   const int ldo = lo_mode == 1 ? 2 * d : (lo_mode == 2 ? d + d / 2 : d);
   auto launch = [&](auto kern, int r, int wpr) {
@@ -375,10 +390,17 @@ void rmsnorm(const float* x, const float* gain, f16* out, int rows, int d, float
   };
   const bool once = (size_t)rows * d * sizeof(float) > 245'000'000;
   if (d <= 1024) {
-    if (rows <= 600) launch(rmsnorm_kernel<2, 2, 2, false>, 2, 2);
+    if (rows <= 1000) launch(rmsnorm_kernel<1, 4, 1, false>, 1, 4);
+    else if (rows <= 3500) launch(rmsnorm_kernel<2, 2, 2, false>, 2, 2);
     else launch(rmsnorm_kernel<4, 1, 4, false>, 4, 1);
+  } else if (d > 4096 && rows <= 700) {
+    launch(rmsnorm_kernel<1, 4, 8, false>, 1, 4);
+  } else if (d > 6144 || (d > 4096 && rows > 3000)) {      // (up to there a second read of what is past 4096 costs less than wider spans)
+    if (once) launch(rmsnorm_kernel<2, 4, 8, true>, 2, 4);
+    else launch(rmsnorm_kernel<2, 4, 8, false>, 2, 4);
   } else {
-    if (rows <= 1400) launch(rmsnorm_kernel<2, 4, 4, false>, 2, 4);
+    if (rows <= 500) launch(rmsnorm_kernel<1, 4, 4, false>, 1, 4);
+    else if (rows <= 1400) launch(rmsnorm_kernel<2, 4, 4, false>, 2, 4);
     else if (once) launch(rmsnorm_kernel<4, 2, 8, true>, 4, 2);
     else launch(rmsnorm_kernel<4, 2, 8, false>, 4, 2);
   }
