@@ -505,6 +505,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
   const f16* w8_base = LO8 ? W8 + (size_t)(n0 / 32) * KB16 * 256 : w_base;
   const unsigned a_block = 64u * (unsigned)lda;        // bytes of a block of 32 rows of A
   const int a_last = (M - 1 - m0) >> 5;                // last block there is (a launch's rows are allocated in whole blocks)
+  // The lanes of rows past M ask for what others do, so that a last tile of few rows has few lines of A to wait for: its workgroup
+  // runs ahead of the others of the same columns and XCD, which find the weights in the L2.  us with whole blocks / this, cold
+  // weights, N 4096: 580 rows K 4096 41.2 / 38.7, K 11008 94 / 88, with low terms 137 / 127; 1160 rows 61 / 57.6, 138 / 133.
+  const unsigned lane_last = (unsigned)(min(lane & 31, (M - 1 - m0) & 31) + (lane & 32)) * 16u;      // in block a_last
   const int a_back = REST ? wave - wave % (REST ? REST : 1) : 0;     // pieces a wave's last one is moved back by
   auto issue_one = [&](int kt, auto I) VLA_INLINE {    // piece I of this wave's share of slab kt (clamped), A first
     constexpr int i = decltype(I)::value;
@@ -513,7 +517,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_f16_kernel(const f16*
       const int j = REST ? i * NW + wave - (i == AP - 1 ? a_back : 0) : wave * AP + i;
       const unsigned blk = (unsigned)min(j / KS16, a_last) * a_block + (unsigned)(j % KS16) * 1024u;
       const bool low = SPLITK && ks >= KTw;
-      load_to_lds_16(low ? a_lo_base : a_base, lane16, blk + 1024u * KS16 * (unsigned)(SPLITK ? kw : ks), lds + (kt % S) * A_STAGE + j * 512);
+      load_to_lds_16(low ? a_lo_base : a_base, j / KS16 < a_last ? lane16 : j / KS16 == a_last ? lane_last : 0u, blk + 1024u * KS16 * (unsigned)(SPLITK ? kw : ks), lds + (kt % S) * A_STAGE + j * 512);
     } else {
       const int j = wave * WP + i - AP;                // piece of the slab: block row j / KS16, 16-k block j % KS16
       const bool low = LO8 && ks >= KTw;
