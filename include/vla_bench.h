@@ -22,13 +22,14 @@ extern "C" {
 int vla_probe(vla_ctx* ctx, int32_t kind, double* value_out, void* hip_stream);
 
 /* Rows of the first launch of a prefill product [rows, k] x [n, k]^T that takes two, one of whole rounds of tiles and one of the
- * rest; 0 where it takes one, and for sizes the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer. */
-int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term);
+ * rest; 0 where it takes one, and for sizes the 16-bit path does not have.  Host only.  two_term: operands of a two-term layer;
+ * span: 32 for the output projection and the down projection, 64 for gate/up and for the QKV product of heads of 64, 128 for that
+ * of heads of 128 (the columns of a row that the product's last step needs together). */
+int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
 /* Which variant of the prefill GEMM a launch over `rows` rows of such a product runs ("128x256", ...: rows x columns of a tile,
  * and its form where there are several): a static text, "" for sizes the 16-bit path does not have.  Of a product of two launches
- * ask for the rows of each.  Host only.  span: 32 for the output projection and the down projection, 64 for gate/up and for the QKV
- * product of heads of 64, 128 for that of heads of 128 (the columns of a row that the product's last step needs together). */
+ * ask for the rows of each.  Host only. */
 const char* vla_gemm_variant(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span);
 
 /* Rows of the tiles that this launch runs: 32 to 128 for residual adds of rows x (n + 1200) <= 2^21, of products no wider

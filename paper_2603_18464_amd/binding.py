@@ -96,7 +96,7 @@ def lib() -> C.CDLL:
         L.vla_gemm_variant.argtypes = [i32] * 5
         L.vla_gemm_variant.restype = C.c_char_p
         L.vla_gemm_tile_rows.argtypes = [i32] * 5
-        L.vla_gemm_first_rows.argtypes = [i32] * 4
+        L.vla_gemm_first_rows.argtypes = [i32] * 5
         L.vla_decode_reads_once.argtypes = [vp, i32, C.c_int64]
         L.vla_batcher_create.argtypes = [i32, C.c_double, C.c_int64, C.POINTER(vp)]
         L.vla_batcher_destroy.argtypes = [vp]
@@ -295,8 +295,8 @@ def vla_gemm_tile_rows(rows: int, n: int, k: int, two_term: bool, span: int) -> 
     return lib().vla_gemm_tile_rows(rows, n, k, int(two_term), span)
 
 
-def vla_gemm_first_rows(rows: int, n: int, k: int, two_term: bool) -> int:
-    return lib().vla_gemm_first_rows(rows, n, k, int(two_term))
+def vla_gemm_first_rows(rows: int, n: int, k: int, two_term: bool, span: int) -> int:
+    return lib().vla_gemm_first_rows(rows, n, k, int(two_term), span)
 
 
 def vla_decode_reads_once(ctx, rows: int, positions: int) -> int:

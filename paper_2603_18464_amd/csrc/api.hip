@@ -1577,9 +1577,9 @@ int32_t vla_gemm_tile_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term,
   return gemm_f16_tile_rows(rows, n, two_pitch(two_term != 0, k), k, span);
 }
 
-int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term) {
-  if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64) return 0;
-  return gemm_f16_first_rows(rows, n, two_pitch(two_term != 0, k));
+int32_t vla_gemm_first_rows(int32_t rows, int32_t n, int32_t k, int32_t two_term, int32_t span) {
+  if (rows <= 0 || n <= 0 || k <= 0 || n % 128 || k % 64 || (span != 32 && span != 64 && span != 128)) return 0;
+  return gemm_f16_first_rows(rows, n, two_pitch(two_term != 0, k), span);
 }
 
 int32_t vla_decode_reads_once(vla_ctx* ctx, int32_t rows, int64_t positions) {

@@ -209,7 +209,7 @@ void gemm_f16_qkv(const GemmF16& g, const RopeKv& o, hipStream_t st);           
 extern const char* const kGemmF16Variants[];
 int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span);
 int gemm_f16_tile_rows(int M, int N, int K, int Kw, int span);    // rows of that launch's tiles
-int gemm_f16_first_rows(int M, int N, int K);    // rows of the first of a product's two launches, 0: it is one
+int gemm_f16_first_rows(int M, int N, int K, int span);    // rows of the first of a product's two launches, 0: it is one
 void pack_weight_f16(const bf16* src, int rows, int K, f16* dst, unsigned char* dst8, int row0, int interleave_mode,
                      int* range_flag, hipStream_t st);
 

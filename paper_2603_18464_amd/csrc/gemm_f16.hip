@@ -1099,10 +1099,13 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
 
 // Rows that go into a first launch of whole rounds where the rest of them costs less in a launch of its own, with lower tiles,
 // than as the last round of all: 0 where it does not.  The second launch costs some 5 us (its own, and the end of the first's
-// last round), and the two have to come to 2.5 % less.  us from the first launch's
-// start to the last one's end, 7B, 18560 rows (73 x 16 tiles of 256 rows: 4.56 rounds; now four whole ones, and 14 x 16 tiles of 160),
-// before the 128x128 waves, with them, and in two launches: down 1311, 1269, 1217; o 537, 530, 515.
-int gemm_f16_first_rows(int M, int N, int K) {
+// last round), and by the model the two have to come to 2.5 % less, those of QKV and gate/up to 4 %.
+// us from the first launch's start to the last one's end, 7B, 18560 rows (73 x 16 tiles of 256 rows: 4.56 rounds; now four whole
+// ones, and 14 x 16 tiles of 160), before the 128x128 waves, with them, and in two launches: down 1311, 1269, 1217; o 537, 530, 515.
+// One launch over two, 261 products of d 768 to 5120 at 1500 to 25000 rows that 2.5 % splits: residual adds 1.023 in the mean and
+// 0.994 at worst, with low terms 1.040 and 1.010; QKV and gate/up that the model gives 4 % 1.026 and 0.983 (QKV of d 4096 at 4806
+// rows), with low terms 1.037 and 1.009, those that it gives less 1.010 and 0.965 (QKV of d 5120 at 12259 rows), 1.015 and 0.981.
+int gemm_f16_first_rows(int M, int N, int K, int span) {
   const auto cost_of = [&](int rows) -> long long {        // 0: not a launch of such tiles
     const TilePick p = pick_tile(rows, N, K);
     return kTileCost[p.tile].bm < 192 ? 0 : rounds_cost(rows, N, tile_rows(p, rows, N));
@@ -1111,7 +1114,7 @@ int gemm_f16_first_rows(int M, int N, int K) {
   if (one <= 2 * 346) return 0;                            // (a round of 256 rows and another)
   const float us_per_cost = (kTileCost[T_256x256].fixed + kTileCost[T_256x256].per_k * (float)K / 1024.0f) / 346.0f;
   const long long launch = (long long)(5.0f / us_per_cost);
-  long long best = one * 39 / 40;
+  long long best = span == EpiResid::kSpan ? one * 39 / 40 : one * 25 / 26;
   int first = 0;
   for (int rows = 160; rows <= 256; rows += 32) {
     const int rounds = (int)(((long long)(M / rows) * (N / 256)) / 256);           // whole ones there are
@@ -1188,7 +1191,7 @@ static void dispatch_whole(const GemmF16& g, const Epi& epi, hipStream_t st) {
 }
 template <class Epi>
 static void dispatch(const GemmF16& g, const Epi& epi, hipStream_t st) {
-  if (const int m = gemm_f16_first_rows(g.M, g.N, g.K)) {
+  if (const int m = gemm_f16_first_rows(g.M, g.N, g.K, Epi::kSpan)) {
     GemmF16 a = g, b = g;
     a.M = m;
     b.M = g.M - m;

@@ -39,16 +39,16 @@ CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 6
 BALANCED = [(768, 1024, 64, [5200]), (1280, 1024, 64, [8000]), (768, 64, 128, [7000])]
 
 
-def parts(rows, n, k, two):
+def parts(rows, n, k, two, span):
     """Rows of each launch of a product."""
-    first = vla_gemm_first_rows(rows, n, k, two)
+    first = vla_gemm_first_rows(rows, n, k, two, span)
     return [first, rows - first] if first else [rows]
 
 
 def launches(d, f, hd, rows):
     for two in (False, True):
         for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-            for m in parts(rows, n, k, two):
+            for m in parts(rows, n, k, two, SPAN[epi]):
                 yield (two, epi), vla_gemm_variant(m, n, k, two, SPAN[epi])
 
 
@@ -74,15 +74,15 @@ def test_the_variant_is_what_the_launch_runs():
         assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
     for rows, n, k, span, want in ((18560, 4096, 11008, 32, [(16384, "256x256 spread"), (2176, "160x256")]),
                                    (9280, 4096, 4096, 32, [(6144, "192x256"), (3136, "224x256")])):
-        assert [(m, vla_gemm_variant(m, n, k, False, span)) for m in parts(rows, n, k, False)] == want, (rows, n, k)
+        assert [(m, vla_gemm_variant(m, n, k, False, span)) for m in parts(rows, n, k, False, span)] == want, (rows, n, k)
     for n, k, span in ((12288, 4096, 128), (22016, 4096, 64), (4096, 11008, 32), (2304, 768, 64), (768, 2048, 32)):
         for rows in range(1, 30000, 173):
             for two in (False, True):
-                for m in parts(rows, n, k, two):
+                for m in parts(rows, n, k, two, span):
                     assert 0 < m <= rows and vla_gemm_variant(m, n, k, two, span).startswith(f"{vla_gemm_tile_rows(m, n, k, two, span)}x")
     assert vla_gemm_tile_rows(300, 512, 768, False, 32) == 32           # of an epilogue that the few-row kernel has, and of one
     assert vla_gemm_tile_rows(300, 512, 768, False, 64) == 64           # that it does not have
-    assert vla_gemm_first_rows(18560, 4000, 4096, False) == vla_gemm_first_rows(0, 4096, 4096, False) == 0
+    assert vla_gemm_first_rows(18560, 4000, 4096, False, 32) == vla_gemm_first_rows(0, 4096, 4096, False, 32) == vla_gemm_first_rows(18560, 4096, 4096, False, 1) == 0
 
 
 def test_the_third_weight_stage_goes_by_the_bytes_that_are_read_again():

@@ -23,7 +23,7 @@ def test_the_cases_reach_every_height():
         for rows in rows_list:
             for two in (False, True):
                 for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-                    for m in V.parts(rows, n, k, two):
+                    for m in V.parts(rows, n, k, two, V.SPAN[epi]):
                         height = vla_gemm_tile_rows(m, n, k, two, V.SPAN[epi])
                         reached.add((two, epi, height))
                         if height == 256:
@@ -61,7 +61,7 @@ def test_the_copies_reach_both_new_heights():
     for d, f, hd, n in COPIES:
         for two in (False, True):
             for epi, cols, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-                for m in V.parts(33 * n, cols, k, two):
+                for m in V.parts(33 * n, cols, k, two, V.SPAN[epi]):
                     reached.add((two and k % 128 == 0, epi, vla_gemm_tile_rows(m, cols, k, two, V.SPAN[epi])))
     assert {(low8, epi, h) for low8 in (False, True) for epi in V.SPAN for h in (160, 224)} <= reached
 

@@ -6,9 +6,9 @@ import pytest
 from paper_2603_18464_amd.binding import vla_gemm_first_rows
 from tests import test_gemm_variants as V
 
-# (d_model, d_ffn, head_dim, rows): gate/up 3072 + 545 rows; QKV of both head sizes 4352 + 1278 and 3808 + 1855; the output
+# (d_model, d_ffn, head_dim, rows): gate/up 4480 + 941 rows; QKV of both head sizes 4352 + 1278 and 4800 + 1763; the output
 # projection 4416 + 2184
-CASES = [(768, 8192, 64, [3617]), (2560, 64, 128, [5630, 5663]), (2560, 64, 64, [5630]), (5632, 704, 64, [6600])]
+CASES = [(768, 8192, 64, [5421]), (2560, 64, 128, [5630, 6563]), (2560, 64, 64, [5630]), (5632, 704, 64, [6600])]
 
 
 def test_every_epilogue_is_split():
@@ -17,7 +17,7 @@ def test_every_epilogue_is_split():
         for rows in rows_list:
             for two in (False, True):
                 for epi, n, k in ((f"qkv{hd}", 3 * d, d), ("resid", d, d), ("gate/up", 2 * f, d), ("resid", d, f)):
-                    first = vla_gemm_first_rows(rows, n, k, two)
+                    first = vla_gemm_first_rows(rows, n, k, two, V.SPAN[epi])
                     assert first % 32 == 0 and 0 <= first < rows
                     if first:
                         split.add((two, epi))
