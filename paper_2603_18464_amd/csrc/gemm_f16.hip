@@ -254,12 +254,12 @@ __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, cons
 //   registers.  A comes from the L2 and W, in a launch of few tiles, from HBM: where the 160 KiB do not hold another stage of
 //   both they hold a third one of W.  Against two stages of each: 192x256 at 290 rows 79 -> 62 us (qkv), 84 -> 68 (gate/up),
 //   191 -> 142 (down), at 18560 rows 1811 -> 1652, 2846 -> 2656, 1760 -> 1493; 256x256 at 290 rows 88 -> 75, 94 -> 82,
-//   212 -> 180, at 18560 rows down 1443 -> 1377 and with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.  (Single-term
-//   256x256 launches of many tiles keep two of each where the weights stay in the caches: see the tile choice.)
+//   212 -> 180, at 18560 rows down 1443 -> 1377 and with low terms 2381 -> 2315, 3988 -> 3900, 2125 -> 1987.
 // * SPREAD: the weights of a slab are requested a k-step after its activations, so that the loads go out evenly.
 // * Both slabs are in fragment order, so that a load is one KiB from one place, with a scalar offset, and a read of the LDS has no
 //   bank conflicts.  A row-major A took an address a lane and eight pieces of 128 bytes a load: us, 18560 rows, that / this,
-//   gate/up 2450 / 2372, down 1336 / 1314, o 548 / 535, with low terms 4 % (gate/up) and 2.5 % (qkv) less, qkv +-1 %; 2338 rows
+//   gate/up 2450 / 2372, down 1336 / 1314, o 548 / 535, with low terms 4 % (gate/up) and 2.5 % (qkv) less, qkv 0 to 2 % more
+//   (1377 / 1404, 1412 / 1427, 1396 / 1394 on three cards); 2338 rows
 //   gate/up 346 / 336, down 176 / 173.  On operands of zeros, where the clock does not drop, 1834 / 1741, 1113 / 977, 465 / 434:
 //   most of what it saves goes into the power limit.
 // * Four waves of 128x128 for the residual add's 256x256 tiles: a third fewer reads of the LDS than eight of 64x128, down 1314 ->
@@ -1004,29 +1004,27 @@ static TilePick pick_tile(int M, int N, int K) {
 // * where several rounds of 64x128 tiles share the compute units (3 stages, two workgroups), and in the eight-wave form of a
 //   launch of few of them, whose four stages do; an epilogue that needs 128 columns of a row together (span 128) cannot have
 //   that form's wave tiles of 32 columns and keeps four waves and six stages;
-// * 256x256, eight waves of 64x128: a third weight stage does nothing for a single-term launch of three rounds and more
-//   whose weights stay in the caches between the tile rows that read them, and costs 1 to 3 % there (a stage's offset is no
-//   power of two, and the chip is bound by power).  The line lies where the weights and half of the activations reach
-//   215 MB of the 256 MB last-level cache.  Three stages over two, weights and activations in MB: gate/up 45 + 76 (d 2048,
-//   18560 rows) +1.7 %, 90 + 152 +1.8, 101 + 114 (d 3072) +2.0, 134 + 152 +1.1, 180 + 19 (7B, 2320 rows) +2.4, 180 + 38 +1.4 and
-//   -0.3, 151 + 152 -0.4, 180 + 76 -1.3, 180 + 152 -1.8, 201 + 76 -3.3, 268 + 38 -4.0; qkv 57 + 228 +2.8, 101 + 152 (7B, 18560
-//   rows) +1.8 to +2.7, 101 + 304 +0.9, 127 + 171 -0.5, 157 + 190 -2.3, 226 + 114 -6.2; heads of 64 as heads of 128.  The
-//   epilogue that adds to the residual rows always gains (-1 to -4 %), and so do low terms (0 to -6 %);
-// * the residual epilogue (four waves of 128x128) and launches of fewer than three rounds request the weights a k-step after the
-//   activations (SPREAD, 18560 rows down 1337 against 1348 us, o 590 against 595; gate/up and qkv the same either way, +-1 %).
+// * 256x256: the residual epilogue (four waves of 128x128) and single-term launches of fewer than three rounds, or whose weights
+//   stay in the caches between the tile rows that read them, request the weights a k-step after the activations (SPREAD); the
+//   others request them together, and so do low terms.  The line lies where the weights and half of the activations reach 170 MB of the
+//   256 MB last-level cache.  SPREAD / together, in % of two stages of both, weights + activations in MB: gate/up 46 + 38 (d
+//   2048, 9280 rows) 0.0 / +0.4, 71 + 95 -0.3 / +0.1, 101 + 114 (d 3072) -0.3 / -0.1, 180 + 38 (7B, 4640 rows) -0.8 / -0.6, 180 + 57
+//   -2.1 / -2.3, 180 + 76 -3.0 / -3.5, 180 + 152 -3.1 / -3.3, 283 + 190 -3.5 / -4.4; qkv 25 + 76 -0.2 / +0.6, 57 + 57 -0.4 / +0.2,
+//   101 + 76 (7B, 9280 rows) -0.9 / -0.3, 101 + 152 -0.1 / 0.0 (on other cards +0.9 / 0.0 and +1.0 / +0.3), 157 + 95 -2.4 / -3.7,
+//   157 + 190 -1.6 / -4.0.  Residual adds gain by it (18560 rows down 1337 against 1348 us, o 590 against 595).
 // (Slabs of 32 k throughout, in four stages of both operands, against slabs of 64 k in two and three: down 203 and 201 us at
 // 2338 rows, 536 and 525 at 6960, 1435 and 1377 at 18560; o 86 and 85, 211 and 206, 570 and 548.)
 constexpr int kFewHeights = 7;                            // gemm_few_kernel's tiles: 32, 48, ... 128 rows
 enum Variant {
   V_FEW, V_FEW_AHEAD = V_FEW + kFewHeights,              // (the first of each; ahead: with workgroups that read the weights ahead)
   V_64x128_8W = V_FEW_AHEAD + kFewHeights, V_64x128, V_64x128_ROUNDS, V_128x128, V_64x256, V_128x256, V_160x256, V_192x256,
-  V_224x256, V_256x256, V_256x256_W3, V_256x256_SPREAD, V_COUNT
+  V_224x256, V_256x256, V_256x256_SPREAD, V_COUNT
 };
 const char* const kGemmF16Variants[] = {
     "32x64", "48x64", "64x64", "80x64", "96x64", "112x64", "128x64",
     "32x64 ahead", "48x64 ahead", "64x64 ahead", "80x64 ahead", "96x64 ahead", "112x64 ahead", "128x64 ahead",
     "64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "160x256", "192x256",
-    "224x256", "256x256", "256x256 3 weight stages", "256x256 spread"};
+    "224x256", "256x256", "256x256 spread"};
 static_assert(sizeof(kGemmF16Variants) / sizeof(char*) == V_COUNT, "a name each");
 
 // Rows of the tiles a launch runs.  Where the model picks 192 or 256 rows, the rounds are balanced: the last one costs a whole
@@ -1092,9 +1090,9 @@ int gemm_f16_variant(int M, int N, int K, int Kw, bool lo8, int span) {
     case 224: return V_224x256;
     default: break;
   }
-  if (lo8) return V_256x256_W3;
-  if (span == EpiResid::kSpan || (long long)((M + 255) / 256) * (N / 256) < 768) return V_256x256_SPREAD;
-  return (2LL * N + M) * Kw > 215'000'000 ? V_256x256_W3 : V_256x256;
+  if (lo8) return V_256x256;
+  const bool few_rounds = (long long)((M + 255) / 256) * (N / 256) < 768;
+  return span == EpiResid::kSpan || few_rounds || (2LL * N + M) * Kw <= 170'000'000 ? V_256x256_SPREAD : V_256x256;
 }
 
 // Rows that go into a first launch of whole rounds where the rest of them costs less in a launch of its own, with lower tiles,
@@ -1164,9 +1162,6 @@ static void dispatch_lo(const GemmF16& g, const Epi& epi, hipStream_t st) {
     case V_192x256: launch<2, 4, 96, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
     case V_224x256: launch<2, 4, 112, 64, 2, 3, 1, false, false, LO8>(g, epi, st); break;
     case V_256x256:
-      if constexpr (!LO8 && !resid) launch<4, 2, 64, 128, 2, 2, 1, false, false, LO8>(g, epi, st);
-      break;
-    case V_256x256_W3:
       if constexpr (LO8 || !resid) launch<4, 2, 64, 128, 2, 3, 1, false, false, LO8>(g, epi, st);
       break;
     default:

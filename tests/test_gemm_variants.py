@@ -12,7 +12,7 @@ from tests import parity as P
 from tests.test_gpu_parity import ragged_obs
 
 ALL = {"64x128 8 waves", "64x128 6 stages", "64x128 3 stages", "128x128", "64x256", "128x256", "160x256", "192x256", "224x256",
-       "256x256", "256x256 3 weight stages", "256x256 spread"}
+       "256x256", "256x256 spread"}
 SPAN = {"resid": 32, "gate/up": 64, "qkv64": 64, "qkv128": 128}
 # Not reached: of the forms of a launch of few 64x128 tiles each epilogue has one; three stages need more than 256 of these
 # tiles to be the fastest choice, which takes a wide matrix of a short contraction (gate/up only); 8-bit low terms have one
@@ -20,15 +20,14 @@ SPAN = {"resid": 32, "gate/up": 64, "qkv64": 64, "qkv128": 128}
 # halves).
 REACHED = {(two, epi): ALL - {"64x128 8 waves" if epi == "qkv128" else "64x128 6 stages"}
            - ({"64x128 3 stages"} if epi != "gate/up" else set())
-           - ({"256x256"} if two or epi == "resid" else set())
-           - ({"256x256 3 weight stages"} if epi == "resid" and not two else set())
+           - ({"256x256"} if epi == "resid" and not two else set())
            - ({"256x256 spread"} if two and epi != "resid" else set())
            for two in (False, True) for epi in SPAN}
-# A single-term product with three weight stages has a matrix of 100 MB or more.  Here for heads of 64; the 7B workloads run
-# the other two (gate/up from 7000 rows on, heads of 128 from 28 000 on).
+# A single-term product that requests its weights together has a matrix of 100 MB or so.  Here for heads of 64; the 7B workloads
+# run the other two (gate/up of any 256-row tiles, heads of 128 from 17 000 rows on).
 BY_7B = [("gate/up", 64 * 290, 22016), ("qkv128", 256 * 290, 12288)]
 for epi, _, _ in BY_7B:
-    REACHED[False, epi] -= {"256x256 3 weight stages"}
+    REACHED[False, epi] -= {"256x256"}
 
 # (d_model, d_ffn, head_dim, rows): three layers, the first two-term, the last one partly on the rows of the head only
 CASES = [(128, 192, 64, [64, 6000]), (768, 64, 128, [2881, 4100, 6000]), (768, 64, 64, [2881, 4100, 6000]),
@@ -61,7 +60,7 @@ def test_the_cases_reach_every_variant():
                     reached[key].add(variant)
     assert reached == REACHED
     for epi, rows, n in BY_7B:
-        assert vla_gemm_variant(rows, n, 4096, False, SPAN[epi]) == "256x256 3 weight stages"
+        assert vla_gemm_variant(rows, n, 4096, False, SPAN[epi]) == "256x256"
     assert vla_gemm_variant(64, 100, 128, False, 32) == vla_gemm_variant(64, 128, 128, False, 1) == ""
 
 
@@ -69,7 +68,7 @@ def test_the_variant_is_what_the_launch_runs():
     """Where the rounds are balanced the launch runs other tiles than the cost model picks: the name is that of the launch.  Where
     a product takes two launches each has one."""
     for rows, n, k, span, want in ((2320, 22016, 4096, 64, "224x256"), (2208, 22016, 4096, 64, "160x256"), (290, 22016, 4096, 64, "160x256"),
-                                   (4100, 12288, 4096, 128, "160x256"), (10533, 22016, 4096, 64, "256x256 3 weight stages"),
+                                   (4100, 12288, 4096, 128, "160x256"), (10533, 22016, 4096, 64, "256x256"),
                                    (2320, 4096, 4096, 32, "160x256")):
         assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
     for rows, n, k, span, want in ((18560, 4096, 11008, 32, [(16384, "256x256 spread"), (2176, "160x256")]),
@@ -85,12 +84,13 @@ def test_the_variant_is_what_the_launch_runs():
     assert vla_gemm_first_rows(18560, 4000, 4096, False, 32) == vla_gemm_first_rows(0, 4096, 4096, False, 32) == vla_gemm_first_rows(18560, 4096, 4096, False, 1) == 0
 
 
-def test_the_third_weight_stage_goes_by_the_bytes_that_are_read_again():
-    """The same tile, with two stages where weights and half of the activations stay below 215 MB: whatever the epilogue."""
+def test_when_weights_are_requested_goes_by_the_bytes_that_are_read_again():
+    """The same tile, spread where weights and half of the activations stay below 170 MB: whatever the epilogue."""
     for span in (64, 128):
-        for rows, n, k, third in ((18560, 12288, 4096, False), (18560, 22016, 4096, True), (2560, 22016, 4096, False),
-                                  (18560, 11008, 2048, False), (18560, 49152, 2048, True), (9280, 18432, 6144, True)):
-            want = "256x256 3 weight stages" if third else "256x256"
+        for rows, n, k, together in ((9280, 12288, 4096, False), (18560, 12288, 4096, True), (18560, 22016, 4096, True),
+                                     (2560, 22016, 4096, True), (18560, 11008, 2048, False), (18560, 16384, 3072, False),
+                                     (18560, 49152, 2048, True), (9280, 18432, 6144, True)):
+            want = "256x256" if together else "256x256 spread"
             assert vla_gemm_variant(rows, n, k, False, span) == want, (rows, n, k)
 
 
