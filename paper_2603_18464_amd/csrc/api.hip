@@ -56,9 +56,9 @@ inline int two_term_layers(const vla_config& c) {
   return n < c.n_layers ? n : c.n_layers;
 }
 inline bool two_term_layer(const vla_config& c, int l) { return l < two_term_layers(c); }
-// Row-major two-term operands of the prefill GEMMs with contraction length K carry their low terms as bytes (and
+// Two-term operands of the prefill GEMMs with contraction length K carry their low terms as bytes (and
 // the GEMM uses the 8-bit copy of its weights for them) when K allows whole pairs of 64-k slabs; otherwise as
-// half precision.  Row pitch of such an operand in halves; mode as the producing kernels take it.  `two`: whether
+// half precision.  Halves a row of such an operand; mode as the producing kernels take it.  `two`: whether
 // the layer at hand is a two-term layer.
 inline bool lo8(bool two, int K) { return two && K % 128 == 0; }
 inline int lo_mode(bool two, int K) { return !two ? 0 : (lo8(two, K) ? 2 : 1); }

@@ -198,7 +198,7 @@ __device__ __forceinline__ void hold32(unsigned& v) {
 
 // C = A * W^T with fused epilogues (f16 MFMA, fp32 accumulation).
 void gemm_f16_resid(const GemmF16& g, float* x, int ldx, hipStream_t st);           // x += C
-// silu(gate)*up; lo_mode 1: also half-precision low terms at column f + j; 2: 8-bit low terms, bytes behind the f halves
+// silu(gate)*up; lo_mode 1: also half-precision low terms at column f + j; 2: 8-bit low terms (act_lo8_index)
 void gemm_f16_swiglu(const GemmF16& g, f16* act, int ldact, int lo_mode, hipStream_t st);
 void gemm_f16_qkv(const GemmF16& g, const RopeKv& o, hipStream_t st);               // RoPE + cache
 // range_flag: device int, bits are OR-ed in when a weight cannot be re-encoded exactly (see pack_weight_kernel);

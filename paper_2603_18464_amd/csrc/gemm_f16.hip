@@ -222,15 +222,15 @@ struct EpiQkv {
 };
 
 // ---- 8-bit low terms --------------------------------------------------------------------------------------
-// Two-term activations may carry their low term as one byte: lo8 = bf8(16 * (a - f16(a))) (1-5-2 format), stored
-// behind the high terms of the same row, A row = [hi: Kw halves | lo8: Kw bytes].  The low-term product then runs
+// Two-term activations may carry their low term as one byte: lo8 = bf8(16 * (a - f16(a))) (1-5-2 format), behind the
+// Kw high terms of a block of 32 rows (act_lo8_index).  The low-term product then runs
 // on v_mfma_f32_16x16x128 in 8-bit formats (twice the rate of the half-precision instruction) against a second
 // copy of the weights, W8 = fp8(w * 16) (1-4-3 format, saturating at +-448, i.e. |w| = 28), so that
 // lo8 * W8 = 2^8 * lo * w lands in the same accumulator as hi * (w * 2^8).  The correction term only has to be good
 // to a few percent (it is itself 2^-12 of the result), which three and two mantissa bits give.
-// Layout: a 128-byte row slab of lo8 has the geometry of a 64-half slab of hi, and W8 is packed so that the 16-byte
-// chunk c (16 k) of a row lies where the 16-byte chunk c (8 k) of the row lies in the fragment-order halves; a lane's
-// operand of the 128-deep product is its 16 bytes of k-step 0 followed by its 16 bytes of k-step 1, for both operands.
+// Layout: 128 k of lo8 have the geometry of 64 k of hi (4 KiB of 32 rows): the 16-byte chunk c (16 k) of a row lies where
+// the 16-byte chunk c (8 k) of the row lies in the halves, and W8 is packed likewise; a lane's operand of the 128-deep product is
+// its 16 bytes of k-step 0 followed by its 16 bytes of k-step 1, for both operands.
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 __device__ __forceinline__ f32x4 mfma_lo8(const f16x8& a0, const f16x8& a1, const f16x8& b0, const f16x8& b1,
@@ -967,8 +967,8 @@ static void launch_few(const GemmF16& g, int ahead, const EpiResid& epi, hipStre
 // matrices of models of d 256 to 5120 at 64 to 37120 rows, single- and two-term, each tile forced in turn) the pick is the
 // fastest in 1015 and 0.30 % slower in the mean; constants that meet the two columns make it 0.38 %, and 0.57 instead of 0.19 %
 // over the 7B matrices among them; the best of a search over both tiles' constants 0.25 %.
-// us single-term, the model's pick (192 and 256 rows are balanced afterwards, tile_rows) and others: 290 rows qkv 50 (64x256; 192x256 64), gate/up 69 (192x256; 64x256 92), o 28
-// (64x128; 73), down 68 (64x128; 180); 580 rows gate/up 112 (128x256; 256x256 163), down 84 (128x128; 191); 870 rows qkv 78
+// us single-term, the model's pick (192 and 256 rows are balanced afterwards, tile_rows) and others: 290 rows qkv 50 (64x256;
+// 192x256 64), gate/up 69 (192x256; 64x256 92), o 28 (64x128; 73) and down 68 (64x128; 180), which gemm_few_kernel runs; 580 rows gate/up 112 (128x256; 256x256 163), down 84 (128x128; 191); 870 rows qkv 78
 // (192x256; 256x256 90); 2320 rows gate/up 378 (256x256; 128x256 389), o 86 (192x256; 256x256 101), down 197 (192x256;
 // 256x256 236); 9216 rows of d 768 gate/up 62 (192x256; 128x256 69).
 // Where it is off most: qkv at 580 rows of d 5120 116 (256x256; 192x256 99), gate/up at 13920 rows of d 768 112 (128x256;
