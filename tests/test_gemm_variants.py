@@ -81,7 +81,8 @@ def test_the_variant_is_what_the_launch_runs():
                     assert 0 < m <= rows and vla_gemm_variant(m, n, k, two, span).startswith(f"{vla_gemm_tile_rows(m, n, k, two, span)}x")
     assert vla_gemm_tile_rows(300, 512, 768, False, 32) == 32           # of an epilogue that the few-row kernel has, and of one
     assert vla_gemm_tile_rows(300, 512, 768, False, 64) == 64           # that it does not have
-    assert vla_gemm_first_rows(18560, 4000, 4096, False, 32) == vla_gemm_first_rows(0, 4096, 4096, False, 32) == vla_gemm_first_rows(18560, 4096, 4096, False, 1) == 0
+    assert vla_gemm_first_rows(18560, 4000, 4096, False, 32) == vla_gemm_first_rows(0, 4096, 4096, False, 32) == 0
+    assert vla_gemm_first_rows(18560, 4096, 4096, False, 1) == 0
 
 
 def test_when_weights_are_requested_goes_by_the_bytes_that_are_read_again():
