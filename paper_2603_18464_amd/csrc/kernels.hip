@@ -378,8 +378,8 @@ __global__ __launch_bounds__(ROWS * WPR * 64) void rmsnorm_kernel(const float* _
 //   d 768   288 rows 2.4 / 2.4, 580 2.5 / 2.5, 870 2.7 / 2.7, 1400 3.1 / 3.0, 2500 4.1 / 3.7, 9280 9.7 / 8.6; with low terms 580 rows
 //           2.6 / 2.7, 870 2.8 / 2.9, 1400 3.3 / 3.2
 //   d 4096  288 rows 3.2 / 3.5, 580 3.7 / 4.6, 1400 5.6 / 6.6, 2500 11.3 / 12.6, 9280 33.8 / 35.6, 18560 79 / 80 (93 without ONCE);
-//           with low terms 288 3.5 / 4.1, 1400 6.9 / 8.8, 9280 39 to 41 / 41 to 46, 18560 92 / 91: what fragment order costs here is a
-//           tenth of what the products that read it gain
+//           with low terms 288 3.5 / 4.1, 1400 6.9 / 8.8, 9280 39 to 41 / 41 to 46, 18560 92 / 91 (eight rows a workgroup, and one or two
+//           waves a row of sixteen and eight pieces, are 3 to 40 % slower than these)
 //   d 5120  288 rows 3.5 / 4.0 (4.5), 2000 10.8 / 12.7, 4640 22.6 / 25.0 (26.5), 18560 100 / 102 (100), with low terms 118 / 125 (152)
 //   d 8192  288 rows 4.7 / 5.3 (6.1), 1400 12.8 / 14.2 (15.0), 4640 34 / 37 (45), 9280 84 / 83 (101), with low terms 99 / 100 (135)
 // One row a workgroup wins while a compute unit has three or four of them (two where a row is four pieces a wave).
